@@ -44,11 +44,18 @@ int validate_shape(const Shape& s) {
 // 3072 x 3072, + 8 to 10 % at 4096, + 14 to 16 % from 8192 on and at 1000 x 3000; 0.90 at
 // 1024).  Rows that see 1024 keys on average (2048 x 2048) are taken where the pairs of row
 // tiles fill a whole number of rounds of the 256 compute units (+ 1 to 3 % then; 3 to 6 %
-// behind otherwise, with compute units idle in the last round).  The kernel itself says
-// which calls it can serve at all (wide_applies()).
+// behind otherwise, with compute units idle in the last round).  A 256-row tile that is mostly
+// padding costs as much as a full one: with 16 positions per head and 4 heads to a kv head, 64
+// sequences over 8192 keys took 1366 us on it against 357 us on the 128-row kernel, which runs
+// the heads of a group in one row tile.  It is taken up to 4/3 of the rows that the 128-row
+// kernel works on (measured over 40 to 2100 rows and 4096 keys, 128-row time over 256-row time:
+// 1.02 to 1.12 at 4/3, 0.87 to 1.00 at 8/5, 0.74 to 0.86 at 2).  The kernel itself says which
+// calls it can serve at all (wide_applies()).
 bool prefers_256_rows(const Shape& s, bool causal) {
     if (s.d != 128 || s.dtype == FLASHD_F32) return false;
     const long wgs = (long)s.B * s.Hq * ((s.Lq + 255) / 256);
+    const long wgs128 = flashd::tile_workgroups(s.B, s.Hq, s.Hkv, s.Lq, s.d);
+    if (3 * 256 * wgs > 4 * 128 * wgs128) return false;
     if (!causal) return wgs >= 256 && s.Lk >= 1536;
     const long seen = (long)s.Lk - s.Lq / 2;        // keys a row sees on average
     const bool whole_rounds = s.Lq % 512 == 0 && (wgs / 2) % 256 == 0;
