@@ -400,7 +400,7 @@ def main() -> int:
         n1 = max(1000, args.steps)
         wall1, ev1 = time_calls(step_c1, n1, 20, 1)
         leg = {"workload": w1.name, "dtype": w1.dtype, "steps": n1,
-               "kernel": "perkey_kernel<F32,64> (flashd_attn_fwd)",
+               "kernel": "tile_f32_kernel<64> (flashd_attn_fwd)",
                "us_per_call_stream": round(ev1 / n1 * 1e3, 2),
                "us_per_call_wall": round(wall1 / n1 * 1e3, 2)}
         if not args.no_cpu:

@@ -70,7 +70,8 @@ typedef enum {
 
 /* How the recurrence is evaluated.  All variants compute the same result. */
 typedef enum {
-    FLASHD_VARIANT_AUTO = 0,     /* TILE (or TILE_256) for f16/bf16, PER_KEY for f32        */
+    FLASHD_VARIANT_AUTO = 0,     /* TILE (or TILE_256) for f16/bf16; for f32 the tile form on
+                                    the matrix cores with fp64 scores (reported as PER_KEY)  */
     FLASHD_VARIANT_TILE = 1,     /* Alg. 3 lifted to key tiles on the matrix cores (f16/bf16),
                                     the (1 - W) factors of the blend deferred to the store   */
     FLASHD_VARIANT_PER_KEY = 2,  /* Alg. 3 literally, one sigmoid per key (any dtype)       */
@@ -134,8 +135,8 @@ size_t flashd_workspace_bytes(int B, int Hq, int Hkv, int Lq, int Lk, int d, int
 int flashd_auto_splits(int B, int Hq, int Hkv, int Lq, int Lk, int d, int dtype, int variant);
 
 /*
- * The variant flashd_attn_fwd (FLASHD_VARIANT_AUTO) runs for this problem: PER_KEY for f32,
- * else TILE, or TILE_256 for calls that kernel can serve and was measured faster on (d = 128,
+ * The variant flashd_attn_fwd (FLASHD_VARIANT_AUTO) runs for this problem: PER_KEY for f32
+ * (which has one tile form of its own, at the precision of PER_KEY), else TILE, or TILE_256 for calls that kernel can serve and was measured faster on (d = 128,
  * one split, at least a workgroup per compute unit, row tiles that are not mostly padding, from
  * 1536 keys on without a mask, and with one where a row sees 1536 keys on average, or 1024 if the row
  * tiles come in whole rounds of the compute units).  Host-only; -1 for invalid arguments.  (Decode shapes,

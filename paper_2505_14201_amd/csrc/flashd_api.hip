@@ -356,7 +356,9 @@ int run(const void* q, const void* k, const void* v, void* o, const Shape& s, in
                       : var == FLASHD_VARIANT_ONLINE_SOFTMAX ? flashd::kTileModeOnline
                       : var == FLASHD_VARIANT_TILE_BLEND   ? flashd::kTileModeBlend
                                                            : flashd::kTileModeLazy;
-    if (var == FLASHD_VARIANT_PER_KEY) e = flashd::launch_perkey(p, st);
+    // fp32 without a variant asked for: the tile form on the matrix cores
+    if (s.dtype == FLASHD_F32 && variant == FLASHD_VARIANT_AUTO) e = flashd::launch_tile_f32(p, st);
+    else if (var == FLASHD_VARIANT_PER_KEY) e = flashd::launch_perkey(p, st);
     else if (flashd::decode_applies(s.Hq, s.Hkv, s.Lq)) e = flashd::launch_decode(p, tmode, st);
     else e = flashd::launch_tile(p, tmode, st);
     return e == hipSuccess ? FLASHD_OK : FLASHD_E_HIP;

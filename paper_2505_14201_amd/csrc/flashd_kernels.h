@@ -11,6 +11,10 @@ namespace flashd {
 // Alg. 3 per key (any dtype); with p.splits > 1 also folds the partials.
 hipError_t launch_perkey(const Problem& p, hipStream_t st);
 
+// Alg. 3 on key tiles for fp32 storage (matrix cores, scores in fp64): what the automatic choice
+// runs for fp32.  With p.splits > 1 also folds the partials.
+hipError_t launch_tile_f32(const Problem& p, hipStream_t st);
+
 // Fold p.splits partial states per query row from p.ws into p.o.
 hipError_t launch_merge_splits(const Problem& p, hipStream_t st);
 

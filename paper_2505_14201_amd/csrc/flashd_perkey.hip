@@ -1,6 +1,6 @@
 // Alg. 3 taken literally: one sigmoid per key (variant PER_KEY), any storage type,
-// fp32 arithmetic on the vector ALU.  This is the exact-by-construction path (fp32
-// inputs use it) and the slow reference for the tiled kernels.
+// fp32 arithmetic on the vector ALU.  This is the exact-by-construction path and the slow
+// reference for the tiled kernels; also home of the merge of key splits, which all paths use.
 //
 // Work split: a wavefront owns R query rows of one (b, h) and one key range
 // (split); the 4 wavefronts of a workgroup share the K and V tiles in LDS.

@@ -1,0 +1,318 @@
+// Alg. 3 on key tiles for fp32 storage, on the matrix cores: scores in fp64
+// (v_mfma_f64_16x16x4), output product in fp32 (v_mfma_f32_16x16x4).  This is what the automatic
+// choice runs for fp32; the literal per-key kernel (variant PER_KEY) forms the same scores with
+// fp64 fma on the vector ALUs, one key per lane, and was bound by them and by the 128 registers
+// of output state that every lane carries (4.4 TFLOP/s).
+//
+// Precision is that of the per-key kernel: dot products, scaled scores and s - ln w in fp64,
+// weights and output accumulation in fp32.
+//
+// Tile form: U = sum_j 2^{s_j - R} v_j and l = sum_j 2^{s_j - R} against a reference R (fp64)
+// that starts at the top score of the row's first block and moves only when a block's top score
+// lies more than kMoveLog2 above it; o = U / l at the store, Lam = R + log2 l (the deferred
+// blend of the f16/bf16 kernels, flashd_mma.h).
+//
+// Mapping.  A workgroup of 4 wavefronts owns 16 query rows of one kv head and one key range;
+// the wavefronts take its 16-key blocks in turn, each with a state of its own, and the four
+// states are folded at the end.  The query heads of a kv group are interleaved (row r is
+// position r / g of head r % g), so K and V are read once for the group and the causal bounds of
+// a row tile stay tight.  Lane (q, c) = (lane / 16, lane % 16) holds of S^T = K Q^T for query row
+// c the keys 4 r + q (r = 0..3), which is the B operand of the r-th step of O^T = V^T P^T as it
+// stands.  The contraction index of the scores and the column index of the output are permuted so
+// that each lane reads K and V as float4 straight from global memory: every wavefront has keys of
+// its own, so LDS would hold nothing that is used twice.  K of the next block is requested before
+// the output product and V before the scores; the rest of the latency is covered by the other
+// wavefronts of the SIMD.
+//
+// What bounds it: the matrix cores.  A block of 16 keys x 16 rows x 64 columns takes 16 fp64
+// instructions of 64 cycles (78.6 TFLOP/s peak) and 16 fp32 ones of 32 cycles.  Measured
+// against the per-key kernel: 2 x 12 heads, 777 causal positions, d = 64 34 us (425 us before; 54
+// TFLOP/s of the 97 that the two kinds of instruction allow together), 4 heads of 1000 positions,
+// d = 128 42 us (391), one head of 128 positions 5 us of kernel (26).
+#include "flashd_common.h"
+#include "flashd_kernels.h"
+#include "flashd_mma.h"
+
+namespace flashd {
+
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+
+constexpr int kF32Waves = 4;
+constexpr int kF32Rows = 16;       // query rows per workgroup
+constexpr int kF32Block = 16;      // keys per wavefront step
+// l and U may grow by 2^kMoveLog2 per key over what the top key alone would give; small, so that
+// values up to 1e32 or so still sum without overflow
+constexpr double kMoveLog2 = 8.0;
+
+// How workgroups map to work: id -> (rank of the row tile, split, unit), all units' longest row
+// tiles first; unit u on XCD u % 8 where the units divide by 8, so that K and V of a head are
+// read into one L2.
+struct F32Sched {
+    int heads;          // query heads interleaved in a unit: Hq / Hkv (1: not interleaved)
+    int rows;           // query rows of a unit: heads * Lq
+    int tiles;          // row tiles of a unit
+    int nx_log2;        // 3: units are dealt over the XCDs, 0: not
+    uint32_t total;     // workgroups of work
+    FastDiv per_rank;   // splits * units per XCD
+    FastDiv per_split;  // units per XCD
+    FastDiv heads_div;
+    FastDiv units_per_b;
+    FastDiv kv_div;     // unit -> kv unit (Hq / Hkv where the heads are not interleaved, else 1)
+};
+
+// x over the four lanes c, c + 16, c + 32, c + 48 of a query row
+template <typename S, typename F>
+__device__ __forceinline__ S row_reduce(S x, F f) {
+    x = f(x, __shfl_xor(x, 16, kWave));
+    return f(x, __shfl_xor(x, 32, kWave));
+}
+
+template <int D>
+__global__ __launch_bounds__(kF32Waves * kWave, D == 64 ? 3 : 2)
+void tile_f32_kernel(Problem p, F32Sched sc) {
+    constexpr int NM = D / 16;             // float4 of K per lane and block
+    constexpr int NB = D / 64;             // 64-column groups of the output
+    constexpr int FROW = D + 4;            // floats per row of the fold buffer (16-byte rows)
+    __shared__ __align__(16) float fold_u[kF32Waves][kF32Rows][FROW];
+    __shared__ double fold_r[kF32Waves][kF32Rows];
+    __shared__ float fold_l[kF32Waves][kF32Rows];
+
+    const int tid = threadIdx.x;
+    const int lane = tid & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int c = lane & 15;
+    const int q = lane >> 4;
+    const double ninf = -__builtin_inf();
+    const double c_log2 = (double)p.scale * 1.4426950408889634074;
+
+    for (uint32_t id = blockIdx.x; id < sc.total; id += gridDim.x) {
+        const uint32_t local = id >> sc.nx_log2;
+        const uint32_t rank = fast_div(local, sc.per_rank);
+        const uint32_t rem = local - rank * sc.per_rank.d;
+        const int sp = (int)fast_div(rem, sc.per_split);
+        const uint32_t unit = ((rem - (uint32_t)sp * sc.per_split.d) << sc.nx_log2) +
+                              (id & ((1u << sc.nx_log2) - 1u));
+        const int tile = p.causal ? sc.tiles - 1 - (int)rank : (int)rank;
+        const uint32_t b = fast_div(unit, sc.units_per_b);
+        const uint32_t hu = unit - b * sc.units_per_b.d;         // first head: hu * heads
+        const size_t kv_unit = fast_div(unit, sc.kv_div);
+
+        // row r of the unit -> row of [B][Hq][Lq], and its query position
+        auto position = [&](int r) { return (int)fast_div((uint32_t)r, sc.heads_div); };
+        auto q_row = [&](int r) {
+            const int pos = position(r);
+            const int head = (int)hu * sc.heads + (r - pos * sc.heads);
+            return ((size_t)b * p.Hq + head) * (size_t)p.Lq + pos;
+        };
+        auto visible = [&](int pos) {
+            return p.causal ? min(max(pos + p.shift + 1, 0), p.Lk) : p.Lk;
+        };
+
+        const int r0 = tile * kF32Rows;
+        const int rlast = min(r0 + kF32Rows, sc.rows) - 1;
+        // rows past the end stand in for the last one and are not stored
+        const int row = min(r0 + c, rlast);
+        const int nvis = visible(position(row));
+        const int nvis_min = visible(position(r0));
+        const int nvis_max = visible(position(rlast));
+        const int nblk_all = (p.Lk + kF32Block - 1) / kF32Block;
+        const int chunk = (nblk_all + p.splits - 1) / p.splits;
+        const int blk_end = min((nvis_max + kF32Block - 1) / kF32Block, (sp + 1) * chunk);
+
+        const float* qg = static_cast<const float*>(p.q) + q_row(row) * D + 4 * q;
+        const float* kg = static_cast<const float*>(p.k) + kv_unit * (size_t)p.Lk * D + 4 * q;
+        const float* vg = static_cast<const float*>(p.v) + kv_unit * (size_t)p.Lk * D + 4 * c;
+        f32x4 qf[NM], kf[NM];
+        auto fetch_k = [&](int blk) __attribute__((always_inline)) {
+            const float* src = kg + (size_t)min(blk * kF32Block + c, p.Lk - 1) * D;
+#pragma unroll
+            for (int m = 0; m < NM; ++m) kf[m] = *reinterpret_cast<const f32x4*>(src + 16 * m);
+        };
+
+        f32x4 U[NB][4];                    // [column group][n]: columns 64 i + 16 q + 4 e + n
+#pragma unroll
+        for (int i = 0; i < NB; ++i)
+#pragma unroll
+            for (int n = 0; n < 4; ++n) U[i][n] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        float l = 0.0f;                    // this lane's keys
+        double R = ninf;
+
+        int blk = sp * chunk + wave;
+        if (blk < blk_end) {
+            fetch_k(blk);
+#pragma unroll
+            for (int m = 0; m < NM; ++m) qf[m] = *reinterpret_cast<const f32x4*>(qg + 16 * m);
+        }
+        for (; blk < blk_end; blk += kF32Waves) {
+            const int j0 = blk * kF32Block;
+            f32x4 vf[NB][4];               // [column group][r]: key 4 r + q, columns 64 i + 4 c ..
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const float* src = vg + (size_t)min(j0 + 4 * r + q, p.Lk - 1) * D;
+#pragma unroll
+                for (int i = 0; i < NB; ++i) vf[i][r] = *reinterpret_cast<const f32x4*>(src + 64 * i);
+            }
+            f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int m = 0; m < NM; ++m) {
+                // d = 128: widen Q anew for every block, its fp64 form would take 64 registers
+                if (D == 128) asm volatile("" : "+v"(qf[m]));
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)kf[m][e], (double)qf[m][e],
+                                                               acc, 0, 0, 0);
+            }
+            if (blk + kF32Waves < blk_end) fetch_k(blk + kF32Waves);
+
+            const bool masked = j0 + kF32Block > nvis_min;
+            double x[4];
+            double top = ninf;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                x[r] = acc[r] * c_log2;
+                if (masked && j0 + 4 * r + q >= nvis) x[r] = ninf;
+                top = fmax(top, x[r]);
+            }
+            if (__builtin_amdgcn_ballot_w64(top > R + kMoveLog2) != 0) {
+                top = row_reduce(top, [](double a, double bb) { return fmax(a, bb); });
+                if (top > R + kMoveLog2) {
+                    const float f = exp2_fast((float)(R - top));       // 0 for a row without keys
+                    l *= f;
+#pragma unroll
+                    for (int i = 0; i < NB; ++i)
+#pragma unroll
+                        for (int n = 0; n < 4; ++n) U[i][n] *= f;
+                    R = top;
+                }
+            }
+            float pw[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                pw[r] = exp2_fast((float)(x[r] - R));
+                if (masked && j0 + 4 * r + q >= nvis) pw[r] = 0.0f;    // also where R is still -inf
+                l += pw[r];
+            }
+            bool plain = true;
+            if (masked) {
+                // a weight of zero does not silence an infinite or NaN value of a hidden key
+                float bad = 0.0f;
+#pragma unroll
+                for (int i = 0; i < NB; ++i)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) bad = fmaf(vf[i][r][e], 0.0f, bad);
+                plain = __builtin_amdgcn_ballot_w64(bad != 0.0f) == 0;
+            }
+            if (plain) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+#pragma unroll
+                    for (int i = 0; i < NB; ++i)
+#pragma unroll
+                        for (int n = 0; n < 4; ++n)
+                            U[i][n] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[i][r][n], pw[r],
+                                                                           U[i][n], 0, 0, 0);
+            } else {
+#pragma unroll 1
+                for (int kk = 0; kk < kF32Block; ++kk) {
+                    const float own = (kk >> 2) == 0 ? pw[0] : (kk >> 2) == 1 ? pw[1]
+                                      : (kk >> 2) == 2 ? pw[2] : pw[3];
+                    const float w = __shfl(own, (kk & 3) * 16 + c, kWave);
+                    if (j0 + kk < nvis) {
+                        const float* src = vg - 4 * c + (size_t)(j0 + kk) * D + 16 * q;
+#pragma unroll
+                        for (int i = 0; i < NB; ++i)
+#pragma unroll
+                            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                                for (int n = 0; n < 4; ++n)
+                                    U[i][n][e] = fmaf(w, src[64 * i + 4 * e + n], U[i][n][e]);
+                    }
+                }
+            }
+        }
+
+        // ---- fold the four wavefront states --------------------------------------------
+        l = row_reduce(l, [](float a, float bb) { return a + bb; });
+        __syncthreads();                   // the fold of the previous id has been read
+#pragma unroll
+        for (int i = 0; i < NB; ++i)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                *reinterpret_cast<f32x4*>(&fold_u[wave][c][64 * i + 16 * q + 4 * e]) =
+                    f32x4{U[i][0][e], U[i][1][e], U[i][2][e], U[i][3][e]};
+        if (q == 0) {
+            fold_r[wave][c] = R;
+            fold_l[wave][c] = l;
+        }
+        __syncthreads();
+        for (int idx = tid; idx < kF32Rows * (D / 4); idx += kF32Waves * kWave) {
+            const int fr = idx / (D / 4);
+            const int t = 4 * (idx % (D / 4));
+            if (r0 + fr > rlast) continue;
+            double top = ninf;
+#pragma unroll
+            for (int w = 0; w < kF32Waves; ++w) top = fmax(top, fold_r[w][fr]);
+            float lt = 0.0f;
+            f32x4 o = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+            for (int w = 0; w < kF32Waves; ++w) {
+                const float lw = fold_l[w][fr];
+                // a wavefront that saw no key: weight 0 (NaN stays NaN)
+                const float f = fold_r[w][fr] == ninf ? lw * 0.0f
+                                                      : exp2_fast((float)(fold_r[w][fr] - top));
+                lt = fmaf(f, lw, lt);
+                o += f * *reinterpret_cast<const f32x4*>(&fold_u[w][fr][t]);
+            }
+            const bool empty = lt == 0.0f;
+            const float inv = empty ? 0.0f : 1.0f / lt;
+            o *= inv;
+            const size_t orow = q_row(r0 + fr);
+            if (!p.partial) {
+                *reinterpret_cast<f32x4*>(static_cast<float*>(p.o) + orow * D + t) = o;
+            } else {
+                float* dst = p.ws + ((size_t)sp * p.B * p.Hq * p.Lq + orow) * (D + 2);
+                *reinterpret_cast<float2*>(dst + t) = float2{o[0], o[1]};
+                *reinterpret_cast<float2*>(dst + t + 2) = float2{o[2], o[3]};
+                if (t == 0)
+                    split_lam(empty ? ninf : (top + log2((double)lt)) * 0.69314718055994530942,
+                              dst[D], dst[D + 1]);
+            }
+        }
+    }
+}
+
+template <int D>
+static hipError_t launch_tile_f32_t(const Problem& p, hipStream_t st) {
+    F32Sched sc;
+    const int g = p.Hq / p.Hkv;
+    // rows of a unit are 32-bit; beyond that the heads run one by one
+    sc.heads = (long)g * p.Lq < (1L << 30) ? g : 1;
+    sc.rows = sc.heads * p.Lq;
+    sc.tiles = (sc.rows + kF32Rows - 1) / kF32Rows;
+    const long units = (long)p.B * (p.Hq / sc.heads);
+    const long total = units * sc.tiles * p.splits;
+    if (total > 0x7fffffffL) return hipErrorInvalidValue;
+    sc.nx_log2 = units % 8 == 0 ? 3 : 0;
+    sc.total = (uint32_t)total;
+    sc.per_rank = make_fast_div((uint32_t)((units >> sc.nx_log2) * p.splits));
+    sc.per_split = make_fast_div((uint32_t)(units >> sc.nx_log2));
+    sc.heads_div = make_fast_div((uint32_t)sc.heads);
+    sc.units_per_b = make_fast_div((uint32_t)(p.Hq / sc.heads));
+    sc.kv_div = make_fast_div((uint32_t)(sc.heads == g ? 1 : g));
+    const unsigned grid = (unsigned)(total < (1L << 22) ? total : (1L << 22));
+    hipLaunchKernelGGL((tile_f32_kernel<D>), dim3(grid), dim3(kF32Waves * kWave), 0, st, p, sc);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || !p.merge) return e;
+    return launch_merge_splits(p, st);
+}
+
+hipError_t launch_tile_f32(const Problem& p, hipStream_t st) {
+    if (p.dtype != 0) return hipErrorInvalidValue;
+    if (p.d == 64) return launch_tile_f32_t<64>(p, st);
+    if (p.d == 128) return launch_tile_f32_t<128>(p, st);
+    return hipErrorInvalidValue;
+}
+
+}  // namespace flashd

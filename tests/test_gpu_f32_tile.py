@@ -1,0 +1,61 @@
+"""The fp32 tile kernel (what the automatic choice runs for fp32) at the edges of its row tiles
+(16 rows, heads of a kv group interleaved), its 16-key blocks and its wavefronts' turns (64
+keys).  Tolerance: that of the fp32 path (gpu_util.F32_REL)."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import attention as oa
+from paper_2505_14201_amd import flashd, synthetic
+from tests.gpu_util import check, run_flashd
+
+pytestmark = pytest.mark.gpu
+AUTO, PER_KEY = flashd.VARIANT_AUTO, flashd.VARIANT_PER_KEY
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,Lq,Lk", [
+    (1, 1, 1, 1, 1), (1, 1, 1, 15, 17), (2, 2, 2, 16, 16), (1, 3, 3, 17, 63),
+    (1, 6, 2, 5, 65),         # 15 interleaved rows
+    (2, 8, 2, 4, 64),         # exactly one row tile of 4 heads
+    (1, 10, 2, 7, 129),       # 35 rows, 5 heads: tiles begin in the middle of a position
+    (8, 1, 1, 33, 80),        # 8 units: dealt over the XCDs
+    (1, 4, 4, 40, 9),         # rows that see no key
+])
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("splits", [1, 3])
+def test_edges(B, Hq, Hkv, Lq, Lk, causal, splits):
+    if splits > Lk:
+        pytest.skip("more splits than keys")
+    for d in (64, 128):
+        w = synthetic.small("t", B, Hq, Hkv, Lq, Lk, d, "f32", causal, seed=9100 + Lq * 7 + Lk + d)
+        q, k, v, _ = synthetic.make_qkv(w)
+        got = run_flashd(q, k, v, causal, w.scale, AUTO, splits)
+        check(got, oa.attn(q, k, v, causal, w.scale), torch.float32, f"d={d}")
+
+
+@pytest.mark.parametrize("std,scale", [(4.0, None), (30.0, None), (4.0, -0.5), (1.0, 0.0)])
+def test_moving_references(std, scale):
+    """Scores that keep climbing past the reference, fall below it for good, or are all alike."""
+    w = synthetic.small("t", 1, 4, 2, 50, 700, 64, "f32", True, seed=9300, qk_std=std)
+    q, k, v, _ = synthetic.make_qkv(w)
+    k = k * torch.linspace(0.1, 1.0, 700).view(1, 1, -1, 1)
+    scale = w.scale if scale is None else scale
+    check(run_flashd(q, k, v, True, scale, AUTO, 1), oa.attn(q, k, v, True, scale), torch.float32)
+
+
+@pytest.mark.parametrize("bad", [float("inf"), float("nan")])
+def test_hidden_values_do_not_reach_a_row(bad):
+    """A value that is infinite or NaN stays out of the rows its key is hidden from, as in the
+    per-key kernel, and reaches every row that sees it."""
+    w = synthetic.small("t", 1, 2, 1, 40, 40, 64, "f32", True, seed=9400)
+    q, k, v, _ = synthetic.make_qkv(w)
+    v[0, 0, 37, 5] = bad
+    got = run_flashd(q, k, v, True, w.scale, AUTO, 1)
+    lit = run_flashd(q, k, v, True, w.scale, PER_KEY, 1)
+    assert torch.isfinite(got[:, :, :37]).all()
+    assert not torch.isfinite(got[:, :, 37:, 5]).any()
+    assert torch.equal(torch.isfinite(got), torch.isfinite(lit))
+    clean = v.clone()
+    clean[0, 0, 37, 5] = 0.0
+    ref = oa.attn(q, k, clean, True, w.scale)
+    check(got[:, :, :37], np.ascontiguousarray(ref[:, :, :37]), torch.float32)
