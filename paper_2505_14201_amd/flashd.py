@@ -108,49 +108,59 @@ def auto_variant(B, Hq, Hkv, Lq, Lk, d, dtype, causal) -> int:
 
 
 def _marshal(q, k, v, o):
-    for name, t in (("q", q), ("k", k), ("v", v), ("o", o)):
-        if not t.is_cuda:
-            raise ValueError(f"{name} must live on the GPU")
-        if not t.is_contiguous():
-            raise ValueError(f"{name} must be contiguous")
-    if q.dtype not in _DTYPE or not (k.dtype == v.dtype == o.dtype == q.dtype):
+    # (written out: this runs on every call, and a loop over the tensors doubles its time)
+    if not (q.is_cuda and k.is_cuda and v.is_cuda and o.is_cuda and q.is_contiguous() and
+            k.is_contiguous() and v.is_contiguous() and o.is_contiguous()):
+        for name, t in (("q", q), ("k", k), ("v", v), ("o", o)):
+            if not t.is_cuda:
+                raise ValueError(f"{name} must live on the GPU")
+            if not t.is_contiguous():
+                raise ValueError(f"{name} must be contiguous")
+    dtype, qs, ks = q.dtype, q.shape, k.shape
+    if dtype not in _DTYPE or not (k.dtype == v.dtype == o.dtype == dtype):
         raise ValueError("q, k, v, o must share one of float32/float16/bfloat16")
-    if q.dim() != 4 or k.dim() != 4 or v.shape != k.shape or o.shape != q.shape:
+    if len(qs) != 4 or len(ks) != 4 or v.shape != ks or o.shape != qs:
         raise ValueError("expected q,o: [B,Hq,Lq,d] and k,v: [B,Hkv,Lk,d]")
-    B, Hq, Lq, d = q.shape
-    Bk, Hkv, Lk, dk = k.shape
+    B, Hq, Lq, d = qs
+    Bk, Hkv, Lk, dk = ks
     if Bk != B or dk != d:
         raise ValueError("batch or head dimension mismatch between q and k")
-    return B, Hq, Hkv, Lq, Lk, d, _DTYPE[q.dtype]
+    return B, Hq, Hkv, Lq, Lk, d, _DTYPE[dtype]
 
 
-def _stream_ptr(stream):
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+# The current device and the raw handle of its current stream.  torch.cuda.current_stream() builds
+# a Stream object around the handle and torch.cuda.device() saves and restores the device: 4.5 us
+# together, of a call that takes 5.
+_current_device = torch._C._cuda_getDevice
+_raw_stream = torch._C._cuda_getCurrentRawStream
+
+
+def _enqueue(fn, device, stream, head, tail=()) -> None:
+    """fn(*head, stream handle, *tail) with `device` (an index) current; raises on a status other
+    than 0."""
+    if device != _current_device():
+        with torch.cuda.device(device):
+            return _enqueue(fn, device, stream, head, tail)
+    rc = fn(*head, _raw_stream(device) if stream is None else stream.cuda_stream, *tail)
+    if rc != 0:
+        raise FlashdError(rc)
 
 
 def attn_fwd(q, k, v, o, causal: bool, scale: float, stream=None) -> None:
     """flashd_attn_fwd: o <- attention(q, k, v), enqueued on `stream` (default: current)."""
     B, Hq, Hkv, Lq, Lk, d, dt = _marshal(q, k, v, o)
-    with torch.cuda.device(q.device):
-        st = _stream_ptr(stream)
-        rc = _lib.flashd_attn_fwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(),
-                                  B, Hq, Hkv, Lq, Lk, d, int(bool(causal)), float(scale), dt, st)
-    if rc != 0:
-        raise FlashdError(rc)
+    _enqueue(_lib.flashd_attn_fwd, q.get_device(), stream, (q.data_ptr(), k.data_ptr(),
+             v.data_ptr(), o.data_ptr(), B, Hq, Hkv, Lq, Lk, d, int(bool(causal)), float(scale),
+             dt))
 
 
 def attn_fwd_static(q, k, v, o, causal: bool, scale: float, stream=None) -> None:
     """flashd_attn_fwd_static: as attn_fwd, split-K scratch in the library's fixed array
     (no allocation; raises FlashdError(E_WORKSPACE) when the problem needs more)."""
     B, Hq, Hkv, Lq, Lk, d, dt = _marshal(q, k, v, o)
-    with torch.cuda.device(q.device):
-        st = _stream_ptr(stream)
-        rc = _lib.flashd_attn_fwd_static(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(),
-                                         B, Hq, Hkv, Lq, Lk, d, int(bool(causal)), float(scale),
-                                         dt, st)
-    if rc != 0:
-        raise FlashdError(rc)
+    _enqueue(_lib.flashd_attn_fwd_static, q.get_device(), stream, (q.data_ptr(), k.data_ptr(),
+             v.data_ptr(), o.data_ptr(), B, Hq, Hkv, Lq, Lk, d, int(bool(causal)), float(scale),
+             dt))
 
 
 def attn_fwd_ex(q, k, v, o, causal: bool, scale: float, variant: int = VARIANT_AUTO,
@@ -163,13 +173,9 @@ def attn_fwd_ex(q, k, v, o, causal: bool, scale: float, variant: int = VARIANT_A
         if not workspace.is_cuda or not workspace.is_contiguous():
             raise ValueError("workspace must be a contiguous GPU tensor")
         ws_ptr, ws_bytes = workspace.data_ptr(), workspace.numel() * workspace.element_size()
-    with torch.cuda.device(q.device):
-        st = _stream_ptr(stream)
-        rc = _lib.flashd_attn_fwd_ex(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(),
-                                     B, Hq, Hkv, Lq, Lk, d, int(bool(causal)), float(scale), dt,
-                                     st, int(variant), int(splits), ws_ptr, ws_bytes)
-    if rc != 0:
-        raise FlashdError(rc)
+    _enqueue(_lib.flashd_attn_fwd_ex, q.get_device(), stream, (q.data_ptr(), k.data_ptr(),
+             v.data_ptr(), o.data_ptr(), B, Hq, Hkv, Lq, Lk, d, int(bool(causal)), float(scale),
+             dt), (int(variant), int(splits), ws_ptr, ws_bytes))
 
 
 def attn_fwd_skipv(q, k, v, o, causal: bool, scale: float, splits: int = 0, workspace=None,
@@ -186,13 +192,9 @@ def attn_fwd_skipv(q, k, v, o, causal: bool, scale: float, splits: int = 0, work
     if counts is not None and not (counts.is_cuda and counts.dtype == torch.int64
                                    and counts.numel() >= 2 and counts.is_contiguous()):
         raise ValueError("counts must be a contiguous GPU int64 tensor of 2 elements")
-    with torch.cuda.device(q.device):
-        rc = _lib.flashd_attn_fwd_skipv(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(),
-                                        B, Hq, Hkv, Lq, Lk, d, int(bool(causal)), float(scale),
-                                        dt, _stream_ptr(stream), int(splits), ws_ptr, ws_bytes,
-                                        None if counts is None else counts.data_ptr())
-    if rc != 0:
-        raise FlashdError(rc)
+    _enqueue(_lib.flashd_attn_fwd_skipv, q.get_device(), stream, (q.data_ptr(), k.data_ptr(),
+             v.data_ptr(), o.data_ptr(), B, Hq, Hkv, Lq, Lk, d, int(bool(causal)), float(scale),
+             dt), (int(splits), ws_ptr, ws_bytes, None if counts is None else counts.data_ptr()))
 
 
 def skip_stats(q, k, causal: bool, scale: float, lo: float = -6.0, hi: float = 11.0,
@@ -209,17 +211,14 @@ def skip_stats(q, k, causal: bool, scale: float, lo: float = -6.0, hi: float = 1
     if Bk != B or dk != d:
         raise ValueError("batch or head dimension mismatch between q and k")
     own = counts is None
-    with torch.cuda.device(q.device):
-        if own:
-            counts = torch.empty(3, dtype=torch.int64, device=q.device)
-        elif not (counts.is_cuda and counts.dtype == torch.int64 and counts.numel() >= 3
-                  and counts.is_contiguous()):
-            raise ValueError("counts must be a contiguous GPU int64 tensor of 3 elements")
-        rc = _lib.flashd_skip_stats(q.data_ptr(), k.data_ptr(), B, Hq, Hkv, Lq, Lk, d,
-                                    int(bool(causal)), float(scale), _DTYPE[q.dtype], float(lo),
-                                    float(hi), counts.data_ptr(), _stream_ptr(stream))
-    if rc != 0:
-        raise FlashdError(rc)
+    if own:
+        counts = torch.empty(3, dtype=torch.int64, device=q.device)
+    elif not (counts.is_cuda and counts.dtype == torch.int64 and counts.numel() >= 3
+              and counts.is_contiguous()):
+        raise ValueError("counts must be a contiguous GPU int64 tensor of 3 elements")
+    _enqueue(_lib.flashd_skip_stats, q.get_device(), stream, (q.data_ptr(), k.data_ptr(), B, Hq,
+             Hkv, Lq, Lk, d, int(bool(causal)), float(scale), _DTYPE[q.dtype], float(lo),
+             float(hi), counts.data_ptr()))
     if not own:
         return None
     c = counts.cpu()
@@ -248,13 +247,9 @@ def attn_fwd_state(q, k, v, causal: bool, scale: float, o=None, state_in=None, s
             raise ValueError(f"{name} must be a contiguous float32 GPU tensor [B, Hq, Lq, d + 2]")
     shift = Lk - Lq if causal_shift is None else int(causal_shift)
     ptr = lambda t: None if t is None else t.data_ptr()
-    with torch.cuda.device(q.device):
-        rc = _lib.flashd_attn_fwd_state(q.data_ptr(), k.data_ptr(), v.data_ptr(), ptr(o),
-                                        ptr(state_in), ptr(state_out), B, Hq, Hkv, Lq, Lk, d,
-                                        int(bool(causal)), shift, float(scale), _DTYPE[q.dtype],
-                                        _stream_ptr(stream))
-    if rc != 0:
-        raise FlashdError(rc)
+    _enqueue(_lib.flashd_attn_fwd_state, q.get_device(), stream, (q.data_ptr(), k.data_ptr(),
+             v.data_ptr(), ptr(o), ptr(state_in), ptr(state_out), B, Hq, Hkv, Lq, Lk, d,
+             int(bool(causal)), shift, float(scale), _DTYPE[q.dtype]))
 
 
 def attn_fwd_kv8(q, k8, v8, o, causal: bool, scale: float, kscale: float, vscale: float,
@@ -272,10 +267,6 @@ def attn_fwd_kv8(q, k8, v8, o, causal: bool, scale: float, kscale: float, vscale
     Bk, Hkv, Lk, dk = k8.shape
     if Bk != B or dk != d:
         raise ValueError("batch or head dimension mismatch between q and k8")
-    with torch.cuda.device(q.device):
-        rc = _lib.flashd_attn_fwd_kv8(q.data_ptr(), k8.data_ptr(), v8.data_ptr(), o.data_ptr(),
-                                      B, Hq, Hkv, Lq, Lk, d, int(bool(causal)), float(scale),
-                                      float(kscale), float(vscale), _DTYPE[q.dtype],
-                                      _stream_ptr(stream))
-    if rc != 0:
-        raise FlashdError(rc)
+    _enqueue(_lib.flashd_attn_fwd_kv8, q.get_device(), stream, (q.data_ptr(), k8.data_ptr(),
+             v8.data_ptr(), o.data_ptr(), B, Hq, Hkv, Lq, Lk, d, int(bool(causal)), float(scale),
+             float(kscale), float(vscale), _DTYPE[q.dtype]))
