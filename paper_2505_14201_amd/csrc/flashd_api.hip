@@ -316,7 +316,8 @@ int run(const void* q, const void* k, const void* v, void* o, const Shape& s, in
     p.q = q; p.k = k; p.v = v; p.o = o;
     p.ws = static_cast<float*>(ws);
     p.B = s.B; p.Hq = s.Hq; p.Hkv = s.Hkv; p.Lq = s.Lq; p.Lk = s.Lk; p.d = s.d;
-    p.Li = flashd::make_fast_div((uint32_t)s.Lq);
+    p.heads = flashd::make_fast_div(1);
+    p.head_rows = s.Lq;
     p.dtype = s.dtype;
     p.causal = causal != 0;
     p.splits = sp;
@@ -444,7 +445,8 @@ int flashd_skip_stats(const void* q, const void* k, int B, int Hq, int Hkv, int 
     Problem p;
     p.q = q; p.k = k; p.v = nullptr; p.o = nullptr; p.ws = nullptr;
     p.B = B; p.Hq = Hq; p.Hkv = Hkv; p.Lq = Lq; p.Lk = Lk; p.d = d;
-    p.Li = flashd::make_fast_div((uint32_t)Lq);
+    p.heads = flashd::make_fast_div(1);
+    p.head_rows = Lq;
     p.dtype = dtype;
     p.causal = causal != 0;
     p.splits = 1;

@@ -58,8 +58,10 @@ struct Problem {
     int wide;           // 1: the tiled prefill takes the 256-row kernel where it can serve the call
     unsigned long long* vskip_counts;   // optional, decode kernel with saturation skips:
                                         // [0] += 32-key blocks visited, [1] += blocks whose V was not fetched
-    FastDiv Li;         // causal rule: row r of a head stands for query position r % Li.d.  Li.d == Lq
-                        // except where the tile kernel runs the heads of a kv group as one head
+    FastDiv heads;      // heads.d query heads run as one, row by row: row r of it is position r / heads.d
+                        // of head r % heads.d (Lq and Hq then count its rows and such heads).  1 except
+                        // where a prefill kernel runs the heads of a kv group that way
+    int head_rows;      // query positions of one head (Lq of the call)
 };
 
 // ---- storage types -------------------------------------------------------

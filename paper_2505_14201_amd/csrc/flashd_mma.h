@@ -619,11 +619,17 @@ __device__ __forceinline__ int visible_at(const Problem& p, int pos) {
 }
 
 // Keys visible to row i of a head as the kernel sees heads (Lq rows, row i standing for
-// position i % Li.d); rows past the end see none.
+// position i / heads.d); rows past the end see none.
 __device__ __forceinline__ int visible_count(const Problem& p, int i) {
     if (i >= p.Lq) return 0;
-    // i % Li, branch-free: the rule runs per lane
-    return visible_at(p, i - (int)(fast_div((uint32_t)i, p.Li) * p.Li.d));
+    return visible_at(p, (int)fast_div((uint32_t)i, p.heads));
+}
+
+// Row i of a head as the kernel sees heads -> its row among those of the head in memory, where
+// the heads that run as one follow each other.
+__device__ __forceinline__ int row_in_memory(const Problem& p, int i) {
+    const int pos = (int)fast_div((uint32_t)i, p.heads);
+    return (i - pos * (int)p.heads.d) * p.head_rows + pos;
 }
 
 }  // namespace flashd

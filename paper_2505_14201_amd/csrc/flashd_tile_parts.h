@@ -178,15 +178,11 @@ struct Item {
     int jbase;                  // first key of tile 0
 };
 
-// Most and fewest keys visible to the rows r0 .. r1 (r0 <= r1 < Lq), or bounds of them.  With
-// the heads of a kv group run as one head (Li.d < Lq) a range of rows may run over the end of a
-// head; the bounds are then those of a whole head, its last and its first position (they only
-// decide which tiles a wavefront may skip and which take the code path without the mask).
+// Most and fewest keys visible to the rows r0 .. r1 (r0 <= r1 < Lq).
 __device__ __forceinline__ void visible_range(const Problem& p, int r0, int r1, int& most,
                                               int& fewest) {
-    const bool whole_head = (int)p.Li.d != p.Lq;
-    most = visible_at(p, whole_head ? (int)p.Li.d - 1 : r1);
-    fewest = visible_at(p, whole_head ? 0 : r0);
+    most = visible_at(p, (int)fast_div((uint32_t)r1, p.heads));
+    fewest = visible_at(p, (int)fast_div((uint32_t)r0, p.heads));
 }
 
 // Item number seq of this workgroup, or an invalid item when the workgroup has run out of
@@ -271,11 +267,9 @@ inline TileSched tile_sched(const Problem& p, int slots_per_xcd, int rows = 32 *
     const long units = (long)p.splits * p.B * p.Hq;
     TileSched sc;
     // Pairing halves the number of virtual workgroups; it pays once there are at least
-    // two rounds of them for all workgroup slots.  (Not with the heads of a kv group run
-    // as one head: the row tiles of such a run do not grow in length from first to last.  Not
-    // with split keys either: a split's share of a long and of a short row tile do not add up
-    // to the same for every pair.)
-    sc.pair = (p.causal && p.splits == 1 && (int)p.Li.d == p.Lq && m_tiles >= 2 &&
+    // two rounds of them for all workgroup slots.  (Not with split keys: a split's share of a
+    // long and of a short row tile do not add up to the same for every pair.)
+    sc.pair = (p.causal && p.splits == 1 && m_tiles >= 2 &&
                m_tiles * units >= 2L * kXcds * slots_per_xcd) ? 1 : 0;
     sc.wg_per_unit = (int)(sc.pair ? (m_tiles + 1) / 2 : m_tiles);
     sc.nx_log2 = units % kXcds == 0 ? 3 : 0;

@@ -918,7 +918,7 @@ bool wide_applies(const Problem& p, int mode) {
     if (mode != kModeLazy) return false;
     if (p.splits != 1 || p.partial || p.merge || p.from_state || !p.store_o) return false;
     if (p.state_out != nullptr || p.kv8) return false;
-    return (int)p.Li.d == p.Lq;
+    return p.heads.d == 1;
 }
 
 template <typename T, int D>
