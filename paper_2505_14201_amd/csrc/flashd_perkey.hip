@@ -302,7 +302,7 @@ void perkey_kernel(Problem p) {
 // earlier keys if one is given (p.state_in).  Writes the output (p.o, if not null) and the
 // state (p.state_out, if not null) as the run seen as one key: (o, s = Lam, ln w = 0).
 //
-// One wavefront per row.  Folded one after the other, o <- o + (o_p - o) W_p with
+// One wavefront per row for up to 8 splits, four for more.  Folded one after the other, o <- o + (o_p - o) W_p with
 // W_p = sigmoid(Lam_p - Lam) and Lam <- Lam_p - ln W_p, the partials end up with the weights
 // e^{Lam_p - Lam_total} (the product of a partial's own W_p and the 1 - W of every later
 // step), and the fold of the Lam alone does not need the o.  So: each lane takes the Lam of
@@ -311,24 +311,31 @@ void perkey_kernel(Problem p) {
 // every exponent at or below zero), and the output is one pass of independent loads,
 // sum_p e^{Lam_p - Lam_total} o_p.  Left to right instead, a launch with 64 splits and few
 // rows waits for memory 64 times in a row (43 us, against 22 us for the kernel that wrote
-// the partials; a few us this way).
-// state_out may be the buffer the single partial came from, or state_in: a wavefront reads
-// all of its row before it writes.
-template <typename T, int D, int kBatch>            // kBatch: partial rows in flight per lane
+// the partials; a few us this way).  It is one wait for memory that bounds the launch: with more
+// than 8 splits the wavefronts of a workgroup share a row, 16 splits each, so that all of its
+// partials are in flight at once (64 splits: 7.8 us as two batches of 32 by one wavefront).
+// state_out may be the buffer the single partial came from, or state_in: all of a row is read
+// before it is written.
+template <typename T, int D, int kShare>            // kShare: wavefronts per row
 __global__ __launch_bounds__(256)
 void merge_splits_kernel(Problem p) {
+    constexpr int kBatch = kShare == 1 ? 8 : 16;   // partial rows per wavefront
+    static_assert(kShare * kBatch == (kShare == 1 ? 8 : 64), "64 splits are the most there are");
     constexpr int E = D / kWave;                   // output elements per lane
     using state_t = typename Chunk<T>::state_t;    // fp32 storage folds s - ln w in fp64
+    __shared__ float share[kShare == 1 ? 1 : kShare][kShare == 1 ? 1 : D];
     const state_t ninf = (state_t)(-__builtin_inff());
     const size_t rows = (size_t)p.B * p.Hq * p.Lq;
     const int lane = threadIdx.x & (kWave - 1);
-    const size_t row = (size_t)blockIdx.x * (256 / kWave) + (threadIdx.x >> 6);
-    if (row >= rows) return;                       // the whole wavefront leaves together
+    const int wave = threadIdx.x >> 6;
+    constexpr int kRows = 4 / kShare;              // rows of a workgroup at a time
+    const int sp0 = kShare == 1 ? 0 : wave * kBatch;     // this wavefront's splits
 
-    // the first batch of partial rows is requested before the weights are known: the loads
-    // do not depend on them, and the fold of the Lam then runs while they are in flight
-    float ob[kBatch][E];
-    auto fetch = [&](int sp0) {
+    for (size_t row = (size_t)blockIdx.x * kRows + (kShare == 1 ? wave : 0); row < rows;
+         row += (size_t)gridDim.x * kRows) {
+        // the partial rows are requested before the weights are known: the loads do not depend
+        // on them, and the fold of the Lam then runs while they are in flight
+        float ob[kBatch][E];
 #pragma unroll
         for (int u = 0; u < kBatch; ++u) {
             const int sp = min(sp0 + u, p.splits - 1);
@@ -336,74 +343,81 @@ void merge_splits_kernel(Problem p) {
 #pragma unroll
             for (int e = 0; e < E; ++e) ob[u][e] = src[lane * E + e];
         }
-    };
-    fetch(0);
-    state_t lam_p = ninf;
-    if (lane < p.splits) {
-        const float* src = p.ws + ((size_t)lane * rows + row) * (D + 2);
-        lam_p = (state_t)src[D] - (state_t)src[D + 1];               // s - ln w
-    }
-    state_t lam_in = ninf;
-    float oin[E];
+        state_t lam_p = ninf;
+        if (lane < p.splits) {
+            const float* src = p.ws + ((size_t)lane * rows + row) * (D + 2);
+            lam_p = (state_t)src[D] - (state_t)src[D + 1];               // s - ln w
+        }
+        state_t lam_in = ninf;
+        float oin[E];
 #pragma unroll
-    for (int e = 0; e < E; ++e) oin[e] = 0.0f;
-    if (p.state_in) {
-        const float* sin = p.state_in + row * (D + 2);
-        lam_in = (state_t)sin[D] - (state_t)sin[D + 1];
+        for (int e = 0; e < E; ++e) oin[e] = 0.0f;
+        if (p.state_in) {
+            const float* sin = p.state_in + row * (D + 2);
+            lam_in = (state_t)sin[D] - (state_t)sin[D + 1];
 #pragma unroll
-        for (int e = 0; e < E; ++e) oin[e] = sin[lane * E + e];
-    }
-    state_t tot = lam_p;
+            for (int e = 0; e < E; ++e) oin[e] = sin[lane * E + e];
+        }
+        state_t tot = lam_p;
 #pragma unroll
-    for (int off = 1; off < kWave; off <<= 1) {
-        const state_t other = __shfl_xor(tot, off);
-        const bool upper = (lane & off) != 0;      // both lanes of a pair fold (lower, upper)
-        float W;
-        merge_weight(upper ? other : tot, upper ? tot : other, W, tot);
-    }
-    {
-        float W;
-        merge_weight(lam_in, tot, W, tot);
-    }
-    const float w_p = lam_p == ninf ? 0.0f : __expf((float)(lam_p - tot));
-    const float w_in = lam_in == ninf ? 0.0f : __expf((float)(lam_in - tot));
+        for (int off = 1; off < kWave; off <<= 1) {
+            const state_t other = __shfl_xor(tot, off);
+            const bool upper = (lane & off) != 0;      // both lanes of a pair fold (lower, upper)
+            float W;
+            merge_weight(upper ? other : tot, upper ? tot : other, W, tot);
+        }
+        {
+            float W;
+            merge_weight(lam_in, tot, W, tot);
+        }
+        const float w_p = lam_p == ninf ? 0.0f : __expf((float)(lam_p - tot));
+        const float w_in = lam_in == ninf ? 0.0f : __expf((float)(lam_in - tot));
 
-    float acc[E];
+        float acc[E];
 #pragma unroll
-    for (int e = 0; e < E; ++e) acc[e] = w_in != 0.0f ? w_in * oin[e] : 0.0f;
-    for (int sp0 = 0; sp0 < p.splits; sp0 += kBatch) {
-        if (sp0 > 0) fetch(sp0);
+        for (int e = 0; e < E; ++e) acc[e] = w_in != 0.0f && sp0 == 0 ? w_in * oin[e] : 0.0f;
 #pragma unroll
         for (int u = 0; u < kBatch; ++u) {
             const float w = sp0 + u < p.splits ? __shfl(w_p, sp0 + u) : 0.0f;
-            if (w != 0.0f) {                       // a partial of weight 0 may hold anything
+            if (w != 0.0f) {                           // a partial of weight 0 may hold anything
 #pragma unroll
                 for (int e = 0; e < E; ++e) acc[e] = fmaf(w, ob[u][e], acc[e]);
             }
         }
-    }
-    if (p.o) {
+        if constexpr (kShare > 1) {
 #pragma unroll
-        for (int e = 0; e < E; ++e) Store<T>::store(p.o, row * D + lane * E + e, acc[e]);
-    }
-    if (p.state_out) {
-        float* dst = p.state_out + row * (D + 2);
+            for (int e = 0; e < E; ++e) share[wave][lane * E + e] = acc[e];
+            __syncthreads();
+            if (wave == 0) {
 #pragma unroll
-        for (int e = 0; e < E; ++e) dst[lane * E + e] = acc[e];
-        if (lane == 0) split_lam(tot, dst[D], dst[D + 1]);
+                for (int w = 1; w < kShare; ++w)
+#pragma unroll
+                    for (int e = 0; e < E; ++e) acc[e] += share[w][lane * E + e];
+            }
+        }
+        if (p.o && (kShare == 1 || wave == 0)) {
+#pragma unroll
+            for (int e = 0; e < E; ++e) Store<T>::store(p.o, row * D + lane * E + e, acc[e]);
+        }
+        if (p.state_out && (kShare == 1 || wave == 0)) {
+            float* dst = p.state_out + row * (D + 2);
+#pragma unroll
+            for (int e = 0; e < E; ++e) dst[lane * E + e] = acc[e];
+            if (lane == 0) split_lam(tot, dst[D], dst[D + 1]);
+        }
+        if (kShare > 1) __syncthreads();           // the shared sums have been read
     }
 }
 
 template <typename T, int D>
 static hipError_t launch_merge_t(const Problem& p, hipStream_t st) {
     const size_t rows = (size_t)p.B * p.Hq * p.Lq;
-    if ((rows + 3) / 4 > 0x7fffffffull) return hipErrorInvalidValue;
-    const unsigned blocks = (unsigned)((rows + 3) / 4);
-    // many splits come with few rows: more loads in flight per lane, fewer round trips
+    const size_t blocks = p.splits > 8 ? rows : (rows + 3) / 4;
+    const unsigned grid = (unsigned)(blocks < (1u << 22) ? blocks : (1u << 22));
     if (p.splits > 8)
-        hipLaunchKernelGGL((merge_splits_kernel<T, D, 32>), dim3(blocks), dim3(256), 0, st, p);
+        hipLaunchKernelGGL((merge_splits_kernel<T, D, 4>), dim3(grid), dim3(256), 0, st, p);
     else
-        hipLaunchKernelGGL((merge_splits_kernel<T, D, 8>), dim3(blocks), dim3(256), 0, st, p);
+        hipLaunchKernelGGL((merge_splits_kernel<T, D, 1>), dim3(grid), dim3(256), 0, st, p);
     return hipGetLastError();
 }
 
