@@ -357,7 +357,7 @@ void decode_kernel(Problem p) {
 // multiplies block b - 4's coefficients with its V (requested an iteration ago), updates the
 // rows with block b's coefficients and only then decides whether to request V(b).  The order
 // of the operations on the accumulator is that of decode_kernel.
-constexpr float kSkipMarginLog2 = 200.0f;
+// (kSkipMarginLog2 in flashd_mma.h: 2^200.)
 
 template <typename T, int D, bool TL>
 __global__ __launch_bounds__(kDecThreads, 2)
@@ -596,6 +596,7 @@ long decode_workgroups(int B, int Hkv) { return (long)B * Hkv; }
 
 hipError_t launch_decode(const Problem& p, int mode, hipStream_t st) {
     if (!decode_applies(p.Hq, p.Hkv, p.Lq)) return hipErrorInvalidValue;
+    if (decode16_applies(p, mode)) return launch_decode16(p, mode, st);
     if (p.dtype == 1 && p.d == 64) return launch_decode_t<F16, 64>(p, mode, st);
     if (p.dtype == 1 && p.d == 128) return launch_decode_t<F16, 128>(p, mode, st);
     if (p.dtype == 2 && p.d == 64) return launch_decode_t<BF16, 64>(p, mode, st);

@@ -40,6 +40,10 @@ long tile_workgroups(int B, int Hq, int Hkv, int Lq, int d);
 // Split-K decode on the matrix cores for (Hq / Hkv) * Lq <= 32 query rows per kv head
 // (f16/bf16); mode as for launch_tile.  With p.splits > 1 also folds the partials.
 hipError_t launch_decode(const Problem& p, int mode, hipStream_t st);
+// The same on 16-column score tiles, for at most 16 rows and the TILE modes; launch_decode hands
+// over to it.
+bool decode16_applies(const Problem& p, int mode);
+hipError_t launch_decode16(const Problem& p, int mode, hipStream_t st);
 bool decode_applies(int Hq, int Hkv, int Lq);
 long decode_workgroups(int B, int Hkv);
 

@@ -25,6 +25,10 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
 
+// How far, in log2 units, a block's top score must lie below a bound of the row's final Lam for its
+// V not to be fetched (the saturation skip of the decode kernels; flashd_decode.hip says why).
+constexpr float kSkipMarginLog2 = 200.0f;
+
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 

@@ -1,0 +1,81 @@
+"""The decode kernel with 16-column score tiles: row counts around its 16 columns, key counts
+around its 32-key blocks and the turns of its four wavefronts, splits with ranges that end inside
+a block or lie past the last key, and what the skip, the fp8 cache and the state add to that."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import attention as oa
+from paper_2505_14201_amd import flashd, synthetic
+from tests.gpu_util import check, run_flashd
+from tests.test_gpu_state import check_state, run_chunks
+
+pytestmark = pytest.mark.gpu
+TILE, AUTO = flashd.VARIANT_TILE, flashd.VARIANT_AUTO
+DT = {"f16": torch.float16, "bf16": torch.bfloat16}
+
+# (B, Hq, Hkv, Lq, Lk, causal)
+SHAPES = [(1, 1, 1, 1, 1, False),
+          (2, 2, 1, 1, 31, False), (1, 2, 2, 1, 32, False), (1, 4, 2, 1, 33, False),
+          (1, 15, 1, 1, 127, False), (1, 16, 1, 1, 129, False),    # 15 and 16 rows
+          (2, 4, 1, 4, 70, True),                                 # 16 rows, causal positions
+          (1, 5, 1, 3, 2, True),                                  # rows that see no key
+          (1, 17, 1, 1, 129, False)]                              # 17: the wider kernel
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("f16", 64), ("f16", 128), ("bf16", 64)])
+def test_edges(shape, dtype, d):
+    B, Hq, Hkv, Lq, Lk, causal = shape
+    w = synthetic.small("t", B, Hq, Hkv, Lq, Lk, d, dtype, causal, seed=9700 + Hq * 5 + Lk)
+    q, k, v, _ = synthetic.make_qkv(w)
+    ref = oa.attn(q, k, v, causal, w.scale)
+    for splits in (1, 2, 5):
+        if splits <= Lk:
+            check(run_flashd(q, k, v, causal, w.scale, TILE, splits), ref, DT[dtype], f"splits={splits}")
+            check(run_flashd(q, k, v, causal, w.scale, AUTO, splits), ref, DT[dtype], f"auto {splits}")
+    check(run_flashd(q, k, v, causal, -w.scale, TILE, 1), oa.attn(q, k, v, causal, -w.scale), DT[dtype],
+          "negative scale")
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+def test_moving_references(dtype):
+    """Keys that grow along the range: every block lies above the reference, by more than the
+    storage type of the coefficients holds."""
+    w = synthetic.small("t", 1, 8, 2, 1, 900, 128, dtype, False, seed=9800, qk_std=4.0)
+    q, k, v, _ = synthetic.make_qkv(w)
+    k = (k.float() * torch.linspace(0.05, 4.0, 900).view(1, 1, -1, 1)).to(k.dtype)
+    ref = oa.attn(q, k, v, False, w.scale)
+    for variant in (TILE, AUTO):
+        for splits in (1, 3):
+            check(run_flashd(q, k, v, False, w.scale, variant, splits), ref, DT[dtype])
+
+
+def test_state_of_a_decode_step():
+    w = synthetic.small("t", 2, 8, 2, 2, 333, 128, "bf16", True, seed=9810)
+    q, k, v, _ = synthetic.make_qkv(w)
+    o, st = run_chunks(q, k, v, True, w.scale, (40, 200), in_place=True)
+    check(o, oa.attn(q, k, v, True, w.scale), torch.bfloat16)
+    check_state(st, oa.attn_state(q, k, v, True, w.scale), 128, torch.bfloat16, "state")
+
+
+@pytest.mark.parametrize("B,Hkv,Lk", [(1, 2, 70), (64, 8, 65)])     # K through LDS, K direct
+@pytest.mark.parametrize("d", [64, 128])
+def test_fp8_cache(B, Hkv, Lk, d):
+    w = synthetic.small("t", B, 4 * Hkv, Hkv, 1, Lk, d, "bf16", False, seed=9820)
+    q, k, v, _ = synthetic.make_qkv(w)
+    k8, v8 = (k.float() * 32).to(torch.float8_e4m3fn), (v.float() * 32).to(torch.float8_e4m3fn)
+    o = torch.full_like(q, float("nan")).cuda()
+    flashd.attn_fwd_kv8(q.cuda(), k8.cuda(), v8.cuda(), o, False, w.scale, 1 / 32, 1 / 32)
+    sc = float(np.float32(w.scale) * np.float32(1 / 32))
+    check(o.cpu(), oa.attn(q, k8.float(), v8.float(), False, sc) / 32, torch.bfloat16)
+
+
+@pytest.mark.parametrize("splits", [8, 9, 16, 17, 64])
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("f32", 64)])
+def test_merge_of_many_splits(splits, dtype, d):
+    """Up to 8 splits a wavefront folds a row, from 9 on four wavefronts share it."""
+    w = synthetic.small("t", 1, 4, 2, 3, 140, d, dtype, True, seed=9830)
+    q, k, v, _ = synthetic.make_qkv(w)
+    t = torch.float32 if dtype == "f32" else DT[dtype]
+    check(run_flashd(q, k, v, True, w.scale, AUTO, splits), oa.attn(q, k, v, True, w.scale), t)
