@@ -77,20 +77,50 @@ size_t partial_bytes(const Shape& s, int n) {
     return (size_t)n * s.B * s.Hq * s.Lq * (size_t)(s.d + 2) * sizeof(float);
 }
 
+// Splits for decode shapes (measured over 3 to 512 (b, kv head) units, 260 to 131072 keys and
+// every split count).
+//   - Short key ranges stay whole: a second launch and its gap cost 4 us, a 32-key block takes a
+//     wavefront 1 us at d = 128 and half of that at 64.  8 units of 600 keys: 8.1 us whole, 9.0
+//     in any number of splits; of 1000 keys 10.5 and 9.0.
+//   - What fills the chip is one workgroup on most compute units, not two: 48 units of 4000 keys
+//     21.2 us in 4 splits (192 workgroups), 25.6 in 6 (288), 21.9 in 8; 160 units 50.6 us whole,
+//     59.4 in 4 splits; 24 units 14.0 in 8, 17.1 in 12.  From 128 units on only long ranges gain
+//     from 2 splits (8000 keys 84 to 88 us, 89 whole; 1500 keys 20.9 and 19.4), and a little
+//     above 256 units, where few compute units would have a second workgroup.
+//   - Up to 8 splits cost the merge the same; with few units more of them pay until a wavefront
+//     has two blocks left (8 units of 16000 keys: 29 us in 8, 17.7 in 32, 16.8 in 64; 4 units of
+//     20000 keys 15.4 in 64), but not against the one workgroup per compute unit once the
+//     ranges are long (8 units of 131072 keys: 84.9 us in 24, 86.6 in 32, 110.9 in 36, 89.8 in 64).
+//   - 17 to 32 query rows: the wider kernel takes 1.5 us a block, half a block is left per
+//     wavefront (4 units of 3000 keys: 20.3 us in 8 splits, 16.2 in 48).
+int decode_splits(const Shape& s) {
+    const long units = flashd::decode_workgroups(s.B, s.Hkv);
+    const long blocks = (s.Lk + 31L) / 32;
+    const bool wide = (long)(s.Hq / s.Hkv) * s.Lq > 16;
+    if (blocks * s.d <= (wide ? 1024 : 2560)) return 1;
+    if (units >= 128) return (units <= 128 ? blocks >= 128 : units > 256 && units < 342 && blocks >= 64) ? 2 : 1;
+    const long few = blocks / 4 < 8 ? blocks / 4 : 8;
+    const long many = blocks / (wide ? 2 : 8);
+    const long most = units <= 8 && blocks < 2048 ? FLASHD_MAX_SPLITS : 192 / units;
+    long sp = few > many ? few : many;
+    if (sp > most) sp = most;
+    return (int)(sp < 1 ? 1 : sp > FLASHD_MAX_SPLITS ? FLASHD_MAX_SPLITS : sp);
+}
+
 // Splits for the automatic choice: enough independent work to fill 256 compute units, but
 // never key ranges shorter than 256 keys.
 int auto_splits(const Shape& s, int variant) {
+    if (variant != FLASHD_VARIANT_PER_KEY && flashd::decode_applies(s.Hq, s.Hkv, s.Lq))
+        return decode_splits(s);
     long units;
     if (variant == FLASHD_VARIANT_PER_KEY) {
         const int rows_per_group = (s.d <= 64 ? 2 : 1) * 4;             // 4 wavefronts
         units = (long)s.B * s.Hq * ceil_div(s.Lq, rows_per_group);      // workgroups
-    } else if (flashd::decode_applies(s.Hq, s.Hkv, s.Lq)) {
-        units = flashd::decode_workgroups(s.B, s.Hkv);
     } else {
         units = flashd::tile_workgroups(s.B, s.Hq, s.Hkv, s.Lq, s.d);
     }
     // Two workgroups are resident per compute unit (512 in all), and one full round of them
-    // is what the matrix-core kernels want: measured over decode, short-query and prefill
+    // is what the tile kernel wants: measured over short-query and prefill
     // shapes of 64 to 512 units, the fastest split count is the one that brings the launch
     // to 256-512 workgroups; more of them only add partial states to write and merge.  The
     // per-key kernel keeps two rounds.
@@ -98,7 +128,7 @@ int auto_splits(const Shape& s, int variant) {
     if (units < 1) units = 1;
     long sp = units >= target ? 1 : ceil_div(target, units);
     // A split costs its partial states: (d + 2) floats per query row written and read back.
-    // With one row per head (decode) that is nothing and 256 keys are enough to pay for a
+    // For the per-key kernel 256 keys are enough to pay for a
     // split; the tile kernel's workgroups carry 128 rows each, and measured over prefill
     // shapes a split only pays once it still holds some 2048 keys (B1 H32 L1024 causal:
     // 23 us unsplit, 39 us in two splits of 512 keys).
@@ -106,8 +136,7 @@ int auto_splits(const Shape& s, int variant) {
     // heads x 8 positions over 4096 keys runs 15 us in 16 splits, 45 us in 2) the partial
     // states are small again: splits of 256 keys are allowed as long as all the partial
     // states together stay within some 40 MB.
-    const bool tile = variant != FLASHD_VARIANT_PER_KEY &&
-                      !flashd::decode_applies(s.Hq, s.Hkv, s.Lq);
+    const bool tile = variant != FLASHD_VARIANT_PER_KEY;
     long by_len = s.Lk / (tile ? 2048 : 256);
     if (tile) {
         const long double per_split = (long double)partial_bytes(s, 1) * 2.0L;   // written and read

@@ -19,3 +19,17 @@ T, W = flashd.VARIANT_TILE, flashd.VARIANT_TILE_256
 ])
 def test_padded_256_row_tiles(B, Hq, Hkv, Lq, Lk, causal, want):
     assert flashd.auto_variant(B, Hq, Hkv, Lq, Lk, 128, flashd.BF16, causal) == want
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,Lq,Lk,d,want", [
+    (1, 32, 8, 1, 640, 128, 1), (1, 32, 8, 1, 641, 128, 5),     # 20 and 21 blocks of 32 keys
+    (1, 32, 8, 1, 1280, 64, 1),
+    (6, 32, 8, 1, 4000, 128, 4),             # 48 units: one workgroup on 192 compute units
+    (20, 32, 8, 1, 4000, 128, 1),            # 160 units stay whole
+    (16, 32, 8, 1, 1500, 128, 1), (16, 32, 8, 1, 8000, 128, 2),
+    (40, 32, 8, 1, 4000, 128, 2), (48, 32, 8, 1, 4000, 128, 1),
+    (1, 32, 8, 1, 131072, 128, 24),
+    (1, 32, 1, 1, 256, 128, 1), (1, 32, 1, 1, 512, 128, 8),     # 32 rows: the wider kernel
+])
+def test_decode_splits(B, Hq, Hkv, Lq, Lk, d, want):
+    assert flashd.auto_splits(B, Hq, Hkv, Lq, Lk, d, flashd.BF16) == want
