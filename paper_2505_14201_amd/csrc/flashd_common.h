@@ -90,6 +90,10 @@ template <> struct Store<F32> {
     static __device__ __forceinline__ void store(void* p, size_t i, float x) {
         static_cast<float*>(p)[i] = x;
     }
+    // 4 consecutive elements starting at element index i (i % 4 == 0)
+    static __device__ __forceinline__ void store4(void* p, size_t i, const float (&x)[4]) {
+        *reinterpret_cast<float4*>(static_cast<float*>(p) + i) = float4{x[0], x[1], x[2], x[3]};
+    }
     // 8 consecutive elements starting at element index i (i % 8 == 0)
     static __device__ __forceinline__ void load8(const void* p, size_t i, float (&out)[8]) {
         const float4* s = reinterpret_cast<const float4*>(static_cast<const float*>(p) + i);
@@ -105,6 +109,12 @@ template <> struct Store<F16> {
     static __device__ __forceinline__ void store(void* p, size_t i, float x) {
         static_cast<_Float16*>(p)[i] = static_cast<_Float16>(x);
     }
+    static __device__ __forceinline__ void store4(void* p, size_t i, const float (&x)[4]) {
+        typedef _Float16 h4 __attribute__((ext_vector_type(4)));
+        *reinterpret_cast<h4*>(static_cast<_Float16*>(p) + i) =
+            h4{static_cast<_Float16>(x[0]), static_cast<_Float16>(x[1]),
+               static_cast<_Float16>(x[2]), static_cast<_Float16>(x[3])};
+    }
     static __device__ __forceinline__ void load8(const void* p, size_t i, float (&out)[8]) {
         typedef _Float16 h8 __attribute__((ext_vector_type(8)));
         h8 a = *reinterpret_cast<const h8*>(static_cast<const _Float16*>(p) + i);
@@ -118,6 +128,10 @@ template <> struct Store<BF16> {
     }
     static __device__ __forceinline__ void store(void* p, size_t i, float x) {
         static_cast<uint16_t*>(p)[i] = f32_to_bf16(x);
+    }
+    static __device__ __forceinline__ void store4(void* p, size_t i, const float (&x)[4]) {
+        *reinterpret_cast<ushort4*>(static_cast<uint16_t*>(p) + i) =
+            ushort4{f32_to_bf16(x[0]), f32_to_bf16(x[1]), f32_to_bf16(x[2]), f32_to_bf16(x[3])};
     }
     static __device__ __forceinline__ void load8(const void* p, size_t i, float (&out)[8]) {
         uint4 a = *reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(p) + i);

@@ -302,37 +302,108 @@ void perkey_kernel(Problem p) {
 // earlier keys if one is given (p.state_in).  Writes the output (p.o, if not null) and the
 // state (p.state_out, if not null) as the run seen as one key: (o, s = Lam, ln w = 0).
 //
-// One wavefront per row for up to 8 splits, four for more.  Folded one after the other, o <- o + (o_p - o) W_p with
-// W_p = sigmoid(Lam_p - Lam) and Lam <- Lam_p - ln W_p, the partials end up with the weights
-// e^{Lam_p - Lam_total} (the product of a partial's own W_p and the 1 - W of every later
-// step), and the fold of the Lam alone does not need the o.  So: each lane takes the Lam of
-// one partial (at most 64 splits), a butterfly of sigmoid merges gives every lane Lam_total
-// (the rule is associative and commutative; no maximum is taken, and Lam_total >= Lam_p keeps
-// every exponent at or below zero), and the output is one pass of independent loads,
-// sum_p e^{Lam_p - Lam_total} o_p.  Left to right instead, a launch with 64 splits and few
-// rows waits for memory 64 times in a row (43 us, against 22 us for the kernel that wrote
-// the partials; a few us this way).  It is one wait for memory that bounds the launch: with more
-// than 8 splits the wavefronts of a workgroup share a row, 16 splits each, so that all of its
-// partials are in flight at once (64 splits: 7.8 us as two batches of 32 by one wavefront).
-// state_out may be the buffer the single partial came from, or state_in: all of a row is read
-// before it is written.
-template <typename T, int D, int kShare>            // kShare: wavefronts per row
+// Folded one after the other, o <- o + (o_p - o) W_p with W_p = sigmoid(Lam_p - Lam) and
+// Lam <- Lam_p - ln W_p, the partials end up with the weights e^{Lam_p - Lam_total} (the product
+// of a partial's own W_p and the 1 - W of every later step), and the fold of the Lam alone does
+// not need the o.  So: the Lam are folded pairwise (the rule is associative and commutative; no
+// maximum is taken, and Lam_total >= Lam_p keeps every exponent at or below zero), and the output
+// is one pass of independent loads, sum_p e^{Lam_p - Lam_total} o_p, requested before the fold.
+// state_out may be the buffer the single partial came from, or state_in: a row belongs to one
+// wavefront (one workgroup in the second kernel), which reads all of it before it writes.
+//
+// Up to 16 splits: D / 4 lanes per row, four columns each; every lane folds the Lam of its row
+// itself, NS of them in log2 NS steps.  What bounds it is the reading of the partials, which
+// prefill shapes with split keys have by the 10 MB: a wavefront per row, its Lam over the lanes
+// and one or two columns per lane, made a call with 32768 rows of 2 partials, d = 64, take 32.9 us,
+// now 23.0 (5.2 of them this kernel); 4 x 8000 rows, d = 128, 50.6 and 46.8; 1 x 1000 keys of a
+// decode step in 8 splits 8.5 and 8.2.
+template <typename T, int D, int NS>                // NS: splits, rounded up to a power of two
+__global__ __launch_bounds__(256)
+void merge_few_kernel(Problem p) {
+    constexpr int kLanes = D / 4;                  // lanes of a row
+    constexpr int kRows = 256 / kLanes;            // rows of a workgroup at a time
+    // rows of partial states are d + 2 floats long, so 8-byte aligned
+    typedef float f4 __attribute__((ext_vector_type(4), aligned(8)));
+    typedef float f2 __attribute__((ext_vector_type(2), aligned(8)));
+    using state_t = typename Chunk<T>::state_t;    // fp32 storage folds s - ln w in fp64
+    const state_t ninf = (state_t)(-__builtin_inff());
+    const size_t rows = (size_t)p.B * p.Hq * p.Lq;
+    const int t = 4 * (threadIdx.x % kLanes);
+
+    for (size_t row = (size_t)blockIdx.x * kRows + threadIdx.x / kLanes; row < rows;
+         row += (size_t)gridDim.x * kRows) {
+        f4 ob[NS];
+        state_t lam[NS];
+#pragma unroll
+        for (int u = 0; u < NS; ++u) {
+            const float* src = p.ws + ((size_t)min(u, p.splits - 1) * rows + row) * (D + 2);
+            ob[u] = *reinterpret_cast<const f4*>(src + t);
+            const f2 sl = *reinterpret_cast<const f2*>(src + D);
+            lam[u] = u < p.splits ? (state_t)sl[0] - (state_t)sl[1] : ninf;   // s - ln w
+        }
+        state_t lam_in = ninf;
+        f4 oin = {0.0f, 0.0f, 0.0f, 0.0f};
+        if (p.state_in) {
+            const float* sin = p.state_in + row * (D + 2);
+            const f2 sl = *reinterpret_cast<const f2*>(sin + D);
+            lam_in = (state_t)sl[0] - (state_t)sl[1];
+            oin = *reinterpret_cast<const f4*>(sin + t);
+        }
+        state_t fold[NS];
+#pragma unroll
+        for (int u = 0; u < NS; ++u) fold[u] = lam[u];
+#pragma unroll
+        for (int n = 1; n < NS; n <<= 1)
+#pragma unroll
+            for (int u = 0; u < NS; u += 2 * n) {
+                float W;
+                merge_weight(fold[u], fold[u + n], W, fold[u]);
+            }
+        state_t tot = fold[0];
+        {
+            float W;
+            merge_weight(lam_in, tot, W, tot);
+        }
+        const float w_in = lam_in == ninf ? 0.0f : __expf((float)(lam_in - tot));
+        float acc[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[e] = w_in != 0.0f ? w_in * oin[e] : 0.0f;
+#pragma unroll
+        for (int u = 0; u < NS; ++u) {
+            const float w = lam[u] == ninf ? 0.0f : __expf((float)(lam[u] - tot));
+            // a partial of weight 0 may hold anything
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[e] = w != 0.0f ? fmaf(w, ob[u][e], acc[e]) : acc[e];
+        }
+        if (p.o) Store<T>::store4(p.o, row * D + t, acc);
+        if (p.state_out) {
+            float* dst = p.state_out + row * (D + 2);
+            *reinterpret_cast<f4*>(dst + t) = f4{acc[0], acc[1], acc[2], acc[3]};
+            if (t == 0) split_lam(tot, dst[D], dst[D + 1]);
+        }
+    }
+}
+
+// 17 to 64 splits: the rows are few then, and one wait for memory bounds the launch.  The four
+// wavefronts of a workgroup share a row, 16 splits each, so that all of its partials are in flight
+// at once (64 splits: 7.8 us as two batches of 32 by one wavefront, 4 us); the lanes take the Lam
+// of a split each and fold them by a butterfly.
+template <typename T, int D>
 __global__ __launch_bounds__(256)
 void merge_splits_kernel(Problem p) {
-    constexpr int kBatch = kShare == 1 ? 8 : 16;   // partial rows per wavefront
-    static_assert(kShare * kBatch == (kShare == 1 ? 8 : 64), "64 splits are the most there are");
+    constexpr int kBatch = 16;                     // partial rows per wavefront
+    constexpr int kShare = 4;                      // wavefronts per row
+    static_assert(kShare * kBatch == 64, "64 splits are the most there are");
     constexpr int E = D / kWave;                   // output elements per lane
-    using state_t = typename Chunk<T>::state_t;    // fp32 storage folds s - ln w in fp64
-    __shared__ float share[kShare == 1 ? 1 : kShare][kShare == 1 ? 1 : D];
+    using state_t = typename Chunk<T>::state_t;
+    __shared__ float share[kShare][D];
     const state_t ninf = (state_t)(-__builtin_inff());
     const size_t rows = (size_t)p.B * p.Hq * p.Lq;
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = threadIdx.x >> 6;
-    constexpr int kRows = 4 / kShare;              // rows of a workgroup at a time
-    const int sp0 = kShare == 1 ? 0 : wave * kBatch;     // this wavefront's splits
+    const int sp0 = wave * kBatch;                 // this wavefront's splits
 
-    for (size_t row = (size_t)blockIdx.x * kRows + (kShare == 1 ? wave : 0); row < rows;
-         row += (size_t)gridDim.x * kRows) {
+    for (size_t row = blockIdx.x; row < rows; row += gridDim.x) {
         // the partial rows are requested before the weights are known: the loads do not depend
         // on them, and the fold of the Lam then runs while they are in flight
         float ob[kBatch][E];
@@ -384,40 +455,41 @@ void merge_splits_kernel(Problem p) {
                 for (int e = 0; e < E; ++e) acc[e] = fmaf(w, ob[u][e], acc[e]);
             }
         }
-        if constexpr (kShare > 1) {
 #pragma unroll
-            for (int e = 0; e < E; ++e) share[wave][lane * E + e] = acc[e];
-            __syncthreads();
-            if (wave == 0) {
+        for (int e = 0; e < E; ++e) share[wave][lane * E + e] = acc[e];
+        __syncthreads();
+        if (wave == 0) {
 #pragma unroll
-                for (int w = 1; w < kShare; ++w)
+            for (int w = 1; w < kShare; ++w)
 #pragma unroll
-                    for (int e = 0; e < E; ++e) acc[e] += share[w][lane * E + e];
+                for (int e = 0; e < E; ++e) acc[e] += share[w][lane * E + e];
+            if (p.o) {
+#pragma unroll
+                for (int e = 0; e < E; ++e) Store<T>::store(p.o, row * D + lane * E + e, acc[e]);
+            }
+            if (p.state_out) {
+                float* dst = p.state_out + row * (D + 2);
+#pragma unroll
+                for (int e = 0; e < E; ++e) dst[lane * E + e] = acc[e];
+                if (lane == 0) split_lam(tot, dst[D], dst[D + 1]);
             }
         }
-        if (p.o && (kShare == 1 || wave == 0)) {
-#pragma unroll
-            for (int e = 0; e < E; ++e) Store<T>::store(p.o, row * D + lane * E + e, acc[e]);
-        }
-        if (p.state_out && (kShare == 1 || wave == 0)) {
-            float* dst = p.state_out + row * (D + 2);
-#pragma unroll
-            for (int e = 0; e < E; ++e) dst[lane * E + e] = acc[e];
-            if (lane == 0) split_lam(tot, dst[D], dst[D + 1]);
-        }
-        if (kShare > 1) __syncthreads();           // the shared sums have been read
+        __syncthreads();                               // the shared sums have been read
     }
 }
 
 template <typename T, int D>
 static hipError_t launch_merge_t(const Problem& p, hipStream_t st) {
     const size_t rows = (size_t)p.B * p.Hq * p.Lq;
-    const size_t blocks = p.splits > 8 ? rows : (rows + 3) / 4;
-    const unsigned grid = (unsigned)(blocks < (1u << 22) ? blocks : (1u << 22));
-    if (p.splits > 8)
-        hipLaunchKernelGGL((merge_splits_kernel<T, D, 4>), dim3(grid), dim3(256), 0, st, p);
-    else
-        hipLaunchKernelGGL((merge_splits_kernel<T, D, 1>), dim3(grid), dim3(256), 0, st, p);
+    constexpr size_t kFewRows = 256 / (D / 4);
+    const size_t blocks = p.splits > 16 ? rows : (rows + kFewRows - 1) / kFewRows;
+    const dim3 grid((unsigned)(blocks < (1u << 22) ? blocks : (1u << 22))), block(256);
+    if (p.splits > 16) hipLaunchKernelGGL((merge_splits_kernel<T, D>), grid, block, 0, st, p);
+    else if (p.splits > 8) hipLaunchKernelGGL((merge_few_kernel<T, D, 16>), grid, block, 0, st, p);
+    else if (p.splits > 4) hipLaunchKernelGGL((merge_few_kernel<T, D, 8>), grid, block, 0, st, p);
+    else if (p.splits > 2) hipLaunchKernelGGL((merge_few_kernel<T, D, 4>), grid, block, 0, st, p);
+    else if (p.splits > 1) hipLaunchKernelGGL((merge_few_kernel<T, D, 2>), grid, block, 0, st, p);
+    else hipLaunchKernelGGL((merge_few_kernel<T, D, 1>), grid, block, 0, st, p);
     return hipGetLastError();
 }
 
