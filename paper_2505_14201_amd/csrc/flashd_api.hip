@@ -93,11 +93,13 @@ size_t partial_bytes(const Shape& s, int n) {
 //     ranges are long (8 units of 131072 keys: 84.9 us in 24, 86.6 in 32, 110.9 in 36, 89.8 in 64).
 //   - 17 to 32 query rows: the wider kernel takes 1.5 us a block, half a block is left per
 //     wavefront (4 units of 3000 keys: 20.3 us in 8 splits, 16.2 in 48).
+//   - Below 512 keys nothing is split, here as in auto_splits: such calls need no scratch memory,
+//     so they can be captured into a graph without a call before.
 int decode_splits(const Shape& s) {
     const long units = flashd::decode_workgroups(s.B, s.Hkv);
     const long blocks = (s.Lk + 31L) / 32;
     const bool wide = (long)(s.Hq / s.Hkv) * s.Lq > 16;
-    if (blocks * s.d <= (wide ? 1024 : 2560)) return 1;
+    if (s.Lk < 512 || blocks * s.d <= (wide ? 1024 : 2560)) return 1;
     if (units >= 128) return (units <= 128 ? blocks >= 128 : units > 256 && units < 342 && blocks >= 64) ? 2 : 1;
     const long few = blocks / 4 < 8 ? blocks / 4 : 8;
     const long many = blocks / (wide ? 2 : 8);

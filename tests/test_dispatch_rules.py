@@ -30,6 +30,7 @@ def test_padded_256_row_tiles(B, Hq, Hkv, Lq, Lk, causal, want):
     (40, 32, 8, 1, 4000, 128, 2), (48, 32, 8, 1, 4000, 128, 1),
     (1, 32, 8, 1, 131072, 128, 24),
     (1, 32, 1, 1, 256, 128, 1), (1, 32, 1, 1, 512, 128, 8),     # 32 rows: the wider kernel
+    (1, 32, 1, 1, 511, 128, 1), (3, 24, 1, 1, 300, 128, 1),     # below 512 keys: no scratch memory
 ])
 def test_decode_splits(B, Hq, Hkv, Lq, Lk, d, want):
     assert flashd.auto_splits(B, Hq, Hkv, Lq, Lk, d, flashd.BF16) == want
