@@ -40,9 +40,11 @@ typedef double f64x4 __attribute__((ext_vector_type(4)));
 constexpr int kF32Waves = 4;
 constexpr int kF32Rows = 16;       // query rows per workgroup
 constexpr int kF32Block = 16;      // keys per wavefront step
-// l and U may grow by 2^kMoveLog2 per key over what the top key alone would give; small, so that
-// values up to 1e32 or so still sum without overflow
 constexpr double kMoveLog2 = 8.0;
+// Weights of up to 2^kMoveLog2 per key can overflow the sum over large values (1e36 and up, some
+// hundred keys), whose blend would not.  A row tile where that happened is done again with the
+// reference this far above the top score: 1e9 keys of 2^(8 - 40) sum to less than a value.
+constexpr double kHeadroomLog2 = 40.0;
 
 // How workgroups map to work: id -> (rank of the row tile, split, unit), all units' longest row
 // tiles first; unit u on XCD u % 8 where the units divide by 8, so that K and V of a head are
@@ -76,6 +78,7 @@ void tile_f32_kernel(Problem p, F32Sched sc) {
     __shared__ __align__(16) float fold_u[kF32Waves][kF32Rows][FROW];
     __shared__ double fold_r[kF32Waves][kF32Rows];
     __shared__ float fold_l[kF32Waves][kF32Rows];
+    __shared__ int over[kF32Waves];        // a sum of the wavefront may overflow in the fold
 
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1);
@@ -119,7 +122,6 @@ void tile_f32_kernel(Problem p, F32Sched sc) {
         const int chunk = (nblk_all + p.splits - 1) / p.splits;
         const int blk_end = min((nvis_max + kF32Block - 1) / kF32Block, (sp + 1) * chunk);
 
-        const float* qg = static_cast<const float*>(p.q) + q_row(row) * D + 4 * q;
         const float* kg = static_cast<const float*>(p.k) + kv_unit * (size_t)p.Lk * D + 4 * q;
         const float* vg = static_cast<const float*>(p.v) + kv_unit * (size_t)p.Lk * D + 4 * c;
         f32x4 qf[NM], kf[NM];
@@ -129,156 +131,178 @@ void tile_f32_kernel(Problem p, F32Sched sc) {
             for (int m = 0; m < NM; ++m) kf[m] = *reinterpret_cast<const f32x4*>(src + 16 * m);
         };
 
-        f32x4 U[NB][4];                    // [column group][n]: columns 64 i + 16 q + 4 e + n
+        for (int pass = 0;; ++pass) {
+            const double head = pass == 0 ? 0.0 : kHeadroomLog2;
+            const double limit = pass == 0 ? kMoveLog2 : kMoveLog2 - kHeadroomLog2;
+            f32x4 U[NB][4];                    // [column group][n]: columns 64 i + 16 q + 4 e + n
 #pragma unroll
-        for (int i = 0; i < NB; ++i)
+            for (int i = 0; i < NB; ++i)
 #pragma unroll
-            for (int n = 0; n < 4; ++n) U[i][n] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-        float l = 0.0f;                    // this lane's keys
-        double R = ninf;
+                for (int n = 0; n < 4; ++n) U[i][n] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+            float l = 0.0f;                    // this lane's keys
+            double R = ninf;
 
-        int blk = sp * chunk + wave;
-        if (blk < blk_end) {
-            fetch_k(blk);
+            int blk = sp * chunk + wave;
+            if (blk < blk_end) {
+                fetch_k(blk);
+                // (the address is formed anew for each pass: kept, it would cost two registers)
+                int col = c;
+                asm volatile("" : "+v"(col));
+                const float* qg = static_cast<const float*>(p.q) +
+                                  q_row(min(r0 + col, rlast)) * D + 4 * q;
 #pragma unroll
-            for (int m = 0; m < NM; ++m) qf[m] = *reinterpret_cast<const f32x4*>(qg + 16 * m);
-        }
-        for (; blk < blk_end; blk += kF32Waves) {
-            const int j0 = blk * kF32Block;
-            f32x4 vf[NB][4];               // [column group][r]: key 4 r + q, columns 64 i + 4 c ..
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const float* src = vg + (size_t)min(j0 + 4 * r + q, p.Lk - 1) * D;
-#pragma unroll
-                for (int i = 0; i < NB; ++i) vf[i][r] = *reinterpret_cast<const f32x4*>(src + 64 * i);
+                for (int m = 0; m < NM; ++m) qf[m] = *reinterpret_cast<const f32x4*>(qg + 16 * m);
             }
-            f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+            for (; blk < blk_end; blk += kF32Waves) {
+                const int j0 = blk * kF32Block;
+                f32x4 vf[NB][4];           // [column group][r]: key 4 r + q, columns 64 i + 4 c ..
 #pragma unroll
-            for (int m = 0; m < NM; ++m) {
-                // d = 128: widen Q anew for every block, its fp64 form would take 64 registers
-                if (D == 128) asm volatile("" : "+v"(qf[m]));
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)kf[m][e], (double)qf[m][e],
-                                                               acc, 0, 0, 0);
-            }
-            if (blk + kF32Waves < blk_end) fetch_k(blk + kF32Waves);
-
-            const bool masked = j0 + kF32Block > nvis_min;
-            double x[4];
-            double top = ninf;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                x[r] = acc[r] * c_log2;
-                if (masked && j0 + 4 * r + q >= nvis) x[r] = ninf;
-                top = fmax(top, x[r]);
-            }
-            if (__builtin_amdgcn_ballot_w64(top > R + kMoveLog2) != 0) {
-                top = row_reduce(top, [](double a, double bb) { return fmax(a, bb); });
-                if (top > R + kMoveLog2) {
-                    const float f = exp2_fast((float)(R - top));       // 0 for a row without keys
-                    l *= f;
+                for (int r = 0; r < 4; ++r) {
+                    const float* src = vg + (size_t)min(j0 + 4 * r + q, p.Lk - 1) * D;
 #pragma unroll
                     for (int i = 0; i < NB; ++i)
-#pragma unroll
-                        for (int n = 0; n < 4; ++n) U[i][n] *= f;
-                    R = top;
+                        vf[i][r] = *reinterpret_cast<const f32x4*>(src + 64 * i);
                 }
-            }
-            float pw[4];
+                f64x4 acc = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                pw[r] = exp2_fast((float)(x[r] - R));
-                if (masked && j0 + 4 * r + q >= nvis) pw[r] = 0.0f;    // also where R is still -inf
-                l += pw[r];
-            }
-            bool plain = true;
-            if (masked) {
-                // a weight of zero does not silence an infinite or NaN value of a hidden key
-                float bad = 0.0f;
+                for (int m = 0; m < NM; ++m) {
+                    // d = 128: widen Q anew for every block, its fp64 form would take 64 registers
+                    if (D == 128) asm volatile("" : "+v"(qf[m]));
 #pragma unroll
-                for (int i = 0; i < NB; ++i)
+                    for (int e = 0; e < 4; ++e)
+                        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(
+                            (double)kf[m][e], (double)qf[m][e], acc, 0, 0, 0);
+                }
+                if (blk + kF32Waves < blk_end) fetch_k(blk + kF32Waves);
+
+                const bool masked = j0 + kF32Block > nvis_min;
+                double x[4];
+                double top = ninf;
 #pragma unroll
-                    for (int r = 0; r < 4; ++r)
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) bad = fmaf(vf[i][r][e], 0.0f, bad);
-                plain = __builtin_amdgcn_ballot_w64(bad != 0.0f) == 0;
-            }
-            if (plain) {
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-#pragma unroll
-                    for (int i = 0; i < NB; ++i)
-#pragma unroll
-                        for (int n = 0; n < 4; ++n)
-                            U[i][n] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[i][r][n], pw[r],
-                                                                           U[i][n], 0, 0, 0);
-            } else {
-#pragma unroll 1
-                for (int kk = 0; kk < kF32Block; ++kk) {
-                    const float own = (kk >> 2) == 0 ? pw[0] : (kk >> 2) == 1 ? pw[1]
-                                      : (kk >> 2) == 2 ? pw[2] : pw[3];
-                    const float w = __shfl(own, (kk & 3) * 16 + c, kWave);
-                    if (j0 + kk < nvis) {
-                        const float* src = vg - 4 * c + (size_t)(j0 + kk) * D + 16 * q;
+                for (int r = 0; r < 4; ++r) {
+                    x[r] = acc[r] * c_log2;
+                    if (masked && j0 + 4 * r + q >= nvis) x[r] = ninf;
+                    top = fmax(top, x[r]);
+                }
+                if (__builtin_amdgcn_ballot_w64(top > R + limit) != 0) {
+                    top = row_reduce(top, [](double a, double bb) { return fmax(a, bb); });
+                    if (top > R + limit) {
+                        // 0 for a row without keys
+                        const float f = exp2_fast((float)(R - head - top));
+                        l *= f;
 #pragma unroll
                         for (int i = 0; i < NB; ++i)
 #pragma unroll
-                            for (int e = 0; e < 4; ++e)
+                            for (int n = 0; n < 4; ++n) U[i][n] *= f;
+                        R = top + head;
+                    }
+                }
+                float pw[4];
 #pragma unroll
-                                for (int n = 0; n < 4; ++n)
-                                    U[i][n][e] = fmaf(w, src[64 * i + 4 * e + n], U[i][n][e]);
+                for (int r = 0; r < 4; ++r) {
+                    pw[r] = exp2_fast((float)(x[r] - R));
+                    if (masked && j0 + 4 * r + q >= nvis) pw[r] = 0.0f;  // also where R is -inf
+                    l += pw[r];
+                }
+                bool plain = true;
+                if (masked) {
+                    // a weight of zero does not silence an infinite or NaN value of a hidden key
+                    float bad = 0.0f;
+#pragma unroll
+                    for (int i = 0; i < NB; ++i)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r)
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) bad = fmaf(vf[i][r][e], 0.0f, bad);
+                    plain = __builtin_amdgcn_ballot_w64(bad != 0.0f) == 0;
+                }
+                if (plain) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+#pragma unroll
+                        for (int i = 0; i < NB; ++i)
+#pragma unroll
+                            for (int n = 0; n < 4; ++n)
+                                U[i][n] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[i][r][n], pw[r],
+                                                                               U[i][n], 0, 0, 0);
+                } else {
+#pragma unroll 1
+                    for (int kk = 0; kk < kF32Block; ++kk) {
+                        const float own = (kk >> 2) == 0 ? pw[0] : (kk >> 2) == 1 ? pw[1]
+                                          : (kk >> 2) == 2 ? pw[2] : pw[3];
+                        const float w = __shfl(own, (kk & 3) * 16 + c, kWave);
+                        if (j0 + kk < nvis) {
+                            const float* src = vg - 4 * c + (size_t)(j0 + kk) * D + 16 * q;
+#pragma unroll
+                            for (int i = 0; i < NB; ++i)
+#pragma unroll
+                                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                                    for (int n = 0; n < 4; ++n)
+                                        U[i][n][e] = fmaf(w, src[64 * i + 4 * e + n], U[i][n][e]);
+                        }
                     }
                 }
             }
-        }
 
-        // ---- fold the four wavefront states --------------------------------------------
-        l = row_reduce(l, [](float a, float bb) { return a + bb; });
-        __syncthreads();                   // the fold of the previous id has been read
+            // ---- fold the four wavefront states ----------------------------------------
+            float bad = 0.0f;                  // NaN where four such sums might overflow
 #pragma unroll
-        for (int i = 0; i < NB; ++i)
+            for (int i = 0; i < NB; ++i)
 #pragma unroll
-            for (int e = 0; e < 4; ++e)
-                *reinterpret_cast<f32x4*>(&fold_u[wave][c][64 * i + 16 * q + 4 * e]) =
-                    f32x4{U[i][0][e], U[i][1][e], U[i][2][e], U[i][3][e]};
-        if (q == 0) {
-            fold_r[wave][c] = R;
-            fold_l[wave][c] = l;
-        }
-        __syncthreads();
-        for (int idx = tid; idx < kF32Rows * (D / 4); idx += kF32Waves * kWave) {
-            const int fr = idx / (D / 4);
-            const int t = 4 * (idx % (D / 4));
-            if (r0 + fr > rlast) continue;
-            double top = ninf;
+                for (int n = 0; n < 4; ++n)
 #pragma unroll
-            for (int w = 0; w < kF32Waves; ++w) top = fmax(top, fold_r[w][fr]);
-            float lt = 0.0f;
-            f32x4 o = {0.0f, 0.0f, 0.0f, 0.0f};
+                    for (int e = 0; e < 4; ++e) bad = fmaf(U[i][n][e] * 4.0f, 0.0f, bad);
+            const bool big = __builtin_amdgcn_ballot_w64(bad != 0.0f) != 0;
+            l = row_reduce(l, [](float a, float bb) { return a + bb; });
+            __syncthreads();                   // the previous fold has been read
 #pragma unroll
-            for (int w = 0; w < kF32Waves; ++w) {
-                const float lw = fold_l[w][fr];
-                // a wavefront that saw no key: weight 0 (NaN stays NaN)
-                const float f = fold_r[w][fr] == ninf ? lw * 0.0f
-                                                      : exp2_fast((float)(fold_r[w][fr] - top));
-                lt = fmaf(f, lw, lt);
-                o += f * *reinterpret_cast<const f32x4*>(&fold_u[w][fr][t]);
+            for (int i = 0; i < NB; ++i)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    *reinterpret_cast<f32x4*>(&fold_u[wave][c][64 * i + 16 * q + 4 * e]) =
+                        f32x4{U[i][0][e], U[i][1][e], U[i][2][e], U[i][3][e]};
+            if (q == 0) {
+                fold_r[wave][c] = R;
+                fold_l[wave][c] = l;
             }
-            const bool empty = lt == 0.0f;
-            const float inv = empty ? 0.0f : 1.0f / lt;
-            o *= inv;
-            const size_t orow = q_row(r0 + fr);
-            if (!p.partial) {
-                *reinterpret_cast<f32x4*>(static_cast<float*>(p.o) + orow * D + t) = o;
-            } else {
-                float* dst = p.ws + ((size_t)sp * p.B * p.Hq * p.Lq + orow) * (D + 2);
-                *reinterpret_cast<float2*>(dst + t) = float2{o[0], o[1]};
-                *reinterpret_cast<float2*>(dst + t + 2) = float2{o[2], o[3]};
-                if (t == 0)
-                    split_lam(empty ? ninf : (top + log2((double)lt)) * 0.69314718055994530942,
-                              dst[D], dst[D + 1]);
+            if (lane == 0) over[wave] = big ? 1 : 0;
+            __syncthreads();
+            if (pass == 0 && (over[0] | over[1] | over[2] | over[3]) != 0) continue;
+            for (int idx = tid; idx < kF32Rows * (D / 4); idx += kF32Waves * kWave) {
+                const int fr = idx / (D / 4);
+                const int t = 4 * (idx % (D / 4));
+                if (r0 + fr > rlast) continue;
+                double top = ninf;
+#pragma unroll
+                for (int w = 0; w < kF32Waves; ++w) top = fmax(top, fold_r[w][fr]);
+                float lt = 0.0f;
+                f32x4 o = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+                for (int w = 0; w < kF32Waves; ++w) {
+                    const float lw = fold_l[w][fr];
+                    // a wavefront that saw no key: weight 0 (NaN stays NaN)
+                    const float f = fold_r[w][fr] == ninf ? lw * 0.0f
+                                                          : exp2_fast((float)(fold_r[w][fr] - top));
+                    lt = fmaf(f, lw, lt);
+                    o += f * *reinterpret_cast<const f32x4*>(&fold_u[w][fr][t]);
+                }
+                const bool empty = lt == 0.0f;
+                const float inv = empty ? 0.0f : 1.0f / lt;
+                o *= inv;
+                const size_t orow = q_row(r0 + fr);
+                if (!p.partial) {
+                    *reinterpret_cast<f32x4*>(static_cast<float*>(p.o) + orow * D + t) = o;
+                } else {
+                    float* dst = p.ws + ((size_t)sp * p.B * p.Hq * p.Lq + orow) * (D + 2);
+                    *reinterpret_cast<float2*>(dst + t) = float2{o[0], o[1]};
+                    *reinterpret_cast<float2*>(dst + t + 2) = float2{o[2], o[3]};
+                    if (t == 0)
+                        split_lam(empty ? ninf : (top + log2((double)lt)) * 0.69314718055994530942,
+                                  dst[D], dst[D + 1]);
+                }
             }
+            break;
         }
     }
 }

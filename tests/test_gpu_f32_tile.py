@@ -59,3 +59,19 @@ def test_hidden_values_do_not_reach_a_row(bad):
     clean[0, 0, 37, 5] = 0.0
     ref = oa.attn(q, k, clean, True, w.scale)
     check(got[:, :, :37], np.ascontiguousarray(ref[:, :, :37]), torch.float32)
+
+
+@pytest.mark.parametrize("sign", [False, True])
+@pytest.mark.parametrize("splits", [1, 3])
+def test_large_values(splits, sign):
+    """Values up to 1e38 on hundreds of keys: sums of unnormalised weights overflow, the output
+    does not.  The second kv head holds ordinary values."""
+    for d in (64, 128):
+        w = synthetic.small("t", 1, 4, 2, 30, 700, d, "f32", True, seed=9500 + d)
+        q, k, v, _ = synthetic.make_qkv(w)
+        big = 2e37 * (1.0 + v[:, :1].abs().clamp(max=4.0))
+        v[:, :1] = torch.where(v[:, :1] < 0, -big, big) if sign else big
+        got = run_flashd(q, k, v, True, w.scale, AUTO, splits)
+        ref = oa.attn(q, k, v, True, w.scale)
+        for h in range(4):
+            check(got[:, h:h + 1], np.ascontiguousarray(ref[:, h:h + 1]), torch.float32, f"d={d} h={h}")
