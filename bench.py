@@ -467,7 +467,7 @@ def main() -> int:
                                                  "traffic": None}}
         if not args.no_decode16:
             # one sequence with a long context: 8 workgroups' worth of (b, kv head) units, so
-            # the keys are split 64 ways and merge_splits_kernel folds the partial states
+            # the keys are split 24 ways and merge_splits_kernel folds the partial states
             gen = torch.Generator().manual_seed(wd.seed + 17)
             Ll = 131072
             q1 = torch.randn((1, wd.Hq, 1, wd.d), generator=gen).to(qg.dtype).cuda()

@@ -74,7 +74,7 @@ def test_fp8_cache(B, Hkv, Lk, d):
 @pytest.mark.parametrize("splits", [8, 9, 16, 17, 64])
 @pytest.mark.parametrize("dtype,d", [("bf16", 128), ("f32", 64)])
 def test_merge_of_many_splits(splits, dtype, d):
-    """Up to 8 splits a wavefront folds a row, from 9 on four wavefronts share it."""
+    """Up to 16 splits d / 4 lanes fold a row, from 17 on four wavefronts share it."""
     w = synthetic.small("t", 1, 4, 2, 3, 140, d, dtype, True, seed=9830)
     q, k, v, _ = synthetic.make_qkv(w)
     t = torch.float32 if dtype == "f32" else DT[dtype]
