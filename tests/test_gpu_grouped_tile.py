@@ -18,7 +18,9 @@ SHAPES = [(3, 1, 11, 40),        # 33: one past the decode kernel
           (4, 1, 32, 200),       # 128: one full row tile
           (6, 2, 43, 43),        # 129: the last tile holds one row
           (5, 1, 77, 300),       # 385, tiles begin inside a position
-          (16, 2, 100, 90)]      # 800, rows that see no key
+          (16, 2, 100, 90),      # 800, rows that see no key
+          (4, 1, 120, 960),      # no row tile saved: interleaved up to 8 keys per position,
+          (4, 1, 120, 961)]      # one head after the other beyond (causal)
 
 
 @pytest.mark.parametrize("shape", SHAPES)
