@@ -377,14 +377,17 @@ void decode16_kernel(Problem p, Dec16Sched sc) {
         f32x4 o = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
         for (int w = 0; w < kD16Waves; ++w) {
-            // a wavefront that saw no key: weight 0 (NaN stays NaN)
-            const float f = fold_r[w][fr] == ninf ? 0.0f : exp2_fast(fold_r[w][fr] - top);
+            // A wavefront without a key of the row is left out: its U holds 0 * V of keys that
+            // other rows see, and that is NaN where such a V is infinite.  (l is 1 or more with a
+            // key, NaN with a NaN score.)
+            if (fold_l[w][fr] == 0.0f) continue;
+            const float f = exp2_fast(fold_r[w][fr] - top);
             lt = fmaf(f, fold_l[w][fr], lt);
             tt = fmaf(f, fold_t[w][fr], tt);
             o += f * *reinterpret_cast<const f32x4*>(&fold[(w * 16 + fr) * FROW + t]);
         }
         const bool empty = lt == 0.0f;
-        o *= (empty ? 0.0f : 1.0f / lt) * oscale;
+        if (!empty) o *= 1.0f / lt * oscale;
         if (!p.partial) {
             *reinterpret_cast<u32x2*>(static_cast<uint16_t*>(p.o) + (row0 + fr) * D + t) =
                 Mma<T>::pack4(o);

@@ -51,6 +51,26 @@ def test_moving_references(dtype):
             check(run_flashd(q, k, v, False, w.scale, variant, splits), ref, DT[dtype])
 
 
+@pytest.mark.parametrize("Lq,Lk", [(2, 33), (2, 65), (2, 97), (3, 2)])
+@pytest.mark.parametrize("bad", [float("inf"), float("nan")])
+@pytest.mark.parametrize("d", [64, 128])
+def test_wavefronts_without_a_key_of_the_row(Lq, Lk, bad, d):
+    """The last key is infinite or NaN in one column and stands in a block of which the first
+    position sees nothing: that position's rows keep their values (zeros where it sees no key at
+    all), the last position's rows, which see it, do not."""
+    w = synthetic.small("t", 1, 4, 1, Lq, Lk, d, "bf16", True, seed=9840 + Lk)
+    q, k, v, _ = synthetic.make_qkv(w)
+    ref = np.ascontiguousarray(oa.attn(q, k, v, True, w.scale)[:, :, :1])
+    v[0, 0, Lk - 1, 5] = bad
+    for variant in (TILE, AUTO):
+        for splits in (1, 2):
+            got = run_flashd(q, k, v, True, w.scale, variant, splits)
+            check(got[:, :, :1], ref, torch.bfloat16, f"variant {variant} splits {splits}")
+            if Lk < Lq:
+                assert torch.count_nonzero(got[:, :, 0]) == 0
+            assert not torch.isfinite(got[:, :, Lq - 1, 5]).any()
+
+
 def test_state_of_a_decode_step():
     w = synthetic.small("t", 2, 8, 2, 2, 333, 128, "bf16", True, seed=9810)
     q, k, v, _ = synthetic.make_qkv(w)
