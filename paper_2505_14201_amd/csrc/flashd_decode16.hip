@@ -323,13 +323,14 @@ void decode16_kernel(Problem p, Dec16Sched sc) {
             for (int i = 0; i < NDB; ++i) U[i] *= f;
         }
         f32x8 pv;
+        // no key yet, or only keys of score -inf: weights of zero
+        const float ref = R == ninf ? 0.0f : R;
         if (general) {
-            const float ref = R == ninf ? 0.0f : R;                  // no key yet: all are hidden
 #pragma unroll
             for (int e = 0; e < 8; ++e) pv[e] = exp2_fast(x[e] - ref);
         } else {
 #pragma unroll
-            for (int e = 0; e < 8; ++e) pv[e] = exp2_fast(fmaf(acc[e >> 2][e & 3], c_log2, -R));
+            for (int e = 0; e < 8; ++e) pv[e] = exp2_fast(fmaf(acc[e >> 2][e & 3], c_log2, -ref));
         }
         const u32x4 bfrag = Mma<T>::pack8(pv);
         f32x4 ps = {0.0f, 0.0f, 0.0f, 0.0f};

@@ -198,10 +198,11 @@ void tile_f32_kernel(Problem p, F32Sched sc) {
                     }
                 }
                 float pw[4];
+                // no key yet, or only keys of score -inf: weights of zero
+                const double ref = R == ninf ? 0.0 : R;
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    pw[r] = exp2_fast((float)(x[r] - R));
-                    if (masked && j0 + 4 * r + q >= nvis) pw[r] = 0.0f;  // also where R is -inf
+                    pw[r] = exp2_fast((float)(x[r] - ref));
                     l += pw[r];
                 }
                 bool plain = true;

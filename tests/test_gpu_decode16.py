@@ -71,6 +71,23 @@ def test_wavefronts_without_a_key_of_the_row(Lq, Lk, bad, d):
             assert not torch.isfinite(got[:, :, Lq - 1, 5]).any()
 
 
+@pytest.mark.parametrize("hidden", [range(0, 64), range(40, 200),
+                                    [j for j in range(300) if j // 32 % 4 == 1]])
+@pytest.mark.parametrize("splits", [1, 2])
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("f16", 64)])
+def test_keys_of_score_minus_infinity(hidden, splits, dtype, d):
+    """Keys whose scores are -inf weigh nothing, also where a wavefront meets them first or meets
+    no others (the last range: all blocks of wavefront 1)."""
+    w = synthetic.small("t", 1, 8, 2, 1, 300, d, dtype, False, seed=9850)
+    q, k, v, _ = synthetic.make_qkv(w)
+    q[..., 5] = q[..., 5].abs() + 0.1
+    left = [j for j in range(300) if j not in set(hidden)]
+    ref = oa.attn(q, k[:, :, left].contiguous(), v[:, :, left].contiguous(), False, w.scale)
+    k[:, :, list(hidden), 5] = float("-inf")
+    for variant in (TILE, AUTO):
+        check(run_flashd(q, k, v, False, w.scale, variant, splits), ref, DT[dtype], f"variant {variant}")
+
+
 def test_state_of_a_decode_step():
     w = synthetic.small("t", 2, 8, 2, 2, 333, 128, "bf16", True, seed=9810)
     q, k, v, _ = synthetic.make_qkv(w)

@@ -61,6 +61,22 @@ def test_hidden_values_do_not_reach_a_row(bad):
     check(got[:, :, :37], np.ascontiguousarray(ref[:, :, :37]), torch.float32)
 
 
+@pytest.mark.parametrize("hidden", [range(0, 64), range(40, 200),
+                                    [j for j in range(300) if j // 16 % 4 == 1]])
+@pytest.mark.parametrize("splits", [1, 2])
+def test_keys_of_score_minus_infinity(hidden, splits):
+    """Keys whose scores are -inf weigh nothing, also where a wavefront meets them first or meets
+    no others (the last range: all blocks of wavefront 1)."""
+    for d in (64, 128):
+        w = synthetic.small("t", 1, 4, 2, 9, 300, d, "f32", False, seed=9450)
+        q, k, v, _ = synthetic.make_qkv(w)
+        q[..., 5] = q[..., 5].abs() + 0.1
+        left = [j for j in range(300) if j not in set(hidden)]
+        ref = oa.attn(q, k[:, :, left].contiguous(), v[:, :, left].contiguous(), False, w.scale)
+        k[:, :, list(hidden), 5] = float("-inf")
+        check(run_flashd(q, k, v, False, w.scale, AUTO, splits), ref, torch.float32, f"d={d}")
+
+
 @pytest.mark.parametrize("sign", [False, True])
 @pytest.mark.parametrize("splits", [1, 3])
 def test_large_values(splits, sign):
