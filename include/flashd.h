@@ -97,7 +97,8 @@ typedef enum {
  * itself (for decode shapes in f16/bf16 the kernel of flashd_attn_fwd_skipv, which leaves out
  * the value fetch of key blocks whose weights have all saturated at 0) and takes split-K
  * scratch memory from a grow-only cache kept per (device, stream);
- * the first call that needs a larger cache allocates (hipMalloc), later calls do not.
+ * the first call that needs a larger cache allocates (hipMalloc), later calls do not.  A call
+ * that needs scratch takes enough for the same problem with fewer keys too.
  * Safe to call from several host threads; calls that share a stream share its cache and are
  * ordered by the stream.
  */
@@ -126,7 +127,8 @@ int flashd_attn_fwd_ex(const void* q, const void* k, const void* v, void* o,
 /*
  * Bytes of workspace flashd_attn_fwd_ex needs: one partial state (o[d], s, ln w) in fp32 per
  * (split, b, h, i) when more than one split is used (the state of Alg. 3, Sec. III-C), else 0.
- * splits == 0 returns the bound for the automatic choice.  Returns 0 for invalid arguments.
+ * splits == 0 returns the bound for the automatic choice at this many keys or fewer (0 if this
+ * problem is not split: then none with fewer keys is).  Returns 0 for invalid arguments.
  */
 size_t flashd_workspace_bytes(int B, int Hq, int Hkv, int Lq, int Lk, int d, int dtype,
                               int variant, int splits);
@@ -217,7 +219,7 @@ int flashd_attn_fwd_skipv(const void* q, const void* k, const void* v, void* o,
  * FLASHD_STATIC_SCRATCH_BYTES that is part of the library's code object (each GPU the library
  * runs on holds one copy until the process ends) instead of the grow-only cache.  Calls no
  * hipMalloc, hipFree or other allocating routine.  A problem whose partial states
- * (flashd_workspace_bytes(..., FLASHD_VARIANT_AUTO, 0)) exceed that size is refused with
+ * (flashd_workspace_bytes(..., flashd_auto_splits(...))) exceed that size is refused with
  * FLASHD_E_WORKSPACE and nothing is enqueued: use flashd_attn_fwd_ex with memory of your own
  * for it.  All calls on one GPU share the array, whatever their stream, and it keeps the last
  * call's contents (every partial state a call reads it has written first, so nothing needs

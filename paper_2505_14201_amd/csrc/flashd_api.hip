@@ -95,7 +95,9 @@ size_t partial_bytes(const Shape& s, int n) {
 //     wavefront (4 units of 3000 keys: 20.3 us in 8 splits, 16.2 in 48).
 //   - Below 512 keys nothing is split, here as in auto_splits: such calls need no scratch memory,
 //     so they can be captured into a graph without a call before.
-int decode_splits(const Shape& s) {
+// or_shorter: the most splits of any call with this many keys or fewer (the choice itself falls
+// from 64 to 192 / units where the ranges get long).
+int decode_splits(const Shape& s, bool or_shorter) {
     const long units = flashd::decode_workgroups(s.B, s.Hkv);
     const long blocks = (s.Lk + 31L) / 32;
     const bool wide = (long)(s.Hq / s.Hkv) * s.Lq > 16;
@@ -103,17 +105,18 @@ int decode_splits(const Shape& s) {
     if (units >= 128) return (units <= 128 ? blocks >= 128 : units > 256 && units < 342 && blocks >= 64) ? 2 : 1;
     const long few = blocks / 4 < 8 ? blocks / 4 : 8;
     const long many = blocks / (wide ? 2 : 8);
-    const long most = units <= 8 && blocks < 2048 ? FLASHD_MAX_SPLITS : 192 / units;
+    const long most = units <= 8 && (blocks < 2048 || or_shorter) ? FLASHD_MAX_SPLITS : 192 / units;
     long sp = few > many ? few : many;
     if (sp > most) sp = most;
     return (int)(sp < 1 ? 1 : sp > FLASHD_MAX_SPLITS ? FLASHD_MAX_SPLITS : sp);
 }
 
 // Splits for the automatic choice: enough independent work to fill 256 compute units, but
-// never key ranges shorter than 256 keys.
-int auto_splits(const Shape& s, int variant) {
+// never key ranges shorter than 256 keys.  or_shorter: the most splits of any call with this many
+// keys or fewer.  Outside the decode shapes the choice never falls as the keys grow.
+int auto_splits(const Shape& s, int variant, bool or_shorter = false) {
     if (variant != FLASHD_VARIANT_PER_KEY && flashd::decode_applies(s.Hq, s.Hkv, s.Lq))
-        return decode_splits(s);
+        return decode_splits(s, or_shorter);
     long units;
     if (variant == FLASHD_VARIANT_PER_KEY) {
         const int rows_per_group = (s.d <= 64 ? 2 : 1) * 4;             // 4 wavefronts
@@ -152,6 +155,14 @@ int auto_splits(const Shape& s, int variant) {
     if (sp > FLASHD_MAX_SPLITS) sp = FLASHD_MAX_SPLITS;
     if (sp < 1) sp = 1;
     return (int)sp;
+}
+
+// Splits whose partial states the scratch memory of a call with sp splits is sized for.  A call of
+// the automatic choice that needs scratch at all takes what every call with fewer keys needs, so
+// that one made at the longest context serves a decode loop, or a graph captured later, at any
+// shorter one.
+int scratch_splits(const Shape& s, int variant, int splits, int sp) {
+    return splits == 0 && sp > 1 ? auto_splits(s, variant, true) : sp;
 }
 
 size_t ws_bytes(const Shape& s, int splits) { return splits <= 1 ? 0 : partial_bytes(s, splits); }
@@ -321,7 +332,9 @@ int run(const void* q, const void* k, const void* v, void* o, const Shape& s, in
     const size_t need_al = (need + 255) & ~(size_t)255;
     const size_t kv_bytes = widen ? (size_t)s.B * s.Hkv * s.Lk * s.d * 2 : 0;   // per tensor
     if (use_cache) {
-        rc = cached_workspace(stream, need_al + 2 * kv_bytes, &ws);
+        const size_t cover = partial_bytes(s, scratch_splits(s, var, splits, sp));
+        const size_t most = need > 0 && cover > need_al ? (cover + 255) & ~(size_t)255 : need_al;
+        rc = cached_workspace(stream, most + 2 * kv_bytes, &ws);
         if (rc != FLASHD_OK) return rc;
     }
     if (mode == WsMode::Static && need > 0) {
@@ -521,7 +534,8 @@ size_t flashd_workspace_bytes(int B, int Hq, int Hkv, int Lq, int Lk, int d, int
     if (validate_shape(s) != FLASHD_OK) return 0;
     const int var = resolve_variant(s, variant);
     if (var < 0 || splits < 0 || splits > FLASHD_MAX_SPLITS || splits > Lk) return 0;
-    return ws_bytes(s, splits == 0 ? auto_splits(s, var) : splits);
+    const int sp = splits == 0 ? auto_splits(s, var) : splits;
+    return ws_bytes(s, scratch_splits(s, var, splits, sp));
 }
 
 int flashd_release_workspace(void) { return release_workspace(); }

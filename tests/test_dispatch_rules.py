@@ -34,3 +34,19 @@ def test_padded_256_row_tiles(B, Hq, Hkv, Lq, Lk, causal, want):
 ])
 def test_decode_splits(B, Hq, Hkv, Lq, Lk, d, want):
     assert flashd.auto_splits(B, Hq, Hkv, Lq, Lk, d, flashd.BF16) == want
+
+
+@pytest.mark.parametrize("dtype", [flashd.BF16, flashd.F32])
+@pytest.mark.parametrize("Hq,Hkv,Lq", [(32, 8, 1), (8, 1, 4), (32, 1, 1), (4, 4, 1), (12, 12, 3), (8, 2, 40)])
+@pytest.mark.parametrize("d", [64, 128])
+def test_scratch_memory_never_falls_with_more_keys(Hq, Hkv, Lq, d, dtype):
+    """Scratch taken at the longest context serves every shorter one, and a problem that needs
+    none has no shorter one that does."""
+    lengths = sorted({int(1.1 ** i) + 1 for i in range(145)} | {511, 512, 2047 * 32, 2047 * 32 + 1})
+    for B in (1, 2, 3, 4, 5, 8, 13, 16, 33, 64):
+        at = [flashd.workspace_bytes(B, Hq, Hkv, Lq, Lk, d, dtype) for Lk in lengths]
+        assert at == sorted(at), B
+        for Lk, have in zip(lengths, at):
+            sp = flashd.auto_splits(B, Hq, Hkv, Lq, Lk, d, dtype)
+            assert have >= flashd.workspace_bytes(B, Hq, Hkv, Lq, Lk, d, dtype, splits=sp)
+            assert (have == 0) == (sp == 1)

@@ -61,3 +61,33 @@ def test_graph_replays_equal_eager(case):
         assert torch.equal(got_o, o), f"{name}: replay {rep} differs from eager"
         assert torch.equal(got_c, cnt), f"{name}: replay {rep} counters differ"
         assert torch.isfinite(o.float()).all()
+
+
+@pytest.mark.parametrize("Lk", [2000, 32768])
+def test_automatic_call_captured_after_one_at_the_longest_context(Lk):
+    """The cache of scratch memory that a call at 131072 keys leaves serves calls at fewer keys,
+    which run in more splits: nothing is allocated inside the capture."""
+    w = synthetic.small("t", 1, 32, 8, 1, Lk, 128, "bf16", False, seed=50)
+    q, k, v = fresh(w, 50)
+    o = torch.empty_like(q)
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(s):
+        flashd.release_workspace()
+        far = torch.zeros(1, 8, 131072, 128, dtype=torch.bfloat16, device="cuda")
+        flashd.attn_fwd(q, far, far, o, False, w.scale)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=s):
+        flashd.attn_fwd(q, k, v, o, False, w.scale)
+    for rep in range(3):
+        qn, kn, vn = fresh(w, 51 + rep)
+        q.copy_(qn); k.copy_(kn); v.copy_(vn)
+        o.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        got = o.clone()
+        o.fill_(float("nan"))
+        flashd.attn_fwd(q, k, v, o, False, w.scale)
+        torch.cuda.synchronize()
+        assert torch.equal(got, o), rep
