@@ -380,12 +380,15 @@ void decode16_kernel(Problem p, Dec16Sched sc) {
         for (int w = 0; w < kD16Waves; ++w) {
             // A wavefront without a key of the row is left out: its U holds 0 * V of keys that
             // other rows see, and that is NaN where such a V is infinite.  (l is 1 or more with a
-            // key, NaN with a NaN score.)
-            if (fold_l[w][fr] == 0.0f) continue;
-            const float f = exp2_fast(fold_r[w][fr] - top);
+            // key, NaN with a NaN score.  By selection: with a branch around it each wavefront's
+            // state is read after the one before.)
+            const bool none = fold_l[w][fr] == 0.0f;
+            const float f = none ? 0.0f : exp2_fast(fold_r[w][fr] - top);
+            const f32x4 u = *reinterpret_cast<const f32x4*>(&fold[(w * 16 + fr) * FROW + t]);
             lt = fmaf(f, fold_l[w][fr], lt);
             tt = fmaf(f, fold_t[w][fr], tt);
-            o += f * *reinterpret_cast<const f32x4*>(&fold[(w * 16 + fr) * FROW + t]);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[e] = fmaf(f, none ? 0.0f : u[e], o[e]);
         }
         const bool empty = lt == 0.0f;
         if (!empty) o *= 1.0f / lt * oscale;
