@@ -133,7 +133,8 @@ int flashd_attn_fwd_ex(const void* q, const void* k, const void* v, void* o,
 size_t flashd_workspace_bytes(int B, int Hq, int Hkv, int Lq, int Lk, int d, int dtype,
                               int variant, int splits);
 
-/* The number of splits the automatic choice takes for this problem (>= 1). */
+/* The number of splits the automatic choice takes for this problem (>= 1; flashd_attn_fwd_kv8, whose
+ * key ranges have half the bytes, may take another). */
 int flashd_auto_splits(int B, int Hq, int Hkv, int Lq, int Lk, int d, int dtype, int variant);
 
 /*

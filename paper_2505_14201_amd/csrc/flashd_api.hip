@@ -77,46 +77,79 @@ size_t partial_bytes(const Shape& s, int n) {
     return (size_t)n * s.B * s.Hq * s.Lq * (size_t)(s.d + 2) * sizeof(float);
 }
 
-// Splits for decode shapes (measured over 3 to 512 (b, kv head) units, 260 to 131072 keys and
-// every split count).
+// Splits for decode shapes (measured over 8 to 640 (b, kv head) units, 700 to 131072 keys and 1 to
+// 64 splits, with 4 and 32 query rows per kv head; times are of one launch among others).
 //   - Short key ranges stay whole: a second launch and its gap cost 4 us, a 32-key block takes a
 //     wavefront 1 us at d = 128 and half of that at 64.  8 units of 600 keys: 8.1 us whole, 9.0
-//     in any number of splits; of 1000 keys 10.5 and 9.0.
-//   - What fills the chip is one workgroup on most compute units, not two: 48 units of 4000 keys
-//     21.2 us in 4 splits (192 workgroups), 25.6 in 6 (288), 21.9 in 8; 160 units 50.6 us whole,
-//     59.4 in 4 splits; 24 units 14.0 in 8, 17.1 in 12.  From 128 units on only long ranges gain
-//     from 2 splits (8000 keys 84 to 88 us, 89 whole; 1500 keys 20.9 and 19.4), and a little
-//     above 256 units, where few compute units would have a second workgroup.
-//   - Up to 8 splits cost the merge the same; with few units more of them pay until a wavefront
-//     has two blocks left (8 units of 16000 keys: 29 us in 8, 17.7 in 32, 16.8 in 64; 4 units of
-//     20000 keys 15.4 in 64), but not against the one workgroup per compute unit once the
-//     ranges are long (8 units of 131072 keys: 84.9 us in 24, 86.6 in 32, 110.9 in 36, 89.8 in 64).
-//   - 17 to 32 query rows: the wider kernel takes 1.5 us a block, half a block is left per
-//     wavefront (4 units of 3000 keys: 20.3 us in 8 splits, 16.2 in 48).
-//   - Below 512 keys nothing is split, here as in auto_splits: such calls need no scratch memory,
-//     so they can be captured into a graph without a call before.
+//     in any number of splits; of 1000 keys 10.5 and 9.0.  Below 512 keys nothing is split, here
+//     as in auto_splits, so that such calls need no scratch memory and can be captured into a graph
+//     without a call before; nor from 512 units on.
+//   - How many workgroups fill the chip depends on what one streams by itself, 32 keys of K and V per
+//     wavefront and step:
+//       16-bit cache, d = 128, up to 16 rows (1.1 us for 64 KB): HBM is the bound from 192 on, three
+//       quarters of the compute units.  48 units of 4000 keys 21.2 us in 4 splits, 25.6 in 6; 24
+//       of 20000 43 in 8, 57 in 12; 8 of 131072 84.9 in 24, 86.6 in 32, 89.8 in 64.
+//       d = 64 from fp8 (0.6 us for 16 KB) or for 17 to 32 rows (0.65 us from fp8, 1.4 us for 32 KB
+//       without): two per compute unit.  64 units of 20000 keys, fp8: 31.0 us in 8 splits, 35.7 in
+//       4, 43.5 in 3; 32 rows without fp8 59.8, 74.1 and 92.8; 160 units of 8000 keys, 32 rows,
+//       59.6 in 3, 66.9 in 2, 101.6 whole.
+//       The others: one per compute unit.  64 units of 60000 keys, fp8, d = 128: 144.6 us in 4
+//       splits, 162 in 3, 183 in 5; 32 rows, d = 128 301 in 4, 337 in 3.
+//   - The second workgroup of a compute unit needs ranges of one or two steps to pay (d = 64, 32
+//     rows: 56 units of 1326 keys with fp8 13.6 us in 4 splits, 14.9 in 5, 15.2 in 8).
+//   - More units than 96: a last round of workgroups that is mostly empty costs more than splits
+//     give.  104 units of 20000 keys take 163 us in two splits, 197 in three and 210 whole; 129
+//     units with fp8, d = 128 take 0.76 of the time whole in three, 0.97 in two.  Above 256 units,
+//     where few compute units have a second workgroup, two splits take 0.90 to 0.95 of the time
+//     whole up to 342 units (16 rows, all types); with more rows a compute unit holds two
+//     workgroups and not three, and only the fp8 cache with d = 64 gains, on long ranges (0.86 to
+//     0.93 at 20000 keys up to 384 units, 1.03 to 1.13 at 3000).  Short ranges stay whole: 127
+//     units of 1500 keys 20.2 us, 20.8 in 2; the slower kernel for 17 to 32 rows gains from 1024
+//     keys on (128 units of 1500 keys, d = 64: 25.7 whole, 19.3 in 4).
+//   - With up to 8 units more splits pay until a wavefront has two blocks left (8 units of 16000
+//     keys: 29 us in 8, 17.7 in 32, 16.8 in 64; 4 units of 20000 keys 15.4 in 64).  Up to 8
+//     splits cost the merge the same, more of them 1 us: 24 units with fp8 take 10.0 us in 8 and
+//     11.0 in 13 (4000 keys, d = 64), 15.0 in 8 and 16.0 in 10 (7779 keys, d = 128), 20 units of
+//     74088 keys 76 in 8 and 62 in 12.
+//   - 17 to 32 query rows: a block takes longer, half a block is left per wavefront (4 units of
+//     3000 keys: 20.3 us in 8 splits, 16.2 in 48).
 // or_shorter: the most splits of any call with this many keys or fewer (the choice itself falls
-// from 64 to 192 / units where the ranges get long).
-int decode_splits(const Shape& s, bool or_shorter) {
+// from 64 where the ranges of few units get long).
+int decode_splits(const Shape& s, int variant, bool fp8, bool or_shorter) {
     const long units = flashd::decode_workgroups(s.B, s.Hkv);
     const long blocks = (s.Lk + 31L) / 32;
-    const bool wide = (long)(s.Hq / s.Hkv) * s.Lq > 16;
-    if (s.Lk < 512 || blocks * s.d <= (wide ? 1024 : 2560)) return 1;
-    if (units >= 128) return (units <= 128 ? blocks >= 128 : units > 256 && units < 342 && blocks >= 64) ? 2 : 1;
+    // the kernel for 17 to 32 rows, which also runs the two ablations
+    const bool wide = (long)(s.Hq / s.Hkv) * s.Lq > 16 || variant == FLASHD_VARIANT_ONLINE_SOFTMAX ||
+                      variant == FLASHD_VARIANT_TILE_BLEND;
+    if (s.Lk < 512 || blocks * s.d <= (wide ? 1024 : 2560) || units >= 512) return 1;
+    const bool fast = !wide && !fp8 && s.d == 128;       // 192 workgroups saturate HBM
+    const bool small = s.d == 64 && (wide || fp8);       // 512 do not
+    const long one = 256 / units, two = 512 / units;     // splits for one, two workgroups per compute unit
+    if (units > 96) {
+        if (blocks < (wide && !fp8 ? 32 : 64)) return 1;
+        if (units > 256)
+            return wide ? (fp8 && small && units < 384 && blocks >= 256 ? 2 : 1) : units < 342 ? 2 : 1;
+        const long more = small || (two == 3 && !fast && blocks >= 128) ? two : 1;
+        return (int)(one > more ? one : more);
+    }
     const long few = blocks / 4 < 8 ? blocks / 4 : 8;
     const long many = blocks / (wide ? 2 : 8);
-    const long most = units <= 8 && (blocks < 2048 || or_shorter) ? FLASHD_MAX_SPLITS : 192 / units;
+    // long enough ranges for the second workgroup of a compute unit
+    const bool deep = blocks / (fp8 ? 8 : 4) >= (two < FLASHD_MAX_SPLITS ? two : FLASHD_MAX_SPLITS);
+    const long most = units <= 8 && (blocks < 2048 || or_shorter) && (!wide || deep) ? FLASHD_MAX_SPLITS
+                      : fast ? 192 / units : small && deep ? two : one;
     long sp = few > many ? few : many;
     if (sp > most) sp = most;
+    if (sp > 8 && units > 8 && !fast && blocks < (sp <= 12 ? 320 : 160)) sp = 8;
     return (int)(sp < 1 ? 1 : sp > FLASHD_MAX_SPLITS ? FLASHD_MAX_SPLITS : sp);
 }
 
 // Splits for the automatic choice: enough independent work to fill 256 compute units, but
 // never key ranges shorter than 256 keys.  or_shorter: the most splits of any call with this many
 // keys or fewer.  Outside the decode shapes the choice never falls as the keys grow.
-int auto_splits(const Shape& s, int variant, bool or_shorter = false) {
+int auto_splits(const Shape& s, int variant, bool fp8 = false, bool or_shorter = false) {
     if (variant != FLASHD_VARIANT_PER_KEY && flashd::decode_applies(s.Hq, s.Hkv, s.Lq))
-        return decode_splits(s, or_shorter);
+        return decode_splits(s, variant, fp8, or_shorter);
     long units;
     if (variant == FLASHD_VARIANT_PER_KEY) {
         const int rows_per_group = (s.d <= 64 ? 2 : 1) * 4;             // 4 wavefronts
@@ -161,8 +194,8 @@ int auto_splits(const Shape& s, int variant, bool or_shorter = false) {
 // the automatic choice that needs scratch at all takes what every call with fewer keys needs, so
 // that one made at the longest context serves a decode loop, or a graph captured later, at any
 // shorter one.
-int scratch_splits(const Shape& s, int variant, int splits, int sp) {
-    return splits == 0 && sp > 1 ? auto_splits(s, variant, true) : sp;
+int scratch_splits(const Shape& s, int variant, bool fp8, int splits, int sp) {
+    return splits == 0 && sp > 1 ? auto_splits(s, variant, fp8, true) : sp;
 }
 
 size_t ws_bytes(const Shape& s, int splits) { return splits <= 1 ? 0 : partial_bytes(s, splits); }
@@ -313,7 +346,7 @@ int run(const void* q, const void* k, const void* v, void* o, const Shape& s, in
         return FLASHD_E_VARIANT;
     const bool widen = k8.on && !flashd::decode_applies(s.Hq, s.Hkv, s.Lq);
     if (splits < 0 || splits > FLASHD_MAX_SPLITS || splits > s.Lk) return FLASHD_E_VARIANT;
-    const int sp = splits == 0 ? auto_splits(s, var) : splits;
+    const int sp = splits == 0 ? auto_splits(s, var, k8.on) : splits;
     // The state entry point always goes through partial states; a single partial may be
     // written straight into the caller's state buffer (unless that is also the input state).
     const bool direct = sa.on && sp == 1 && sa.out != nullptr && sa.out != sa.in;
@@ -332,7 +365,7 @@ int run(const void* q, const void* k, const void* v, void* o, const Shape& s, in
     const size_t need_al = (need + 255) & ~(size_t)255;
     const size_t kv_bytes = widen ? (size_t)s.B * s.Hkv * s.Lk * s.d * 2 : 0;   // per tensor
     if (use_cache) {
-        const size_t cover = partial_bytes(s, scratch_splits(s, var, splits, sp));
+        const size_t cover = partial_bytes(s, scratch_splits(s, var, k8.on, splits, sp));
         const size_t most = need > 0 && cover > need_al ? (cover + 255) & ~(size_t)255 : need_al;
         rc = cached_workspace(stream, most + 2 * kv_bytes, &ws);
         if (rc != FLASHD_OK) return rc;
@@ -535,7 +568,7 @@ size_t flashd_workspace_bytes(int B, int Hq, int Hkv, int Lq, int Lk, int d, int
     const int var = resolve_variant(s, variant);
     if (var < 0 || splits < 0 || splits > FLASHD_MAX_SPLITS || splits > Lk) return 0;
     const int sp = splits == 0 ? auto_splits(s, var) : splits;
-    return ws_bytes(s, scratch_splits(s, var, splits, sp));
+    return ws_bytes(s, scratch_splits(s, var, false, splits, sp));
 }
 
 int flashd_release_workspace(void) { return release_workspace(); }

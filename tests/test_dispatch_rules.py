@@ -36,6 +36,22 @@ def test_decode_splits(B, Hq, Hkv, Lq, Lk, d, want):
     assert flashd.auto_splits(B, Hq, Hkv, Lq, Lk, d, flashd.BF16) == want
 
 
+@pytest.mark.parametrize("units,rows,Lk,d,want", [
+    (96, 4, 8000, 128, 2), (97, 4, 8000, 128, 2), (127, 4, 8000, 128, 2), (128, 4, 8000, 128, 2),
+    (129, 4, 8000, 128, 1), (97, 4, 2016, 128, 1), (97, 4, 2017, 128, 2),
+    (160, 4, 8000, 64, 3), (171, 4, 8000, 64, 1), (256, 4, 8000, 64, 1), (257, 4, 8000, 64, 2),
+    (341, 4, 8000, 64, 2), (342, 4, 8000, 64, 1),
+    # 17 to 32 rows, d = 64: two workgroups per compute unit; d = 128: one
+    (64, 32, 20000, 64, 8), (128, 32, 1500, 64, 4), (256, 32, 20000, 64, 2), (257, 32, 20000, 64, 1),
+    (64, 17, 20000, 128, 4), (128, 32, 20000, 128, 2), (170, 32, 20000, 128, 3), (171, 32, 20000, 128, 1),
+    (511, 32, 20000, 64, 1), (512, 4, 20000, 128, 1),
+    # 9 to 12 splits only of long ranges
+    (24, 4, 10208, 64, 8), (24, 4, 10209, 64, 10),
+])
+def test_decode_splits_by_what_a_workgroup_streams(units, rows, Lk, d, want):
+    assert flashd.auto_splits(units, rows, 1, 1, Lk, d, flashd.BF16) == want
+
+
 @pytest.mark.parametrize("dtype", [flashd.BF16, flashd.F32])
 @pytest.mark.parametrize("Hq,Hkv,Lq", [(32, 8, 1), (8, 1, 4), (32, 1, 1), (4, 4, 1), (12, 12, 3), (8, 2, 40)])
 @pytest.mark.parametrize("d", [64, 128])
