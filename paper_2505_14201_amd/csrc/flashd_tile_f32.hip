@@ -4,8 +4,8 @@
 // fp64 fma on the vector ALUs, one key per lane, and was bound by them and by the 128 registers
 // of output state that every lane carries (4.4 TFLOP/s).
 //
-// Precision is that of the per-key kernel: dot products, scaled scores and s - ln w in fp64,
-// weights and output accumulation in fp32.
+// Precision is that of the per-key kernel: dot products and scaled scores in fp64, weights in
+// fp32, l (hence s - ln w) and U in fp64 sums of short fp32 ones (kF32Chain).
 //
 // Tile form: U = sum_j 2^{s_j - R} v_j and l = sum_j 2^{s_j - R} against a reference R (fp64)
 // that starts at the top score of the row's first block and moves only when a block's top score
@@ -26,9 +26,9 @@
 //
 // What bounds it: the matrix cores.  A block of 16 keys x 16 rows x 64 columns takes 16 fp64
 // instructions of 64 cycles (78.6 TFLOP/s peak) and 16 fp32 ones of 32 cycles.  Measured
-// against the per-key kernel: 2 x 12 heads, 777 causal positions, d = 64 34 us (425 us before; 54
+// against the per-key kernel: 2 x 12 heads, 777 causal positions, d = 64 36 us (425 us before; 52
 // TFLOP/s of the 97 that the two kinds of instruction allow together), 4 heads of 1000 positions,
-// d = 128 42 us (391), one head of 128 positions 5 us of kernel (26).
+// d = 128 41 us (391), one head of 128 positions 5.5 us of kernel (26).
 #include "flashd_common.h"
 #include "flashd_kernels.h"
 #include "flashd_mma.h"
@@ -41,6 +41,15 @@ constexpr int kF32Waves = 4;
 constexpr int kF32Rows = 16;       // query rows per workgroup
 constexpr int kF32Block = 16;      // keys per wavefront step
 constexpr double kMoveLog2 = 8.0;
+// Blocks of a wavefront whose sums are formed in fp32; then they join sums in fp64, which lie in
+// LDS, each lane's its own.  In fp32 throughout, U and l lose what the per-key kernel keeps, whose
+// blend moves o by a part of itself.  Relative error against fp64 on N(0, 1) inputs (2-norm;
+// per-key kernel, fp32 throughout, chains of 8, 6 and 4): 300 keys 1.8e-7, 1.8, 1.8, 1.8, 1.6;
+// 777 keys 1.9e-7, 2.6, 2.1, 1.9, 1.7; 2048 keys 2.6e-7, 4.0, 2.3, 1.9, 1.7; 131072 keys 1.4e-6,
+// 3.3e-6, 2.2e-7, 1.9e-7, 1.7e-7; 524288 equal keys, where every step rounds the same way, 1.8e-7
+// and 5.4e-4 in fp32 throughout.  Time of 2 x 12 heads, 777 causal positions, d = 64: 34.8 us in
+// fp32 throughout, 35.7, 36.2 and 36.8 in chains; 8 heads of 2048, d = 128: 234, 237, 238, 242.
+constexpr int kF32Chain = 6;
 // Weights of up to 2^kMoveLog2 per key can overflow the sum over large values (1e36 and up, some
 // hundred keys), whose blend would not.  A row tile where that happened is done again with the
 // reference this far above the top score: 1e9 keys of 2^(8 - 40) sum to less than a value.
@@ -75,7 +84,11 @@ void tile_f32_kernel(Problem p, F32Sched sc) {
     constexpr int NM = D / 16;             // float4 of K per lane and block
     constexpr int NB = D / 64;             // 64-column groups of the output
     constexpr int FROW = D + 4;            // floats per row of the fold buffer (16-byte rows)
-    __shared__ __align__(16) float fold_u[kF32Waves][kF32Rows][FROW];
+    constexpr int NV = D / 4;              // sums per lane
+    static_assert(NV * kWave * 2 >= kF32Rows * FROW, "a wavefront's fold rows lie in its fp64 sums");
+    // a wavefront's fp64 sums, [sum][lane], each lane its own: U, l and the reference they stand
+    // at; for the fold its rows in fp32
+    __shared__ __align__(16) double sums[kF32Waves][(NV + 2) * kWave];
     __shared__ double fold_r[kF32Waves][kF32Rows];
     __shared__ float fold_l[kF32Waves][kF32Rows];
     __shared__ int over[kF32Waves];        // a sum of the wavefront may overflow in the fold
@@ -85,6 +98,7 @@ void tile_f32_kernel(Problem p, F32Sched sc) {
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c = lane & 15;
     const int q = lane >> 4;
+    double* mine = &sums[wave][lane];
     const double ninf = -__builtin_inf();
     const double c_log2 = (double)p.scale * 1.4426950408889634074;
 
@@ -141,6 +155,12 @@ void tile_f32_kernel(Problem p, F32Sched sc) {
                 for (int n = 0; n < 4; ++n) U[i][n] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
             float l = 0.0f;                    // this lane's keys
             double R = ninf;
+            int done = 0;                      // blocks of this wavefront
+            // what brings the fp64 sums to the present reference
+            auto to_reference = [&]() __attribute__((always_inline)) {
+                const double R64 = mine[(NV + 1) * kWave];
+                return R64 == R ? 1.0 : (double)exp2_fast((float)(R64 - R));
+            };
 
             int blk = sp * chunk + wave;
             if (blk < blk_end) {
@@ -244,6 +264,35 @@ void tile_f32_kernel(Problem p, F32Sched sc) {
                         }
                     }
                 }
+                if (__builtin_expect(++done % kF32Chain == 0, 0)) {
+                    if (done == kF32Chain) {
+                        mine[NV * kWave] = (double)l;
+#pragma unroll
+                        for (int at = 0; at < NV; ++at)
+                            mine[at * kWave] = (double)U[at / 16][(at / 4) % 4][at % 4];
+                    } else {
+                        const double f = to_reference();
+                        mine[NV * kWave] = fma(mine[NV * kWave], f, (double)l);
+#pragma unroll
+                        for (int at = 0; at < NV; ++at)
+                            mine[at * kWave] =
+                                fma(mine[at * kWave], f, (double)U[at / 16][(at / 4) % 4][at % 4]);
+                    }
+                    mine[(NV + 1) * kWave] = R;
+                    l = 0.0f;
+#pragma unroll
+                    for (int at = 0; at < NV; ++at) U[at / 16][(at / 4) % 4][at % 4] = 0.0f;
+                }
+            }
+            double l64 = (double)l;
+            if (done >= kF32Chain) {
+                const double f = to_reference();
+                l64 = fma(mine[NV * kWave], f, l64);
+#pragma unroll
+                for (int at = 0; at < NV; ++at) {
+                    const double u = fma(mine[at * kWave], f, (double)U[at / 16][(at / 4) % 4][at % 4]);
+                    U[at / 16][(at / 4) % 4][at % 4] = (float)u;
+                }
             }
 
             // ---- fold the four wavefront states ----------------------------------------
@@ -255,13 +304,14 @@ void tile_f32_kernel(Problem p, F32Sched sc) {
 #pragma unroll
                     for (int e = 0; e < 4; ++e) bad = fmaf(U[i][n][e] * 4.0f, 0.0f, bad);
             const bool big = __builtin_amdgcn_ballot_w64(bad != 0.0f) != 0;
-            l = row_reduce(l, [](float a, float bb) { return a + bb; });
+            l = row_reduce((float)l64, [](float a, float bb) { return a + bb; });
             __syncthreads();                   // the previous fold has been read
+            float* rows = reinterpret_cast<float*>(sums[wave]);
 #pragma unroll
             for (int i = 0; i < NB; ++i)
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
-                    *reinterpret_cast<f32x4*>(&fold_u[wave][c][64 * i + 16 * q + 4 * e]) =
+                    *reinterpret_cast<f32x4*>(&rows[c * FROW + 64 * i + 16 * q + 4 * e]) =
                         f32x4{U[i][0][e], U[i][1][e], U[i][2][e], U[i][3][e]};
             if (q == 0) {
                 fold_r[wave][c] = R;
@@ -286,7 +336,8 @@ void tile_f32_kernel(Problem p, F32Sched sc) {
                     const float f = fold_r[w][fr] == ninf ? lw * 0.0f
                                                           : exp2_fast((float)(fold_r[w][fr] - top));
                     lt = fmaf(f, lw, lt);
-                    o += f * *reinterpret_cast<const f32x4*>(&fold_u[w][fr][t]);
+                    o += f * *reinterpret_cast<const f32x4*>(
+                                 reinterpret_cast<const float*>(sums[w]) + fr * FROW + t);
                 }
                 const bool empty = lt == 0.0f;
                 const float inv = empty ? 0.0f : 1.0f / lt;
@@ -305,6 +356,7 @@ void tile_f32_kernel(Problem p, F32Sched sc) {
             }
             break;
         }
+        if (id + gridDim.x < sc.total) __syncthreads();   // the fold has been read, sums is free
     }
 }
 

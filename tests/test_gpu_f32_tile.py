@@ -8,6 +8,7 @@ import torch
 from oracle import attention as oa
 from paper_2505_14201_amd import flashd, synthetic
 from tests.gpu_util import check, run_flashd
+from tests.test_gpu_state import check_state, run_chunks
 
 pytestmark = pytest.mark.gpu
 AUTO, PER_KEY = flashd.VARIANT_AUTO, flashd.VARIANT_PER_KEY
@@ -91,3 +92,34 @@ def test_large_values(splits, sign):
         ref = oa.attn(q, k, v, True, w.scale)
         for h in range(4):
             check(got[:, h:h + 1], np.ascontiguousarray(ref[:, h:h + 1]), torch.float32, f"d={d} h={h}")
+
+
+@pytest.mark.parametrize("Lk", [319, 321, 383, 385, 705, 770, 1100])
+@pytest.mark.parametrize("d", [64, 128])
+def test_sums_that_join_in_fp64(Lk, d):
+    """A wavefront's sums join those in fp64 after every 6 blocks (384 keys of a row): key counts
+    around that, values of mean 1, references that move in between, and the state."""
+    w = synthetic.small("t", 1, 4, 2, 21, Lk, d, "f32", True, seed=9600 + Lk, qk_std=2.0)
+    q, k, v, _ = synthetic.make_qkv(w)
+    k = k * torch.linspace(0.1, 2.0, Lk).view(1, 1, -1, 1)
+    v = v + 1.0
+    for splits in (1, 2):
+        check(run_flashd(q, k, v, True, w.scale, AUTO, splits), oa.attn(q, k, v, True, w.scale),
+              torch.float32, f"splits={splits}")
+    o, st = run_chunks(q, k, v, True, w.scale, (Lk // 2,), in_place=True)
+    check(o, oa.attn(q, k, v, True, w.scale), torch.float32)
+    check_state(st, oa.attn_state(q, k, v, True, w.scale), d, torch.float32, "state")
+
+
+def test_long_sums_lose_nothing():
+    """300000 keys of equal score, in one range: sums in fp32 would round the same way at every key
+    (2e-4 of the result).  The weights are all 1, so what is left is the rounding of chains of 6
+    blocks (96 additions of 2^-24 each, at most 6e-6) and of the output."""
+    q = torch.zeros(1, 1, 16, 64)
+    gen = torch.Generator().manual_seed(9650)
+    k = torch.randn(1, 1, 300000, 64, generator=gen)
+    v = 0.7 + 7e-4 * torch.randn(1, 1, 300000, 64, generator=gen)
+    got = run_flashd(q, k, v, False, 0.125, AUTO, 1)
+    ref = v.double().mean(2, keepdim=True)
+    err = ((got.double() - ref).abs() / ref.abs()).max().item()
+    assert err <= 6.5e-6, err
