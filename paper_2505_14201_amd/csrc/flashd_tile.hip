@@ -494,22 +494,34 @@ static bool heads_as_one(int Hq, int Hkv, int Lq) {
     return g > 1 && g * Lq <= (1L << 30);          // row numbers are 32-bit
 }
 
-// Few causal queries late in a context have all row tiles of about one length, so that the closer
-// bounds give nothing: where no row tile is saved either, the heads run one after the other beyond
-// 8 keys per position.  512 x 4096 gains 1 to 3 % interleaved; 247 x 2304 between + 2 and - 2 %
-// (38 x 32/8 heads 400 us against 395, 31 x 8/1 82.2 against 80.2), 17 x 16/2 of 250 x 4000,
-// d = 64, 112 us against 109.
-static bool late_queries(const Problem& p) {
+// Where the heads run one after the other all the same, if no row tile is saved (measured over 270
+// calls of 2, 4 and 8 heads to a kv head, 32 to 8192 positions, 128 to 16384 keys; time interleaved
+// over time one after the other, and its 5th and 95th percentiles):
+//   - keys in splits: 1.03 (0.95 to 1.13), 4 x 16/4 heads, 512 x 1304, d = 64 28.9 us against
+//     26.1.  All workgroups are resident at once then, K and V come from the caches, and each writes
+//     its partial states to rows of all the heads.
+//   - a state read or written by fewer workgroups than there are compute units: 1.04 (0.95 to 1.12),
+//     16 x 4/1 heads, 128 x 128 12.0 us against 10.7; from 256 workgroups on 0.99.
+//   - the last position sees more than 8 keys per position: all row tiles are of about one length,
+//     and closer bounds give nothing.  On average still 0.96 (0.87 to 1.04), but 38 x 32/8 heads,
+//     128 x 4305, take 510 us interleaved and 422 one after the other (128 x 2952 353 and 295).
+// Otherwise, whole keys and output only, 0.90 (0.81 to 0.98): the g heads of a group share K and V in
+// the cache of one XCD.
+static bool heads_apart(const Problem& p) {
     constexpr long kBM = 32 * kNW;
     const long g = p.Hq / p.Hkv;
-    const bool fewer = (g * p.Lq + kBM - 1) / kBM < g * ((p.Lq + kBM - 1) / kBM);
-    return p.causal && !fewer && p.Lk > 8L * p.Lq;
+    const long tiles = (g * p.Lq + kBM - 1) / kBM;
+    if (tiles < g * ((p.Lq + kBM - 1) / kBM)) return false;
+    if (p.splits > 1) return true;
+    if ((p.partial || p.from_state) && tiles * p.B * p.Hkv < 256) return true;
+    const long last = (long)p.Lq + p.shift < p.Lk ? (long)p.Lq + p.shift : p.Lk;
+    return p.causal && last > 8L * p.Lq;
 }
 
 template <typename T, int D>
 static hipError_t launch_tile_t(const Problem& p_in, int mode, hipStream_t st) {
     Problem p = p_in;
-    if (heads_as_one(p.Hq, p.Hkv, p.Lq) && !late_queries(p)) {
+    if (heads_as_one(p.Hq, p.Hkv, p.Lq) && !heads_apart(p)) {
         p.heads = make_fast_div((uint32_t)(p.Hq / p.Hkv));
         p.Lq *= p.Hq / p.Hkv;
         p.Hq = p.Hkv;
