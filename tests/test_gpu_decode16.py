@@ -96,16 +96,22 @@ def test_state_of_a_decode_step():
     check_state(st, oa.attn_state(q, k, v, True, w.scale), 128, torch.bfloat16, "state")
 
 
-@pytest.mark.parametrize("B,Hkv,Lk", [(1, 2, 70), (64, 8, 65)])     # K through LDS, K direct
-@pytest.mark.parametrize("d", [64, 128])
-def test_fp8_cache(B, Hkv, Lk, d):
-    w = synthetic.small("t", B, 4 * Hkv, Hkv, 1, Lk, d, "bf16", False, seed=9820)
-    q, k, v, _ = synthetic.make_qkv(w)
-    k8, v8 = (k.float() * 32).to(torch.float8_e4m3fn), (v.float() * 32).to(torch.float8_e4m3fn)
-    o = torch.full_like(q, float("nan")).cuda()
-    flashd.attn_fwd_kv8(q.cuda(), k8.cuda(), v8.cuda(), o, False, w.scale, 1 / 32, 1 / 32)
+# K through LDS, K direct from 512 workgroups on; the last in 2 splits of its own accord
+@pytest.mark.parametrize("B,Hkv,Lq,Lk", [(1, 2, 1, 70), (64, 8, 1, 65), (64, 8, 4, 67), (33, 8, 1, 2050)])
+@pytest.mark.parametrize("dtype,d", [("bf16", 64), ("bf16", 128), ("f16", 64), ("f16", 128)])
+def test_fp8_cache(B, Hkv, Lq, Lk, dtype, d):
+    w = synthetic.small("t", B, 4 * Hkv, Hkv, Lq, Lk, d, dtype, Lq > 1, seed=9820)
+    gen = torch.Generator(device="cuda").manual_seed(9820 + Lk)
+    q = torch.randn(B, 4 * Hkv, Lq, d, device="cuda", generator=gen).to(DT[dtype])
+    k8, v8 = ((torch.randn(B, Hkv, Lk, d, device="cuda", generator=gen) * 32).to(torch.float8_e4m3fn)
+              for _ in "kv")
+    o = torch.full_like(q, float("nan"))
+    flashd.attn_fwd_kv8(q, k8, v8, o, w.causal, w.scale, 1 / 32, 1 / 32)
+    assert torch.isfinite(o.float()).all()
     sc = float(np.float32(w.scale) * np.float32(1 / 32))
-    check(o.cpu(), oa.attn(q, k8.float(), v8.float(), False, sc) / 32, torch.bfloat16)
+    for b in sorted({0, B // 2, B - 1}):
+        ref = oa.attn(q[b:b + 1].cpu(), k8[b:b + 1].cpu().float(), v8[b:b + 1].cpu().float(), w.causal, sc) / 32
+        check(o[b:b + 1].cpu(), ref, DT[dtype], f"b={b}")
 
 
 @pytest.mark.parametrize("splits", [8, 9, 16, 17, 64])

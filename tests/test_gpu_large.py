@@ -88,13 +88,17 @@ def test_long_queries_offsets_beyond_32_bits():
     torch.cuda.empty_cache()
 
 
-def test_long_keys_fp32_per_key_kernel():
+@pytest.mark.parametrize("variant", [flashd.VARIANT_PER_KEY, flashd.VARIANT_AUTO],
+                         ids=["per_key_kernel", "tile_kernel"])
+def test_long_keys_fp32(variant):
     need_memory(40)
     k = normal((B, H, LONG, D), torch.float32, 4301)
     v = normal((B, H, LONG, D), torch.float32, 4302)
     q = normal((B, H, 1, D), torch.float32, 4303)
     o = torch.full_like(q, float("nan"))
-    flashd.attn_fwd(q, k, v, o, False, SCALE)
+    nbytes = flashd.workspace_bytes(B, H, H, 1, LONG, D, flashd.F32, variant)
+    ws = torch.empty(max(nbytes, 16), dtype=torch.uint8, device="cuda")
+    flashd.attn_fwd_ex(q, k, v, o, False, SCALE, variant, 0, ws)
     torch.cuda.synchronize()
     for (b, h) in UNITS:
         sl = (slice(b, b + 1), slice(h, h + 1))

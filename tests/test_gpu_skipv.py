@@ -15,8 +15,8 @@ pytestmark = pytest.mark.gpu
 DT = {"f16": torch.float16, "bf16": torch.bfloat16}
 
 
-def run_both(w, splits):
-    q, k, v, _ = synthetic.make_qkv(w)
+def run_both(w, splits, qkv=None):
+    q, k, v = qkv or synthetic.make_qkv(w)[:3]
     qg, kg, vg = q.cuda(), k.cuda(), v.cuda()
     dt = {"f16": 1, "bf16": 2}[w.dtype]
     nbytes = flashd.workspace_bytes(w.B, w.Hq, w.Hkv, w.Lq, w.Lk, w.d, dt, flashd.VARIANT_TILE,
@@ -47,6 +47,46 @@ SHAPES = PEAKED_SHAPES + [
     (2, 8, 2, 4, 2000, 64, "f16", True, 1),          # several positions, causal
     (1, 4, 4, 7, 1500, 64, "bf16", True, 3),
 ]
+# 17 to 32 query rows per kv head: the kernel with 32-column score tiles
+WIDE_SHAPES = [
+    (1, 32, 1, 1, 2000, 128, "bf16", False, 1),
+    (2, 34, 2, 1, 1500, 64, "f16", False, 1),        # 17 rows
+    (1, 20, 1, 1, 3000, 64, "f16", False, 3),
+    (1, 32, 1, 1, 2500, 128, "bf16", False, 2),
+    (2, 8, 1, 4, 1300, 128, "bf16", True, 1),        # several positions, causal
+    (1, 5, 1, 5, 1111, 64, "bf16", True, 2),
+]
+
+
+def group_with_dominant_key(shape, at):
+    """Queries of a kv group that differ little, and key `at` far along their common direction:
+    its score lies some hundred above every other key's, for every row."""
+    B, Hq, Hkv, Lq, Lk, d, dtype, causal, splits = shape
+    w = synthetic.small("wide", B, Hq, Hkv, Lq, Lk, d, dtype, causal, seed=8400 + Lk, qk_std=4.0)
+    q, k, v, _ = synthetic.make_qkv(w)
+    common = q.float().view(B, Hkv, -1, d)[:, :, :1]
+    q = (common + 0.1 * q.float().view(B, Hkv, -1, d)).view(B, Hq, Lq, d).to(q.dtype)
+    k[:, :, at] = (2.0 * common[:, :, 0]).to(k.dtype)
+    return w, (q, k, v)
+
+
+@pytest.mark.parametrize("shape", WIDE_SHAPES)
+@pytest.mark.parametrize("late", [False, True])
+def test_17_to_32_rows_skip_value_blocks_and_keep_the_result(shape, late):
+    """The dominant key first: what follows it in its split is skipped.  Last (every position sees
+    it): what was accumulated before must give way to it, and nothing before it may be skipped on
+    its account."""
+    B, Hq, Hkv, Lq, Lk, d, dtype, causal, splits = shape
+    w, qkv = group_with_dominant_key(shape, Lk - 20 if late else 3)
+    q, k, v, base, skip, visited, skipped = run_both(w, splits, qkv)
+    ref = oa.attn(q, k, v, causal, w.scale)
+    check(skip, ref, DT[dtype], f"{shape} skipv")
+    check(base, ref, DT[dtype], f"{shape} tile")
+    assert torch.equal(base.view(torch.int16), skip.view(torch.int16))
+    if late:
+        assert skipped < 0.1 * visited
+    else:
+        assert skipped > 0.3 * visited / splits
 
 
 @pytest.mark.parametrize("shape", PEAKED_SHAPES)
@@ -70,7 +110,7 @@ def test_peaked_scores_skip_value_blocks_and_keep_the_result(shape):
         f"{shape}: only {skipped} of {visited} blocks skipped ({nsplits} splits)"
 
 
-@pytest.mark.parametrize("shape", SHAPES)
+@pytest.mark.parametrize("shape", SHAPES + WIDE_SHAPES)
 def test_ordinary_scores_skip_nothing_and_match_bit_for_bit(shape):
     B, Hq, Hkv, Lq, Lk, d, dtype, causal, splits = shape
     w = synthetic.small("plain", B, Hq, Hkv, Lq, Lk, d, dtype, causal, seed=8200 + Lk)
