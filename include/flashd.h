@@ -71,7 +71,8 @@ typedef enum {
 /* How the recurrence is evaluated.  All variants compute the same result. */
 typedef enum {
     FLASHD_VARIANT_AUTO = 0,     /* TILE (or TILE_256) for f16/bf16; for f32 the tile form on
-                                    the matrix cores with fp64 scores (reported as PER_KEY)  */
+                                    the matrix cores with fp64 scores (reported as PER_KEY;
+                                    AUTO is the only way to ask for it)                      */
     FLASHD_VARIANT_TILE = 1,     /* Alg. 3 lifted to key tiles on the matrix cores (f16/bf16),
                                     the (1 - W) factors of the blend deferred to the store   */
     FLASHD_VARIANT_PER_KEY = 2,  /* Alg. 3 literally, one sigmoid per key (any dtype)       */
@@ -138,12 +139,15 @@ size_t flashd_workspace_bytes(int B, int Hq, int Hkv, int Lq, int Lk, int d, int
 int flashd_auto_splits(int B, int Hq, int Hkv, int Lq, int Lk, int d, int dtype, int variant);
 
 /*
- * The variant flashd_attn_fwd (FLASHD_VARIANT_AUTO) runs for this problem: PER_KEY for f32
- * (which has one tile form of its own, at the precision of PER_KEY), else TILE, or TILE_256 for calls that kernel can serve and was measured faster on (d = 128,
- * one split, at least a workgroup per compute unit, row tiles that are not mostly padding, from
- * 1536 keys on without a mask, and with one where a row sees 1536 keys on average, or 1024 if the row
- * tiles come in whole rounds of the compute units).  Host-only; -1 for invalid arguments.  (Decode shapes,
- * (Hq / Hkv) * Lq <= 32, report TILE: they run the tile form on the split-K decode kernel.)
+ * The variant flashd_attn_fwd (FLASHD_VARIANT_AUTO) runs for this problem: PER_KEY for f32, else
+ * TILE, or TILE_256 for calls that kernel can serve and was measured faster on (d = 128, one
+ * split, at least a workgroup per compute unit, row tiles that are not mostly padding, from 1536
+ * keys on without a mask, and with one where a row sees 1536 keys on average, or 1024 if the row
+ * tiles come in whole rounds of the compute units).  Host-only; -1 for invalid arguments.
+ * Passed to flashd_attn_fwd_ex the answer gives the kernel that AUTO runs, save for f32: AUTO runs
+ * its tile form there, at the precision of PER_KEY and up to twelve times faster, but not with the
+ * same bits; pass FLASHD_VARIANT_AUTO itself to get it.  (Decode shapes, (Hq / Hkv) * Lq <= 32,
+ * report TILE: they run the tile form on the split-K decode kernel.)
  */
 int flashd_auto_variant(int B, int Hq, int Hkv, int Lq, int Lk, int d, int dtype, int causal);
 
@@ -195,8 +199,9 @@ int flashd_attn_fwd_kv8(const void* q, const void* k8, const void* v8, void* o,
  * output as it is, so the value vector need not be loaded), for decode shapes only:
  * (Hq / Hkv) * Lq <= 32 and f16/bf16 storage, else FLASHD_E_VARIANT.  Variant TILE's
  * arithmetic; per 32-key block the scores are formed first, and the block's V is fetched only
- * if, for some query row of the kv group, the block's top score lies within 2^200 of the
- * largest s_last - ln w_last that row has reached so far (the test is on the full argument of
+ * if, for some query row of the kv group, the block's top score lies within 2^200 of a bound of
+ * that row's s_last - ln w_last from below: the largest reached so far, or up to 16 query rows per
+ * kv head the largest score (the test is on the full argument of
  * the sigmoid, where the weight is exactly 0 in fp32, not on the paper's static range of score
  * differences, which is an approximation).  K is always read.  The result is that of
  * flashd_attn_fwd_ex(..., FLASHD_VARIANT_TILE, splits, ...) to the last bit on inputs where

@@ -81,7 +81,7 @@ size_t partial_bytes(const Shape& s, int n) {
 // 64 splits, with 4 and 32 query rows per kv head; times are of one launch among others).
 //   - Short key ranges stay whole: a second launch and its gap cost 4 us, a 32-key block takes a
 //     wavefront 1 us at d = 128 and half of that at 64.  8 units of 600 keys: 8.1 us whole, 9.0
-//     in any number of splits; of 1000 keys 10.5 and 9.0.  Below 512 keys nothing is split, here
+//     in any number of splits; of 1000 keys 10.5 and 9.5.  Below 512 keys nothing is split, here
 //     as in auto_splits, so that such calls need no scratch memory and can be captured into a graph
 //     without a call before; nor from 512 units on.
 //   - How many workgroups fill the chip depends on what one streams by itself, 32 keys of K and V per
@@ -161,7 +161,8 @@ int auto_splits(const Shape& s, int variant, bool fp8 = false, bool or_shorter =
     // is what the tile kernel wants: measured over short-query and prefill
     // shapes of 64 to 512 units, the fastest split count is the one that brings the launch
     // to 256-512 workgroups; more of them only add partial states to write and merge.  The
-    // per-key kernel keeps two rounds.
+    // per-key kernel keeps two rounds, and so does the fp32 tile kernel that AUTO runs in its
+    // place, for which the rule has not been measured.
     const long target = variant == FLASHD_VARIANT_PER_KEY ? 1024 : 512;
     if (units < 1) units = 1;
     long sp = units >= target ? 1 : ceil_div(target, units);

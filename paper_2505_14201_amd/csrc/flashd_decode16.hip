@@ -37,7 +37,7 @@
 // one block behind K, and is requested before the block's exponentials.
 //
 // Measured (bf16, d = 128, 32 / 8 heads, one position; before, on the 32-column kernels and their
-// splits): 1 x 1000 keys 9.0 us (13.6), 4 x 3000 13.8 (18.0), 16 x 600 9.7 (15.6), 20 x 4000 51 (59),
+// splits): 1 x 1000 keys 9.5 us (13.5), 4 x 3000 13.8 (18.0), 16 x 600 9.7 (15.6), 20 x 4000 51 (59),
 // 64 x 8192 309 (312: 6.9 TB/s, HBM's rate).
 #include "flashd_common.h"
 #include "flashd_kernels.h"
@@ -126,8 +126,8 @@ void decode16_kernel(Problem p, Dec16Sched sc) {
                              ? 2 * kD16Waves * STAGE : 4 * kD16Waves * 16 * FROW;
     __shared__ __align__(16) char lds[kLds];
     __shared__ float fold_r[kD16Waves][16], fold_l[kD16Waves][16], fold_t[kD16Waves][16];
-    // per row: the largest score any wavefront has seen, a bound of Lam from below (volatile: the
-    // other wavefronts' stores must be looked at on every block)
+    // per row: the largest score any wavefront has seen, a bound of Lam from below (by atomics: the
+    // other wavefronts' must be looked at on every block)
     __shared__ float top_seen[SKIP ? 16 : 1];
 
     const int tid = threadIdx.x;

@@ -616,7 +616,7 @@ __device__ __forceinline__ void row_finish(float lam, float beta, float& fin, fl
     }
 }
 
-// Keys visible to query position pos of a head (0 <= pos < Li.d).
+// Keys visible to query position pos of a head (0 <= pos < head_rows).
 __device__ __forceinline__ int visible_at(const Problem& p, int pos) {
     if (!p.causal) return p.Lk;
     return min(max(pos + p.shift + 1, 0), p.Lk);

@@ -315,8 +315,7 @@ void perkey_kernel(Problem p) {
 // itself, NS of them in log2 NS steps.  What bounds it is the reading of the partials, which
 // prefill shapes with split keys have by the 10 MB: a wavefront per row, its Lam over the lanes
 // and one or two columns per lane, made a call with 32768 rows of 2 partials, d = 64, take 32.9 us,
-// now 23.0 (5.2 of them this kernel); 4 x 8000 rows, d = 128, 50.6 and 46.8; 1 x 1000 keys of a
-// decode step in 8 splits 8.5 and 8.2.
+// now 23.0 (5.2 of them this kernel); 4 x 8000 rows, d = 128, 50.6 and 46.8.
 template <typename T, int D, int NS>                // NS: splits, rounded up to a power of two
 __global__ __launch_bounds__(256)
 void merge_few_kernel(Problem p) {
