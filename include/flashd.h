@@ -74,7 +74,9 @@ typedef enum {
                                     the matrix cores with fp64 scores (reported as PER_KEY;
                                     AUTO is the only way to ask for it)                      */
     FLASHD_VARIANT_TILE = 1,     /* Alg. 3 lifted to key tiles on the matrix cores (f16/bf16),
-                                    the (1 - W) factors of the blend deferred to the store   */
+                                    the (1 - W) factors of the blend deferred to the store;
+                                    with splits == 0 small calls take kernels with 32 or 64
+                                    query rows per workgroup, splits given the 128-row one   */
     FLASHD_VARIANT_PER_KEY = 2,  /* Alg. 3 literally, one sigmoid per key (any dtype)       */
     FLASHD_VARIANT_ONLINE_SOFTMAX = 3, /* ablation: Alg. 2 (running max, sum, final division)
                                           on the same tiling as TILE (f16/bf16)             */
@@ -135,7 +137,9 @@ size_t flashd_workspace_bytes(int B, int Hq, int Hkv, int Lq, int Lk, int d, int
                               int variant, int splits);
 
 /* The number of splits the automatic choice takes for this problem (>= 1; flashd_attn_fwd_kv8, whose
- * key ranges have half the bytes, may take another). */
+ * key ranges have half the bytes, may take another).  Outside the decode shapes it is the most that
+ * it takes, and what scratch memory is sized for: small calls in f16/bf16 run with fewer, or none,
+ * where a kernel with 32 or 64 query rows per workgroup is faster. */
 int flashd_auto_splits(int B, int Hq, int Hkv, int Lq, int Lk, int d, int dtype, int variant);
 
 /*
@@ -147,7 +151,8 @@ int flashd_auto_splits(int B, int Hq, int Hkv, int Lq, int Lk, int d, int dtype,
  * Passed to flashd_attn_fwd_ex the answer gives the kernel that AUTO runs, save for f32: AUTO runs
  * its tile form there, at the precision of PER_KEY and up to twelve times faster, but not with the
  * same bits; pass FLASHD_VARIANT_AUTO itself to get it.  (Decode shapes, (Hq / Hkv) * Lq <= 32,
- * report TILE: they run the tile form on the split-K decode kernel.)
+ * report TILE: they run the tile form on the split-K decode kernel.)  The answer belongs with
+ * splits == 0.
  */
 int flashd_auto_variant(int B, int Hq, int Hkv, int Lq, int Lk, int d, int dtype, int causal);
 

@@ -2,6 +2,8 @@
 // per-(device, stream) workspace cache, and dispatch to the kernel launchers.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+#include <cmath>
 #include <cstring>
 #include <map>
 #include <mutex>
@@ -191,6 +193,97 @@ int auto_splits(const Shape& s, int variant, bool fp8 = false, bool or_shorter =
     return (int)sp;
 }
 
+// ---- kernels for prefill calls that the 128-row kernel does not fill the chip with ----------
+// Which kernel, and in how many of the splits above, is decided by an estimate of each one's time:
+// the chain of its longest row tile, its work on the whole chip and its way to K and V, whichever
+// is the longest (smoothed), and what it reads and writes of states.  The figures are fits over 2500
+// calls of 1 to 64 sequences, 4 to 32 heads, 8 to 12288 positions and 16 to 117000 keys, causal or
+// not, whole or in chunks; the estimates are within 7 to 13 % on average.  By it 900 calls that the
+// 256-row kernel does not take went to 0.92 (d = 128) and 0.89 (d = 64) of their time on average,
+// down to 0.45: 5 x 16 heads, 182 x 882, d = 128 29.3 -> 17.2 us, 3 x 16 heads of 681, causal, d = 64
+// 22.0 -> 11.2, 1 x 16/2 heads of 664 17.9 either way.
+enum class RowKernel { Tile, Tile64, Short };
+
+struct RowCost {
+    int rows, keys;     // query rows of a workgroup, keys that it steps over at a time
+    double start;       // us: launch, first loads, fold, store
+    double chain;       // us a step of the longest row tile
+    double work, wg;    // us a step, and a workgroup, of one compute unit's share of all
+    double state;       // us per MB of states and partial states, read and written
+    double kv;          // us per MB of K and V (of the 32- and 64-row kernels more than fitted: where memory is
+                        // the bound, 64 x 32/8 heads, 16 x 8192, the 64-row one took 368 us and the 128-row one 310)
+};
+
+double row_estimate(const RowCost& c, const Shape& s, bool causal, int shift, int splits, int states) {
+    const double g = s.Hq / s.Hkv, units = (double)s.B * s.Hkv, lq = s.Lq, lk = s.Lk;
+    const double tiles = std::ceil(g * lq / c.rows);
+    double most = lk, mean = lk;            // keys the last row, and a row on average, sees
+    if (causal) {
+        // row i sees min(max(i + shift + 1, 0), lk)
+        const double lo = std::min(std::max(-(double)shift - 1.0, 0.0), lq);
+        const double hi = std::min(std::max(lk - shift - 1.0, lo), lq);
+        mean = ((hi - lo) * (lo + hi + 2.0 * shift + 1.0) * 0.5 + (lq - hi) * lk) / lq;
+        most = std::min(std::max(lq + shift, 0.0), lk);
+    }
+    const double wgs = units * tiles * splits;
+    const double chain = c.chain * std::ceil(most / ((double)c.keys * splits));
+    // row tiles of equal length end together, the fullest compute unit's last (the 128-row kernel, which
+    // the others have to beat, by the average)
+    const double share = causal || c.rows == 128 ? wgs / 256.0 : std::ceil(wgs / 256.0);
+    const double work = share * (c.work * (mean / ((double)splits * c.keys) + 0.5) + c.wg);
+    // K and V are read into every L2 that a unit's row tiles run beside
+    const double reads = (long)units % 8 == 0 ? 1.0 : std::min(8.0, tiles);
+    const double kv = c.kv * units * most * s.d * 4e-6 * reads;
+    const double p2 = chain * chain, q2 = work * work, r2 = kv * kv;
+    const double state_mb = (double)s.B * s.Hq * lq * (s.d + 2) * 4e-6;
+    double t = c.start + std::sqrt(std::sqrt(p2 * p2 + q2 * q2 + r2 * r2)) +
+               c.state * state_mb * (states + (splits > 1 ? 2 * splits : 0));
+    if (splits > 1) t += splits > 8 ? 4.6 : 3.6;        // the merge
+    return t;
+}
+
+struct RowPlan { RowKernel kernel; int splits; };
+
+// splits: those of the rule above, which are also what scratch memory is sized for: the plan has
+// no more.  states: states read and written by the call.  fp8: K and V are fp8, which the 32-row
+// kernel reads as such and the others need widened first.
+RowPlan row_plan(const Shape& s, bool causal, int shift, int splits, int states, bool fp8) {
+    static const RowCost kTile[2] = {{128, 64, 3.7, 1.03, 0.65, 0.86, 0.21, 0.16},
+                                     {128, 64, 6.2, 1.15, 1.10, 0.62, 0.19, 0.14}};
+    static const RowCost kTile64[2] = {{64, 64, 4.4, 0.55, 0.34, 0.73, 0.16, 0.18},
+                                       {64, 64, 5.9, 0.74, 0.59, 1.74, 0.16, 0.17}};
+    static const RowCost kShort[2] = {{32, 128, 3.8, 0.57, 0.42, 0.52, 0.15, 0.18},
+                                      {32, 128, 5.1, 0.82, 0.77, 1.67, 0.13, 0.17}};
+    const int w = s.d == 128 ? 1 : 0;
+    RowPlan plan{RowKernel::Tile, splits};
+    const long g = s.Hq / s.Hkv;
+    // (row numbers are 32-bit; of two key tiles there is nothing to share out)
+    if (g * s.Lq > (1L << 30) || s.Lk <= 128) return plan;
+    const long wgs = (long)s.B * s.Hkv * ceil_div(g * s.Lq, kShort[w].rows);
+    // beyond this the 128-row kernel has rounds of workgroups to even things out by
+    if (wgs > 2048) return plan;
+    const double widen = fp8 ? 3.0 + (double)s.B * s.Hkv * s.Lk * s.d * 1.5e-6 : 0.0;
+    // The 128-row kernel stays where it is not clearly behind, and over long split ranges where the
+    // estimate is at its worst (5 x 32/8 heads, 66 x 9530 112 us on the 32-row kernel, 88 on it).
+    double best = (row_estimate(kTile[w], s, causal, shift, splits, states) + widen) /
+                  (splits > 1 && s.Lk > 2500 ? 1.2 : 1.05);
+    const double t64 = row_estimate(kTile64[w], s, causal, shift, 1, states) + widen;
+    if (t64 < best) {
+        best = t64;
+        plan = {RowKernel::Tile64, 1};
+    }
+    for (int sp : {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64}) {
+        // one workgroup per compute unit (two at d = 64), which the ranges share out
+        if (sp > splits || (sp > 1 && (wgs * sp > (w ? 320 : 512) || s.Lk / sp < 256))) break;
+        const double t = row_estimate(kShort[w], s, causal, shift, sp, states);
+        if (t < best) {
+            best = t;
+            plan = {RowKernel::Short, sp};
+        }
+    }
+    return plan;
+}
+
 // Splits whose partial states the scratch memory of a call with sp splits is sized for.  A call of
 // the automatic choice that needs scratch at all takes what every call with fewer keys needs, so
 // that one made at the longest context serves a decode loop, or a graph captured later, at any
@@ -345,17 +438,30 @@ int run(const void* q, const void* k, const void* v, void* o, const Shape& s, in
     // the skip lives in the split-K decode kernel (f16/bf16, at most 32 query rows per kv head)
     if (sk.on && (s.dtype == FLASHD_F32 || !flashd::decode_applies(s.Hq, s.Hkv, s.Lq)))
         return FLASHD_E_VARIANT;
-    const bool widen = k8.on && !flashd::decode_applies(s.Hq, s.Hkv, s.Lq);
+    const bool decode = flashd::decode_applies(s.Hq, s.Hkv, s.Lq);
     if (splits < 0 || splits > FLASHD_MAX_SPLITS || splits > s.Lk) return FLASHD_E_VARIANT;
-    const int sp = splits == 0 ? auto_splits(s, var, k8.on) : splits;
+    const int sp_most = splits == 0 ? auto_splits(s, var, k8.on) : splits;
+    // a shift of Lk or more shows every key and one below -Lq none: clamping the caller's
+    // value there changes no result and keeps i + shift inside 32 bits
+    const int shift = !sa.on ? s.Lk - s.Lq : sa.shift > s.Lk ? s.Lk : sa.shift < -s.Lq - 1 ? -s.Lq - 1 : sa.shift;
+    const bool auto_wide = !sa.on && !k8.on && !sk.on && sp_most == 1 && prefers_256_rows(s, causal != 0);
+    const bool wide = var == FLASHD_VARIANT_TILE_256 || (variant == FLASHD_VARIANT_AUTO && auto_wide);
+    RowPlan plan{RowKernel::Tile, sp_most};
+    if (var == FLASHD_VARIANT_TILE && splits == 0 && !decode && !auto_wide)
+        plan = row_plan(s, causal != 0, shift, sp_most,
+                        (sa.in != nullptr ? 1 : 0) + (sa.out != nullptr ? 1 : 0), k8.on);
+    const int sp = plan.splits;
+    const bool widen = k8.on && !decode && plan.kernel != RowKernel::Short;
     // The state entry point always goes through partial states; a single partial may be
     // written straight into the caller's state buffer (unless that is also the input state).
     const bool direct = sa.on && sp == 1 && sa.out != nullptr && sa.out != sa.in;
     // The tile kernel can start from the state itself and write both results: no partial
     // states, no merge kernel.
-    const bool in_kernel = sa.on && sp == 1 && var == FLASHD_VARIANT_TILE &&
-                           !flashd::decode_applies(s.Hq, s.Hkv, s.Lq);
-    const size_t need = sa.on ? ((direct || in_kernel) ? 0 : partial_bytes(s, sp)) : ws_bytes(s, sp);
+    const bool in_kernel = sa.on && sp == 1 && var == FLASHD_VARIANT_TILE && !decode;
+    // (by the splits of the rule, also where the plan has fewer: what scratch memory suffices for
+    // does not depend on the kernel that runs)
+    const size_t need = sa.on ? ((sp_most == 1 && (direct || in_kernel)) ? 0 : partial_bytes(s, sp_most))
+                              : ws_bytes(s, sp_most);
     if (mode == WsMode::Caller && need > 0 && (workspace == nullptr || workspace_bytes < need))
         return FLASHD_E_WORKSPACE;
     if (mode == WsMode::Static && need > kScratchBytes) return FLASHD_E_WORKSPACE;
@@ -364,9 +470,9 @@ int run(const void* q, const void* k, const void* v, void* o, const Shape& s, in
     if (rc != FLASHD_OK) return rc;
     void* ws = workspace;
     const size_t need_al = (need + 255) & ~(size_t)255;
-    const size_t kv_bytes = widen ? (size_t)s.B * s.Hkv * s.Lk * s.d * 2 : 0;   // per tensor
+    const size_t kv_bytes = k8.on && !decode ? (size_t)s.B * s.Hkv * s.Lk * s.d * 2 : 0;   // per tensor
     if (use_cache) {
-        const size_t cover = partial_bytes(s, scratch_splits(s, var, k8.on, splits, sp));
+        const size_t cover = partial_bytes(s, scratch_splits(s, var, k8.on, splits, sp_most));
         const size_t most = need > 0 && cover > need_al ? (cover + 255) & ~(size_t)255 : need_al;
         rc = cached_workspace(stream, most + 2 * kv_bytes, &ws);
         if (rc != FLASHD_OK) return rc;
@@ -401,10 +507,7 @@ int run(const void* q, const void* k, const void* v, void* o, const Shape& s, in
     p.splits = sp;
     p.scale = score_scale;
     p.oscale = out_scale;
-    // a shift of Lk or more shows every key and one below -Lq none: clamping the caller's
-    // value there changes no result and keeps i + shift inside 32 bits
-    const int shift_in = sa.shift > s.Lk ? s.Lk : (sa.shift < -s.Lq - 1 ? -s.Lq - 1 : sa.shift);
-    p.shift = sa.on ? shift_in : s.Lk - s.Lq;
+    p.shift = shift;
     p.partial = (sp > 1 || sa.on) ? 1 : 0;
     p.store_o = p.partial ? 0 : 1;
     p.merge = p.partial;
@@ -412,9 +515,7 @@ int run(const void* q, const void* k, const void* v, void* o, const Shape& s, in
     p.state_in = sa.in;
     p.state_out = sa.out;
     p.vskip_counts = sk.counts;
-    p.wide = (var == FLASHD_VARIANT_TILE_256 ||
-              (variant == FLASHD_VARIANT_AUTO && !sa.on && !k8.on && !sk.on && sp == 1 &&
-               prefers_256_rows(s, causal != 0))) ? 1 : 0;
+    p.wide = wide ? 1 : 0;
     if (in_kernel) {
         p.partial = sa.out != nullptr ? 1 : 0;     // the "partial" is the state handed out
         p.store_o = o != nullptr ? 1 : 0;
@@ -429,8 +530,7 @@ int run(const void* q, const void* k, const void* v, void* o, const Shape& s, in
     hipError_t e;
     // The automatic choice takes the decode kernel with the saturation skip: on inputs where
     // nothing can be skipped it returns the bits of the unskipped kernel at the same speed.
-    const bool auto_skip = variant == FLASHD_VARIANT_AUTO && !k8.on && s.dtype != FLASHD_F32 &&
-                           flashd::decode_applies(s.Hq, s.Hkv, s.Lq);
+    const bool auto_skip = variant == FLASHD_VARIANT_AUTO && !k8.on && s.dtype != FLASHD_F32 && decode;
     const int tmode = (sk.on || auto_skip)                 ? flashd::kTileModeLazySkipV
                       : var == FLASHD_VARIANT_ONLINE_SOFTMAX ? flashd::kTileModeOnline
                       : var == FLASHD_VARIANT_TILE_BLEND   ? flashd::kTileModeBlend
@@ -438,7 +538,9 @@ int run(const void* q, const void* k, const void* v, void* o, const Shape& s, in
     // fp32 without a variant asked for: the tile form on the matrix cores
     if (s.dtype == FLASHD_F32 && variant == FLASHD_VARIANT_AUTO) e = flashd::launch_tile_f32(p, st);
     else if (var == FLASHD_VARIANT_PER_KEY) e = flashd::launch_perkey(p, st);
-    else if (flashd::decode_applies(s.Hq, s.Hkv, s.Lq)) e = flashd::launch_decode(p, tmode, st);
+    else if (decode) e = flashd::launch_decode(p, tmode, st);
+    else if (plan.kernel == RowKernel::Short) e = flashd::launch_short(p, st);
+    else if (plan.kernel == RowKernel::Tile64) e = flashd::launch_tile64(p, st);
     else e = flashd::launch_tile(p, tmode, st);
     return e == hipSuccess ? FLASHD_OK : FLASHD_E_HIP;
 }

@@ -34,6 +34,12 @@ hipError_t launch_tile(const Problem& p, int mode, hipStream_t st);
 bool wide_applies(const Problem& p, int mode);
 hipError_t launch_wide(const Problem& p, int mode, hipStream_t st);
 
+// 32 rows per workgroup, their keys shared out over its wavefronts (variant TILE, f16/bf16, also
+// with K and V in fp8).  With p.merge also folds the partials.
+hipError_t launch_short(const Problem& p, hipStream_t st);
+// 64 rows per workgroup, two wavefronts to a row's keys.
+hipError_t launch_tile64(const Problem& p, hipStream_t st);
+
 // Number of workgroups launch_tile uses per split.
 long tile_workgroups(int B, int Hq, int Hkv, int Lq, int d);
 
