@@ -1,4 +1,5 @@
-"""Compile libflashd.so for gfx950 with hipcc (cross-compiles without a GPU)."""
+"""Compile libflashd.so for gfx950 with hipcc (cross-compiles without a GPU) and the Python binding's
+native part with g++."""
 from __future__ import annotations
 
 import os
@@ -16,12 +17,35 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
          "-Wall", "-Wno-unused-command-line-argument"]
 
 
+BINDING = os.path.join(HERE, "_flashd_binding.so")
+BINDING_SOURCE = os.path.join(CSRC, "flashd_binding.cpp")
+
+
 def stale() -> bool:
-    if not os.path.exists(LIB):
+    if not os.path.exists(LIB) or not os.path.exists(BINDING):
         return True
-    t = os.path.getmtime(LIB)
-    deps = [os.path.join(CSRC, s) for s in SOURCES + HEADERS]
+    t = min(os.path.getmtime(LIB), os.path.getmtime(BINDING))
+    deps = [os.path.join(CSRC, s) for s in SOURCES + HEADERS] + [BINDING_SOURCE]
     return any(os.path.getmtime(d) > t for d in deps)
+
+
+def build_binding(verbose: bool = False) -> str:
+    import sysconfig
+
+    import torch
+    from torch.utils.cpp_extension import include_paths
+    lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}",
+           *[a for d in (*include_paths(), sysconfig.get_paths()["include"]) for a in ("-isystem", d)],
+           BINDING_SOURCE, "-o", BINDING, "-L", lib, "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10",
+           f"-Wl,-rpath,{lib}"]
+    if verbose:
+        print(" ".join(cmd))
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("g++ failed:\n" + r.stderr)
+    return BINDING
 
 
 def build(force: bool = True, verbose: bool = False) -> str:
@@ -37,6 +61,7 @@ def build(force: bool = True, verbose: bool = False) -> str:
         raise RuntimeError("hipcc failed:\n" + err)
     if verbose and err.strip():
         print(err)
+    build_binding(verbose)
     return LIB
 
 

@@ -1,4 +1,5 @@
-"""Thin ctypes binding over libflashd.so: argument marshalling only.
+"""Thin binding over libflashd.so: argument marshalling only (ctypes, and for the calls of the
+serving path a native module in front of it).
 
 Function names mirror the C ABI in include/flashd.h.  Tensors are torch CUDA
 (ROCm) tensors used purely as owners of device memory; every step of the
@@ -73,6 +74,11 @@ def _load() -> ctypes.CDLL:
 
 
 _lib = _load()
+try:
+    from . import _flashd_binding as _native
+except ImportError as e:
+    raise ImportError("the binding's native part is missing: build it with "
+                      "`python -m paper_2505_14201_amd.build`") from e
 
 
 def raw() -> ctypes.CDLL:
@@ -134,6 +140,12 @@ def _marshal(q, k, v, o):
 _current_device = torch._C._cuda_getDevice
 _raw_stream = torch._C._cuda_getCurrentRawStream
 
+# The native forms of attn_fwd, attn_fwd_kv8 and attn_fwd_state: they return the status of the call, or
+# None where an argument is out of the ordinary and nothing has been enqueued.
+_native.bind(*(ctypes.cast(f, ctypes.c_void_p).value
+               for f in (_lib.flashd_attn_fwd, _lib.flashd_attn_fwd_kv8, _lib.flashd_attn_fwd_state)),
+             _current_device, _raw_stream)
+
 
 def _enqueue(fn, device, stream, head, tail=()) -> None:
     """fn(*head, stream handle, *tail) with `device` (an index) current; raises on a status other
@@ -148,6 +160,12 @@ def _enqueue(fn, device, stream, head, tail=()) -> None:
 
 def attn_fwd(q, k, v, o, causal: bool, scale: float, stream=None) -> None:
     """flashd_attn_fwd: o <- attention(q, k, v), enqueued on `stream` (default: current)."""
+    if stream is None:
+        rc = _native.attn_fwd(q, k, v, o, causal, scale)
+        if rc is not None:
+            if rc != 0:
+                raise FlashdError(rc)
+            return
     B, Hq, Hkv, Lq, Lk, d, dt = _marshal(q, k, v, o)
     _enqueue(_lib.flashd_attn_fwd, q.get_device(), stream, (q.data_ptr(), k.data_ptr(),
              v.data_ptr(), o.data_ptr(), B, Hq, Hkv, Lq, Lk, d, int(bool(causal)), float(scale),
@@ -229,6 +247,12 @@ def attn_fwd_state(q, k, v, causal: bool, scale: float, o=None, state_in=None, s
                    causal_shift=None, stream=None) -> None:
     """flashd_attn_fwd_state: one chunk of keys with the Alg. 3 state handed in and out.
     States are float32 GPU tensors [B, Hq, Lq, d + 2]; causal_shift defaults to Lk - Lq."""
+    if stream is None:
+        rc = _native.attn_fwd_state(q, k, v, causal, scale, o, state_in, state_out, causal_shift)
+        if rc is not None:
+            if rc != 0:
+                raise FlashdError(rc)
+            return
     for name, t in (("q", q), ("k", k), ("v", v)):
         if not t.is_cuda or not t.is_contiguous():
             raise ValueError(f"{name} must be a contiguous GPU tensor")
@@ -256,6 +280,12 @@ def attn_fwd_kv8(q, k8, v8, o, causal: bool, scale: float, kscale: float, vscale
                  stream=None) -> None:
     """flashd_attn_fwd_kv8: K and V as torch.float8_e4m3fn tensors [B, Hkv, Lk, d] (the real
     values are kscale * k8 and vscale * v8); q and o float16 or bfloat16."""
+    if stream is None:
+        rc = _native.attn_fwd_kv8(q, k8, v8, o, causal, scale, kscale, vscale)
+        if rc is not None:
+            if rc != 0:
+                raise FlashdError(rc)
+            return
     for name, t in (("q", q), ("k8", k8), ("v8", v8), ("o", o)):
         if not t.is_cuda or not t.is_contiguous():
             raise ValueError(f"{name} must be a contiguous GPU tensor")
