@@ -450,6 +450,13 @@ int run(const void* q, const void* k, const void* v, void* o, const Shape& s, in
     if (var == FLASHD_VARIANT_TILE && splits == 0 && !decode && !auto_wide)
         plan = row_plan(s, causal != 0, shift, sp_most,
                         (sa.in != nullptr ? 1 : 0) + (sa.out != nullptr ? 1 : 0), k8.on);
+    // The rule for fp32 counts the per-key kernel's workgroups, of 4 or 8 rows; of the tile kernel's, of
+    // 16, one on every compute unit is enough (d = 64; us whole, in two splits: 480 of them over
+    // 639 keys 25.0, 31.0; 410 over 1306 43.2, 49.9; 273 over 725 18.5, 21.1; but 218 over 1732
+    // 35.5 and 30.5 in three).
+    if (variant == FLASHD_VARIANT_AUTO && splits == 0 && s.dtype == FLASHD_F32 &&
+        (long)s.B * s.Hkv * ceil_div((long)(s.Hq / s.Hkv) * s.Lq, 16) >= 256)
+        plan.splits = 1;
     const int sp = plan.splits;
     const bool widen = k8.on && !decode && plan.kernel != RowKernel::Short;
     // The state entry point always goes through partial states; a single partial may be

@@ -24,6 +24,9 @@
 // the output product and V before the scores; the rest of the latency is covered by the other
 // wavefronts of the SIMD.
 //
+// The score product runs as two chains, and for d = 64 Q stays in fp64 for the whole row tile: 3 %
+// on causal calls (2 x 12 heads, 777 positions 36.9 -> 35.7 us), 1 % on others.
+//
 // What bounds it: the matrix cores.  A block of 16 keys x 16 rows x 64 columns takes 16 fp64
 // instructions of 64 cycles (78.6 TFLOP/s peak) and 16 fp32 ones of 32 cycles.  Measured
 // against the per-key kernel: 2 x 12 heads, 777 causal positions, d = 64 36 us (425 us before; 52
@@ -139,6 +142,8 @@ void tile_f32_kernel(Problem p, F32Sched sc) {
         const float* kg = static_cast<const float*>(p.k) + kv_unit * (size_t)p.Lk * D + 4 * q;
         const float* vg = static_cast<const float*>(p.v) + kv_unit * (size_t)p.Lk * D + 4 * c;
         f32x4 qf[NM], kf[NM];
+        // d = 64: Q in fp64 for the whole row tile (for d = 128 that would take 64 registers)
+        double qd[D == 64 ? NM : 1][4];
         auto fetch_k = [&](int blk) __attribute__((always_inline)) {
             const float* src = kg + (size_t)min(blk * kF32Block + c, p.Lk - 1) * D;
 #pragma unroll
@@ -172,6 +177,15 @@ void tile_f32_kernel(Problem p, F32Sched sc) {
                                   q_row(min(r0 + col, rlast)) * D + 4 * q;
 #pragma unroll
                 for (int m = 0; m < NM; ++m) qf[m] = *reinterpret_cast<const f32x4*>(qg + 16 * m);
+                if constexpr (D == 64) {
+#pragma unroll
+                    for (int m = 0; m < NM; ++m)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            qd[m][e] = (double)qf[m][e];
+                            asm volatile("" : "+v"(qd[m][e]));
+                        }
+                }
             }
             for (; blk < blk_end; blk += kF32Waves) {
                 const int j0 = blk * kF32Block;
@@ -183,16 +197,17 @@ void tile_f32_kernel(Problem p, F32Sched sc) {
                     for (int i = 0; i < NB; ++i)
                         vf[i][r] = *reinterpret_cast<const f32x4*>(src + 64 * i);
                 }
-                f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+                f64x4 acc2[2] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};
 #pragma unroll
                 for (int m = 0; m < NM; ++m) {
-                    // d = 128: widen Q anew for every block, its fp64 form would take 64 registers
+                    // d = 128: widen Q anew for every block
                     if (D == 128) asm volatile("" : "+v"(qf[m]));
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
-                        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(
-                            (double)kf[m][e], (double)qf[m][e], acc, 0, 0, 0);
+                        acc2[e & 1] = __builtin_amdgcn_mfma_f64_16x16x4f64(
+                            (double)kf[m][e], D == 64 ? qd[D == 64 ? m : 0][e] : (double)qf[m][e], acc2[e & 1], 0, 0, 0);
                 }
+                const f64x4 acc = acc2[0] + acc2[1];
                 if (blk + kF32Waves < blk_end) fetch_k(blk + kF32Waves);
 
                 const bool masked = j0 + kF32Block > nvis_min;
