@@ -76,7 +76,8 @@ typedef enum {
     FLASHD_VARIANT_TILE = 1,     /* Alg. 3 lifted to key tiles on the matrix cores (f16/bf16),
                                     the (1 - W) factors of the blend deferred to the store;
                                     with splits == 0 small calls take kernels with 32 or 64
-                                    query rows per workgroup, splits given the 128-row one   */
+                                    query rows per workgroup, splits given the 128-row one,
+                                    and some decode calls twice the wavefronts              */
     FLASHD_VARIANT_PER_KEY = 2,  /* Alg. 3 literally, one sigmoid per key (any dtype)       */
     FLASHD_VARIANT_ONLINE_SOFTMAX = 3, /* ablation: Alg. 2 (running max, sum, final division)
                                           on the same tiling as TILE (f16/bf16)             */

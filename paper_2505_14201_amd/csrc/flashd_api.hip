@@ -146,6 +146,21 @@ int decode_splits(const Shape& s, int variant, bool fp8, bool or_shorter) {
     return (int)(sp < 1 ? 1 : sp > FLASHD_MAX_SPLITS ? FLASHD_MAX_SPLITS : sp);
 }
 
+// Decode calls of up to 16 rows per kv head that the rule above leaves whole and that run on 8
+// wavefronts per workgroup instead of 4: a workgroup alone on its compute unit waits for its own loads,
+// and 8 have twice as many under way.  Device times, 4 wavefronts and then 8: bf16 d = 64, 32 units of
+// 352 keys 5.2 and 4.8 us, of 1200 10.9 and 8.8, 192 of 2000 18.3 and 16.2; fp8 d = 64, 32 of 600 5.5
+// and 4.9, of 1200 8.6 and 7.0, 256 of 2000 14.2 and 11.5; up to 256 keys, one block for each of the
+// 8, level.  d = 128 has the loads of two such already: from fp8 at 128 to 192 units and over 800
+// keys 0.90 to 0.97 of the time, elsewhere 0.93 to 1.09, in 16 bits 0.94 to 1.12.  Against splits
+// it was 0.95 to 1.24 and those stay.
+bool decode_on_eight(const Shape& s, bool fp8, int splits) {
+    const long units = flashd::decode_workgroups(s.B, s.Hkv);
+    if (splits > 1 || units > 256 || (long)(s.Hq / s.Hkv) * s.Lq > 16) return false;
+    if (s.d == 64) return s.Lk > 256;
+    return fp8 && units >= 128 && units <= 192 && s.Lk > 800;
+}
+
 // Splits for the automatic choice: enough independent work to fill 256 compute units, but
 // never key ranges shorter than 256 keys.  or_shorter: the most splits of any call with this many
 // keys or fewer.  Outside the decode shapes the choice never falls as the keys grow.
@@ -450,6 +465,8 @@ int run(const void* q, const void* k, const void* v, void* o, const Shape& s, in
     if (var == FLASHD_VARIANT_TILE && splits == 0 && !decode && !auto_wide)
         plan = row_plan(s, causal != 0, shift, sp_most,
                         (sa.in != nullptr ? 1 : 0) + (sa.out != nullptr ? 1 : 0), k8.on);
+    const bool eight = decode && var == FLASHD_VARIANT_TILE && splits == 0 && !sa.on &&
+                       decode_on_eight(s, k8.on, sp_most);
     // The rule for fp32 counts the per-key kernel's workgroups, of 4 or 8 rows; of the tile kernel's, of
     // 16, one on every compute unit is enough (d = 64; us whole, in two splits: 480 of them over
     // 639 keys 25.0, 31.0; 410 over 1306 43.2, 49.9; 273 over 725 18.5, 21.1; but 218 over 1732
@@ -523,6 +540,7 @@ int run(const void* q, const void* k, const void* v, void* o, const Shape& s, in
     p.state_out = sa.out;
     p.vskip_counts = sk.counts;
     p.wide = wide ? 1 : 0;
+    p.many = eight ? 1 : 0;
     if (in_kernel) {
         p.partial = sa.out != nullptr ? 1 : 0;     // the "partial" is the state handed out
         p.store_o = o != nullptr ? 1 : 0;
@@ -646,6 +664,7 @@ int flashd_skip_stats(const void* q, const void* k, int B, int Hq, int Hkv, int 
     p.state_in = nullptr;
     p.state_out = nullptr;
     p.wide = 0;
+    p.many = 0;
     p.vskip_counts = nullptr;
     p.kv8 = 0;
     p.kscale = p.vscale = p.oscale = 1.0f;

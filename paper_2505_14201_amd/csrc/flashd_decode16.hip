@@ -9,8 +9,9 @@
 // (half the bytes for the same instructions).  Here the tiles are 16 columns wide
 // (v_mfma_f32_16x16x32): half the vector and half the matrix work per key.
 //
-// Mapping.  A workgroup of 4 wavefronts owns one (b, kv head, key split); wavefront w takes the
-// 32-key blocks w, w + 4, ... with a state of its own, the four are folded at the end.  Lane
+// Mapping.  A workgroup of W wavefronts owns one (b, kv head, key split); wavefront w takes the
+// 32-key blocks w, w + W, ... with a state of its own, the W are folded at the end.  W is 4; 8 for
+// the whole calls that decode_on_eight in flashd_api.hip names, with its figures.  Lane
 // (q, c) = (lane / 16, lane % 16): S^T = K Q^T comes as two 16-key tiles of which the lane holds,
 // for query row c, the keys 4 q + r and 16 + 4 q + r (r = 0..3).  Rounded and packed, these are the
 // eight B elements of the lane for O^T = V^T P^T over the whole block; V^T comes from the
@@ -47,7 +48,6 @@
 
 namespace flashd {
 
-constexpr int kD16Waves = 4;
 constexpr int kD16Block = 32;      // keys per wavefront step
 
 struct Dec16Sched {
@@ -106,8 +106,8 @@ __device__ __forceinline__ u32x4 widen8(uint32_t lo, uint32_t hi) {
 // FP8: 0 K and V in the storage type T, 1 and 2 in fp8; 2 reads K as the operand it is, straight
 // from global memory (see launch_decode16_t).  SKIP: leave out the V fetch of blocks whose
 // weights have all saturated at 0.
-template <typename T, int D, int FP8, bool TL, bool SKIP>
-__global__ __launch_bounds__(kD16Waves * kWave, D == 64 ? 4 : 3)
+template <typename T, int D, int FP8, bool TL, bool SKIP, int W>
+__global__ __launch_bounds__(W * kWave, D == 64 ? 4 : W == 8 ? 2 : 3)
 void decode16_kernel(Problem p, Dec16Sched sc) {
     constexpr bool kTL = TL && Mma<T>::kRoundedSum;
     constexpr bool KV8 = FP8 != 0, KDIRECT = FP8 == 2;
@@ -122,10 +122,10 @@ void decode16_kernel(Problem p, Dec16Sched sc) {
     constexpr int VROW = D + 16;
     constexpr int STAGE = kD16Block * VROW;     // elements per wavefront
     constexpr int FROW = D + 4;                 // floats per row of the fold buffer
-    constexpr int kLds = 2 * kD16Waves * STAGE > 4 * kD16Waves * 16 * FROW
-                             ? 2 * kD16Waves * STAGE : 4 * kD16Waves * 16 * FROW;
+    constexpr int kLds = 2 * W * STAGE > 4 * W * 16 * FROW
+                             ? 2 * W * STAGE : 4 * W * 16 * FROW;
     __shared__ __align__(16) char lds[kLds];
-    __shared__ float fold_r[kD16Waves][16], fold_l[kD16Waves][16], fold_t[kD16Waves][16];
+    __shared__ float fold_r[W][16], fold_l[W][16], fold_t[W][16];
     // per row: the largest score any wavefront has seen, a bound of Lam from below (by atomics: the
     // other wavefronts' must be looked at on every block)
     __shared__ float top_seen[SKIP ? 16 : 1];
@@ -244,12 +244,12 @@ void decode16_kernel(Problem p, Dec16Sched sc) {
 
     u32x4 pending_p = {0u, 0u, 0u, 0u};
     bool pending = false;                // SKIP, wavefront-uniform: a V fetch is under way
-    for (; blk < blk_end; blk += kD16Waves) {
+    for (; blk < blk_end; blk += W) {
         const int j0 = blk * kD16Block;
         // S^T = K Q^T, two 16-key tiles
         if (!KDIRECT) {
             stage(kreg, Set<KROW>{});
-            fetch_k(blk + kD16Waves);
+            fetch_k(blk + W);
         }
         f32x4 acc[2];
 #pragma unroll
@@ -267,11 +267,11 @@ void decode16_kernel(Problem p, Dec16Sched sc) {
                 }
                 acc[t] = Mma16<T>::mfma(a, qf[kk], acc[t]);
             }
-        if (KDIRECT) fetch_k(blk + kD16Waves);
+        if (KDIRECT) fetch_k(blk + W);
         else stage_done();
         if (!SKIP) {
             stage(vreg, Set<VROW>{});
-            fetch_v(blk + kD16Waves, true);
+            fetch_v(blk + W, true);
         } else if (pending) {
             stage(vreg, Set<VROW>{});
             output_product(pending_p);
@@ -368,16 +368,16 @@ void decode16_kernel(Problem p, Dec16Sched sc) {
     }
     __syncthreads();
     const float oscale = KV8 ? p.vscale : 1.0f;
-    for (int idx = tid; idx < sc.nrows * (D / 4); idx += kD16Waves * kWave) {
+    for (int idx = tid; idx < sc.nrows * (D / 4); idx += W * kWave) {
         const int fr = idx / (D / 4);
         const int t = 4 * (idx % (D / 4));
         float top = fold_r[0][fr];
 #pragma unroll
-        for (int w = 1; w < kD16Waves; ++w) top = fmaxf(top, fold_r[w][fr]);
+        for (int w = 1; w < W; ++w) top = fmaxf(top, fold_r[w][fr]);
         float lt = 0.0f, tt = 0.0f;
         f32x4 o = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-        for (int w = 0; w < kD16Waves; ++w) {
+        for (int w = 0; w < W; ++w) {
             // A wavefront without a key of the row is left out: its U holds 0 * V of keys that
             // other rows see, and that is NaN where such a V is infinite.  (l is 1 or more with a
             // key, NaN with a NaN score.  By selection: with a branch around it each wavefront's
@@ -409,7 +409,7 @@ void decode16_kernel(Problem p, Dec16Sched sc) {
 
 template <typename T, int D>
 static hipError_t launch_decode16_t(const Problem& p, int mode, hipStream_t st) {
-    const dim3 grid((unsigned)p.splits, (unsigned)p.Hkv, (unsigned)p.B), block(kD16Waves * kWave);
+    const dim3 grid((unsigned)p.splits, (unsigned)p.Hkv, (unsigned)p.B), block(4 * kWave);
     Dec16Sched sc;
     sc.nrows = p.Hq / p.Hkv * p.Lq;
     const int blocks = (p.Lk + kD16Block - 1) / kD16Block;
@@ -418,18 +418,24 @@ static hipError_t launch_decode16_t(const Problem& p, int mode, hipStream_t st) 
     // the true log-sum-exp is wanted wherever the state leaves the kernel
     const bool tl = p.partial != 0;
     if (mode == kTileModeLazySkipV && p.kv8) return hipErrorInvalidValue;
-    if (mode == kTileModeLazySkipV) {
-        if (tl) hipLaunchKernelGGL((decode16_kernel<T, D, 0, true, true>), grid, block, 0, st, p, sc);
-        else hipLaunchKernelGGL((decode16_kernel<T, D, 0, false, true>), grid, block, 0, st, p, sc);
+    const dim3 eight(8 * kWave);
+    if (p.many && p.kv8) {
+        hipLaunchKernelGGL((decode16_kernel<T, D, 1, false, false, 8>), grid, eight, 0, st, p, sc);
+    } else if (D == 64 && p.many) {
+        if (mode == kTileModeLazySkipV) hipLaunchKernelGGL((decode16_kernel<T, 64, 0, false, true, 8>), grid, eight, 0, st, p, sc);
+        else hipLaunchKernelGGL((decode16_kernel<T, 64, 0, false, false, 8>), grid, eight, 0, st, p, sc);
+    } else if (mode == kTileModeLazySkipV) {
+        if (tl) hipLaunchKernelGGL((decode16_kernel<T, D, 0, true, true, 4>), grid, block, 0, st, p, sc);
+        else hipLaunchKernelGGL((decode16_kernel<T, D, 0, false, true, 4>), grid, block, 0, st, p, sc);
     } else if (!p.kv8) {
-        if (tl) hipLaunchKernelGGL((decode16_kernel<T, D, 0, true, false>), grid, block, 0, st, p, sc);
-        else hipLaunchKernelGGL((decode16_kernel<T, D, 0, false, false>), grid, block, 0, st, p, sc);
+        if (tl) hipLaunchKernelGGL((decode16_kernel<T, D, 0, true, false, 4>), grid, block, 0, st, p, sc);
+        else hipLaunchKernelGGL((decode16_kernel<T, D, 0, false, false, 4>), grid, block, 0, st, p, sc);
     } else if ((long)p.splits * p.B * p.Hkv >= 512) {
-        if (tl) hipLaunchKernelGGL((decode16_kernel<T, D, 2, true, false>), grid, block, 0, st, p, sc);
-        else hipLaunchKernelGGL((decode16_kernel<T, D, 2, false, false>), grid, block, 0, st, p, sc);
+        if (tl) hipLaunchKernelGGL((decode16_kernel<T, D, 2, true, false, 4>), grid, block, 0, st, p, sc);
+        else hipLaunchKernelGGL((decode16_kernel<T, D, 2, false, false, 4>), grid, block, 0, st, p, sc);
     } else {
-        if (tl) hipLaunchKernelGGL((decode16_kernel<T, D, 1, true, false>), grid, block, 0, st, p, sc);
-        else hipLaunchKernelGGL((decode16_kernel<T, D, 1, false, false>), grid, block, 0, st, p, sc);
+        if (tl) hipLaunchKernelGGL((decode16_kernel<T, D, 1, true, false, 4>), grid, block, 0, st, p, sc);
+        else hipLaunchKernelGGL((decode16_kernel<T, D, 1, false, false, 4>), grid, block, 0, st, p, sc);
     }
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess || !p.merge) return e;
