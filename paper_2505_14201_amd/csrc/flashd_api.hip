@@ -272,9 +272,23 @@ RowPlan row_plan(const Shape& s, bool causal, int shift, int splits, int states,
     const int w = s.d == 128 ? 1 : 0;
     RowPlan plan{RowKernel::Tile, splits};
     const long g = s.Hq / s.Hkv;
-    // (row numbers are 32-bit; of two key tiles there is nothing to share out)
-    if (g * s.Lq > (1L << 30) || s.Lk <= 128) return plan;
+    if (g * s.Lq > (1L << 30)) return plan;             // row numbers are 32-bit
     const long wgs = (long)s.B * s.Hkv * ceil_div(g * s.Lq, kShort[w].rows);
+    // Up to two key tiles the start and the end of a workgroup are most of its time, and what counts is
+    // that each has a compute unit to itself (device times, 128-row kernel and then the smaller one):
+    // 32 rows, 8 heads of 512 x 128 d = 128 6.9 and 5.9 us, with a state 9.8 and 7.2, d = 64 5.2 and
+    // 4.0, with a state 7.0 and 4.6 (0.60 to 0.95 of the time over 434 sizes); 64 rows, 32 heads of
+    // 300 x 128 with a state 10.4 and 9.3 (0.82 to 1.015 over 62).  One key tile at d = 128
+    // without a state is level (5.75 and 5.8) and stays, but from fp8 the 32-row kernel needs no
+    // widening launch.
+    if (s.Lk <= 128) {
+        if (wgs <= 256 && (s.Lk > 64 || w == 0 || fp8 || (states > 0 && g * s.Lq >= 128)))
+            plan = {RowKernel::Short, 1};
+        else if (wgs > 256 && (s.Lk > 64 || w == 0 || states > 0) &&
+                 (long)s.B * s.Hkv * ceil_div(g * s.Lq, kTile64[w].rows) <= 256)
+            plan = {RowKernel::Tile64, 1};
+        return plan;
+    }
     // beyond this the 128-row kernel has rounds of workgroups to even things out by
     if (wgs > 2048) return plan;
     const double widen = fp8 ? 3.0 + (double)s.B * s.Hkv * s.Lk * s.d * 1.5e-6 : 0.0;

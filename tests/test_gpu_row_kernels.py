@@ -91,3 +91,22 @@ def test_infinite_values_behind_the_mask(shape):
     rows = slice(0, Lq - 32)                     # none of them sees a key of the last block
     assert bool(torch.isfinite(got[:, :, rows].float()).all())
     assert np.abs(got[:, :, rows].double().numpy() - ref[:, :, rows]).max() <= 2e-2
+
+
+# one and two key tiles; the last takes 64 rows per workgroup
+FEW_KEYS = [(1, 2, 1, 33, 1), (2, 4, 2, 40, 64), (1, 2, 2, 150, 65), (3, 8, 8, 130, 128), (2, 16, 16, 300, 127)]
+
+
+@pytest.mark.parametrize("shape", FEW_KEYS)
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64), ("f16", 128), ("f16", 64)])
+@pytest.mark.parametrize("causal", [False, True])
+def test_at_most_two_key_tiles(shape, dtype, d, causal):
+    w = synthetic.small("t", *shape, d, dtype, causal, seed=4700 + shape[3] + shape[4])
+    q, k, v, _ = synthetic.make_qkv(w)
+    check(run_flashd(q, k, v, causal, w.scale, use_ex=False), oa.attn(q, k, v, causal, w.scale), DT[dtype])
+    got, ref = run_and_ref(w, 2.0 ** -5, 0.03)
+    check(got, ref, DT[dtype], "fp8")
+    if shape[4] > 1:
+        o, st = run_chunks(q, k, v, causal, w.scale, (shape[4] // 2 + 1,), in_place=True)
+        check(o, oa.attn(q, k, v, causal, w.scale), DT[dtype])
+        check_state(st, oa.attn_state(q, k, v, causal, w.scale), d, DT[dtype], "state")
