@@ -49,3 +49,28 @@ def test_rows_without_a_new_key(d, in_place, seen):
         lo, hi = old.clamp(max=0.5), old.clamp(min=0.5)
         assert bool((new >= lo - 1e-2).all()) and bool((new <= hi + 1e-2).all())
         assert not torch.equal(new, old)
+
+
+# a call for each of the kernels with 128, 64 and 32 query rows per workgroup, and two in fp32 and decode
+@pytest.mark.parametrize("B,H,Lq,Lk,d,dtype", [
+    (2, 16, 2200, 320, 64, torch.bfloat16), (2, 16, 2200, 320, 128, torch.float16),
+    (4, 16, 190, 192, 64, torch.bfloat16), (1, 4, 64, 160, 128, torch.bfloat16),
+    (1, 2, 40, 50, 64, torch.float32), (1, 4, 3, 300, 128, torch.bfloat16)])
+@pytest.mark.parametrize("in_place", [False, True])
+def test_empty_states_go_out_as_zeros(B, H, Lq, Lk, d, dtype, in_place):
+    """A state that holds no key says so by s = -inf alone, its o may be anything: a row without keys
+    of the call has zeros in the output and in the state handed out."""
+    gen = torch.Generator().manual_seed(72 + Lq)
+    q, k, v = (torch.randn(B, H, n, d, generator=gen).to(dtype).cuda() for n in (Lq, Lk, Lk))
+    st = torch.full((B, H, Lq, d + 2), float("nan"), device="cuda")
+    st[..., d], st[..., d + 1] = float("-inf"), 0.0
+    out = st if in_place else torch.full_like(st, float("nan"))
+    o = torch.full_like(q, float("nan"))
+    seen = Lq // 3                                  # rows that see a key, behind those that do not
+    flashd.attn_fwd_state(q, k, v, True, d ** -0.5, o=o, state_in=st, state_out=out, causal_shift=-(Lq - seen))
+    torch.cuda.synchronize()
+    assert torch.isfinite(o).all() and torch.isfinite(out[..., :d]).all()
+    rows = slice(0, Lq - seen)
+    assert torch.count_nonzero(o[:, :, rows]) == 0 and torch.count_nonzero(out[:, :, rows, :d]) == 0
+    assert torch.isneginf(out[:, :, rows, d] - out[:, :, rows, d + 1]).all()
+    assert torch.isfinite(out[:, :, Lq - seen:]).all() and bool((o[:, :, Lq - seen:] != 0).any(-1).all())
