@@ -2,8 +2,6 @@
 // per-(device, stream) workspace cache, and dispatch to the kernel launchers.
 #include <hip/hip_runtime.h>
 
-#include <algorithm>
-#include <cmath>
 #include <cstring>
 #include <map>
 #include <mutex>
@@ -13,12 +11,17 @@
 #include "../../include/flashd.h"
 #include "flashd_common.h"
 #include "flashd_kernels.h"
+#include "flashd_plan.h"
 
 namespace {
 
+using flashd::ceil_div;
+using flashd::decode_on_eight;
 using flashd::Problem;
-
-struct Shape { int B, Hq, Hkv, Lq, Lk, d, dtype; };
+using flashd::row_plan;
+using flashd::RowKernel;
+using flashd::RowPlan;
+using flashd::Shape;
 
 int validate_shape(const Shape& s) {
     if (s.B < 1 || s.Hq < 1 || s.Hkv < 1 || s.Lq < 1 || s.Lk < 1) return FLASHD_E_SHAPE;
@@ -71,8 +74,6 @@ int resolve_variant(const Shape& s, int variant) {
     if (s.dtype == FLASHD_F32 && variant != FLASHD_VARIANT_PER_KEY) return -1;
     return variant;
 }
-
-int ceil_div(long a, long b) { return (int)((a + b - 1) / b); }
 
 // n partial states (o[d], s, ln w) per query row
 size_t partial_bytes(const Shape& s, int n) {
@@ -146,21 +147,6 @@ int decode_splits(const Shape& s, int variant, bool fp8, bool or_shorter) {
     return (int)(sp < 1 ? 1 : sp > FLASHD_MAX_SPLITS ? FLASHD_MAX_SPLITS : sp);
 }
 
-// Decode calls of up to 16 rows per kv head that the rule above leaves whole and that run on 8
-// wavefronts per workgroup instead of 4: a workgroup alone on its compute unit waits for its own loads,
-// and 8 have twice as many under way.  Device times, 4 wavefronts and then 8: bf16 d = 64, 32 units of
-// 352 keys 5.2 and 4.8 us, of 1200 10.9 and 8.8, 192 of 2000 18.3 and 16.2; fp8 d = 64, 32 of 600 5.5
-// and 4.9, of 1200 8.6 and 7.0, 256 of 2000 14.2 and 11.5; up to 256 keys, one block for each of the
-// 8, level.  d = 128 has the loads of two such already: from fp8 at 128 to 192 units and over 800
-// keys 0.90 to 0.97 of the time, elsewhere 0.93 to 1.09, in 16 bits 0.94 to 1.12.  Against splits
-// it was 0.95 to 1.24 and those stay.
-bool decode_on_eight(const Shape& s, bool fp8, int splits) {
-    const long units = flashd::decode_workgroups(s.B, s.Hkv);
-    if (splits > 1 || units > 256 || (long)(s.Hq / s.Hkv) * s.Lq > 16) return false;
-    if (s.d == 64) return s.Lk > 256;
-    return fp8 && units >= 128 && units <= 192 && s.Lk > 800;
-}
-
 // Splits for the automatic choice: enough independent work to fill 256 compute units, but
 // never key ranges shorter than 256 keys.  or_shorter: the most splits of any call with this many
 // keys or fewer.  Outside the decode shapes the choice never falls as the keys grow.
@@ -206,111 +192,6 @@ int auto_splits(const Shape& s, int variant, bool fp8 = false, bool or_shorter =
     if (sp > FLASHD_MAX_SPLITS) sp = FLASHD_MAX_SPLITS;
     if (sp < 1) sp = 1;
     return (int)sp;
-}
-
-// ---- kernels for prefill calls that the 128-row kernel does not fill the chip with ----------
-// Which kernel, and in how many of the splits above, is decided by an estimate of each one's time:
-// the chain of its longest row tile, its work on the whole chip and its way to K and V, whichever
-// is the longest (smoothed), and what it reads and writes of states.  The figures are fits over 2500
-// calls of 1 to 64 sequences, 4 to 32 heads, 8 to 12288 positions and 16 to 117000 keys, causal or
-// not, whole or in chunks; the estimates are within 7 to 13 % on average.  By it 900 calls that the
-// 256-row kernel does not take went to 0.92 (d = 128) and 0.89 (d = 64) of their time on average,
-// down to 0.45: 5 x 16 heads, 182 x 882, d = 128 29.3 -> 17.2 us, 3 x 16 heads of 681, causal, d = 64
-// 22.0 -> 11.2, 1 x 16/2 heads of 664 17.9 either way.
-enum class RowKernel { Tile, Tile64, Short };
-
-struct RowCost {
-    int rows, keys;     // query rows of a workgroup, keys that it steps over at a time
-    double start;       // us: launch, first loads, fold, store
-    double chain;       // us a step of the longest row tile
-    double work, wg;    // us a step, and a workgroup, of one compute unit's share of all
-    double state;       // us per MB of states and partial states, read and written
-    double kv;          // us per MB of K and V (of the 32- and 64-row kernels more than fitted: where memory is
-                        // the bound, 64 x 32/8 heads, 16 x 8192, the 64-row one took 368 us and the 128-row one 310)
-};
-
-double row_estimate(const RowCost& c, const Shape& s, bool causal, int shift, int splits, int states) {
-    const double g = s.Hq / s.Hkv, units = (double)s.B * s.Hkv, lq = s.Lq, lk = s.Lk;
-    const double tiles = std::ceil(g * lq / c.rows);
-    double most = lk, mean = lk;            // keys the last row, and a row on average, sees
-    if (causal) {
-        // row i sees min(max(i + shift + 1, 0), lk)
-        const double lo = std::min(std::max(-(double)shift - 1.0, 0.0), lq);
-        const double hi = std::min(std::max(lk - shift - 1.0, lo), lq);
-        mean = ((hi - lo) * (lo + hi + 2.0 * shift + 1.0) * 0.5 + (lq - hi) * lk) / lq;
-        most = std::min(std::max(lq + shift, 0.0), lk);
-    }
-    const double wgs = units * tiles * splits;
-    const double chain = c.chain * std::ceil(most / ((double)c.keys * splits));
-    // row tiles of equal length end together, the fullest compute unit's last (the 128-row kernel, which
-    // the others have to beat, by the average)
-    const double share = causal || c.rows == 128 ? wgs / 256.0 : std::ceil(wgs / 256.0);
-    const double work = share * (c.work * (mean / ((double)splits * c.keys) + 0.5) + c.wg);
-    // K and V are read into every L2 that a unit's row tiles run beside
-    const double reads = (long)units % 8 == 0 ? 1.0 : std::min(8.0, tiles);
-    const double kv = c.kv * units * most * s.d * 4e-6 * reads;
-    const double p2 = chain * chain, q2 = work * work, r2 = kv * kv;
-    const double state_mb = (double)s.B * s.Hq * lq * (s.d + 2) * 4e-6;
-    double t = c.start + std::sqrt(std::sqrt(p2 * p2 + q2 * q2 + r2 * r2)) +
-               c.state * state_mb * (states + (splits > 1 ? 2 * splits : 0));
-    if (splits > 1) t += splits > 8 ? 4.6 : 3.6;        // the merge
-    return t;
-}
-
-struct RowPlan { RowKernel kernel; int splits; };
-
-// splits: those of the rule above, which are also what scratch memory is sized for: the plan has
-// no more.  states: states read and written by the call.  fp8: K and V are fp8, which the 32-row
-// kernel reads as such and the others need widened first.
-RowPlan row_plan(const Shape& s, bool causal, int shift, int splits, int states, bool fp8) {
-    static const RowCost kTile[2] = {{128, 64, 3.7, 1.03, 0.65, 0.86, 0.21, 0.16},
-                                     {128, 64, 6.2, 1.15, 1.10, 0.62, 0.19, 0.14}};
-    static const RowCost kTile64[2] = {{64, 64, 4.4, 0.55, 0.34, 0.73, 0.16, 0.18},
-                                       {64, 64, 5.9, 0.74, 0.59, 1.74, 0.16, 0.17}};
-    static const RowCost kShort[2] = {{32, 128, 3.8, 0.57, 0.42, 0.52, 0.15, 0.18},
-                                      {32, 128, 5.1, 0.82, 0.77, 1.67, 0.13, 0.17}};
-    const int w = s.d == 128 ? 1 : 0;
-    RowPlan plan{RowKernel::Tile, splits};
-    const long g = s.Hq / s.Hkv;
-    if (g * s.Lq > (1L << 30)) return plan;             // row numbers are 32-bit
-    const long wgs = (long)s.B * s.Hkv * ceil_div(g * s.Lq, kShort[w].rows);
-    // Up to two key tiles the start and the end of a workgroup are most of its time, and what counts is
-    // that each has a compute unit to itself (device times, 128-row kernel and then the smaller one):
-    // 32 rows, 8 heads of 512 x 128 d = 128 6.9 and 5.9 us, with a state 9.8 and 7.2, d = 64 5.2 and
-    // 4.0, with a state 7.0 and 4.6 (0.60 to 0.95 of the time over 434 sizes); 64 rows, 32 heads of
-    // 300 x 128 with a state 10.4 and 9.3 (0.82 to 1.015 over 62).  One key tile at d = 128
-    // without a state is level (5.75 and 5.8) and stays, but from fp8 the 32-row kernel needs no
-    // widening launch.
-    if (s.Lk <= 128) {
-        if (wgs <= 256 && (s.Lk > 64 || w == 0 || fp8 || (states > 0 && g * s.Lq >= 128)))
-            plan = {RowKernel::Short, 1};
-        else if (wgs > 256 && (s.Lk > 64 || w == 0 || states > 0) &&
-                 (long)s.B * s.Hkv * ceil_div(g * s.Lq, kTile64[w].rows) <= 256)
-            plan = {RowKernel::Tile64, 1};
-        return plan;
-    }
-    // beyond this the 128-row kernel has rounds of workgroups to even things out by
-    if (wgs > 2048) return plan;
-    const double widen = fp8 ? 3.0 + (double)s.B * s.Hkv * s.Lk * s.d * 1.5e-6 : 0.0;
-    // The 128-row kernel stays where it is not clearly behind, and over long split ranges where the
-    // estimate is at its worst (5 x 32/8 heads, 66 x 9530 112 us on the 32-row kernel, 88 on it).
-    double best = (row_estimate(kTile[w], s, causal, shift, splits, states) + widen) /
-                  (splits > 1 && s.Lk > 2500 ? 1.2 : 1.05);
-    const double t64 = row_estimate(kTile64[w], s, causal, shift, 1, states) + widen;
-    if (t64 < best) {
-        best = t64;
-        plan = {RowKernel::Tile64, 1};
-    }
-    for (int sp : {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64}) {
-        // one workgroup per compute unit (two at d = 64), which the ranges share out
-        if (sp > splits || (sp > 1 && (wgs * sp > (w ? 320 : 512) || s.Lk / sp < 256))) break;
-        const double t = row_estimate(kShort[w], s, causal, shift, sp, states);
-        if (t < best) {
-            best = t;
-            plan = {RowKernel::Short, sp};
-        }
-    }
-    return plan;
 }
 
 // Splits whose partial states the scratch memory of a call with sp splits is sized for.  A call of

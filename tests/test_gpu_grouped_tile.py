@@ -1,6 +1,7 @@
-"""The 128-row prefill kernel with the heads of a kv group interleaved row by row: row tiles that
-begin inside a position, end exactly at the last row, or hold fewer rows than a wavefront; with
-and without splits and with the state handed on."""
+"""Prefill with the heads of a kv group interleaved row by row: row tiles that begin inside a
+position, end exactly at the last row, or hold fewer rows than a wavefront.  With splits given, on the
+128-row kernel; with the state handed on, at most of these sizes on the kernel with 32 query rows per workgroup
+(the 128-row kernel with states: test_gpu_tile_state.py)."""
 import pytest
 import torch
 

@@ -64,7 +64,8 @@ def test_scales_that_are_not_powers_of_two_and_every_fp8_code():
     check(og.cpu(), ref, torch.bfloat16, "all codes")
 
 
-# prefill shapes: K and V are widened into scratch memory first, then the tile kernel runs
+# prefill shapes, small ones: the kernel with 32 query rows per workgroup reads the fp8 data itself (larger
+# calls, whose K and V are widened into scratch memory first: test_gpu_tile_state.py)
 PREFILL = [(1, 4, 2, 200, 333, 128), (2, 2, 2, 333, 200, 64), (1, 8, 8, 130, 130, 128),
            (1, 2, 1, 64, 2000, 64)]
 

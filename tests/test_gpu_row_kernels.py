@@ -21,10 +21,18 @@ SHORT = [(1, 1, 1, 33, 129),         # one row and one key past a tile and four 
          (1, 3, 1, 85, 545),
          (1, 2, 2, 200, 180),        # causal: rows that see no key
          (1, 2, 1, 40, 3001)]        # few rows and many keys: key splits
-TILE64 = [(2, 32, 8, 300, 300),      # 38 row tiles of 64 rows per kv head, the last of 48 rows
+# which kernel these take depends on d, the mask and states: 64 rows, 32 or 128
+TILE64 = [(2, 32, 8, 300, 300),      # 19 row tiles of 64 rows per kv head, the last of 48 rows
           (4, 16, 16, 193, 193),     # one row and one key past three tiles
           (3, 32, 8, 157, 129),      # causal: rows that see no key
-          (5, 16, 16, 500, 530)]     # d = 64 as well
+          (5, 16, 16, 500, 530)]
+# 64 rows with and without a mask
+TILE64_ALL = {64: [(3, 32, 8, 300, 385),       # 19 row tiles per kv head, the last of 48 rows
+                   (4, 16, 16, 500, 385)],     # causal: rows that see no key
+              128: [(5, 16, 16, 129, 129),     # one row and one key past two tiles
+                    (5, 16, 16, 150, 129)]}
+# and under a mask in two chunks
+TILE64_STATES = {64: [TILE64[1], *TILE64_ALL[64]], 128: [TILE64[1], TILE64_ALL[128][1]]}
 
 
 @pytest.mark.parametrize("shape", SHORT + TILE64)
@@ -37,6 +45,15 @@ def test_output(shape, dtype, d, causal):
     check(got, oa.attn(q, k, v, causal, w.scale), DT[dtype], str(shape))
     again = run_flashd(q, k, v, causal, w.scale)
     assert torch.equal(got.view(torch.int16), again.view(torch.int16))
+
+
+@pytest.mark.parametrize("shape,d", [(s, d) for d in TILE64_ALL for s in TILE64_ALL[d]])
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("causal", [False, True])
+def test_output_of_64_rows(shape, d, dtype, causal):
+    w = synthetic.small("t", *shape, d, dtype, causal, seed=4150 + shape[3] + shape[4])
+    q, k, v, _ = synthetic.make_qkv(w)
+    check(run_flashd(q, k, v, causal, w.scale, use_ex=False), oa.attn(q, k, v, causal, w.scale), DT[dtype], str(shape))
 
 
 @pytest.mark.parametrize("shape", [SHORT[2], SHORT[4], TILE64[1], TILE64[2]])
@@ -62,6 +79,17 @@ def test_states(shape, dtype, d, in_place):
     """Chunks of keys, the first of which some rows do not see and the last of which some see
     nothing of."""
     w = synthetic.small("t", *shape, d, dtype, True, seed=4400 + shape[3])
+    q, k, v, _ = synthetic.make_qkv(w)
+    o, st = run_chunks(q, k, v, True, w.scale, (shape[4] // 2 + 1,), in_place=in_place)
+    check(o, oa.attn(q, k, v, True, w.scale), DT[dtype])
+    check_state(st, oa.attn_state(q, k, v, True, w.scale), d, DT[dtype], "state")
+
+
+@pytest.mark.parametrize("shape,d", [(s, d) for d in TILE64_STATES for s in TILE64_STATES[d]])
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("in_place", [False, True])
+def test_states_of_64_rows(shape, d, dtype, in_place):
+    w = synthetic.small("t", *shape, d, dtype, True, seed=4450 + shape[3])
     q, k, v, _ = synthetic.make_qkv(w)
     o, st = run_chunks(q, k, v, True, w.scale, (shape[4] // 2 + 1,), in_place=in_place)
     check(o, oa.attn(q, k, v, True, w.scale), DT[dtype])

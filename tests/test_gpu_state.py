@@ -143,8 +143,9 @@ def test_extreme_causal_shifts_show_every_key_or_none(shape, dtype):
 
 @pytest.mark.parametrize("causal", [False, True])
 def test_state_passing_with_query_heads_run_as_one_head(causal):
-    """Few positions per head and several query heads per kv head: the tile kernel packs the
-    group's heads into one run of rows; the state layout must not notice."""
+    """Few positions per head and several query heads per kv head: the prefill kernels (at this size the one
+    with 32 query rows per workgroup) pack the group's heads into one run of rows; the state layout must not
+    notice."""
     B, Hq, Hkv, Lq, Lk, d = 2, 8, 2, 24, 400, 128
     w = synthetic.small("state", B, Hq, Hkv, Lq, Lk, d, "bf16", causal, seed=940)
     q, k, v, _ = synthetic.make_qkv(w)

@@ -1,0 +1,117 @@
+"""Which kernel a call of the automatic choice runs on: the rules of flashd_plan.h, compiled for the host,
+and the shapes of the GPU tests that mean to reach a certain kernel."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+from paper_2505_14201_amd import flashd
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+CSRC = os.path.join(os.path.dirname(HERE), "paper_2505_14201_amd", "csrc")
+
+PROGRAM = r"""
+#include <cstdio>
+#include "flashd_plan.h"
+using namespace flashd;
+int main() {
+    Shape s;
+    int causal, shift, splits, states, fp8;
+    while (std::scanf("%d %d %d %d %d %d %d %d %d %d %d %d", &s.B, &s.Hq, &s.Hkv, &s.Lq, &s.Lk, &s.d, &s.dtype,
+                      &causal, &shift, &splits, &states, &fp8) == 12) {
+        if ((long)(s.Hq / s.Hkv) * s.Lq <= 32) {
+            std::printf("decode %d\n", states == 0 && decode_on_eight(s, fp8 != 0, splits) ? 8 : 4);
+        } else {
+            const RowPlan p = row_plan(s, causal != 0, shift, splits, states, fp8 != 0);
+            std::printf("%s %d\n", p.kernel == RowKernel::Short ? "32" : p.kernel == RowKernel::Tile64 ? "64" : "128",
+                        p.splits);
+        }
+    }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    """plan(calls) -> [(kernel, splits or wavefronts)]; a call is (B, Hq, Hkv, Lq, Lk, d, causal) and optionally
+    shift, states (how many states are read and written) and fp8."""
+    if shutil.which("g++") is None:
+        pytest.skip("needs g++ to compile the header")
+    tmp = tmp_path_factory.mktemp("plan")
+    src, exe = tmp / "plan.cpp", tmp / "plan"
+    src.write_text(PROGRAM)
+    subprocess.run(["g++", "-O1", "-std=c++17", "-Wall", "-I", CSRC, "-o", str(exe), str(src)], check=True)
+
+    def ask(calls):
+        lines, wide = [], []
+        for B, Hq, Hkv, Lq, Lk, d, causal, *more in calls:
+            shift, states, fp8 = (more + [None, 0, 0][len(more):])
+            shift = Lk - Lq if shift is None else max(min(shift, Lk), -Lq - 1)
+            sp = flashd.auto_splits(B, Hq, Hkv, Lq, Lk, d, flashd.BF16)
+            lines.append(f"{B} {Hq} {Hkv} {Lq} {Lk} {d} {flashd.BF16} {int(causal)} {shift} {sp} {states} {int(fp8)}")
+            wide.append(not states and not fp8 and flashd.auto_variant(B, Hq, Hkv, Lq, Lk, d, flashd.BF16, causal)
+                        == flashd.VARIANT_TILE_256)
+        out = subprocess.run([str(exe)], input="\n".join(lines), capture_output=True, text=True, check=True).stdout
+        got = [(k, int(n)) for k, n in (l.split() for l in out.splitlines())]
+        assert len(got) == len(calls)
+        return [("256", 1) if w else g for w, g in zip(wide, got)]
+    return ask
+
+
+BOTH, MASKS = (64, 128), (False, True)
+
+
+def test_shapes_for_32_rows_per_workgroup(plan):
+    from tests.test_gpu_row_kernels import SHORT
+    calls = [(*s, d, c) for s in SHORT for d in BOTH for c in MASKS]
+    calls += [(*s, d, True, None, 0, 1) for s in SHORT for d in BOTH]                       # fp8
+    calls += [(*s[:4], s[4] // 2 + 1, d, True, s[4] - s[3], 1) for s in SHORT for d in BOTH]     # a first chunk
+    for call, (kernel, splits) in zip(calls, plan(calls)):
+        assert kernel == "32", call
+        assert (splits > 1) == (call[4] > 1000), call
+
+
+def test_shapes_for_64_rows_per_workgroup(plan):
+    from tests.test_gpu_row_kernels import FEW_KEYS, TILE64_ALL, TILE64_STATES
+    calls = [(*s, d, c) for d in TILE64_ALL for s in TILE64_ALL[d] for c in MASKS]
+    for d in TILE64_STATES:
+        for B, Hq, Hkv, Lq, Lk in TILE64_STATES[d]:
+            cut = Lk // 2 + 1
+            calls += [(B, Hq, Hkv, Lq, cut, d, True, Lk - Lq, 1), (B, Hq, Hkv, Lq, Lk - cut, d, True, Lk - Lq - cut, 2)]
+    calls += [(*FEW_KEYS[-1], d, c) for d in BOTH for c in MASKS] + [(*FEW_KEYS[-1], 128, True, None, 0, 1)]
+    for call, got in zip(calls, plan(calls)):
+        assert got == ("64", 1), call
+
+
+def test_shapes_of_at_most_two_key_tiles(plan):
+    from tests.test_gpu_row_kernels import FEW_KEYS
+    for s, d128 in zip(FEW_KEYS, ("128", "128", "32", "32", "64")):
+        d64 = "64" if d128 == "64" else "32"
+        assert [k for k, _ in plan([(*s, d, c) for d in BOTH for c in MASKS])] == [d64, d64, d128, d128], s
+        assert [k for k, _ in plan([(*s, d, True, None, 0, 1) for d in BOTH])] == [d64, d64], s        # fp8
+
+
+def test_shapes_for_the_128_row_kernel(plan):
+    from tests import test_gpu_tile_state as t
+    calls = [(2, 16, 16, 2200, 320, d, True, -n, 2) for d in BOTH for n in (2200, 1900)]    # test_gpu_state_rows.py
+    for B, Hq, Hkv, Lq, Lk, cuts, shift in t.CHUNKS:
+        k0 = 0
+        for k1 in (*cuts, Lk):
+            calls += [(B, Hq, Hkv, Lq, k1 - k0, d, c, shift - k0, 2 if k0 else 1) for d in BOTH for c in MASKS]
+            k0 = k1
+    calls += [(*s, d, c, None, 0, 1) for s in t.FP8 for d in BOTH for c in MASKS]
+    for call, got in zip(calls, plan(calls)):
+        assert got == ("128", 1), call
+
+
+def test_shapes_that_carry_states(plan):
+    from tests.test_gpu_state_rows import EMPTY
+    calls = [(B, H, H, Lq, Lk, d, True, -(Lq - Lq // 3), 2) for B, H, Lq, Lk, d, _ in EMPTY[:4]]
+    assert [k for k, _ in plan(calls)] == ["128", "128", "64", "32"]
+
+
+def test_shapes_for_decode_on_eight_wavefronts(plan):
+    from tests.test_gpu_decode_eight import ON_FP8, SHAPES
+    calls = [(*s, True) for s in SHAPES] + [(*s, True, None, 0, 1) for s in ON_FP8]
+    assert plan(calls) == [("decode", 8)] * len(calls)
