@@ -33,7 +33,7 @@ void tile64_kernel(Problem p, RowSched sc) {
     constexpr int kCols = D / KW;             // the columns they are
     constexpr int FROW = kCols + 4;           // floats per row of the staged output
     __shared__ __align__(1024) uint16_t lds[2 * kSlots * kTile];     // K tiles, V tiles
-    __shared__ float fold_r[kNW][32], fold_l[kNW][32], fold_t[kNW][32], from_in[kNW][32];
+    __shared__ float fold_r[kNW][32], fold_l[kNW][32], fold_t[kTL ? kNW : 1][32], from_in[kNW][32];
     static_assert(4 * kNW * 32 * D <= (int)sizeof(lds) && FROW <= D, "the fold lies in the tiles' LDS");
 
     const int tid = threadIdx.x;
@@ -141,7 +141,7 @@ void tile64_kernel(Problem p, RowSched sc) {
     if (hh == 0) {
         fold_r[wave][c] = st.R;
         fold_l[wave][c] = st.l;
-        fold_t[wave][c] = kTL ? st.ltrue : st.l;
+        if (kTL) fold_t[wave][c] = st.ltrue;
     }
     __syncthreads();                     // also: nobody reads the tiles any more
     float lam_out, w_in = 0.0f;
@@ -155,7 +155,7 @@ void tile64_kernel(Problem p, RowSched sc) {
 #pragma unroll
         for (int w = 0; w < KW; ++w) top = fmaxf(top, fold_r[2 * w + (wave & 1)][c]);
         const float f_in = r_in == ninf ? 0.0f : exp2_fast(r_in - top);
-        float lt = f_in, tt = f_in;
+        float lt = f_in;         // by the unrounded sums where they are at hand, see flashd_short.hip
 #pragma unroll
         for (int w = 0; w < KW; ++w) {
             // A state without a key of the row is left out: its U holds 0 * V of keys that other
@@ -163,15 +163,14 @@ void tile64_kernel(Problem p, RowSched sc) {
             // NaN with a NaN score.)
             const float lw = fold_l[2 * w + (wave & 1)][c];
             const float fw = lw == 0.0f ? 0.0f : exp2_fast(fold_r[2 * w + (wave & 1)][c] - top);
-            lt = fmaf(fw, lw, lt);
-            tt = fmaf(fw, fold_t[2 * w + (wave & 1)][c], tt);
+            lt = fmaf(fw, kTL ? fold_t[2 * w + (wave & 1)][c] : lw, lt);
         }
         const float f = st.l == 0.0f ? 0.0f : exp2_fast(st.R - top);
         const bool empty = lt == 0.0f;
-        lam_out = empty ? ninf : (top + log2_fast(tt)) * kLn2;
+        lam_out = empty ? ninf : (top + log2_fast(lt)) * kLn2;
         const float fin = empty ? 0.0f : 1.0f / lt;
         w_in = f_in * fin;
-        const float mul = f * fin * p.oscale;
+        const float mul = (kTL && st.l != 0.0f ? f * st.ltrue * __builtin_amdgcn_rcpf(st.l) : f) * fin * p.oscale;
         const bool none = st.l == 0.0f;
 #pragma unroll
         for (int i = 0; i < NDB; ++i)

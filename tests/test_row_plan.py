@@ -105,6 +105,13 @@ def test_shapes_for_the_128_row_kernel(plan):
         assert got == ("128", 1), call
 
 
+def test_shapes_of_the_precision_tests(plan):
+    from tests import test_gpu_row_precision as t
+    calls = [(B, H, H, Lq, b - a, d, False, None, 2 if a else 1) for B, H, Lq, Lk in t.SHAPES for d in BOTH
+             for chunks in (1, 2) for a, b in t.cuts(Lk, chunks)]
+    assert not [c for c, (k, _) in zip(calls, plan(calls)) if k == "128"]
+
+
 def test_shapes_that_carry_states(plan):
     from tests.test_gpu_state_rows import EMPTY
     calls = [(B, H, H, Lq, Lk, d, True, -(Lq - Lq // 3), 2) for B, H, Lq, Lk, d, _ in EMPTY[:4]]
