@@ -102,10 +102,15 @@ template <typename T, int NDB, bool TL>
 __device__ __forceinline__ void top_first_pack(f32x16& acc, u32x4 (&bfrag)[2], RowState& st, f32x16 (&U)[NDB],
                                                float c_log2, bool masked, int lim) {
     const float ninf = -__builtin_inff();
-    const float scale = masked ? 1.0f : c_log2;      // what is left to scale the scores by
+    // A hidden key's dot product becomes -inf, which a positive c_log2 leaves as it is: scores under a mask are
+    // scaled and referred in one fma like the others.  (Any other c_log2, 0 or NaN, is applied here: it would
+    // take a hidden key away from -inf.)
+    const bool scaled = masked && !(c_log2 > 0.0f);
+    const float scale = scaled ? 1.0f : c_log2;      // what is left to scale the scores by
     if (masked) {
+        const float by = scaled ? c_log2 : 1.0f;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[r] = 8 * (r >> 2) + (r & 3) >= lim ? ninf : acc[r] * c_log2;
+        for (int r = 0; r < 16; ++r) acc[r] = 8 * (r >> 2) + (r & 3) >= lim ? ninf : acc[r] * by;
     }
     float top = acc[0];
 #pragma unroll

@@ -46,3 +46,24 @@ def test_wavefronts_are_weighed_by_unrounded_sums(B, H, Lq, Lk, d, chunks):
     # scores up to some 30 (44 in log2 units, an fp32 spacing of 2^-18) on either side of the
     # ratio, exponentials and sums a few units of 2^-24
     assert err <= 2.0 ** -17, err
+
+
+MASKED = [(1, 4, 64, 128), (2, 3, 40, 100), (2, 16, 300, 127)]
+
+
+@pytest.mark.parametrize("B,H,Lq,Lk", MASKED)
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("scale", [0.1, -0.1])
+def test_a_mask_that_hides_nothing_from_a_row_changes_no_bit_of_it(B, H, Lq, Lk, dtype, d, scale):
+    """The last row sees every key with and without a mask, on 32-key blocks that are masked for the rows
+    before it and on ones that are not; scores of up to some hundred."""
+    q, k, v = qkv(B, H, Lq, Lk, d, dtype, 4.0, 8200 + Lk)
+    got = []
+    for causal in (False, True):
+        st = torch.empty(B, H, Lq, d + 2, device="cuda")
+        flashd.attn_fwd_state(q.cuda(), k.cuda(), v.cuda(), causal, scale, state_out=st)
+        torch.cuda.synchronize()
+        got.append(st[:, :, -1].cpu())
+    assert torch.isfinite(got[0]).all()
+    assert torch.equal(*got)

@@ -109,6 +109,7 @@ def test_shapes_of_the_precision_tests(plan):
     from tests import test_gpu_row_precision as t
     calls = [(B, H, H, Lq, b - a, d, False, None, 2 if a else 1) for B, H, Lq, Lk in t.SHAPES for d in BOTH
              for chunks in (1, 2) for a, b in t.cuts(Lk, chunks)]
+    calls += [(B, H, H, Lq, Lk, d, c, None, 1) for B, H, Lq, Lk in t.MASKED for d in BOTH for c in MASKS]
     assert not [c for c, (k, _) in zip(calls, plan(calls)) if k == "128"]
 
 
