@@ -3,13 +3,15 @@ serving path a native module in front of it).
 
 Function names mirror the C ABI in include/flashd.h.  Tensors are torch CUDA
 (ROCm) tensors used purely as owners of device memory; every step of the
-computation runs inside the library's HIP kernels.  There is no fallback: if the
+computation runs inside the library's HIP kernels.  There is no fallback for them: if the
 shared library has not been built, importing this module raises.
 """
 from __future__ import annotations
 
 import ctypes
 import os
+import sys
+import warnings
 
 import torch
 
@@ -76,9 +78,19 @@ def _load() -> ctypes.CDLL:
 _lib = _load()
 try:
     from . import _flashd_binding as _native
+    _built, _here = _native.built_for, "torch {} and Python {}.{}".format(torch.__version__.split("+")[0],
+                                                                          *sys.version_info[:2])
+    if _built != _here:
+        raise ImportError(f"built for {_built}, this is {_here}")
 except ImportError as e:
-    raise ImportError("the binding's native part is missing: build it with "
-                      "`python -m paper_2505_14201_amd.build`") from e
+    # Missing, or built for another Python or torch than this one.  The C library is tied to neither,
+    # and every call has its ctypes form.
+    warnings.warn(f"the native part of the binding does not load ({e}): calls go through ctypes and cost some "
+                  "3 us of host time more; build it with `python -m paper_2505_14201_amd.build`", RuntimeWarning)
+
+    class _native:
+        """Stands in for the native part: leaves every call to the Python form."""
+        bind = attn_fwd = attn_fwd_kv8 = attn_fwd_state = staticmethod(lambda *args: None)
 
 
 def raw() -> ctypes.CDLL:

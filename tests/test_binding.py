@@ -1,4 +1,9 @@
 """The native part of the binding: what it takes itself and what it leaves to the Python form."""
+import os
+import shutil
+import subprocess
+import sys
+
 import pytest
 import torch
 
@@ -9,6 +14,10 @@ NATIVE = flashd._native
 
 def tensors(device="cpu", dtype=torch.bfloat16, d=64):
     return [torch.zeros(1, h, n, d, dtype=dtype, device=device) for h, n in ((4, 3), (2, 40), (2, 40), (4, 3))]
+
+
+def test_the_native_part_is_built_for_this_torch_and_python():
+    assert NATIVE.built_for == f"torch {torch.__version__.split('+')[0]} and Python 3.{sys.version_info[1]}"
 
 
 def test_anything_but_gpu_tensors_is_left_to_the_python_form():
@@ -23,6 +32,38 @@ def test_anything_but_gpu_tensors_is_left_to_the_python_form():
                  lambda: flashd.attn_fwd_state(q, k, v, True, 1.0, o=o)):
         with pytest.raises(ValueError, match="GPU"):
             call()
+
+
+@pytest.mark.parametrize("there", [False, True])
+def test_the_package_works_without_its_native_part(tmp_path, there):
+    """Missing, or there and not loadable (built for another Python or torch): a warning that says which,
+    and the same calls, checks and messages through ctypes."""
+    pkg = os.path.dirname(flashd.__file__)
+    shutil.copytree(pkg, tmp_path / "paper_2505_14201_amd", ignore=shutil.ignore_patterns(
+        "csrc", "__pycache__", "_flashd_binding*", "libflashd.so"))
+    os.symlink(os.path.join(pkg, "libflashd.so"), tmp_path / "paper_2505_14201_amd" / "libflashd.so")
+    if there:
+        (tmp_path / "paper_2505_14201_amd" / "_flashd_binding.so").write_bytes(b"not a shared object")
+    code = """
+import warnings
+with warnings.catch_warnings(record=True) as seen:
+    warnings.simplefilter("always")
+    from paper_2505_14201_amd import flashd
+assert [w for w in seen if w.category is RuntimeWarning and "ctypes" in str(w.message)], seen
+import torch
+q = torch.zeros(1, 4, 3, 64)
+for call in (lambda: flashd.attn_fwd(q, q, q, q, True, 1.0),
+             lambda: flashd.attn_fwd_kv8(q, q, q, q, True, 1.0, 1.0, 1.0),
+             lambda: flashd.attn_fwd_state(q, q, q, True, 1.0, o=q)):
+    try:
+        call()
+    except ValueError as e:
+        assert "GPU" in str(e)
+    else:
+        raise AssertionError
+assert flashd.version() >= 100
+"""
+    subprocess.run([sys.executable, "-c", code], check=True, cwd=tmp_path)
 
 
 @pytest.mark.gpu
