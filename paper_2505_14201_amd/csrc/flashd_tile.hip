@@ -232,13 +232,15 @@ __device__ __forceinline__ void tile_math(const uint16_t* lds, TileRegs<D>& g, i
 // the math of tile t, one barrier per tile.  A workgroup may own two row tiles (a long and a
 // short one under a causal mask, so that all workgroups carry the same work); the copy
 // pipeline runs on across the change of row tile.
-// ST: states are handed in or out (partial states, state_in, state_out).  Where the coefficient
-// sums are those of the rounded coefficients the unrounded sum is carried as well then (TL in the
-// functions above), so that the Lam handed out is the true log-sum-exp.
-template <typename T, int D, int MODE, bool ST>
+// ST: 1 a state is handed in, 2 states are handed out (partial states, state_out).  Where the
+// coefficient sums are those of the rounded coefficients the unrounded sum is carried as well with 2
+// (TL in the functions above), so that the Lam handed out is the true log-sum-exp; a call that
+// takes a state and hands out none, the last of a chunked prompt, does without (bf16, 3 x 14/2 heads,
+// 1733 x 7313, d = 64 227 us with it and 206 without; 4 x 32 heads, 2048 x 1024 causal 147.7 and 141.7).
+template <typename T, int D, int MODE, int ST>
 __global__ __launch_bounds__(kNW * 64, 2)
 void tile_kernel(Problem p, TileSched sc) {
-    constexpr bool kTL = ST && Mma<T>::kRoundedSum && MODE == kModeLazy;
+    constexpr bool kTL = ST == 2 && Mma<T>::kRoundedSum && MODE == kModeLazy;
     using C = TileCfg<D>;
     constexpr int NKK = D / 16;       // k-steps of the score product
     constexpr int NDB = D / 32;       // 32-wide blocks of the head dimension
@@ -277,7 +279,7 @@ void tile_kernel(Problem p, TileSched sc) {
                          8 * ((4 * i + 2 * half + ((t & 3) >> 1)) ^ C::swz_v(tq)) + 4 * (t & 1);
         // Q fragments: B operand of S^T = K Q^T, kept for the whole row tile.  (A row tile that sees no
         // key, of a chunk that begins behind its rows, does without.)
-        if (!ST || cur.n > 0) {
+        if (ST == 0 || cur.n > 0) {
             const int qr = row_in_memory(p, min(cur.wrow0 + col, p.Lq - 1));
 #pragma unroll
             for (int kk = 0; kk < NKK; ++kk)
@@ -376,7 +378,7 @@ void tile_kernel(Problem p, TileSched sc) {
         }
 
         // The next row tile's Q fragments: requested now, needed after the epilogue.
-        if (nxt.valid && (!ST || nxt.n > 0)) {
+        if (nxt.valid && (ST == 0 || nxt.n > 0)) {
             const int qr = row_in_memory(p, min(nxt.wrow0 + col, p.Lq - 1));
 #pragma unroll
             for (int kk = 0; kk < NKK; ++kk)
@@ -458,7 +460,7 @@ void tile_kernel(Problem p, TileSched sc) {
                             cur.og + (size_t)row_in_memory(p, cur.wrow0 + r) * D + 8 * c));
             }
         }
-        if (ST && p.partial && !keep && cur.wrow0 + col < p.Lq) {
+        if (ST == 2 && p.partial && !keep && cur.wrow0 + col < p.Lq) {
             // partial state (o, s, ln w) in natural-log units: the run is one key of score Lam
             float* dst = p.ws + ((size_t)cur.unit * (size_t)p.Lq +
                                  row_in_memory(p, cur.wrow0 + col)) * (D + 2);
@@ -539,11 +541,12 @@ static hipError_t launch_tile_t(const Problem& p_in, int mode, hipStream_t st) {
     }
     const long m_tiles = (p.Lq + 32 * kNW - 1) / (32 * kNW);
     if (m_tiles * p.splits * p.B * p.Hq > 0x7fffffffL) return hipErrorInvalidValue;
-    const bool states = p.partial || p.from_state;
-    const int per_cu = mode == kModeOnline  ? resident_per_cu<tile_kernel<T, D, kModeOnline, false>>()
-                       : mode == kModeBlend ? resident_per_cu<tile_kernel<T, D, kModeBlend, false>>()
-                       : states             ? resident_per_cu<tile_kernel<T, D, kModeLazy, true>>()
-                                            : resident_per_cu<tile_kernel<T, D, kModeLazy, false>>();
+    const int states = p.partial ? 2 : p.from_state ? 1 : 0;
+    const int per_cu = mode == kModeOnline  ? resident_per_cu<tile_kernel<T, D, kModeOnline, 0>>()
+                       : mode == kModeBlend ? resident_per_cu<tile_kernel<T, D, kModeBlend, 0>>()
+                       : states == 2        ? resident_per_cu<tile_kernel<T, D, kModeLazy, 2>>()
+                       : states == 1        ? resident_per_cu<tile_kernel<T, D, kModeLazy, 1>>()
+                                            : resident_per_cu<tile_kernel<T, D, kModeLazy, 0>>();
     const TileSched sc = tile_sched(p, per_cu * kCusPerXcd);
     // One workgroup per virtual workgroup, handed out by the hardware as slots free up.
     // (The kernel can also walk several virtual workgroups per workgroup, but a fixed split
@@ -551,10 +554,12 @@ static hipError_t launch_tile_t(const Problem& p_in, int mode, hipStream_t st) {
     // and runs a third faster, and only dynamic hand-out evens that out.)
     const long wgs = sc.total;
     dim3 grid((unsigned)wgs);
+    // (the ablations take no state in)
     const auto kernel =
-        mode == kModeOnline  ? (states ? tile_kernel<T, D, kModeOnline, true> : tile_kernel<T, D, kModeOnline, false>)
-        : mode == kModeBlend ? (states ? tile_kernel<T, D, kModeBlend, true> : tile_kernel<T, D, kModeBlend, false>)
-        : states             ? tile_kernel<T, D, kModeLazy, true> : tile_kernel<T, D, kModeLazy, false>;
+        mode == kModeOnline  ? (states ? tile_kernel<T, D, kModeOnline, 2> : tile_kernel<T, D, kModeOnline, 0>)
+        : mode == kModeBlend ? (states ? tile_kernel<T, D, kModeBlend, 2> : tile_kernel<T, D, kModeBlend, 0>)
+        : states == 2        ? tile_kernel<T, D, kModeLazy, 2>
+        : states == 1        ? tile_kernel<T, D, kModeLazy, 1> : tile_kernel<T, D, kModeLazy, 0>;
     hipLaunchKernelGGL(kernel, grid, dim3(kNW * 64), 0, st, p, sc);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || !p.merge) return e;

@@ -41,15 +41,21 @@ def test_chunks_with_the_state_handed_on(case, dtype, d, causal, in_place, std):
     o = guards[0].view(q.dtype, q.shape)
     st, k0 = None, 0
     for k1 in (*cuts, Lk):
-        out = st
+        out, before = st, st if st is None else st.clone()
         if st is None or not in_place:
             guards.append(Guarded(B * Hq * Lq * (d + 2) * 4))
             out = guards[-1].view(torch.float32, (B, Hq, Lq, d + 2))
         flashd.attn_fwd_state(qg, k[:, :, k0:k1].contiguous().cuda(), v[:, :, k0:k1].contiguous().cuda(), causal,
                               d ** -0.5, o=o, state_in=st, state_out=out, causal_shift=shift - k0)
         st, k0 = out, k1
+    # a last chunk that hands out no state has the same output
+    alone = torch.full_like(o, float("nan"))
+    a = cuts[-1]
+    flashd.attn_fwd_state(qg, k[:, :, a:].contiguous().cuda(), v[:, :, a:].contiguous().cuda(), causal, d ** -0.5,
+                          o=alone, state_in=before, causal_shift=shift - a)
     torch.cuda.synchronize()
     assert all(x.intact() for x in guards)
+    assert torch.equal(alone, o)
     o, st, g = o.cpu(), st.cpu(), Hq // Hkv
     for b, h in ((0, 0), (B - 1, Hkv - 1)):
         ref = oa.attn_state(of_kv_head(q, b, h, g), of_kv_head(k, b, h), of_kv_head(v, b, h), causal, d ** -0.5,

@@ -100,6 +100,7 @@ def test_shapes_for_the_128_row_kernel(plan):
         for k1 in (*cuts, Lk):
             calls += [(B, Hq, Hkv, Lq, k1 - k0, d, c, shift - k0, 2 if k0 else 1) for d in BOTH for c in MASKS]
             k0 = k1
+        calls += [(B, Hq, Hkv, Lq, Lk - cuts[-1], d, c, shift - cuts[-1], 1) for d in BOTH for c in MASKS]
     calls += [(*s, d, c, None, 0, 1) for s in t.FP8 for d in BOTH for c in MASKS]
     for call, got in zip(calls, plan(calls)):
         assert got == ("128", 1), call
