@@ -128,6 +128,23 @@ inline RowPlan row_plan(const Shape& s, bool causal, int shift, int splits, int 
             plan = {RowKernel::Short, sp};
         }
     }
+    // K and V of more than 100 MB, which no cache holds, are read again by every further round of workgroups,
+    // and the smaller row tiles have more of those than the estimate sees: then the 128-row kernel stays (16-bit
+    // K and V; its time and the other's).  32 rows, more than two workgroups on a compute unit: 13 x 24/8 heads,
+    // 46 x 5093 91 and 111 us, 25 x 96/8, 11 x 9065, d = 64 233 and 264; from 196 MB on with fewer as well,
+    // 16 x 5 heads, 155 x 5306 68 and 92.  64 rows, more than two where the 128-row tiles are all resident, or
+    // more than four: 4 x 64 heads, 152 x 1223 42 and 64, 34 x 12, 147 x 2012 150 and 187.  Of 36000 drawn calls
+    // that the estimate takes from the 128-row kernel 115 that were slower by it (1.22 on average) go back, and
+    // 31 that were not (0.88); 161 slower ones are left, a third of them by more than 10 %.
+    const double most = causal ? std::min(std::max((double)s.Lq + shift, 0.0), (double)s.Lk) : s.Lk;
+    const double kv_mb = (double)s.B * s.Hkv * most * s.d * 4e-6;
+    if (plan.kernel == RowKernel::Short && !fp8 && (kv_mb > 196.0 || (kv_mb > 100.0 && wgs * plan.splits > 512)))
+        plan = {RowKernel::Tile, splits};
+    if (plan.kernel == RowKernel::Tile64 && kv_mb > 100.0) {
+        const long wgs64 = (long)s.B * s.Hkv * ceil_div(g * s.Lq, kTile64[w].rows);
+        const long wgs128 = (long)s.B * s.Hkv * ceil_div(g * s.Lq, kTile[w].rows) * splits;
+        if (wgs64 > 1024 || (wgs64 > 512 && wgs128 <= 512)) plan = {RowKernel::Tile, splits};
+    }
     return plan;
 }
 

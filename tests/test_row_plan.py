@@ -124,3 +124,15 @@ def test_shapes_for_decode_on_eight_wavefronts(plan):
     from tests.test_gpu_decode_eight import ON_FP8, SHAPES
     calls = [(*s, True) for s in SHAPES] + [(*s, True, None, 0, 1) for s in ON_FP8]
     assert plan(calls) == [("decode", 8)] * len(calls)
+
+
+def test_large_keys_and_values_stay_on_the_128_row_kernel(plan):
+    """More than 100 MB of K and V, which every round of workgroups reads again; the next ones are on either side of
+    a line (bytes, workgroups) of the rule."""
+    calls = [(13, 24, 8, 46, 5093, 128, True), (25, 96, 8, 11, 9065, 64, True), (16, 5, 5, 155, 5306, 128, True),
+             (4, 64, 64, 152, 1223, 128, True), (34, 12, 12, 147, 2012, 128, True)]
+    assert [k for k, _ in plan(calls)] == ["128"] * 5
+    assert plan([(13, 24, 8, 46, 1800, 128, True), (13, 24, 8, 42, 2500, 128, True)]) == [("32", 1), ("32", 1)]
+    assert [k for k, _ in plan([(B, 12, 12, 145, 1779, 128, True) for B in (14, 15)])] == ["64", "128"]
+    # fp8: half the bytes, and the 128-row kernel would need them widened
+    assert plan([(13, 24, 8, 46, 5093, 128, True, None, 0, 1)])[0][0] == "32"
