@@ -17,6 +17,7 @@ namespace {
 
 using flashd::ceil_div;
 using flashd::decode_on_eight;
+using flashd::f32_runs_whole;
 using flashd::Problem;
 using flashd::row_plan;
 using flashd::RowKernel;
@@ -164,8 +165,8 @@ int auto_splits(const Shape& s, int variant, bool fp8 = false, bool or_shorter =
     // is what the tile kernel wants: measured over short-query and prefill
     // shapes of 64 to 512 units, the fastest split count is the one that brings the launch
     // to 256-512 workgroups; more of them only add partial states to write and merge.  The
-    // per-key kernel keeps two rounds, and so does the fp32 tile kernel that AUTO runs in its
-    // place, for which the rule has not been measured.
+    // per-key kernel keeps two rounds; the fp32 tile kernel that AUTO runs in its place takes its
+    // splits from here too, or runs whole (f32_runs_whole).
     const long target = variant == FLASHD_VARIANT_PER_KEY ? 1024 : 512;
     if (units < 1) units = 1;
     long sp = units >= target ? 1 : ceil_div(target, units);
@@ -362,12 +363,8 @@ int run(const void* q, const void* k, const void* v, void* o, const Shape& s, in
                         (sa.in != nullptr ? 1 : 0) + (sa.out != nullptr ? 1 : 0), k8.on);
     const bool eight = decode && var == FLASHD_VARIANT_TILE && splits == 0 && !sa.on &&
                        decode_on_eight(s, k8.on, sp_most);
-    // The rule for fp32 counts the per-key kernel's workgroups, of 4 or 8 rows; of the tile kernel's, of
-    // 16, one on every compute unit is enough (d = 64; us whole, in two splits: 480 of them over
-    // 639 keys 25.0, 31.0; 410 over 1306 43.2, 49.9; 273 over 725 18.5, 21.1; but 218 over 1732
-    // 35.5 and 30.5 in three).
     if (variant == FLASHD_VARIANT_AUTO && splits == 0 && s.dtype == FLASHD_F32 &&
-        (long)s.B * s.Hkv * ceil_div((long)(s.Hq / s.Hkv) * s.Lq, 16) >= 256)
+        f32_runs_whole(s, causal != 0, shift, sa.on, sp_most))
         plan.splits = 1;
     const int sp = plan.splits;
     const bool widen = k8.on && !decode && plan.kernel != RowKernel::Short;

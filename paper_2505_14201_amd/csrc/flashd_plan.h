@@ -26,6 +26,42 @@ inline bool decode_on_eight(const Shape& s, bool fp8, int splits) {
     return fp8 && units >= 128 && units <= 192 && s.Lk > 800;
 }
 
+// fp32 calls that run whole on the tile kernel although the rule for splits, which counts the per-key
+// kernel's workgroups of 4 or 8 rows, would split them.  Row tiles have 16 rows, and 256 of them run as one
+// round; in splits the rounds are shorter and more, and it counts how many of them there are all in all
+// (9200 drawn calls of 256 to 1100 row tiles and 512 to 16384 keys; us in the rule's splits, then whole; where
+// not said otherwise d = 64, one sequence):
+//   - as many, or nearly: whole.  8 heads of 1000 x 1306 51 and 46, x 8192 255 and 257, 700 of one row over 2000
+//     keys 145 and 133.  One round alone leaves a wavefront to a SIMD, which long ranges notice: 64 heads of
+//     63 x 13491 237 and 306, but 256 of one row over 1300 38 and 32.
+//   - down to 0.79 of them: whole in place of three splits (400 heads of one row over 2000 keys 85 and 80), in place of
+//     two below 1000 keys (637 of 3 x 1061 75 and 67).  d = 128 has more to gain from splits: 400 heads of
+//     one row over 3000 keys 154 and 161.
+//   - fewer: split.  8 heads of 545 x 1306 40 and 46, x 8192 193 and 253.  But row tiles of unequal length even out by
+//     themselves, where the first row sees at most 0.6 of what the last sees (8 heads of 545 x 1000 under a
+//     mask 33 and 27), and up to 600 keys the second launch takes as much as the splits give.
+// A call with a state runs the merge anyway, so it has less to gain whole.  Against the rule's splits the calls
+// take 0.961 of the time, where always the better of the two gives 0.959; of 9300 others 10 are slower by more
+// than 6 %, 1.13 at most.
+inline bool f32_runs_whole(const Shape& s, bool causal, int shift, bool states, int splits) {
+    const long g = s.Hq / s.Hkv, units = (long)s.B * s.Hkv;
+    if (units * ceil_div(g * s.Lq, 16) < 256) return false;
+    // rows that see a key, keys that the first and the last row see
+    const long rows = causal ? std::min(std::max((long)s.Lq + shift, 0L), (long)s.Lq) : s.Lq;
+    const long least = causal ? std::min(std::max(shift + 1L, 0L), (long)s.Lk) : s.Lk;
+    const long most = causal ? std::min(std::max((long)s.Lq + shift, 0L), (long)s.Lk) : s.Lk;
+    if (most <= 500) return true;
+    const long tiles = units * ceil_div(g * rows, 16);
+    if (tiles < 256) return tiles >= 200 && least == 0;
+    const long rounds = (tiles + 255) / 256, in_splits = (tiles * splits + 255) / 256;
+    if (16 * in_splits > 15 * rounds * splits) return rounds > 1 || least < 2000;
+    if (states) return 3 * least <= most && least < 1300;
+    if (100 * in_splits > 79 * rounds * splits &&
+        (splits > 2 ? s.d == 64 || least < 2000 : s.d == 64 && least < 1000))
+        return true;
+    return least <= 600 || (5 * least <= 3 * most && least < 1300);
+}
+
 // ---- kernels for prefill calls that the 128-row kernel does not fill the chip with ----------
 // Which kernel, and in how many of the splits of the rule, is decided by an estimate of each one's time:
 // the chain of its longest row tile, its work on the whole chip and its way to K and V, whichever

@@ -20,7 +20,9 @@ int main() {
     int causal, shift, splits, states, fp8;
     while (std::scanf("%d %d %d %d %d %d %d %d %d %d %d %d", &s.B, &s.Hq, &s.Hkv, &s.Lq, &s.Lk, &s.d, &s.dtype,
                       &causal, &shift, &splits, &states, &fp8) == 12) {
-        if ((long)(s.Hq / s.Hkv) * s.Lq <= 32) {
+        if (s.dtype == 0) {
+            std::printf("f32 %d\n", f32_runs_whole(s, causal != 0, shift, states != 0, splits) ? 1 : splits);
+        } else if ((long)(s.Hq / s.Hkv) * s.Lq <= 32) {
             std::printf("decode %d\n", states == 0 && decode_on_eight(s, fp8 != 0, splits) ? 8 : 4);
         } else {
             const RowPlan p = row_plan(s, causal != 0, shift, splits, states, fp8 != 0);
@@ -34,8 +36,8 @@ int main() {
 
 @pytest.fixture(scope="module")
 def plan(tmp_path_factory):
-    """plan(calls) -> [(kernel, splits or wavefronts)]; a call is (B, Hq, Hkv, Lq, Lk, d, causal) and optionally
-    shift, states (how many states are read and written) and fp8."""
+    """plan(calls, dtype) -> [(kernel, splits or wavefronts)]; a call is (B, Hq, Hkv, Lq, Lk, d, causal) and
+    optionally shift, states (how many states are read and written) and fp8."""
     if shutil.which("g++") is None:
         pytest.skip("needs g++ to compile the header")
     tmp = tmp_path_factory.mktemp("plan")
@@ -43,14 +45,14 @@ def plan(tmp_path_factory):
     src.write_text(PROGRAM)
     subprocess.run(["g++", "-O1", "-std=c++17", "-Wall", "-I", CSRC, "-o", str(exe), str(src)], check=True)
 
-    def ask(calls):
+    def ask(calls, dtype=flashd.BF16):
         lines, wide = [], []
         for B, Hq, Hkv, Lq, Lk, d, causal, *more in calls:
             shift, states, fp8 = (more + [None, 0, 0][len(more):])
             shift = Lk - Lq if shift is None else max(min(shift, Lk), -Lq - 1)
-            sp = flashd.auto_splits(B, Hq, Hkv, Lq, Lk, d, flashd.BF16)
-            lines.append(f"{B} {Hq} {Hkv} {Lq} {Lk} {d} {flashd.BF16} {int(causal)} {shift} {sp} {states} {int(fp8)}")
-            wide.append(not states and not fp8 and flashd.auto_variant(B, Hq, Hkv, Lq, Lk, d, flashd.BF16, causal)
+            sp = flashd.auto_splits(B, Hq, Hkv, Lq, Lk, d, dtype)
+            lines.append(f"{B} {Hq} {Hkv} {Lq} {Lk} {d} {dtype} {int(causal)} {shift} {sp} {states} {int(fp8)}")
+            wide.append(not states and not fp8 and flashd.auto_variant(B, Hq, Hkv, Lq, Lk, d, dtype, causal)
                         == flashd.VARIANT_TILE_256)
         out = subprocess.run([str(exe)], input="\n".join(lines), capture_output=True, text=True, check=True).stdout
         got = [(k, int(n)) for k, n in (l.split() for l in out.splitlines())]
@@ -136,3 +138,23 @@ def test_large_keys_and_values_stay_on_the_128_row_kernel(plan):
     assert [k for k, _ in plan([(B, 12, 12, 145, 1779, 128, True) for B in (14, 15)])] == ["64", "128"]
     # fp8: half the bytes, and the 128-row kernel would need them widened
     assert plan([(13, 24, 8, 46, 5093, 128, True, None, 0, 1)])[0][0] == "32"
+
+
+@pytest.mark.parametrize("H,Lq,Lk,d,causal,whole,with_state", [
+    # as many rounds of row tiles in splits: whole, a single one up to 2000 keys
+    (256, 1, 1999, 64, 0, 1, 1), (256, 1, 2000, 64, 0, 0, 0), (64, 63, 13491, 64, 0, 0, 0),
+    (8, 1000, 8192, 64, 0, 1, 1), (8, 1000, 8192, 64, 1, 1, 1), (700, 1, 2000, 128, 0, 1, 1),
+    # nearly as many: by splits, keys and d
+    (400, 1, 2000, 64, 0, 1, 0), (400, 1, 2000, 128, 0, 0, 0), (400, 1, 1300, 128, 0, 1, 0),
+    (637, 1, 999, 64, 0, 1, 0), (637, 1, 1000, 64, 0, 0, 0), (637, 1, 999, 128, 0, 0, 0),
+    # fewer: split, but under a mask that rows see unequally of, and up to 600 keys
+    (8, 545, 1306, 64, 0, 0, 0), (8, 545, 8192, 64, 1, 0, 0), (8, 545, 1000, 64, 1, 1, 0), (8, 545, 1306, 64, 1, 1, 0),
+    (8, 545, 1364, 64, 1, 0, 0), (32, 130, 601, 64, 0, 0, 0), (32, 130, 600, 64, 0, 1, 0),
+    # rows that see no key
+    (7, 1094, 542, 64, 1, 1, 1), (2, 2073, 1176, 64, 1, 0, 0),
+])
+def test_fp32_calls_that_run_whole(plan, H, Lq, Lk, d, causal, whole, with_state):
+    call = (1, H, H, Lq, Lk, d, causal)
+    assert flashd.auto_splits(*call[:6], flashd.F32) > 1
+    assert (plan([call], flashd.F32)[0][1] == 1) == bool(whole)
+    assert (plan([(*call, None, 2)], flashd.F32)[0][1] == 1) == bool(with_state)
