@@ -13,16 +13,21 @@ inline int ceil_div(long a, long b) { return (int)((a + b - 1) / b); }
 
 // Decode calls of up to 16 rows per kv head that the rule for splits leaves whole and that run on 8
 // wavefronts per workgroup instead of 4: a workgroup alone on its compute unit waits for its own loads,
-// and 8 have twice as many under way.  Device times, 4 wavefronts and then 8: bf16 d = 64, 32 units of
-// 352 keys 5.2 and 4.8 us, of 1200 10.9 and 8.8, 192 of 2000 18.3 and 16.2; fp8 d = 64, 32 of 600 5.5
-// and 4.9, of 1200 8.6 and 7.0, 256 of 2000 14.2 and 11.5; up to 256 keys, one block for each of the
-// 8, level.  d = 128 has the loads of two such already: from fp8 at 128 to 192 units and over 800
-// keys 0.90 to 0.97 of the time, elsewhere 0.93 to 1.09, in 16 bits 0.94 to 1.12.  Against splits
-// it was 0.95 to 1.24 and those stay.
+// and 8 have twice as many under way.  Device times, 4 wavefronts and then 8:
+//   - d = 64, bf16: 32 units of 352 keys 5.2 and 4.8 us, of 1200 10.9 and 8.8, 192 of 2000 18.3 and 16.2, 171 of
+//     8000 62 and 58, of 65536 453 and 430.  With more units HBM is the bound on long ranges and nothing is left to
+//     gain: 0.97 to 1.01 at 192 to 256 units over 3000 keys and more, 1.01 to 1.02 at 240 and 256 from 12000 on,
+//     so from 8192 keys only up to 208 units.  Up to 256 keys, one block for each of the 8, level.
+//   - d = 64, fp8: 32 units of 600 keys 5.5 and 4.9, of 1200 8.6 and 7.0, 256 of 2000 14.2 and 11.5; longer ones
+//     are split.
+//   - d = 128 has the loads of two such already: from fp8 0.85 to 0.97 of the time at 128 to 192 units (10 counts
+//     of them) over 900 to 40000 keys, 136 of 4000 31.8 and 27.0, 176 of 20000 152 and 138; at other counts 0.93 to
+//     1.09, in 16 bits 0.94 to 1.12.
+// Against splits it was 0.95 to 1.24 and those stay.
 inline bool decode_on_eight(const Shape& s, bool fp8, int splits) {
     const long units = (long)s.B * s.Hkv;
     if (splits > 1 || units > 256 || (long)(s.Hq / s.Hkv) * s.Lq > 16) return false;
-    if (s.d == 64) return s.Lk > 256;
+    if (s.d == 64) return s.Lk > 256 && (units <= 208 || s.Lk <= 8192);
     return fp8 && units >= 128 && units <= 192 && s.Lk > 800;
 }
 

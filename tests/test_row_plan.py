@@ -126,6 +126,9 @@ def test_shapes_for_decode_on_eight_wavefronts(plan):
     from tests.test_gpu_decode_eight import ON_FP8, SHAPES
     calls = [(*s, True) for s in SHAPES] + [(*s, True, None, 0, 1) for s in ON_FP8]
     assert plan(calls) == [("decode", 8)] * len(calls)
+    # many units over long ranges have HBM as their bound
+    calls = [(13, 64, 16, 1, 65536, 64, False), (19, 44, 11, 1, 8192, 64, False), (19, 44, 11, 1, 8193, 64, False)]
+    assert plan(calls) == [("decode", n) for n in (8, 8, 4)]
 
 
 def test_large_keys_and_values_stay_on_the_128_row_kernel(plan):
