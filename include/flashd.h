@@ -140,7 +140,9 @@ size_t flashd_workspace_bytes(int B, int Hq, int Hkv, int Lq, int Lk, int d, int
 /* The number of splits the automatic choice takes for this problem (>= 1; flashd_attn_fwd_kv8, whose
  * key ranges have half the bytes, may take another).  Outside the decode shapes it is the most that
  * it takes, and what scratch memory is sized for: small calls in f16/bf16 run with fewer, or none,
- * where a kernel with 32 or 64 query rows per workgroup is faster. */
+ * where a kernel with 32 or 64 query rows per workgroup is faster, and fp32 calls whole where splits save
+ * nothing.  Passed to flashd_attn_fwd_ex the answer gives the 128-row kernel (decode: 4 wavefronts) in that many
+ * splits; what AUTO runs is had with splits == 0. */
 int flashd_auto_splits(int B, int Hq, int Hkv, int Lq, int Lk, int d, int dtype, int variant);
 
 /*
@@ -190,9 +192,10 @@ int flashd_attn_fwd_state(const void* q, const void* k, const void* v, void* o,
  * o are in the storage type `dtype` (FLASHD_F16 or FLASHD_BF16).  K and V cross HBM as fp8
  * and are widened exactly to `dtype` inside the kernel; everything else is the arithmetic
  * of flashd_attn_fwd (kscale joins the score scale, vscale the output).
- * For decode shapes ((Hq / Hkv) * Lq <= 32) the kernel reads the fp8 data itself; for other
- * shapes K and V are first widened into scratch memory (2 * B * Hkv * Lk * d * 2 bytes from the
- * grow-only cache) and the f16/bf16 kernel runs on that.  FLASHD_F32 gives FLASHD_E_VARIANT.
+ * For decode shapes ((Hq / Hkv) * Lq <= 32) the kernel reads the fp8 data itself.  For other
+ * shapes scratch memory for K and V in `dtype` is taken from the grow-only cache (2 * B * Hkv * Lk *
+ * d * 2 bytes); small calls read the fp8 data themselves all the same, for the others K and V are widened
+ * into it first and the f16/bf16 kernel runs on that.  FLASHD_F32 gives FLASHD_E_VARIANT.
  * Other conventions and errors as for flashd_attn_fwd.
  */
 int flashd_attn_fwd_kv8(const void* q, const void* k8, const void* v8, void* o,

@@ -343,8 +343,8 @@ int run(const void* q, const void* k, const void* v, void* o, const Shape& s, in
     if ((uintptr_t)sk.counts & 7u) return FLASHD_E_ALIGN;
     const int var = resolve_variant(s, variant);
     if (var < 0) return FLASHD_E_VARIANT;
-    // fp8 K/V: the split-K decode kernel reads that storage itself; for other shapes K and V
-    // are first widened (exactly) into scratch memory
+    // fp8 K/V: the decode kernels and the prefill kernel with 32 query rows per workgroup read that
+    // storage themselves; for the other kernels K and V are first widened (exactly) into scratch memory
     if (k8.on && s.dtype == FLASHD_F32) return FLASHD_E_VARIANT;
     // the skip lives in the split-K decode kernel (f16/bf16, at most 32 query rows per kv head)
     if (sk.on && (s.dtype == FLASHD_F32 || !flashd::decode_applies(s.Hq, s.Hkv, s.Lq)))
@@ -386,6 +386,8 @@ int run(const void* q, const void* k, const void* v, void* o, const Shape& s, in
     if (rc != FLASHD_OK) return rc;
     void* ws = workspace;
     const size_t need_al = (need + 255) & ~(size_t)255;
+    // (Also where the plan needs nothing widened: a call with fewer keys may, and is to find its scratch
+    // memory taken by this one, for instance when it is captured into a graph.)
     const size_t kv_bytes = k8.on && !decode ? (size_t)s.B * s.Hkv * s.Lk * s.d * 2 : 0;   // per tensor
     if (use_cache) {
         const size_t cover = partial_bytes(s, scratch_splits(s, var, k8.on, splits, sp_most));

@@ -11,7 +11,7 @@
 //
 // Mapping.  A workgroup of W wavefronts owns one (b, kv head, key split); wavefront w takes the
 // 32-key blocks w, w + W, ... with a state of its own, the W are folded at the end.  W is 4; 8 for
-// the whole calls that decode_on_eight in flashd_api.hip names, with its figures.  Lane
+// the whole calls that decode_on_eight in flashd_plan.h names, with its figures.  Lane
 // (q, c) = (lane / 16, lane % 16): S^T = K Q^T comes as two 16-key tiles of which the lane holds,
 // for query row c, the keys 4 q + r and 16 + 4 q + r (r = 0..3).  Rounded and packed, these are the
 // eight B elements of the lane for O^T = V^T P^T over the whole block; V^T comes from the
@@ -139,7 +139,7 @@ void decode16_kernel(Problem p, Dec16Sched sc) {
     const size_t unit = (size_t)blockIdx.z * p.Hkv + blockIdx.y;        // (b, kv head)
     const float ninf = -__builtin_inff();
 
-    // 32-key blocks of this split; wavefront w takes blk_begin + w, + 4, ...  Position 0 sees the
+    // 32-key blocks of this split; wavefront w takes blk_begin + w, + W, ...  Position 0 sees the
     // fewest keys, position Lq - 1 the most.
     const int nvis_min = visible_at(p, 0);
     const int nvis_max = visible_at(p, p.Lq - 1);
@@ -353,7 +353,7 @@ void decode16_kernel(Problem p, Dec16Sched sc) {
         }
     }
 
-    // ---- fold the four wavefront states -------------------------------------------------
+    // ---- fold the wavefronts' states ----------------------------------------------------
     l = quad_sum(l);
     if (kTL) ltrue = quad_sum(ltrue);
     __syncthreads();                                   // stages are dead, reuse the LDS

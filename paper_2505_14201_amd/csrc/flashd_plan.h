@@ -72,9 +72,9 @@ inline bool f32_runs_whole(const Shape& s, bool causal, int shift, bool states, 
 // the chain of its longest row tile, its work on the whole chip and its way to K and V, whichever
 // is the longest (smoothed), and what it reads and writes of states.  The figures are fits over 2500
 // calls of 1 to 64 sequences, 4 to 32 heads, 8 to 12288 positions and 16 to 117000 keys, causal or
-// not, whole or in chunks; the estimates are within 7 to 13 % on average.  By it 900 calls that the
-// 256-row kernel does not take went to 0.92 (d = 128) and 0.89 (d = 64) of their time on average,
-// down to 0.45: 5 x 16 heads, 182 x 882, d = 128 29.3 -> 17.2 us, 3 x 16 heads of 681, causal, d = 64
+// not, whole or in chunks; the estimates are within 7 to 13 % on average.  By it 900 drawn calls, of which the
+// 128-row kernel keeps most, went to 0.96 (d = 128) and 0.92 (d = 64) of their time on average,
+// the least to 0.45: 5 x 16 heads, 182 x 882, d = 128 29.3 -> 17.2 us, 3 x 16 heads of 681, causal, d = 64
 // 22.0 -> 11.2, 1 x 16/2 heads of 664 17.9 either way.
 enum class RowKernel { Tile, Tile64, Short };
 

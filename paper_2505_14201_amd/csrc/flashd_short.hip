@@ -9,9 +9,10 @@
 // states in memory and second launch as a split over workgroups needs.
 //
 // What bounds it: a block is one chain (K through LDS, scores, top score, exponentials, V through
-// LDS, output product) of 0.8 us at d = 128 and 0.5 at 64 with one workgroup on a compute unit; two
-// share it at 1.5 us a block, which is what LDS takes and hands out of K and V (32 KB a wavefront and
-// block) beside the loads.  Direct global->LDS copies in place of registers, with the scores
+// LDS, output product) of 0.8 us at d = 128 and 0.5 at 64 with one workgroup on a compute unit, whose LDS
+// is then busy 27 % of the time (16 % at 64), its matrix cores 15 % and a wavefront's vector work 24 %: the chain.
+// Two share it at 1.5 us a block; from fp8 LDS is busy 52 % of the time then, a third of that for bank conflicts
+// of the widened rows.  Direct global->LDS copies in place of registers, with the scores
 // of the next block formed before the coefficients of this one, ran at 0.9: no shorter.  Measured (bf16;
 // 128-row kernel, then this): 1 x 8 heads, 1024 x 1024, d = 128 23.0 and 12.2 us (64 row tiles of 128),
 // 5 x 12, 101 x 383 13.1 and 8.3, 1 x 16 of 576 causal, d = 64 13.8 and 7.4.

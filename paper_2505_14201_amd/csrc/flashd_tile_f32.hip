@@ -28,7 +28,9 @@
 // on causal calls (2 x 12 heads, 777 positions 36.9 -> 35.7 us), 1 % on others.
 //
 // What bounds it: the matrix cores.  A block of 16 keys x 16 rows x 64 columns takes 16 fp64
-// instructions of 64 cycles (78.6 TFLOP/s peak) and 16 fp32 ones of 32 cycles.  Measured
+// instructions of 64 cycles (78.6 TFLOP/s peak) and 16 fp32 ones of 32 cycles.  On the causal call below they
+// are busy 57 % of the time, three wavefronts to a SIMD wait 64 % of theirs to issue, and every compute unit has
+// work to the end.  Measured
 // against the per-key kernel: 2 x 12 heads, 777 causal positions, d = 64 36 us (425 us before; 52
 // TFLOP/s of the 97 that the two kinds of instruction allow together), 4 heads of 1000 positions,
 // d = 128 41 us (391), one head of 128 positions 5.5 us of kernel (26).
