@@ -37,6 +37,7 @@ def build_binding(verbose: bool = False) -> str:
     lib = os.path.join(os.path.dirname(torch.__file__), "lib")
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}",
+           f'-DFLASHD_TORCH="{torch.__version__}"',
            *[a for d in (*include_paths(), sysconfig.get_paths()["include"]) for a in ("-isystem", d)],
            BINDING_SOURCE, "-o", BINDING, "-L", lib, "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10",
            f"-Wl,-rpath,{lib}"]

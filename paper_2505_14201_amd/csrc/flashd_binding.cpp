@@ -11,7 +11,6 @@
 
 #include <ATen/core/Tensor.h>
 #include <torch/csrc/autograd/python_variable.h>
-#include <torch/version.h>
 
 #include <cstdint>
 
@@ -218,7 +217,9 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_flashd_binding", nullptr, -1, met
 PyMODINIT_FUNC PyInit__flashd_binding() {
     PyObject* m = PyModule_Create(&module);
     // tensors are read through torch's C++ headers, so another version's may not be handed in
-    const char* built_for = "torch " TORCH_VERSION " and Python " Py_STRINGIFY(PY_MAJOR_VERSION) "." Py_STRINGIFY(PY_MINOR_VERSION);
+    // (FLASHD_TORCH: torch.__version__ at the build)
+    const char* built_for =
+        "torch " FLASHD_TORCH " and Python " Py_STRINGIFY(PY_MAJOR_VERSION) "." Py_STRINGIFY(PY_MINOR_VERSION);
     if (m != nullptr && PyModule_AddStringConstant(m, "built_for", built_for) != 0) Py_CLEAR(m);
     return m;
 }

@@ -78,8 +78,7 @@ def _load() -> ctypes.CDLL:
 _lib = _load()
 try:
     from . import _flashd_binding as _native
-    _built, _here = _native.built_for, "torch {} and Python {}.{}".format(torch.__version__.split("+")[0],
-                                                                          *sys.version_info[:2])
+    _built, _here = _native.built_for, "torch {} and Python {}.{}".format(torch.__version__, *sys.version_info[:2])
     if _built != _here:
         raise ImportError(f"built for {_built}, this is {_here}")
 except ImportError as e:

@@ -17,7 +17,7 @@ def tensors(device="cpu", dtype=torch.bfloat16, d=64):
 
 
 def test_the_native_part_is_built_for_this_torch_and_python():
-    assert NATIVE.built_for == f"torch {torch.__version__.split('+')[0]} and Python 3.{sys.version_info[1]}"
+    assert NATIVE.built_for == f"torch {torch.__version__} and Python 3.{sys.version_info[1]}"
 
 
 def test_anything_but_gpu_tensors_is_left_to_the_python_form():
