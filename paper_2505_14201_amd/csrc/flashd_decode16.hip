@@ -82,25 +82,6 @@ __device__ __forceinline__ float quad_sum(float x) {
     return pair_sum(__uint_as_float(a[0]) + __uint_as_float(a[1]));
 }
 
-// 16 bytes at byte offset `off` of the `bytes` bytes from `base` on; zeros past them.  Streaming
-// (non-temporal): every byte of K and V is read exactly once per launch, and this part reads 7.0
-// TB/s that way against 6.15 with ordinary loads.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t kv_window(const char* base, int64_t bytes) {
-    const int64_t most = 1 << 30;
-    const int n = (int)(bytes < 0 ? 0 : bytes < most ? bytes : most);
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(base), 0, n, 0x00020000);
-}
-__device__ __forceinline__ u32x4 kv_load(__amdgpu_buffer_rsrc_t w, int off) {
-    return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(w, off, 0, 2));
-}
-
-// 8 fp8 values -> 8 values of the storage type T
-template <typename T>
-__device__ __forceinline__ u32x4 widen8(uint32_t lo, uint32_t hi) {
-    return u32x4{Mma<T>::from_fp8_lo(lo), Mma<T>::from_fp8_hi(lo), Mma<T>::from_fp8_lo(hi),
-                 Mma<T>::from_fp8_hi(hi)};
-}
-
 // TL: the state is handed out and the coefficient sums are those of the rounded coefficients, so
 // the unrounded sum is carried as well (the Lam handed out is then the true log-sum-exp).
 // FP8: 0 K and V in the storage type T, 1 and 2 in fp8; 2 reads K as the operand it is, straight
@@ -155,14 +136,14 @@ void decode16_kernel(Problem p, Dec16Sched sc) {
         const auto w = kv_window(kg + at, range - at);
 #pragma unroll
         for (int n = 0; n < NV; ++n)
-            kreg[n] = kv_load(w, KDIRECT ? (c + 16 * (n & 1)) * (D * ESZ) + 64 * (n >> 1) + 16 * q
+            kreg[n] = kv_load<2>(w, KDIRECT ? (c + 16 * (n & 1)) * (D * ESZ) + 64 * (n >> 1) + 16 * q
                                          : 1024 * n + 16 * lane);
     };
     auto fetch_v = [&](int blk_, bool wanted) __attribute__((always_inline)) {
         const int64_t at = (int64_t)blk_ * kBlockBytes;
         const auto w = kv_window(vg + at, wanted ? range - at : 0);
 #pragma unroll
-        for (int n = 0; n < NV; ++n) vreg[n] = kv_load(w, 1024 * n + 16 * lane);
+        for (int n = 0; n < NV; ++n) vreg[n] = kv_load<2>(w, 1024 * n + 16 * lane);
     };
     int blk = blk_begin + wave;
     fetch_k(blk);

@@ -636,4 +636,24 @@ __device__ __forceinline__ int row_in_memory(const Problem& p, int i) {
     return (i - pos * (int)p.heads.d) * p.head_rows + pos;
 }
 
+// 16 bytes at byte offset `off` of the `bytes` bytes from `base` on; zeros past them.  POLICY 2:
+// streaming (non-temporal), for K and V that are read exactly once per launch: this part reads 7.0 TB/s
+// that way against 6.15 with ordinary loads (0).
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t kv_window(const char* base, int64_t bytes) {
+    const int64_t most = 1 << 30;
+    const int n = (int)(bytes < 0 ? 0 : bytes < most ? bytes : most);
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(base), 0, n, 0x00020000);
+}
+template <int POLICY>
+__device__ __forceinline__ u32x4 kv_load(__amdgpu_buffer_rsrc_t w, int off) {
+    return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(w, off, 0, POLICY));
+}
+
+// 8 fp8 values -> 8 values of the storage type T
+template <typename T>
+__device__ __forceinline__ u32x4 widen8(uint32_t lo, uint32_t hi) {
+    return u32x4{Mma<T>::from_fp8_lo(lo), Mma<T>::from_fp8_hi(lo), Mma<T>::from_fp8_lo(hi),
+                 Mma<T>::from_fp8_hi(hi)};
+}
+
 }  // namespace flashd

@@ -32,23 +32,6 @@ constexpr int kShortWaves = 4;
 constexpr int kShortRows = 32;       // query rows per workgroup
 constexpr int kShortBlock = 32;      // keys per wavefront step
 
-// 16 bytes at byte offset `off` of the `bytes` bytes from `base` on; zeros past them.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t short_window(const char* base, int64_t bytes) {
-    const int64_t most = 1 << 30;
-    const int n = (int)(bytes < 0 ? 0 : bytes < most ? bytes : most);
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(base), 0, n, 0x00020000);
-}
-__device__ __forceinline__ u32x4 short_load(__amdgpu_buffer_rsrc_t w, int off) {
-    return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(w, off, 0, 0));
-}
-
-// 8 fp8 values -> 8 values of the storage type T
-template <typename T>
-__device__ __forceinline__ u32x4 short_widen8(uint32_t lo, uint32_t hi) {
-    return u32x4{Mma<T>::from_fp8_lo(lo), Mma<T>::from_fp8_hi(lo), Mma<T>::from_fp8_lo(hi),
-                 Mma<T>::from_fp8_hi(hi)};
-}
-
 template <int N> struct ShortInt { static constexpr int value = N; };
 
 // TL: the state is handed out and the coefficient sums are those of the rounded coefficients, so
@@ -95,9 +78,9 @@ void short_kernel(Problem p, RowSched sc) {
     u32x4 kreg[NV], vreg[NV];
     auto fetch = [&](const char* base, int blk_, u32x4 (&reg)[NV]) __attribute__((always_inline)) {
         const int64_t at = (int64_t)blk_ * kBlockBytes;
-        const auto w = short_window(base + at, range - at);
+        const auto w = kv_window(base + at, range - at);
 #pragma unroll
-        for (int n = 0; n < NV; ++n) reg[n] = short_load(w, 1024 * n + 16 * lane);
+        for (int n = 0; n < NV; ++n) reg[n] = kv_load<0>(w, 1024 * n + 16 * lane);
     };
     int blk = blk_begin + wave;
     fetch(kg, blk, kreg);
@@ -136,8 +119,8 @@ void short_kernel(Problem p, RowSched sc) {
             const int ch = n * kWave + lane;
             uint16_t* dst = &vs[(ch / CPR) * ROW + (FP8 ? 16 : 8) * (ch % CPR)];
             if constexpr (FP8) {
-                *reinterpret_cast<u32x4*>(dst) = short_widen8<T>(reg[n][0], reg[n][1]);
-                *reinterpret_cast<u32x4*>(dst + 8) = short_widen8<T>(reg[n][2], reg[n][3]);
+                *reinterpret_cast<u32x4*>(dst) = widen8<T>(reg[n][0], reg[n][1]);
+                *reinterpret_cast<u32x4*>(dst + 8) = widen8<T>(reg[n][2], reg[n][3]);
             } else {
                 *reinterpret_cast<u32x4*>(dst) = reg[n];
             }
