@@ -176,7 +176,8 @@ inline RowPlan row_plan(const Shape& s, bool causal, int shift, int splits, int 
     // 16 x 5 heads, 155 x 5306 68 and 92.  64 rows, more than two where the 128-row tiles are all resident, or
     // more than four: 4 x 64 heads, 152 x 1223 42 and 64, 34 x 12, 147 x 2012 150 and 187.  Of 36000 drawn calls
     // that the estimate takes from the 128-row kernel 115 that were slower by it (1.22 on average) go back, and
-    // 31 that were not (0.88); 161 slower ones are left, a third of them by more than 10 %.
+    // 31 that were not (0.88); 161 slower ones are left, a third of them by more than 10 %.  Of 13700 others (129
+    // to 24000 keys, any number of heads, states) 26 are slower than on the 128-row kernel alone by more than 5 %.
     const double most = causal ? std::min(std::max((double)s.Lq + shift, 0.0), (double)s.Lk) : s.Lk;
     const double kv_mb = (double)s.B * s.Hkv * most * s.d * 4e-6;
     if (plan.kernel == RowKernel::Short && !fp8 && (kv_mb > 196.0 || (kv_mb > 100.0 && wgs * plan.splits > 512)))
