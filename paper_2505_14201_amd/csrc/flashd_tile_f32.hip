@@ -1,11 +1,11 @@
-// Alg. 3 on key tiles for fp32 storage, on the matrix cores: scores in fp64
-// (v_mfma_f64_16x16x4), output product in fp32 (v_mfma_f32_16x16x4).  This is what the automatic
-// choice runs for fp32; the literal per-key kernel (variant PER_KEY) forms the same scores with
-// fp64 fma on the vector ALUs, one key per lane, and was bound by them and by the 128 registers
-// of output state that every lane carries (4.4 TFLOP/s).
+// Alg. 3 on key tiles for fp32 storage, on the matrix cores: scores beyond fp32 precision, output
+// product in fp32 (v_mfma_f32_16x16x4).  This is what the automatic choice runs for fp32; the
+// literal per-key kernel (variant PER_KEY) forms its scores with fp64 fma on the vector ALUs, one
+// key per lane, and was bound by them and by the 128 registers of output state that every lane
+// carries (4.4 TFLOP/s).
 //
-// Precision is that of the per-key kernel: dot products and scaled scores in fp64, weights in
-// fp32, l (hence s - ln w) and U in fp64 sums of short fp32 ones (kF32Chain).
+// Precision is that of the per-key kernel: dot products and scaled scores as good as in fp64,
+// weights in fp32, l (hence s - ln w) and U in fp64 sums of short fp32 ones (kF32Chain).
 //
 // Tile form: U = sum_j 2^{s_j - R} v_j and l = sum_j 2^{s_j - R} against a reference R (fp64)
 // that starts at the top score of the row's first block and moves only when a block's top score
@@ -14,38 +14,59 @@
 //
 // Mapping.  A workgroup of 4 wavefronts owns 16 query rows of one kv head and one key range;
 // the wavefronts take its 16-key blocks in turn, each with a state of its own, and the four
-// states are folded at the end.  The query heads of a kv group are interleaved (row r is
-// position r / g of head r % g), so K and V are read once for the group and the causal bounds of
-// a row tile stay tight.  Lane (q, c) = (lane / 16, lane % 16) holds of S^T = K Q^T for query row
-// c the keys 4 r + q (r = 0..3), which is the B operand of the r-th step of O^T = V^T P^T as it
+// states are folded at the end.  The query heads of a kv group are interleaved (row r is position
+// r / g of head r % g), so K and V are read once for the group and the causal bounds of a row tile
+// stay tight.  Lane (q, c) = (lane / 16, lane % 16) holds of S^T = K Q^T for query row c the keys
+// 4 q + r (r = 0..3), the r-th of which is the B operand of the r-th step of O^T = V^T P^T as it
 // stands.  The contraction index of the scores and the column index of the output are permuted so
 // that each lane reads K and V as float4 straight from global memory: every wavefront has keys of
 // its own, so LDS would hold nothing that is used twice.  K of the next block is requested before
 // the output product and V before the scores; the rest of the latency is covered by the other
 // wavefronts of the SIMD.
 //
-// The score product runs as two chains, and for d = 64 Q stays in fp64 for the whole row tile: 3 %
-// on causal calls (2 x 12 heads, 777 positions 36.9 -> 35.7 us), 1 % on others.
+// Scores, two ways (SLICED, sliced_scores()):
+//   - fp64, v_mfma_f64_16x16x4: 16 instructions of 64 cycles for 16 keys x 16 rows x 64 columns, as
+//     two chains, Q widened once for d = 64.
+//   - sliced: a row of Q or K, scaled by a power of two to at most 2^kSliceLog2, is the sum of three
+//     fp16 values per element (slice8), and six products of slices, v_mfma_f32_16x16x32_f16, give the
+//     score.  The product of the leading slices is one of integers and exact in fp32, 64 columns at a
+//     time; it and the sum of the others, 2^-10 of its size, are joined in fp64.  What is left out is
+//     below 2^-31 of the product of the largest elements.  12 instructions of 16 cycles and 110 vector instructions in
+//     place of 1024 cycles and 20.  Error of the output against fp64, 2-norm, sliced and in fp64: 2 x
+//     12 heads of 777 causal positions, d = 64 1.23e-7 and 1.23e-7; 8 heads of 2048, d = 128 2.03e-7
+//     both; 4 heads of 1000 1.93e-7 both.
+//     A block whose rows do not lend themselves to it (infinities, exponents more than kSliceSpan
+//     apart or beyond kSliceMin, kSliceMax) is formed in fp64, each by itself.
 //
-// What bounds it: the matrix cores.  A block of 16 keys x 16 rows x 64 columns takes 16 fp64
-// instructions of 64 cycles (78.6 TFLOP/s peak) and 16 fp32 ones of 32 cycles.  On the causal call below they
-// are busy 57 % of the time, three wavefronts to a SIMD wait 64 % of theirs to issue, and every compute unit has
-// work to the end.  Measured
-// against the per-key kernel: 2 x 12 heads, 777 causal positions, d = 64 36 us (425 us before; 52
-// TFLOP/s of the 97 that the two kinds of instruction allow together), 4 heads of 1000 positions,
-// d = 128 41 us (391), one head of 128 positions 5.5 us of kernel (26).
+// What bounds it: vector and matrix instructions, which hardly overlap.  Sliced, d = 64, a block takes a
+// wavefront 265 vector instructions of 4 cycles and 704 cycles of the matrix pipe (512 of them the fp32 output
+// product); 16 heads of 2048 causal positions run at the sum of the two (67 % and 39 % of the time).  Tried on it
+// and not kept: two groups of 16 rows on the same sliced K (two wavefronts per SIMD and not three: 102 us against
+// 98), V requested a block ahead (level), a raised wavefront priority for the longer row tiles (level), scores
+// against R in pairs of fp32 in place of fp64 (level, and 2 % more error).
+// Measured (us; in fp64, sliced): 2 x 12 heads, 777 causal positions, d = 64 35.0, 31.8 (per-key kernel 425); 16 of
+// 2048 129, 98; 4 of 1000, d = 128, no mask 41.9, 34.3; 8 of 2048 243, 177; 16 of 1200, causal 96.8, 75.7.
 #include "flashd_common.h"
 #include "flashd_kernels.h"
 #include "flashd_mma.h"
 
+#include <algorithm>
+
 namespace flashd {
 
 typedef double f64x4 __attribute__((ext_vector_type(4)));
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int kF32Waves = 4;
 constexpr int kF32Rows = 16;       // query rows per workgroup
 constexpr int kF32Block = 16;      // keys per wavefront step
 constexpr double kMoveLog2 = 8.0;
+// Rows of Q and K are scaled to below 2^kSliceLog2 in size before they are sliced (64 products of
+// integers of that size add up to at most 2^24), K by one power of two for all rows of a block, whose
+// largest elements lie within kSliceSpan powers of two of it.
+constexpr int kSliceLog2 = 9, kSliceSpan = 8;
+constexpr float kSliceMin = 0x1p-100f, kSliceMax = 0x1p100f;
 // Blocks of a wavefront whose sums are formed in fp32; then they join sums in fp64, which lie in
 // LDS, each lane's its own.  In fp32 throughout, U and l lose what the per-key kernel keeps, whose
 // blend moves o by a part of itself.  Relative error against fp64 on N(0, 1) inputs (2-norm;
@@ -76,6 +97,58 @@ struct F32Sched {
     FastDiv kv_div;     // unit -> kv unit (Hq / Hkv where the heads are not interleaved, else 1)
 };
 
+// Eight fp32 values, scaled by sc to at most 2^kSliceLog2 in size, as the sum of three fp16 values
+// each: the nearest integer, the rest rounded to 11 bits and what is left then; the remainder is at
+// most 2^-25.  (The matrix instructions take fp16 values below 2^-14 as they are.)
+struct Sliced {
+    f16x8 s1, s2, s3;
+};
+__device__ __forceinline__ Sliced slice8(f32x4 lo, f32x4 hi, float sc) {
+    uint32_t w1[4], w2[4], w3[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const float ta = (i < 2 ? lo[2 * i] : hi[2 * i - 4]) * sc;
+        const float tb = (i < 2 ? lo[2 * i + 1] : hi[2 * i - 3]) * sc;
+        const float na = __builtin_rintf(ta), nb = __builtin_rintf(tb);
+        const float ra = ta - na, rb = tb - nb;
+        const f16x2 h2 = __builtin_convertvector(f32x2{ra, rb}, f16x2);
+        w1[i] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(na, nb));
+        w2[i] = __builtin_bit_cast(uint32_t, h2);
+        w3[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(
+                    f32x2{fmaf((float)h2[0], -1.0f, ra), fmaf((float)h2[1], -1.0f, rb)}, f16x2));
+    }
+    return {__builtin_bit_cast(f16x8, u32x4{w1[0], w1[1], w1[2], w1[3]}),
+            __builtin_bit_cast(f16x8, u32x4{w2[0], w2[1], w2[2], w2[3]}),
+            __builtin_bit_cast(f16x8, u32x4{w3[0], w3[1], w3[2], w3[3]})};
+}
+
+// The largest of a value over the four lanes c, c + 16, c + 32, c + 48, in all of them
+__device__ __forceinline__ float quad_max(float x) {
+    const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+    const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+// hi and lo joined with those of the lane N further round its row of 16
+template <int N> __device__ __forceinline__ void turn16(float& hi, float& lo) {
+    hi = fmaxf(hi, __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(hi), 0x120 + N, 0xf, 0xf, true)));
+    lo = fminf(lo, __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(lo), 0x120 + N, 0xf, 0xf, true)));
+}
+template <int N> __device__ __forceinline__ float largest(const f32x4 (&x)[N]) {
+    float m = 0.0f;
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) m = fmaxf(m, fabsf(x[i][e]));
+    return quad_max(m);
+}
+__device__ __forceinline__ f32x4 mfma16(f16x8 a, f16x8 b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ bool sliceable(float a) { return a == 0.0f || (a >= kSliceMin && a < kSliceMax); }
+// 2^n, n in -126 .. 127
+__device__ __forceinline__ float power_of_two(int n) { return __uint_as_float((uint32_t)(127 + n) << 23); }
+
 // x over the four lanes c, c + 16, c + 32, c + 48 of a query row
 template <typename S, typename F>
 __device__ __forceinline__ S row_reduce(S x, F f) {
@@ -83,10 +156,21 @@ __device__ __forceinline__ S row_reduce(S x, F f) {
     return f(x, __shfl_xor(x, 32, kWave));
 }
 
-template <int D>
+// log2.  CALLED: by a function call.  Inlined, the constants of the logarithm sit in registers from the
+// start of the kernel on, also where no partial states are written; with slices that takes scratch
+// memory, whose set-up costs every launch 0.7 us.  The call costs one that writes them 0.3 us.
+__device__ __attribute__((noinline)) double log2_called(double x) { return log2(x); }
+template <bool CALLED> __device__ __forceinline__ double log2_of(double x) {
+    if constexpr (CALLED) return log2_called(x);
+    return log2(x);
+}
+
+// SLICED: scores from fp16 slices, else in fp64.
+template <int D, bool SLICED>
 __global__ __launch_bounds__(kF32Waves * kWave, D == 64 ? 3 : 2)
 void tile_f32_kernel(Problem p, F32Sched sc) {
     constexpr int NM = D / 16;             // float4 of K per lane and block
+    constexpr int NK = D / 32;             // steps of the score product, sliced
     constexpr int NB = D / 64;             // 64-column groups of the output
     constexpr int FROW = D + 4;            // floats per row of the fold buffer (16-byte rows)
     constexpr int NV = D / 4;              // sums per lane
@@ -141,27 +225,47 @@ void tile_f32_kernel(Problem p, F32Sched sc) {
         const int chunk = (nblk_all + p.splits - 1) / p.splits;
         const int blk_end = min((nvis_max + kF32Block - 1) / kF32Block, (sp + 1) * chunk);
 
-        const float* kg = static_cast<const float*>(p.k) + kv_unit * (size_t)p.Lk * D + 4 * q;
-        const float* vg = static_cast<const float*>(p.v) + kv_unit * (size_t)p.Lk * D + 4 * c;
-        f32x4 qf[NM], kf[NM];
-        // d = 64: Q in fp64 for the whole row tile (for d = 128 that would take 64 registers)
-        double qd[D == 64 ? NM : 1][4];
+        const float* kg = static_cast<const float*>(p.k) + kv_unit * (size_t)p.Lk * D;
+        const float* vg = static_cast<const float*>(p.v) + kv_unit * (size_t)p.Lk * D;
+        f32x4 kf[NM], vf[NB][4];           // V: [column group][r], key 4 q + r, columns 64 i + 4 c ..
+        // Operand row c of the score product.  In fp64 its output row 4 r + q lies in register r of the
+        // lanes q, otherwise row 4 q + r: either way the scores of key 4 q + r end up there.
+        const int krow = SLICED ? c : 4 * (c & 3) + (c >> 2);
+        // (a scalar base and a 32-bit offset per lane)
         auto fetch_k = [&](int blk) __attribute__((always_inline)) {
-            const float* src = kg + (size_t)min(blk * kF32Block + c, p.Lk - 1) * D;
+            const char* base = reinterpret_cast<const char*>(kg + (size_t)blk * kF32Block * D);
+            const uint32_t off = (uint32_t)min(krow, p.Lk - 1 - blk * kF32Block) * (4 * D) + 16 * q;
 #pragma unroll
-            for (int m = 0; m < NM; ++m) kf[m] = *reinterpret_cast<const f32x4*>(src + 16 * m);
+            for (int m = 0; m < NM; ++m) kf[m] = *reinterpret_cast<const f32x4*>(base + off + 64 * m);
         };
+        auto fetch_v = [&](int blk) __attribute__((always_inline)) {
+            const char* base = reinterpret_cast<const char*>(vg + (size_t)blk * kF32Block * D);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const uint32_t off = (uint32_t)min(4 * q + r, p.Lk - 1 - blk * kF32Block) * (4 * D) + 16 * c;
+#pragma unroll
+                for (int i = 0; i < NB; ++i) vf[i][r] = *reinterpret_cast<const f32x4*>(base + off + 256 * i);
+            }
+        };
+        // SLICED: Q, each row scaled by the exponent of its largest element; that exponent; whether some
+        // row does not lend itself to it
+        Sliced qs[NK];
+        int eq = 0;
+        bool q64 = false;
+        // fp64: Q, for d = 64 widened once for the whole row tile (for d = 128 that would take 64 registers)
+        f32x4 qf[SLICED ? 1 : NM];
+        double qd[!SLICED && D == 64 ? NM : 1][4];
 
         for (int pass = 0;; ++pass) {
             const double head = pass == 0 ? 0.0 : kHeadroomLog2;
             const double limit = pass == 0 ? kMoveLog2 : kMoveLog2 - kHeadroomLog2;
             f32x4 U[NB][4];                    // [column group][n]: columns 64 i + 16 q + 4 e + n
+            float l = 0.0f;                    // this lane's keys
+            double R = ninf;
 #pragma unroll
             for (int i = 0; i < NB; ++i)
 #pragma unroll
                 for (int n = 0; n < 4; ++n) U[i][n] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-            float l = 0.0f;                    // this lane's keys
-            double R = ninf;
             int done = 0;                      // blocks of this wavefront
             // what brings the fp64 sums to the present reference
             auto to_reference = [&]() __attribute__((always_inline)) {
@@ -177,48 +281,112 @@ void tile_f32_kernel(Problem p, F32Sched sc) {
                 asm volatile("" : "+v"(col));
                 const float* qg = static_cast<const float*>(p.q) +
                                   q_row(min(r0 + col, rlast)) * D + 4 * q;
+                f32x4 x[NM];
 #pragma unroll
-                for (int m = 0; m < NM; ++m) qf[m] = *reinterpret_cast<const f32x4*>(qg + 16 * m);
-                if constexpr (D == 64) {
+                for (int m = 0; m < NM; ++m) x[m] = *reinterpret_cast<const f32x4*>(qg + 16 * m);
+                if constexpr (SLICED) {
+                    const float qmax = largest(x);
+                    const bool odd = __builtin_amdgcn_ballot_w64(!sliceable(qmax)) != 0;
+                    q64 = q64 || odd;
+                    eq = odd ? 0 : __builtin_amdgcn_frexp_expf(qmax);
+                    const float s = odd ? 0.0f : power_of_two(kSliceLog2 - eq);
 #pragma unroll
-                    for (int m = 0; m < NM; ++m)
+                    for (int i = 0; i < NK; ++i) qs[i] = slice8(x[2 * i], x[2 * i + 1], s);
+                } else {
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            qd[m][e] = (double)qf[m][e];
-                            asm volatile("" : "+v"(qd[m][e]));
+                    for (int m = 0; m < NM; ++m) {
+                        qf[m] = x[m];
+                        if constexpr (D == 64) {
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) {
+                                qd[m][e] = (double)qf[m][e];
+                                asm volatile("" : "+v"(qd[m][e]));
+                            }
                         }
+                    }
                 }
             }
+            int ek = 0;                        // exponent that K is sliced by (rows below 2^ek)
+            uint32_t klo = 0x80000000u;        // bits of 2^(ek - kSliceSpan); at first no row is in range
             for (; blk < blk_end; blk += kF32Waves) {
                 const int j0 = blk * kF32Block;
-                f32x4 vf[NB][4];           // [column group][r]: key 4 r + q, columns 64 i + 4 c ..
+                fetch_v(blk);
+                f64x4 x;
+                bool by64 = !SLICED || q64;
+                if constexpr (SLICED) {
+                    const float kmax = largest(kf);
+                    if (__builtin_amdgcn_ballot_w64(__float_as_uint(kmax) - klo >= (uint32_t)kSliceSpan << 23) != 0) {
+                        // the first block, or rows outside the range that K is sliced by
+                        float hi = kmax, lo = kmax == 0.0f ? kSliceMax : kmax;
+                        turn16<8>(hi, lo); turn16<4>(hi, lo); turn16<2>(hi, lo); turn16<1>(hi, lo);
+                        ek = __builtin_amdgcn_readfirstlane(__builtin_amdgcn_frexp_expf(hi));
+                        const bool fits = hi == 0.0f || (sliceable(hi) && sliceable(lo) &&
+                                                         __builtin_amdgcn_frexp_expf(lo) > ek - kSliceSpan);
+                        by64 = by64 || __builtin_amdgcn_ballot_w64(!fits) != 0;
+                        if (by64) ek = 0;
+                        klo = by64 ? 0x80000000u : (uint32_t)(127 + ek - kSliceSpan) << 23;
+                    }
+                    if (__builtin_expect(!by64, 1)) {
+                        const float s = power_of_two(kSliceLog2 - ek);
+                        const f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
+                        f32x4 whole[NB], rest, rest2;      // whole: 64 columns each, exact
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const float* src = vg + (size_t)min(j0 + 4 * r + q, p.Lk - 1) * D;
+                        for (int i = 0; i < NK; ++i) {
+                            const Sliced ks = slice8(kf[2 * i], kf[2 * i + 1], s);
+                            whole[i / 2] = mfma16(ks.s1, qs[i].s1, i % 2 == 0 ? zero : whole[i / 2]);
+                            rest = mfma16(ks.s1, qs[i].s2, i == 0 ? zero : rest);
+                            rest2 = mfma16(ks.s2, qs[i].s1, i == 0 ? zero : rest2);
+                            rest = mfma16(ks.s1, qs[i].s3, rest);
+                            rest2 = mfma16(ks.s2, qs[i].s2, rest2);
+                            rest = mfma16(ks.s3, qs[i].s1, rest);
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+                        const double cs = __builtin_amdgcn_ldexp(c_log2, eq + ek - 2 * kSliceLog2);
 #pragma unroll
-                    for (int i = 0; i < NB; ++i)
-                        vf[i][r] = *reinterpret_cast<const f32x4*>(src + 64 * i);
+                        for (int r = 0; r < 4; ++r) {
+                            x[r] = (double)whole[0][r] + (double)(rest[r] + rest2[r]);
+                            if (NB == 2) x[r] += (double)whole[NB - 1][r];
+                            x[r] *= cs;
+                        }
+                    }
+                    if (__builtin_expect(by64, 0)) {
+                        // in fp64, K and Q read again
+                        int col = c, grp = q;
+                        asm volatile("" : "+v"(col), "+v"(grp));
+                        const float* ksrc = kg + (size_t)min(j0 + 4 * (col & 3) + (col >> 2), p.Lk - 1) * D + 4 * grp;
+                        const float* qsrc = static_cast<const float*>(p.q) +
+                                            q_row(min(r0 + col, rlast)) * D + 4 * grp;
+                        f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 1
+                        for (int m = 0; m < NM; ++m) {
+                            const f32x4 kv = *reinterpret_cast<const f32x4*>(ksrc + 16 * m);
+                            const f32x4 qv = *reinterpret_cast<const f32x4*>(qsrc + 16 * m);
+#pragma unroll
+                            for (int e = 0; e < 4; ++e)
+                                acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)kv[e], (double)qv[e], acc, 0, 0, 0);
+                        }
+                        x = acc * c_log2;
+                    }
+                } else {
+                    f64x4 acc[2] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};
+#pragma unroll
+                    for (int m = 0; m < NM; ++m) {
+                        // d = 128: widen Q anew for every block
+                        if (D == 128) asm volatile("" : "+v"(qf[m]));
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            acc[e & 1] = __builtin_amdgcn_mfma_f64_16x16x4f64(
+                                (double)kf[m][e], D == 64 ? qd[D == 64 ? m : 0][e] : (double)qf[m][e], acc[e & 1], 0, 0, 0);
+                    }
+                    x = (acc[0] + acc[1]) * c_log2;
                 }
-                f64x4 acc2[2] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};
-#pragma unroll
-                for (int m = 0; m < NM; ++m) {
-                    // d = 128: widen Q anew for every block
-                    if (D == 128) asm volatile("" : "+v"(qf[m]));
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        acc2[e & 1] = __builtin_amdgcn_mfma_f64_16x16x4f64(
-                            (double)kf[m][e], D == 64 ? qd[D == 64 ? m : 0][e] : (double)qf[m][e], acc2[e & 1], 0, 0, 0);
-                }
-                const f64x4 acc = acc2[0] + acc2[1];
                 if (blk + kF32Waves < blk_end) fetch_k(blk + kF32Waves);
 
                 const bool masked = j0 + kF32Block > nvis_min;
-                double x[4];
                 double top = ninf;
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    x[r] = acc[r] * c_log2;
-                    if (masked && j0 + 4 * r + q >= nvis) x[r] = ninf;
+                    if (masked && j0 + 4 * q + r >= nvis) x[r] = ninf;
                     top = fmax(top, x[r]);
                 }
                 if (__builtin_amdgcn_ballot_w64(top > R + limit) != 0) {
@@ -262,15 +430,15 @@ void tile_f32_kernel(Problem p, F32Sched sc) {
 #pragma unroll
                             for (int n = 0; n < 4; ++n)
                                 U[i][n] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[i][r][n], pw[r],
-                                                                               U[i][n], 0, 0, 0);
+                                                                                  U[i][n], 0, 0, 0);
                 } else {
 #pragma unroll 1
                     for (int kk = 0; kk < kF32Block; ++kk) {
-                        const float own = (kk >> 2) == 0 ? pw[0] : (kk >> 2) == 1 ? pw[1]
-                                          : (kk >> 2) == 2 ? pw[2] : pw[3];
-                        const float w = __shfl(own, (kk & 3) * 16 + c, kWave);
+                        const float own = (kk & 3) == 0 ? pw[0] : (kk & 3) == 1 ? pw[1]
+                                          : (kk & 3) == 2 ? pw[2] : pw[3];
+                        const float w = __shfl(own, (kk >> 2) * 16 + c, kWave);
                         if (j0 + kk < nvis) {
-                            const float* src = vg - 4 * c + (size_t)(j0 + kk) * D + 16 * q;
+                            const float* src = vg + (size_t)(j0 + kk) * D + 16 * q;
 #pragma unroll
                             for (int i = 0; i < NB; ++i)
 #pragma unroll
@@ -291,9 +459,11 @@ void tile_f32_kernel(Problem p, F32Sched sc) {
                         const double f = to_reference();
                         mine[NV * kWave] = fma(mine[NV * kWave], f, (double)l);
 #pragma unroll
-                        for (int at = 0; at < NV; ++at)
+                        for (int at = 0; at < NV; ++at) {
                             mine[at * kWave] =
                                 fma(mine[at * kWave], f, (double)U[at / 16][(at / 4) % 4][at % 4]);
+                            if (SLICED && at % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+                        }
                     }
                     mine[(NV + 1) * kWave] = R;
                     l = 0.0f;
@@ -301,6 +471,9 @@ void tile_f32_kernel(Problem p, F32Sched sc) {
                     for (int at = 0; at < NV; ++at) U[at / 16][(at / 4) % 4][at % 4] = 0.0f;
                 }
             }
+
+            // ---- fold the four wavefront states ----------------------------------------
+            float bad = 0.0f;                  // NaN where four such sums might overflow
             double l64 = (double)l;
             if (done >= kF32Chain) {
                 const double f = to_reference();
@@ -311,24 +484,18 @@ void tile_f32_kernel(Problem p, F32Sched sc) {
                     U[at / 16][(at / 4) % 4][at % 4] = (float)u;
                 }
             }
-
-            // ---- fold the four wavefront states ----------------------------------------
-            float bad = 0.0f;                  // NaN where four such sums might overflow
 #pragma unroll
-            for (int i = 0; i < NB; ++i)
-#pragma unroll
-                for (int n = 0; n < 4; ++n)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) bad = fmaf(U[i][n][e] * 4.0f, 0.0f, bad);
-            const bool big = __builtin_amdgcn_ballot_w64(bad != 0.0f) != 0;
+            for (int at = 0; at < NV; ++at)
+                bad = fmaf(U[at / 16][(at / 4) % 4][at % 4] * 4.0f, 0.0f, bad);
             l = row_reduce((float)l64, [](float a, float bb) { return a + bb; });
+            const bool big = __builtin_amdgcn_ballot_w64(bad != 0.0f) != 0;
             __syncthreads();                   // the previous fold has been read
             float* rows = reinterpret_cast<float*>(sums[wave]);
 #pragma unroll
             for (int i = 0; i < NB; ++i)
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
-                    *reinterpret_cast<f32x4*>(&rows[c * FROW + 64 * i + 16 * q + 4 * e]) =
+                    *reinterpret_cast<f32x4*>(&rows[(c) * FROW + 64 * i + 16 * q + 4 * e]) =
                         f32x4{U[i][0][e], U[i][1][e], U[i][2][e], U[i][3][e]};
             if (q == 0) {
                 fold_r[wave][c] = R;
@@ -337,7 +504,10 @@ void tile_f32_kernel(Problem p, F32Sched sc) {
             if (lane == 0) over[wave] = big ? 1 : 0;
             __syncthreads();
             if (pass == 0 && (over[0] | over[1] | over[2] | over[3]) != 0) continue;
-            for (int idx = tid; idx < kF32Rows * (D / 4); idx += kF32Waves * kWave) {
+            // (the thread's index afresh: the addresses below are formed here and not kept)
+            int tid_now = tid;
+            asm volatile("" : "+v"(tid_now));
+            for (int idx = tid_now; idx < kF32Rows * (D / 4); idx += kF32Waves * kWave) {
                 const int fr = idx / (D / 4);
                 const int t = 4 * (idx % (D / 4));
                 if (r0 + fr > rlast) continue;
@@ -367,7 +537,7 @@ void tile_f32_kernel(Problem p, F32Sched sc) {
                     *reinterpret_cast<float2*>(dst + t) = float2{o[0], o[1]};
                     *reinterpret_cast<float2*>(dst + t + 2) = float2{o[2], o[3]};
                     if (t == 0)
-                        split_lam(empty ? ninf : (top + log2((double)lt)) * 0.69314718055994530942,
+                        split_lam(empty ? ninf : (top + log2_of<SLICED>((double)lt)) * 0.69314718055994530942,
                                   dst[D], dst[D + 1]);
                 }
             }
@@ -375,6 +545,21 @@ void tile_f32_kernel(Problem p, F32Sched sc) {
         }
         if (id + gridDim.x < sc.total) __syncthreads();   // the fold has been read, sums is free
     }
+}
+
+// Where the scores are formed from slices (120 shapes of 4, 24 and 96 heads, 64 to 512 positions and short
+// queries over 600 to 2000 keys; time sliced over time in fp64).  Slicing Q and the first block of K costs
+// a wavefront some 0.4 us, a block then saves 0.2 at d = 64 and 0.45 at d = 128.
+//   d = 128: from more than 128 keys per split on 0.81 to 0.99, 1.01 for 4 heads of 512 in splits; 128
+//   keys 0.94 to 1.03, 64 1.05 to 1.08.
+//   d = 64: where compute units have more than one workgroup and more than 160 keys 0.85 to 0.99; with
+//   a workgroup each at most, whose wavefronts wait for memory and not for the matrix cores, 1.00 to 1.05;
+//   160 keys 0.97 to 1.05, 64 1.06 to 1.09.
+static bool sliced_scores(const Problem& p, long workgroups) {
+    const long blocks = (p.Lk + kF32Block - 1L) / kF32Block;
+    const long most = p.causal ? std::min((long)p.Lk, (long)p.Lq + p.shift) : (long)p.Lk;
+    const long keys = std::min((blocks + p.splits - 1) / p.splits * kF32Block, most);
+    return p.d == 128 ? keys > 128 : keys > 160 && workgroups > 256;
 }
 
 template <int D>
@@ -396,7 +581,8 @@ static hipError_t launch_tile_f32_t(const Problem& p, hipStream_t st) {
     sc.units_per_b = make_fast_div((uint32_t)(p.Hq / sc.heads));
     sc.kv_div = make_fast_div((uint32_t)(sc.heads == g ? 1 : g));
     const unsigned grid = (unsigned)(total < (1L << 22) ? total : (1L << 22));
-    hipLaunchKernelGGL((tile_f32_kernel<D>), dim3(grid), dim3(kF32Waves * kWave), 0, st, p, sc);
+    const auto kernel = sliced_scores(p, total) ? tile_f32_kernel<D, true> : tile_f32_kernel<D, false>;
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(kF32Waves * kWave), 0, st, p, sc);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess || !p.merge) return e;
     return launch_merge_splits(p, st);

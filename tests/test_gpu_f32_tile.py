@@ -123,3 +123,43 @@ def test_long_sums_lose_nothing():
     ref = v.double().mean(2, keepdim=True)
     err = ((got.double() - ref).abs() / ref.abs()).max().item()
     assert err <= 6.5e-6, err
+
+
+@pytest.mark.parametrize("kind", ["normal", "far apart", "zero keys", "large", "small", "positive", "huge scores",
+                                  "infinite key"])
+@pytest.mark.parametrize("B,H,Lq,Lk,d", [
+    (1, 1, 20, 128, 128), (1, 1, 17, 129, 128), (1, 2, 100, 700, 128),     # fp64 up to 128 keys, sliced beyond
+    (2, 12, 170, 160, 64), (2, 12, 170, 161, 64), (2, 12, 176, 333, 64),   # sliced from 161 keys on
+])
+@pytest.mark.parametrize("causal", [False, True])
+def test_sliced_scores(kind, B, H, Lq, Lk, d, causal):
+    """Scores from fp16 slices of Q and K, and the blocks that go through fp64 beside them: keys whose
+    sizes lie far apart within a block, exponents beyond the sliced range, an infinite key.  On both
+    sides of the rule that chooses them."""
+    w = synthetic.small("t", B, H, H, Lq, Lk, d, "f32", causal, seed=9700 + Lk + Lq)
+    q, k, v, _ = synthetic.make_qkv(w)
+    scale = w.scale
+    if kind == "far apart":
+        k = k * torch.pow(2.0, -(torch.arange(Lk) * 7 % 23).float()).view(1, 1, -1, 1)
+        q[:, :, ::3] *= 2.0 ** -40
+    elif kind == "zero keys":
+        k[:, :, 5::7] = 0.0
+        q[:, :, 4::9] = 0.0
+    elif kind in ("large", "small"):
+        # exponents of Q or of K beyond those that are sliced; the other and the scale undo them
+        e = 110 if kind == "large" else -110
+        eq, ek = (e, -e // 5) if causal else (-e // 5, e)
+        q, k, scale = q * 2.0 ** eq, k * 2.0 ** ek, scale * 2.0 ** -(eq + ek)
+    elif kind == "positive":
+        q, k = 1.0 + q.abs().clamp(max=0.99), 1.0 + k.abs().clamp(max=0.99)
+    elif kind == "huge scores":
+        q, k = q * 8.0, k * 8.0
+    ref_k, ref_v = k, v
+    if kind == "infinite key":
+        if causal:
+            pytest.skip("the keys left out below would move the mask")
+        q[..., 3] = q[..., 3].abs() + 0.5
+        left = [j for j in range(Lk) if j % 37 != 11]
+        ref_k, ref_v = k[:, :, left].contiguous(), v[:, :, left].contiguous()
+        k[:, :, 11::37, 3] = float("-inf")
+    check(run_flashd(q, k, v, causal, scale, AUTO, 0), oa.attn(q, ref_k, ref_v, causal, scale), torch.float32, kind)
