@@ -18,6 +18,7 @@ namespace {
 using flashd::ceil_div;
 using flashd::decode_on_eight;
 using flashd::f32_runs_whole;
+using flashd::prefers_256_rows;
 using flashd::Problem;
 using flashd::row_plan;
 using flashd::RowKernel;
@@ -38,34 +39,6 @@ int validate_shape(const Shape& s) {
     const long double nk = (long double)s.B * s.Hkv * s.Lk * s.d;
     if (nq > 1.0e12L || nk > 1.0e12L) return FLASHD_E_SHAPE;
     return FLASHD_OK;
-}
-
-// Where the automatic choice takes the 256-row prefill kernel (measured against the 128-row
-// kernel over batch sizes, head counts and lengths): it needs a workgroup per compute unit to
-// be busy at all (256 of them; twice that under a causal mask, whose row tiles differ in
-// length and run in pairs), and row tiles long enough to outweigh what it pays at every change
-// of row tile with only one workgroup on the compute unit (about 8 us, four to five periods of
-// 64 keys): 1536 keys without a mask (+ 8 % at 1536 and 2048, + 12 to 16 % from 4096 on; level
-// at 1024), and under a causal mask rows that see 1536 keys on average, Lk - Lq / 2 (+ 6 % at
-// 3072 x 3072, + 8 to 10 % at 4096, + 14 to 16 % from 8192 on and at 1000 x 3000; 0.90 at
-// 1024).  Rows that see 1024 keys on average (2048 x 2048) are taken where the pairs of row
-// tiles fill a whole number of rounds of the 256 compute units (+ 1 to 3 % then; 3 to 6 %
-// behind otherwise, with compute units idle in the last round).  A 256-row tile that is mostly
-// padding costs as much as a full one: with 16 positions per head and 4 heads to a kv head, 64
-// sequences over 8192 keys took 1366 us on it against 357 us on the 128-row kernel, which runs
-// the heads of a group in one row tile.  It is taken up to 4/3 of the rows that the 128-row
-// kernel works on (measured over 40 to 2100 rows and 4096 keys, 128-row time over 256-row time:
-// 1.02 to 1.12 at 4/3, 0.87 to 1.00 at 8/5, 0.74 to 0.86 at 2).  The kernel itself says which
-// calls it can serve at all (wide_applies()).
-bool prefers_256_rows(const Shape& s, bool causal) {
-    if (s.d != 128 || s.dtype == FLASHD_F32) return false;
-    const long wgs = (long)s.B * s.Hq * ((s.Lq + 255) / 256);
-    const long wgs128 = flashd::tile_workgroups(s.B, s.Hq, s.Hkv, s.Lq, s.d);
-    if (3 * 256 * wgs > 4 * 128 * wgs128) return false;
-    if (!causal) return wgs >= 256 && s.Lk >= 1536;
-    const long seen = (long)s.Lk - s.Lq / 2;        // keys a row sees on average
-    const bool whole_rounds = s.Lq % 512 == 0 && (wgs / 2) % 256 == 0;
-    return wgs >= 512 && (seen >= 1536 || (seen >= 1024 && whole_rounds));
 }
 
 int resolve_variant(const Shape& s, int variant) {

@@ -67,6 +67,91 @@ inline bool f32_runs_whole(const Shape& s, bool causal, int shift, bool states, 
     return least <= 600 || (5 * least <= 3 * most && least < 1300);
 }
 
+// ---- the two prefill kernels ----------------------------------------------------------------
+// Under a causal mask a workgroup can take a long and a short row tile, so that all carry the same work; the
+// pairs then run in rounds of `slots` workgroups, the last of which may be nearly empty, while single row
+// tiles, longest first, even out by themselves.  Measured over 840 calls of 1 to 40 sequences, 8 to 32 heads and
+// 300 to 12288 keys, d = 128 (time single over time in pairs, both prefill kernels; waste: by how much the
+// rounds exceed the pairs):
+//   - up to 4 rounds, more than 800 keys: waste above 0.4 0.68 to 0.93 (128-row kernel 2 x 16/2 heads of 4288, 1.05
+//     rounds, 0.75; 256-row 2 x 12 of 5568 289 us and 177), 0.2 to 0.4 0.84 to 1.02, 0.05 to 0.2 0.88 to 1.02,
+//     below 0.95 to 1.08.
+//   - more rounds: 0.15 to 0.4 0.94 to 0.99, below 0.95 to 1.1.
+//   - row tiles of less than 800 keys, where starting a workgroup costs as much as rounds waste: 0.2 to 0.4 0.9 to
+//     1.0, below 0.97 to 1.04; less than 500 keys 1.06 to 1.12 up to 0.4, 0.84 to 0.91 above.
+//   - K and V of more than 200 MB (100 at d = 64), which the last-level cache does not hold: pairs run a few heads at a
+//     time, single row tiles all of them.  Up to 0.25 0.96 to 1.23, up to 0.4 0.88 to 1.08, above 0.89 to 0.96.
+// (d = 64, 90 calls: 0.96 of the time on average, 0.76 to 1.02.)
+inline bool rows_in_pairs(long m_tiles, long units, long slots, int Lk, int d, double kv_mb) {
+    if (m_tiles < 2 || m_tiles * units < 2 * slots) return false;
+    const double rounds = (double)((m_tiles + 1) / 2) * (double)units / (double)slots;
+    const double waste = std::ceil(rounds) / rounds - 1.0;
+    return waste <= (Lk < 500 || 128.0 * kv_mb > 200.0 * d ? 0.4 : Lk < 800 ? 0.2 : rounds < 4.0 ? 0.05 : 0.15);
+}
+
+// Time of a prefill kernel at d = 128, in us.  Both terms count steps of 64 keys, a row tile's start among them: those
+// of the compute unit that ends last, and the average, which sets the clock (the part is at its power limit while
+// all compute units work).  Fits over the calls above; within 5 % on average (1 % in the mean), 11 % at the 2nd
+// and 98th percentile.
+struct PrefillCost {
+    int rows, slots;            // query rows of a workgroup, workgroups that run at once
+    double start;               // steps that starting and storing a row tile counts for
+    double last, share;         // us per step
+    double launch, kv;          // us, and us per MB of K and V
+};
+
+// g: query heads that run as one, row by row
+inline double prefill_estimate(const PrefillCost& c, const Shape& s, bool causal, long g) {
+    const double units = (double)s.B * (double)(s.Hq / g), tiles = std::ceil((double)g * s.Lq / c.rows);
+    double most = ceil_div(s.Lk, 64), least = most, all = tiles * most;
+    if (causal) {
+        const double off = std::max((double)s.Lk - s.Lq, 0.0), step = (double)c.rows / (double)g;
+        most = s.Lk / 64.0;
+        least = std::min(off + step, (double)s.Lk) / 64.0;
+        all = ((tiles - 1.0) * off + step * (tiles - 1.0) * tiles / 2.0 + s.Lk) / 64.0 + 0.5 * tiles;
+    }
+    const double rounds = tiles * units / c.slots, open = std::ceil(rounds) - rounds;
+    const double share = (all + c.start * tiles) * units / c.slots;
+    const double last = causal ? share + (least + c.start) * open : (rounds + open) * (most + c.start);
+    return c.launch + c.last * std::max(most + c.start, last) + c.share * share +
+           c.kv * (double)s.B * s.Hkv * s.Lk * s.d * 4e-6;
+}
+
+// Where the automatic choice takes the 256-row prefill kernel: within the limits below, where its estimate is not
+// behind that of the 128-row kernel.  Of 840 calls drawn as above 400 are within the limits and 46 of those go to the
+// 128-row kernel by the estimate; with row tiles in pairs or not as above all 840 take 0.97 of the time that the
+// limits alone and pairs throughout gave, 0.62 to 1.04 (1.12 in one case), 1 % more than with the better of the two
+// kernels everywhere.  What is left lies outside the limits: there scores that keep passing the rows' references
+// (standard deviation 4, planted dominant keys) cost the 256-row kernel more than it gains on others (6 x 32
+// heads of 2841, causal, 1143 us and 488).
+//   - a workgroup per compute unit, two under a causal mask;
+//   - 1536 keys without a mask, rows that see 1536 keys on average under a causal one, or 1024 where pairs of row tiles
+//     fill whole rounds: what it pays at every change of row tile with only one workgroup on the compute unit is
+//     about 8 us, four to five periods of 64 keys;
+//   - no row tiles that are mostly padding: up to 4/3 of the rows that the 128-row kernel works on (64 sequences of 16
+//     positions and 4 heads to a kv head over 8192 keys 1366 and 357 us).  At 4/3 itself the estimate is 3 % high (32 x
+//     32 heads, 384 x 4096, causal), hence the margin.
+inline bool prefers_256_rows(const Shape& s, bool causal) {
+    if (s.d != 128 || s.dtype == 0) return false;
+    static const PrefillCost kWide = {256, 256, 5.0, 1.148, 0.437, 2.3, 0.009};
+    static const PrefillCost kTile = {128, 512, 2.0, 0.98, 0.937, 2.3, 0.055};
+    const long g = s.Hq / s.Hkv, lq = s.Lq;
+    const long wgs = (long)s.B * s.Hq * ((lq + 255) / 256);
+    const long tiles128 = (g * lq + 127) / 128;
+    if (3 * 256 * wgs > 4 * 128 * (long)s.B * s.Hkv * tiles128) return false;
+    if (causal) {
+        const long seen = (long)s.Lk - lq / 2;          // keys a row sees on average
+        const bool whole_rounds = lq % 512 == 0 && (wgs / 2) % 256 == 0;
+        if (wgs < 512 || seen < (whole_rounds ? 1024 : 1536)) return false;
+    } else if (wgs < 256 || s.Lk < 1536) {
+        return false;
+    }
+    // (the 128-row kernel runs the heads of a group as one where that saves row tiles or the rows are not late)
+    const bool as_one = tiles128 < g * ((lq + 127) / 128) || !causal || s.Lk <= 8 * lq;
+    return prefill_estimate(kWide, s, causal, 1) <
+           (causal ? 1.035 : 1.0) * prefill_estimate(kTile, s, causal, as_one ? g : 1);
+}
+
 // ---- kernels for prefill calls that the 128-row kernel does not fill the chip with ----------
 // Which kernel, and in how many of the splits of the rule, is decided by an estimate of each one's time:
 // the chain of its longest row tile, its work on the whole chip and its way to K and V, whichever

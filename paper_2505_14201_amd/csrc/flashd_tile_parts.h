@@ -6,6 +6,7 @@
 #include "flashd_common.h"
 #include "flashd_kernels.h"
 #include "flashd_mma.h"
+#include "flashd_plan.h"
 
 #include <algorithm>
 
@@ -266,11 +267,11 @@ inline TileSched tile_sched(const Problem& p, int slots_per_xcd, int rows = 32 *
     const long m_tiles = (p.Lq + rows - 1) / rows;
     const long units = (long)p.splits * p.B * p.Hq;
     TileSched sc;
-    // Pairing halves the number of virtual workgroups; it pays once there are at least
-    // two rounds of them for all workgroup slots.  (Not with split keys: a split's share of a
-    // long and of a short row tile do not add up to the same for every pair.)
-    sc.pair = (p.causal && p.splits == 1 && m_tiles >= 2 &&
-               m_tiles * units >= 2L * kXcds * slots_per_xcd) ? 1 : 0;
+    // (Not with split keys: a split's share of a long and of a short row tile do not add up to the
+    // same for every pair.)
+    sc.pair = (p.causal && p.splits == 1 &&
+               rows_in_pairs(m_tiles, units, (long)kXcds * slots_per_xcd, p.Lk, p.d,
+                             (double)p.B * p.Hkv * p.Lk * p.d * 4e-6)) ? 1 : 0;
     sc.wg_per_unit = (int)(sc.pair ? (m_tiles + 1) / 2 : m_tiles);
     sc.nx_log2 = units % kXcds == 0 ? 3 : 0;
     static_assert(kXcds == 8, "the unit -> XCD mapping shifts by 3");

@@ -21,6 +21,17 @@ def test_padded_256_row_tiles(B, Hq, Hkv, Lq, Lk, causal, want):
     assert flashd.auto_variant(B, Hq, Hkv, Lq, Lk, 128, flashd.BF16, causal) == want
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,Lq,Lk,causal,want", [
+    # the estimate: a last round of 256-row tiles that is nearly empty goes to the 128-row kernel
+    (3, 8, 8, 2642, 2642, False, T), (3, 8, 8, 4096, 4096, False, W), (8, 8, 8, 2048, 2048, False, W),
+    (11, 8, 1, 2176, 2176, False, T),
+    # under a causal mask row tiles even out one by one
+    (2, 12, 12, 5568, 5568, True, W), (1, 32, 8, 4599, 10897, True, W), (1, 16, 2, 10240, 10240, True, W),
+])
+def test_rounds_of_256_row_tiles(B, Hq, Hkv, Lq, Lk, causal, want):
+    assert flashd.auto_variant(B, Hq, Hkv, Lq, Lk, 128, flashd.BF16, causal) == want
+
+
 @pytest.mark.parametrize("B,Hq,Hkv,Lq,Lk,d,want", [
     (1, 32, 8, 1, 640, 128, 1), (1, 32, 8, 1, 641, 128, 5),     # 20 and 21 blocks of 32 keys
     (1, 32, 8, 1, 1280, 64, 1),

@@ -164,3 +164,20 @@ def test_the_automatic_choice_takes_the_wide_kernel_where_it_says_so():
     auto = run_flashd(q, k, v, True, w.scale, use_ex=False)
     tile = run_flashd(q, k, v, True, w.scale, flashd.VARIANT_TILE, 0)
     assert torch.equal(auto.view(torch.int16), tile.view(torch.int16))
+
+
+@pytest.mark.parametrize("variant,B,Hq,Hkv,Lq,Lk,d", [
+    (WIDE, 2, 32, 32, 2200, 2200, 128),                # 320 pairs for 256 compute units: row tiles one by one
+    (WIDE, 4, 32, 32, 1024, 1100, 128),                # 256 pairs: in pairs
+    (flashd.VARIANT_TILE, 2, 32, 32, 2200, 2200, 128), # 576 pairs for 512 workgroups: one by one
+    (flashd.VARIANT_TILE, 3, 12, 4, 4010, 4020, 128),  # heads of a group as one, 564 pairs
+    (flashd.VARIANT_TILE, 3, 32, 32, 2200, 2250, 64),  # 864 pairs for 768
+    (flashd.VARIANT_TILE, 8, 32, 32, 520, 520, 64),    # 768 pairs, the middle row tile by itself
+])
+def test_row_tiles_in_pairs_or_one_by_one(variant, B, Hq, Hkv, Lq, Lk, d):
+    """Both ways of handing out the row tiles of a causal call (rows_in_pairs), through both prefill
+    kernels: every row tile exactly once, wherever it runs."""
+    w = synthetic.small("pairs", B, Hq, Hkv, Lq, Lk, d, "bf16", True, seed=9800 + B)
+    q, k, v, _ = synthetic.make_qkv(w)
+    got = run_flashd(q, k, v, True, w.scale, variant, 1)
+    sampled(got, q, k, v, w, 512, 39, f"B={B} Hq={Hq} Lq={Lq} d={d}")
