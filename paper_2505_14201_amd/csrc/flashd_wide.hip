@@ -19,10 +19,16 @@
 //     instruction; operand reads and copies are spread over the slots as well.
 //   * The coefficients of a block are formed speculatively against the rows' present references
 //     and used one step later, after the sum of each row's coefficients has been looked at: a
-//     sum beyond LazyLimit::kMaxPsum means a score far above the row's reference, and the block
-//     goes through the plain steps instead, which look at the row's top score first and move
-//     the reference there if it lies more than LazyLimit::kMoveLog2 above it (the saturation of
-//     Sec. III-C in tile form).  Nothing risky ever reaches U.
+//     sum beyond LazyLimit::kMaxPsum means a score far above the row's reference, and the block's
+//     coefficients are formed again (wide_refit), by the checked step: it looks at the row's top score
+//     first and moves the reference if that lies more than LazyLimit::kMoveLog2 above it (the
+//     saturation of Sec. III-C in tile form).  Nothing risky ever reaches U, and the block is used by
+//     the next step like any other.
+//   * For 32 periods of 64 keys after that the wavefront's fused steps look at the top scores first, 46
+//     vector instructions more, and scale U themselves where a reference moves.  Scores of standard
+//     deviation 4 with planted dominant keys (us; plain steps after every risky block, and now): 6 x 32
+//     heads of 2841, causal 1146 and 814; 3 x 12, 5384 x 12133, fp16 2138 and 1604; 2 x 16 of 8000, fp16
+//     1186 and 822.  On scores that stay near their references level: 4 x 32 of 2048 158.5 and 159.2.
 //   * The output accumulators, the Q fragments and the matrix operands live in fixed
 //     accumulation registers that only inline assembly touches (flashd_wide_regs.h).
 //
@@ -50,6 +56,14 @@ constexpr int kWideKB = 32;                     // keys per step of a wavefront 
 // reference (the largest of them is then at least 2^-8: far inside the range of either storage
 // type, whose rounding of a coefficient is relative).
 constexpr float kWideMinStart = 0.125f;
+
+// Periods of 64 keys after the last moved reference for which a wavefront looks at the top scores first.
+constexpr int kWideWary = 32;
+// A reference that moves goes this far above the top score (log2 units), so that the next one to move it has to
+// lie that much higher.  bf16: weights of 2^-40 are as good as ones of 1, and 86 more powers of two are left below.
+// fp16 has no room for it.
+template <typename T> constexpr float kWideAbove = 0.0f;
+template <> constexpr float kWideAbove<BF16> = 40.0f;
 
 // A row's state in this kernel, the lazy form of flashd_mma.h with the blend factor kept as its
 // reciprocal: o = U / l, where l = 1 / beta is the sum of 2^{s_j - R} over the keys seen so far.
@@ -319,8 +333,8 @@ __device__ __forceinline__ void wide_request_first_k(const uint16_t* kb, const W
 // Nothing this step does to block b is final before its end: the coefficients are used by the
 // NEXT step, after the sum of each row's coefficients has been looked at here.  A sum beyond
 // LazyLimit::kMaxPsum (or no number at all) means a score far above the row's reference: the
-// step returns true, the row state is left as it was, and the caller takes block b through the
-// plain steps, which move the reference (the saturation of Sec. III-C in tile form).  Otherwise
+// step returns true, the row state is left as it was, and the caller forms the coefficients of
+// block b again (wide_refit), which moves the reference.  Otherwise
 //     1/beta' = 1/beta + psum,
 // which costs nothing here: the coefficients are summed straight onto the rows' l = 1 / beta.
 // copy_hook(i), i = 0..3: called in slots 1, 5, 9, 13 (PENDING only: among the matrix
@@ -331,13 +345,17 @@ __device__ __forceinline__ void wide_request_first_k(const uint16_t* kb, const W
 // the ones at offsets >= lim[rb] are hidden from its row of row block rb: their score counts as
 // -inf and their coefficient is 0.  (Two more vector instructions per key; no row may be empty
 // as for any fused step.)
-template <typename T, int D, bool PENDING, bool MASKED, typename Hook>
+// CHECKED: each row's top score is looked at first, and a reference that it lies more than
+// LazyLimit::kMoveLog2 above moves before the coefficients are formed; U, which the step has by its end
+// multiplied all earlier blocks into, is scaled there.  No block is risky then (short of a sum that is no
+// number).  moved: some reference has.
+template <typename T, int D, bool PENDING, bool MASKED, bool CHECKED, typename Hook>
 __device__ __forceinline__ bool wide_step(const uint16_t* kb, const uint16_t* kb_ahead,
                                           const uint16_t* vb_prev, WideRegs<D>& g,
                                           const f32x16 (&acc)[kWideRB], f32x16 (&accn)[kWideRB],
                                           float c_log2, uint32_t ones, const WidePacked& prev,
                                           WidePacked& cur, const int (&lim)[kWideRB],
-                                          const Hook& copy_hook) {
+                                          bool& moved, const Hook& copy_hook) {
     static_assert(D == 128 && kWideRB == 2, "the slots below are laid out for this shape");
     constexpr int NDB = D / 32;
     float ref[kWideRB], l[kWideRB];
@@ -345,6 +363,23 @@ __device__ __forceinline__ bool wide_step(const uint16_t* kb, const uint16_t* kb
     for (int rb = 0; rb < kWideRB; ++rb) {
         ref[rb] = g.st[rb].R;
         l[rb] = g.st[rb].l;
+    }
+    float f[kWideRB] = {1.0f, 1.0f};
+    if (CHECKED) {
+#pragma unroll
+        for (int rb = 0; rb < kWideRB; ++rb) {
+            float m = -__builtin_inff();
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                m = fmaxf(m, MASKED && 8 * (r >> 2) + (r & 3) >= lim[rb] ? -__builtin_inff() : acc[rb][r]);
+            m = pair_max(m) * c_log2;
+            const bool move = m - ref[rb] > LazyLimit<T>::kMoveLog2;
+            const float to = m + kWideAbove<T>;
+            f[rb] = move ? exp2_fast(ref[rb] - to) : 1.0f;
+            ref[rb] = move ? to : ref[rb];
+            l[rb] *= f[rb];
+        }
+        moved = __builtin_amdgcn_ballot_w64(f[0] != 1.0f || f[1] != 1.0f) != 0;
     }
     // key k of the 32: row block k & 1, score register k >> 1
     float x[33], pe[32];
@@ -445,6 +480,14 @@ __device__ __forceinline__ bool wide_step(const uint16_t* kb, const uint16_t* kb
         // the scores just formed are read by vector instructions next
         mma_fence(accn);
     }
+    if (CHECKED && __builtin_expect(moved, 0)) {
+#pragma unroll
+        for (int rb = 0; rb < kWideRB; ++rb) {
+            if (__builtin_amdgcn_ballot_w64(f[rb] != 1.0f) != 0) wide_scale_u<D>(rb, f[rb]);
+            g.st[rb].l *= f[rb];
+            g.st[rb].R = ref[rb];
+        }
+    }
     // what the block added to this lane's part of the rows' sums: beyond the limit (or no
     // number) if any of its coefficients was
     const bool bad = !(l[0] - g.st[0].l <= LazyLimit<T>::kMaxPsum) ||
@@ -476,8 +519,8 @@ __device__ __forceinline__ void wide_first_general(WideRegs<D>& g, const f32x16 
         const bool empty = g.st[rb].one == 0.0f;
         const float mref = (m == ninf) ? 0.0f : m;
         const bool move = empty || (m - g.st[rb].R > LazyLimit<T>::kMoveLog2);
-        c.ref[rb] = move ? mref : g.st[rb].R;
-        c.f[rb] = empty ? 0.0f : (move ? exp2_fast(g.st[rb].R - mref) : 1.0f);
+        c.ref[rb] = move ? mref + kWideAbove<T> : g.st[rb].R;
+        c.f[rb] = empty ? 0.0f : (move ? exp2_fast(g.st[rb].R - c.ref[rb]) : 1.0f);
         c.empty[rb] = empty;
         // (an empty row holds zeros: nothing to scale)
         if (__builtin_amdgcn_ballot_w64(c.f[rb] != 1.0f && !empty) != 0) wide_scale_u<D>(rb, c.f[rb]);
@@ -504,6 +547,35 @@ __device__ __forceinline__ void wide_first_general(WideRegs<D>& g, const f32x16 
     }
 }
 
+// The row state after a block whose coefficients were formed by wide_first_general,
+//     l' = f l + psum   (l = 1 / beta: the carried sum of coefficients, against the reference
+//                        used; each lane of a row keeps its own part).
+template <int D>
+__device__ __forceinline__ void wide_update(WideRegs<D>& g, const WideCoef& c) {
+#pragma unroll
+    for (int rb = 0; rb < kWideRB; ++rb) {
+        // false only for an empty row that sees no key here (a row that is not empty has a sum
+        // above zero against its reference, and the block's top score has coefficient 1 against
+        // a reference that moves)
+        const bool has = !c.empty[rb] || c.psum[rb] > 0.0f;
+        g.st[rb].l = has ? fmaf(c.f[rb], g.st[rb].l, c.half[rb]) : g.st[rb].l;
+        g.st[rb].R = has ? c.ref[rb] : g.st[rb].R;
+        g.st[rb].one = has ? 1.0f : g.st[rb].one;
+    }
+}
+
+// After a fused step that found its block risky: the coefficients again, by the checked step (see
+// wide_first_general; no row is empty, but for the first block, whose fresh rows hold nothing), and the row
+// state with them.  U holds the blocks before, so the block stays pending like any other
+// that a fused step has taken.
+template <typename T, int D>
+__device__ __forceinline__ void wide_refit(WideRegs<D>& g, const f32x16 (&acc)[kWideRB], float c_log2,
+                                           int jb, const int (&nvis)[kWideRB], WidePacked& out) {
+    WideCoef c;
+    wide_first_general<T, D>(g, acc, c_log2, jb, nvis, c, out);
+    wide_update<D>(g, c);
+}
+
 // The output product of a block on its own, U <- U + P V over the block's 32 keys (vb: its V
 // rows in LDS; b0, b1: the coefficients of its first and last 16 keys, packed).
 template <typename T, int D>
@@ -523,23 +595,11 @@ __device__ __forceinline__ void wide_pv(const uint16_t* vb, const WideRegs<D>& g
         for (int rb = 0; rb < kWideRB; ++rb) wp_mma<T>(rb, m, m / NDB == 0 ? b0[rb] : b1[rb]);
 }
 
-// Second half of a block's step by plain steps: the update of the row state,
-//     l' = f l + psum   (l = 1 / beta: the carried sum of coefficients, against the reference
-//                        used; each lane of a row keeps its own part),
-// and the output product.
+// Second half of a block's step by plain steps: the update of the row state and the output product.
 template <typename T, int D>
 __device__ __forceinline__ void wide_second(const uint16_t* vb, WideRegs<D>& g, const WideCoef& c,
                                             const WidePacked& pk) {
-#pragma unroll
-    for (int rb = 0; rb < kWideRB; ++rb) {
-        // false only for an empty row that sees no key here (a row that is not empty has a sum
-        // above zero against its reference, and the block's top score has coefficient 1 against
-        // a reference that moves)
-        const bool has = !c.empty[rb] || c.psum[rb] > 0.0f;
-        g.st[rb].l = has ? fmaf(c.f[rb], g.st[rb].l, c.half[rb]) : g.st[rb].l;
-        g.st[rb].R = has ? c.ref[rb] : g.st[rb].R;
-        g.st[rb].one = has ? 1.0f : g.st[rb].one;
-    }
+    wide_update<D>(g, c);
     wide_pv<T, D>(vb, g, pk.g0, pk.g1);
 }
 
@@ -706,34 +766,42 @@ void wide_kernel(Problem p, TileSched sc) {
         // there, both of tiles that lie wholly inside the keys) go out one at a time.
         const int t_hi = min(min(min((b_fused - 1) >> 1, (b_nomask - 1) >> 1), n - 4),
                              (p.Lk - cur.jbase) / kBC - 4);
-        // 0: nothing of period t is done; 1: a fused step found block 2 t risky (the scores of
-        // the next block are there, the K copies are out); 2: the same for block 2 t + 1 (both
-        // copies are out)
+        int wary = 0;               // periods for which the fused steps look at the top scores first
+        bool moved = false;
+        // 0: nothing of period t is done; 1: a fused step found block 2 t risky (all of it is done but
+        // the coefficients, the K copies are out); 2: the same for block 2 t + 1 (both copies are out)
         int resume = 0;
         while (t < n) {
             // ---- the common case as a loop of its own: periods both of whose blocks are
             // taken by fused steps that find nothing risky
             if (pending) {
-                while (t <= t_hi) {
-                    if (__builtin_expect(wide_step<T, D, true, false>(
-                                             kslot(0) + kWideKB * D, kslot(1),
-                                             vslot(3) + kWideKB * D, g, acc[0], acc[1], c_log2,
-                                             ones, pk[1], pk[0], nolim, khook), 0)) {
-                        resume = 1;
-                        break;
+                auto run = [&](auto checked) __attribute__((always_inline)) {
+                    constexpr bool C = decltype(checked)::value != 0;
+                    while (t <= t_hi && (!C || wary > 0)) {
+                        bool first = false, second = false;
+                        if (__builtin_expect(wide_step<T, D, true, false, C>(
+                                                 kslot(0) + kWideKB * D, kslot(1),
+                                                 vslot(3) + kWideKB * D, g, acc[0], acc[1], c_log2,
+                                                 ones, pk[1], pk[0], nolim, first, khook), 0)) {
+                            resume = 1;
+                            break;
+                        }
+                        if (__builtin_expect(wide_step<T, D, true, false, C>(
+                                                 kslot(1), kslot(1) + kWideKB * D, vslot(0), g, acc[1],
+                                                 acc[0], c_log2, ones, pk[0], pk[1], nolim, second, vhook), 0)) {
+                            resume = 2;
+                            break;
+                        }
+                        if (C) wary = first || second ? kWideWary : wary - 1;
+                        __builtin_amdgcn_s_waitcnt(0x0F70 | 8);       // vmcnt(8)
+                        asm volatile("" ::: "memory");
+                        __builtin_amdgcn_s_barrier();
+                        asm volatile("" ::: "memory");
+                        ++t;
                     }
-                    if (__builtin_expect(wide_step<T, D, true, false>(
-                                             kslot(1), kslot(1) + kWideKB * D, vslot(0), g, acc[1],
-                                             acc[0], c_log2, ones, pk[0], pk[1], nolim, vhook), 0)) {
-                        resume = 2;
-                        break;
-                    }
-                    __builtin_amdgcn_s_waitcnt(0x0F70 | 8);       // vmcnt(8)
-                    asm volatile("" ::: "memory");
-                    __builtin_amdgcn_s_barrier();
-                    asm volatile("" ::: "memory");
-                    ++t;
-                }
+                };
+                if (__builtin_expect(wary > 0, 0)) run(IntC<1>{});
+                if (resume == 0) run(IntC<0>{});
                 if (t >= n) break;
             }
             // ---- any other period
@@ -744,15 +812,14 @@ void wide_kernel(Problem p, TileSched sc) {
             const uint16_t* knext = kslot(1);
             const uint16_t* vcur = vslot(0);
             const uint16_t* vprev = vslot(3);
-            // Block b = 2 t + KB by plain steps (have_next: the scores of block b + 1 are there
-            // already, a fused step that found block b risky has formed them).
-            auto plain = [&](auto kbc, bool have_next) __attribute__((always_inline)) {
+            // Block b = 2 t + KB by plain steps.
+            auto plain = [&](auto kbc) __attribute__((always_inline)) {
                 constexpr int KB = decltype(kbc)::value;
                 const int b = 2 * t + KB;
                 const uint16_t* kn = KB == 0 ? kcur + kWideKB * D : knext;
                 const uint16_t* vb = vcur + KB * kWideKB * D;
                 const int jb = cur.jbase + b * kWideKB;
-                if (!have_next && b + 1 < nbw) wide_scores<T, D>(kn, g, acc[KB ^ 1]);
+                if (b + 1 < nbw) wide_scores<T, D>(kn, g, acc[KB ^ 1]);
                 WideCoef c;
                 wide_first_general<T, D>(g, acc[KB], c_log2, jb + 4 * hh, nvis, c, pk[KB]);
                 wide_second<T, D>(vb, g, c, pk[KB]);
@@ -760,7 +827,8 @@ void wide_kernel(Problem p, TileSched sc) {
             };
             // Block b = 2 t + KB of the row tile.  K rows of block b + 1 in kn, of block b + 2
             // in ka; V rows of block b - 1 in vp.
-            auto block = [&](auto kbc) __attribute__((always_inline)) {
+            // found_risky: by a fused step of the inner loop.
+            auto block = [&](auto kbc, bool found_risky) __attribute__((always_inline)) {
                 constexpr int KB = decltype(kbc)::value;
                 const int b = 2 * t + KB;
                 const uint16_t* kn = KB == 0 ? kcur + kWideKB * D : knext;
@@ -773,62 +841,54 @@ void wide_kernel(Problem p, TileSched sc) {
                     pending = false;
                     return;
                 }
-                bool have_next = false;
-                if (b <= b_fused) {
-                    bool risky;
-                    // offsets from the key in the lane's score register 0 at which its rows'
-                    // hidden keys begin (none: 64)
-                    int lim[kWideRB];
-#pragma unroll
-                    for (int rb = 0; rb < kWideRB; ++rb)
-                        lim[rb] = b > b_nomask ? nvis[rb] - (cur.jbase + b * kWideKB + 4 * hh) : 64;
-                    if (pending) {
-                        risky = wide_step<T, D, true, true>(kn, ka, vp, g, acc[KB], acc[KB ^ 1],
-                                                            c_log2, ones, pk[KB ^ 1], pk[KB], lim,
-                                                            nohook);
-                    } else {
-                        if (!k_ahead) wide_request_first_k<D>(kn, g);
-                        risky = wide_step<T, D, false, true>(kn, ka, vp, g, acc[KB], acc[KB ^ 1],
-                                                             c_log2, ones, pk[KB ^ 1], pk[KB], lim,
-                                                             nohook);
-                    }
-                    if (b == 0 && !risky) {
-                        // the rows were empty and zero was their reference
-                        bool low = false;
+                if (__builtin_expect(b <= b_fused, 1)) {
+                    bool risky = found_risky;
+                    if (__builtin_expect(!found_risky, 1)) {
+                        // offsets from the key in the lane's score register 0 at which its rows'
+                        // hidden keys begin (none: 64)
+                        int lim[kWideRB];
 #pragma unroll
                         for (int rb = 0; rb < kWideRB; ++rb)
-                            low = low || !(pair_sum(g.st[rb].l) >= kWideMinStart);
-                        risky = __builtin_amdgcn_ballot_w64(low) != 0;
+                            lim[rb] = b > b_nomask ? nvis[rb] - (cur.jbase + b * kWideKB + 4 * hh) : 64;
+                        if (pending) {
+                            risky = wide_step<T, D, true, true, false>(kn, ka, vp, g, acc[KB], acc[KB ^ 1],
+                                                                           c_log2, ones, pk[KB ^ 1], pk[KB], lim,
+                                                                           moved, nohook);
+                        } else {
+                            if (!k_ahead) wide_request_first_k<D>(kn, g);
+                            risky = wide_step<T, D, false, true, false>(kn, ka, vp, g, acc[KB], acc[KB ^ 1],
+                                                                        c_log2, ones, pk[KB ^ 1], pk[KB], lim,
+                                                                        moved, nohook);
+                        }
+                        if (b == 0 && !risky) {
+                            // the rows were empty and zero was their reference
+                            bool low = false;
 #pragma unroll
-                        for (int rb = 0; rb < kWideRB; ++rb) {
-                            g.st[rb].l = risky ? 0.0f : g.st[rb].l;
-                            g.st[rb].one = risky ? 0.0f : 1.0f;
+                            for (int rb = 0; rb < kWideRB; ++rb)
+                                low = low || !(pair_sum(g.st[rb].l) >= kWideMinStart);
+                            risky = __builtin_amdgcn_ballot_w64(low) != 0;
+#pragma unroll
+                            for (int rb = 0; rb < kWideRB; ++rb) {
+                                g.st[rb].l = risky ? 0.0f : g.st[rb].l;
+                                g.st[rb].one = risky ? 0.0f : 1.0f;
+                            }
                         }
                     }
+                    if (__builtin_expect(risky, 0)) {
+                        wide_refit<T, D>(g, acc[KB], c_log2, cur.jbase + b * kWideKB + 4 * hh, nvis, pk[KB]);
+                        if (b > 0) wary = kWideWary;
+                    }
                     k_ahead = true;
-                    have_next = true;
-                    pending = !risky;
-                    if (!risky) return;
-                } else if (pending) {
-                    wide_pv<T, D>(vp, g, pk[KB ^ 1].g0, pk[KB ^ 1].g1);
-                    pending = false;
+                    pending = true;
+                    return;
                 }
-                plain(kbc, have_next);
+                if (pending) wide_pv<T, D>(vp, g, pk[KB ^ 1].g0, pk[KB ^ 1].g1);
+                pending = false;
+                plain(kbc);
             };
-            bool kdone = false, vdone = false;
-            if (resume == 1) {
-                pending = false;
-                plain(IntC<0>{}, true);
-                block(IntC<1>{});
-                kdone = true;
-            } else if (resume == 2) {
-                pending = false;
-                plain(IntC<1>{}, true);
-                kdone = vdone = true;
-            } else {
-                block(IntC<0>{});
-                block(IntC<1>{});
-            }
+            const bool kdone = resume != 0, vdone = resume == 2;
+            if (resume != 2) block(IntC<0>{}, resume == 1);
+            block(IntC<1>{}, resume == 2);
             resume = 0;
             if (kcopy && !kdone)
                 wide_copy<D, false>(cur.kg, j0 + 3 * kBC, p.Lk, dl, wave, lane, lds + ((t + 3) & 3) * kTile);
