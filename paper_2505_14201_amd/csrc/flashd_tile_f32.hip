@@ -39,8 +39,8 @@
 //     apart or beyond kSliceMin, kSliceMax) is formed in fp64, each by itself.
 //
 // What bounds it: vector and matrix instructions, which hardly overlap.  Sliced, d = 64, a block takes a
-// wavefront 265 vector instructions of 4 cycles and 704 cycles of the matrix pipe (512 of them the fp32 output
-// product); 16 heads of 2048 causal positions run at the sum of the two (67 % and 39 % of the time).  Tried on it
+// wavefront 250 vector instructions of 4 cycles and 704 cycles of the matrix pipe (512 of them the fp32 output
+// product); 16 heads of 2048 causal positions run at the sum of the two (67 % and 41 % of the time).  Tried on it
 // and not kept: two groups of 16 rows on the same sliced K (two wavefronts per SIMD and not three: 102 us against
 // 98), V requested a block ahead (level), a raised wavefront priority for the longer row tiles (level), scores
 // against R in pairs of fp32 in place of fp64 (level, and 2 % more error).
