@@ -150,7 +150,8 @@ int flashd_auto_splits(int B, int Hq, int Hkv, int Lq, int Lk, int d, int dtype,
  * TILE, or TILE_256 for calls that kernel can serve and was measured faster on (d = 128, one
  * split, at least a workgroup per compute unit, row tiles that are not mostly padding, from 1536
  * keys on without a mask, and with one where a row sees 1536 keys on average, or 1024 if the row
- * tiles come in whole rounds of the compute units).  Host-only; -1 for invalid arguments.
+ * tiles come in whole rounds of the compute units; and not behind TILE by an estimate of both
+ * times).  Host-only; -1 for invalid arguments.
  * Passed to flashd_attn_fwd_ex the answer gives the kernel that AUTO runs, save for f32: AUTO runs
  * its tile form there, at the precision of PER_KEY and up to twelve times faster, but not with the
  * same bits; pass FLASHD_VARIANT_AUTO itself to get it.  (Decode shapes, (Hq / Hkv) * Lq <= 32,
