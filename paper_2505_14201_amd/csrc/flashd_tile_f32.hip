@@ -4,8 +4,9 @@
 // key per lane, and was bound by them and by the 128 registers of output state that every lane
 // carries (4.4 TFLOP/s).
 //
-// Precision is that of the per-key kernel: dot products and scaled scores as good as in fp64,
-// weights in fp32, l (hence s - ln w) and U in fp64 sums of short fp32 ones (kF32Chain).
+// Weights are fp32, l (hence s - ln w) and U fp64 sums of short fp32 ones (kF32Chain); scores are fp64 or, up to a
+// size (kSliceScore), sums of fp16 slices whose error is below that of an fp32 weight.  The output is then as far
+// from fp64 as with fp64 scores throughout.
 //
 // Tile form: U = sum_j 2^{s_j - R} v_j and l = sum_j 2^{s_j - R} against a reference R (fp64)
 // that starts at the top score of the row's first block and moves only when a block's top score
@@ -27,25 +28,31 @@
 // Scores, two ways (SLICED, sliced_scores()):
 //   - fp64, v_mfma_f64_16x16x4: 16 instructions of 64 cycles for 16 keys x 16 rows x 64 columns, as
 //     two chains, Q widened once for d = 64.
-//   - sliced: a row of Q or K, scaled by a power of two to at most 2^kSliceLog2, is the sum of three
-//     fp16 values per element (slice8), and six products of slices, v_mfma_f32_16x16x32_f16, give the
-//     score.  The product of the leading slices is one of integers and exact in fp32, 64 columns at a
-//     time; it and the sum of the others, 2^-10 of its size, are joined in fp64.  What is left out is
-//     below 2^-31 of the product of the largest elements.  12 instructions of 16 cycles and 110 vector instructions in
-//     place of 1024 cycles and 20.  Error of the output against fp64, 2-norm, sliced and in fp64: 2 x
-//     12 heads of 777 causal positions, d = 64 1.23e-7 and 1.23e-7; 8 heads of 2048, d = 128 2.03e-7
-//     both; 4 heads of 1000 1.93e-7 both.
-//     A block whose rows do not lend themselves to it (infinities, exponents more than kSliceSpan
-//     apart or beyond kSliceMin, kSliceMax) is formed in fp64, each by itself.
+//   - sliced (the splitting of a product into short exact ones of Ozaki, Ogita, Oishi and Rump): a row of Q or K, scaled
+//     by a power of two to at most 2^kSliceLog2, is the sum of three fp16 values per element (slice8), and six
+//     products of slices, v_mfma_f32_16x16x32_f16, give the score.  The product of the leading slices is one of
+//     integers and exact in fp32, 64 columns at a time; it and the sum of the others, 2^-10 of its size, are joined
+//     in fp64.  12 instructions of 16 cycles and 110 vector instructions in place of 1024 cycles and 20.
+//     What is left out of a column is at most 1.25 x 2^-31 of the product of the largest elements of both rows,
+//     whatever the score: an element that meets a zero counts as well.  So a wavefront goes over to fp64, for the
+//     rest of its keys, at the first block where |scale| log2(e) times the bound on that product exceeds
+//     kSliceScore, or whose rows do not lend themselves to slices (infinities, exponents more than kSliceSpan
+//     apart or beyond kSliceMin, kSliceMax).  Up to kSliceScore = 24 the error of a
+//     score is 1.5e-8 (log2 units, rms; at most 9e-7 at d = 64), less than the rounding of a weight.  Error of the output against fp64, 2-norm, sliced and in fp64:
+//     2 x 12 heads of 777 causal positions, d = 64 1.23e-7 both, at standard deviation 2 1.69e-7 both; 8 heads of
+//     2048, d = 128 2.03e-7 both; 4 heads of 1000 1.93e-7 both.  Standard scale and N(0, 1) inputs reach 12 at
+//     most; standard deviation 4 is beyond it.
+//   The two are loops of their own, so that each keeps its operands in registers and no more.
 //
 // What bounds it: vector and matrix instructions, which hardly overlap.  Sliced, d = 64, a block takes a
 // wavefront 250 vector instructions of 4 cycles and 704 cycles of the matrix pipe (512 of them the fp32 output
-// product); 16 heads of 2048 causal positions run at the sum of the two (67 % and 41 % of the time).  Tried on it
+// product); 16 heads of 2048 causal positions run at the sum of the two.  Tried on it
 // and not kept: two groups of 16 rows on the same sliced K (two wavefronts per SIMD and not three: 102 us against
 // 98), V requested a block ahead (level), a raised wavefront priority for the longer row tiles (level), scores
 // against R in pairs of fp32 in place of fp64 (level, and 2 % more error).
-// Measured (us; in fp64, sliced): 2 x 12 heads, 777 causal positions, d = 64 35.0, 31.8 (per-key kernel 425); 16 of
-// 2048 129, 98; 4 of 1000, d = 128, no mask 41.9, 34.3; 8 of 2048 243, 177; 16 of 1200, causal 96.8, 75.7.
+// Measured (us; in fp64, sliced, and where Q and K of standard deviation 4 send every block to fp64 from there): 2 x
+// 12 heads, 777 causal positions, d = 64 34.9, 30.1, 41.7 (per-key kernel 425); 16 of 2048 125, 95.6, 135; 4 of 1000,
+// d = 128, no mask 41.2, 34.5, 47.3; 8 of 2048 241, 174, 252; 16 of 1200, causal 97.0, 74.2, 107.
 #include "flashd_common.h"
 #include "flashd_kernels.h"
 #include "flashd_mma.h"
@@ -67,6 +74,11 @@ constexpr double kMoveLog2 = 8.0;
 // largest elements lie within kSliceSpan powers of two of it.
 constexpr int kSliceLog2 = 9, kSliceSpan = 8;
 constexpr float kSliceMin = 0x1p-100f, kSliceMax = 0x1p100f;
+// Largest |scale| log2(e) 2^(eq + ek) that is sliced, 2^eq and 2^ek the powers of two above the largest elements of
+// the query row and of the K rows.  Without a limit the output is 0.5 % further from fp64 at standard deviation 4
+// and 60 % at 16, and where one column of K is 2^10 and Q zero there the error is 12 times that of fp64 scores
+// (one of 2^20 1300 times).
+constexpr float kSliceScore = 24.0f;
 // Blocks of a wavefront whose sums are formed in fp32; then they join sums in fp64, which lie in
 // LDS, each lane's its own.  In fp32 throughout, U and l lose what the per-key kernel keeps, whose
 // blend moves o by a part of itself.  Relative error against fp64 on N(0, 1) inputs (2-norm;
@@ -190,6 +202,7 @@ void tile_f32_kernel(Problem p, F32Sched sc) {
     double* mine = &sums[wave][lane];
     const double ninf = -__builtin_inf();
     const double c_log2 = (double)p.scale * 1.4426950408889634074;
+    const float reach = (float)fabs(c_log2);
 
     for (uint32_t id = blockIdx.x; id < sc.total; id += gridDim.x) {
         const uint32_t local = id >> sc.nx_log2;
@@ -230,7 +243,7 @@ void tile_f32_kernel(Problem p, F32Sched sc) {
         f32x4 kf[NM], vf[NB][4];           // V: [column group][r], key 4 q + r, columns 64 i + 4 c ..
         // Operand row c of the score product.  In fp64 its output row 4 r + q lies in register r of the
         // lanes q, otherwise row 4 q + r: either way the scores of key 4 q + r end up there.
-        const int krow = SLICED ? c : 4 * (c & 3) + (c >> 2);
+        int krow = 4 * (c & 3) + (c >> 2);
         // (a scalar base and a 32-bit offset per lane)
         auto fetch_k = [&](int blk) __attribute__((always_inline)) {
             const char* base = reinterpret_cast<const char*>(kg + (size_t)blk * kF32Block * D);
@@ -247,14 +260,14 @@ void tile_f32_kernel(Problem p, F32Sched sc) {
                 for (int i = 0; i < NB; ++i) vf[i][r] = *reinterpret_cast<const f32x4*>(base + off + 256 * i);
             }
         };
-        // SLICED: Q, each row scaled by the exponent of its largest element; that exponent; whether some
-        // row does not lend itself to it
-        Sliced qs[NK];
-        int eq = 0;
-        bool q64 = false;
-        // fp64: Q, for d = 64 widened once for the whole row tile (for d = 128 that would take 64 registers)
-        f32x4 qf[SLICED ? 1 : NM];
-        double qd[!SLICED && D == 64 ? NM : 1][4];
+        auto fetch_q = [&](f32x4 (&x)[NM]) __attribute__((always_inline)) {
+            // (the address is formed anew each time: kept, it would cost two registers)
+            int col = c, grp = q;
+            asm volatile("" : "+v"(col), "+v"(grp));
+            const float* qg = static_cast<const float*>(p.q) + q_row(min(r0 + col, rlast)) * D + 4 * grp;
+#pragma unroll
+            for (int m = 0; m < NM; ++m) x[m] = *reinterpret_cast<const f32x4*>(qg + 16 * m);
+        };
 
         for (int pass = 0;; ++pass) {
             const double head = pass == 0 ? 0.0 : kHeadroomLog2;
@@ -274,112 +287,9 @@ void tile_f32_kernel(Problem p, F32Sched sc) {
             };
 
             int blk = sp * chunk + wave;
-            if (blk < blk_end) {
-                fetch_k(blk);
-                // (the address is formed anew for each pass: kept, it would cost two registers)
-                int col = c;
-                asm volatile("" : "+v"(col));
-                const float* qg = static_cast<const float*>(p.q) +
-                                  q_row(min(r0 + col, rlast)) * D + 4 * q;
-                f32x4 x[NM];
-#pragma unroll
-                for (int m = 0; m < NM; ++m) x[m] = *reinterpret_cast<const f32x4*>(qg + 16 * m);
-                if constexpr (SLICED) {
-                    const float qmax = largest(x);
-                    const bool odd = __builtin_amdgcn_ballot_w64(!sliceable(qmax)) != 0;
-                    q64 = q64 || odd;
-                    eq = odd ? 0 : __builtin_amdgcn_frexp_expf(qmax);
-                    const float s = odd ? 0.0f : power_of_two(kSliceLog2 - eq);
-#pragma unroll
-                    for (int i = 0; i < NK; ++i) qs[i] = slice8(x[2 * i], x[2 * i + 1], s);
-                } else {
-#pragma unroll
-                    for (int m = 0; m < NM; ++m) {
-                        qf[m] = x[m];
-                        if constexpr (D == 64) {
-#pragma unroll
-                            for (int e = 0; e < 4; ++e) {
-                                qd[m][e] = (double)qf[m][e];
-                                asm volatile("" : "+v"(qd[m][e]));
-                            }
-                        }
-                    }
-                }
-            }
-            int ek = 0;                        // exponent that K is sliced by (rows below 2^ek)
-            uint32_t klo = 0x80000000u;        // bits of 2^(ek - kSliceSpan); at first no row is in range
-            for (; blk < blk_end; blk += kF32Waves) {
+            // What follows the scores of a block (log2 units; x[r]: key 4 q + r)
+            auto take = [&](f64x4 x) __attribute__((always_inline)) {
                 const int j0 = blk * kF32Block;
-                fetch_v(blk);
-                f64x4 x;
-                bool by64 = !SLICED || q64;
-                if constexpr (SLICED) {
-                    const float kmax = largest(kf);
-                    if (__builtin_amdgcn_ballot_w64(__float_as_uint(kmax) - klo >= (uint32_t)kSliceSpan << 23) != 0) {
-                        // the first block, or rows outside the range that K is sliced by
-                        float hi = kmax, lo = kmax == 0.0f ? kSliceMax : kmax;
-                        turn16<8>(hi, lo); turn16<4>(hi, lo); turn16<2>(hi, lo); turn16<1>(hi, lo);
-                        ek = __builtin_amdgcn_readfirstlane(__builtin_amdgcn_frexp_expf(hi));
-                        const bool fits = hi == 0.0f || (sliceable(hi) && sliceable(lo) &&
-                                                         __builtin_amdgcn_frexp_expf(lo) > ek - kSliceSpan);
-                        by64 = by64 || __builtin_amdgcn_ballot_w64(!fits) != 0;
-                        if (by64) ek = 0;
-                        klo = by64 ? 0x80000000u : (uint32_t)(127 + ek - kSliceSpan) << 23;
-                    }
-                    if (__builtin_expect(!by64, 1)) {
-                        const float s = power_of_two(kSliceLog2 - ek);
-                        const f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
-                        f32x4 whole[NB], rest, rest2;      // whole: 64 columns each, exact
-#pragma unroll
-                        for (int i = 0; i < NK; ++i) {
-                            const Sliced ks = slice8(kf[2 * i], kf[2 * i + 1], s);
-                            whole[i / 2] = mfma16(ks.s1, qs[i].s1, i % 2 == 0 ? zero : whole[i / 2]);
-                            rest = mfma16(ks.s1, qs[i].s2, i == 0 ? zero : rest);
-                            rest2 = mfma16(ks.s2, qs[i].s1, i == 0 ? zero : rest2);
-                            rest = mfma16(ks.s1, qs[i].s3, rest);
-                            rest2 = mfma16(ks.s2, qs[i].s2, rest2);
-                            rest = mfma16(ks.s3, qs[i].s1, rest);
-                            __builtin_amdgcn_sched_barrier(0);
-                        }
-                        const double cs = __builtin_amdgcn_ldexp(c_log2, eq + ek - 2 * kSliceLog2);
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) {
-                            x[r] = (double)whole[0][r] + (double)(rest[r] + rest2[r]);
-                            if (NB == 2) x[r] += (double)whole[NB - 1][r];
-                            x[r] *= cs;
-                        }
-                    }
-                    if (__builtin_expect(by64, 0)) {
-                        // in fp64, K and Q read again
-                        int col = c, grp = q;
-                        asm volatile("" : "+v"(col), "+v"(grp));
-                        const float* ksrc = kg + (size_t)min(j0 + 4 * (col & 3) + (col >> 2), p.Lk - 1) * D + 4 * grp;
-                        const float* qsrc = static_cast<const float*>(p.q) +
-                                            q_row(min(r0 + col, rlast)) * D + 4 * grp;
-                        f64x4 acc = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll 1
-                        for (int m = 0; m < NM; ++m) {
-                            const f32x4 kv = *reinterpret_cast<const f32x4*>(ksrc + 16 * m);
-                            const f32x4 qv = *reinterpret_cast<const f32x4*>(qsrc + 16 * m);
-#pragma unroll
-                            for (int e = 0; e < 4; ++e)
-                                acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)kv[e], (double)qv[e], acc, 0, 0, 0);
-                        }
-                        x = acc * c_log2;
-                    }
-                } else {
-                    f64x4 acc[2] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};
-#pragma unroll
-                    for (int m = 0; m < NM; ++m) {
-                        // d = 128: widen Q anew for every block
-                        if (D == 128) asm volatile("" : "+v"(qf[m]));
-#pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            acc[e & 1] = __builtin_amdgcn_mfma_f64_16x16x4f64(
-                                (double)kf[m][e], D == 64 ? qd[D == 64 ? m : 0][e] : (double)qf[m][e], acc[e & 1], 0, 0, 0);
-                    }
-                    x = (acc[0] + acc[1]) * c_log2;
-                }
                 if (blk + kF32Waves < blk_end) fetch_k(blk + kF32Waves);
 
                 const bool masked = j0 + kF32Block > nvis_min;
@@ -470,6 +380,108 @@ void tile_f32_kernel(Problem p, F32Sched sc) {
 #pragma unroll
                     for (int at = 0; at < NV; ++at) U[at / 16][(at / 4) % 4][at % 4] = 0.0f;
                 }
+            };
+            if (SLICED) krow = c;
+            if (blk < blk_end) fetch_k(blk);
+
+            // ---- scores from slices, up to the first block that needs fp64
+            if constexpr (SLICED) {
+                if (blk < blk_end) {
+                    // Q, each row scaled by the exponent of its largest element, and that exponent
+                    f32x4 xq[NM];
+                    fetch_q(xq);
+                    const float qmax = largest(xq);
+                    const int eq = __builtin_amdgcn_frexp_expf(qmax);
+                    Sliced qs[NK];
+#pragma unroll
+                    for (int i = 0; i < NK; ++i)
+                        qs[i] = slice8(xq[2 * i], xq[2 * i + 1], power_of_two(kSliceLog2 - eq));
+                    bool far = __builtin_amdgcn_ballot_w64(!sliceable(qmax)) != 0;
+                    int ek = 0;                        // exponent that K is sliced by (rows below 2^ek)
+                    uint32_t klo = 0x80000000u;        // bits of 2^(ek - kSliceSpan); at first no row is in range
+#pragma unroll 1
+                    for (; !far && blk < blk_end; blk += far ? 0 : kF32Waves) {
+                        fetch_v(blk);
+                        const float kmax = largest(kf);
+                        if (__builtin_amdgcn_ballot_w64(__float_as_uint(kmax) - klo >= (uint32_t)kSliceSpan << 23) != 0) {
+                            // the first block, or rows outside the range that K is sliced by
+                            float hi = kmax, lo = kmax == 0.0f ? kSliceMax : kmax;
+                            turn16<8>(hi, lo); turn16<4>(hi, lo); turn16<2>(hi, lo); turn16<1>(hi, lo);
+                            ek = __builtin_amdgcn_readfirstlane(__builtin_amdgcn_frexp_expf(hi));
+                            klo = (uint32_t)(127 + ek - kSliceSpan) << 23;
+                            const bool fits = hi == 0.0f || (sliceable(hi) && sliceable(lo) &&
+                                                             __builtin_amdgcn_frexp_expf(lo) > ek - kSliceSpan);
+                            const bool close = __builtin_amdgcn_ldexpf(reach, eq + ek) <= kSliceScore;
+                            far = __builtin_amdgcn_ballot_w64(!fits || !close) != 0;
+                        }
+                        if (__builtin_expect(!far, 1)) {
+                            const float s = power_of_two(kSliceLog2 - ek);
+                            const f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
+                            f32x4 whole[NB], rest, rest2;      // whole: 64 columns each, exact
+#pragma unroll
+                            for (int i = 0; i < NK; ++i) {
+                                const Sliced ks = slice8(kf[2 * i], kf[2 * i + 1], s);
+                                whole[i / 2] = mfma16(ks.s1, qs[i].s1, i % 2 == 0 ? zero : whole[i / 2]);
+                                rest = mfma16(ks.s1, qs[i].s2, i == 0 ? zero : rest);
+                                rest2 = mfma16(ks.s2, qs[i].s1, i == 0 ? zero : rest2);
+                                rest = mfma16(ks.s1, qs[i].s3, rest);
+                                rest2 = mfma16(ks.s2, qs[i].s2, rest2);
+                                rest = mfma16(ks.s3, qs[i].s1, rest);
+                                __builtin_amdgcn_sched_barrier(0);
+                            }
+                            const double cs = __builtin_amdgcn_ldexp(c_log2, eq + ek - 2 * kSliceLog2);
+                            f64x4 x;
+#pragma unroll
+                            for (int r = 0; r < 4; ++r) {
+                                x[r] = (double)whole[0][r] + (double)(rest[r] + rest2[r]);
+                                if (NB == 2) x[r] += (double)whole[NB - 1][r];
+                                x[r] *= cs;
+                            }
+                            take(x);
+                        }
+                    }
+                    if (blk < blk_end) {
+                        // (opaque, so that nothing of the loop above is kept for the one below)
+                        int col = c;
+                        asm volatile("" : "+v"(col), "+s"(blk));
+                        krow = 4 * (col & 3) + (col >> 2);
+                        fetch_k(blk);
+                    }
+                }
+            }
+
+            // ---- scores in fp64
+            if (blk < blk_end) {
+                // Q, for d = 64 widened once (for d = 128 that would take 64 registers)
+                f32x4 qf[NM];
+                double qd[D == 64 ? NM : 1][4];
+                fetch_q(qf);
+                if constexpr (D == 64) {
+#pragma unroll
+                    for (int m = 0; m < NM; ++m)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            qd[m][e] = (double)qf[m][e];
+                            asm volatile("" : "+v"(qd[m][e]));
+                        }
+                }
+                for (; blk < blk_end; blk += kF32Waves) {
+                    fetch_v(blk);
+                    f64x4 acc[2] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};
+#pragma unroll
+                    for (int m = 0; m < NM; ++m) {
+                        // d = 128: widen Q anew for every block
+                        if (D == 128) asm volatile("" : "+v"(qf[m]));
+                        // (four registers in turn: one alone would be written only once the product before has read it)
+                        double kd[4] = {(double)kf[m][0], (double)kf[m][1], (double)kf[m][2], (double)kf[m][3]};
+                        asm volatile("" : "+v"(kd[0]), "+v"(kd[1]), "+v"(kd[2]), "+v"(kd[3]));
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            acc[e & 1] = __builtin_amdgcn_mfma_f64_16x16x4f64(
+                                kd[e], D == 64 ? qd[D == 64 ? m : 0][e] : (double)qf[m][e], acc[e & 1], 0, 0, 0);
+                    }
+                    take((acc[0] + acc[1]) * c_log2);
+                }
             }
 
             // ---- fold the four wavefront states ----------------------------------------
@@ -550,11 +562,10 @@ void tile_f32_kernel(Problem p, F32Sched sc) {
 // Where the scores are formed from slices (120 shapes of 4, 24 and 96 heads, 64 to 512 positions and short
 // queries over 600 to 2000 keys; time sliced over time in fp64).  Slicing Q and the first block of K costs
 // a wavefront some 0.4 us, a block then saves 0.2 at d = 64 and 0.45 at d = 128.
-//   d = 128: from more than 128 keys per split on 0.81 to 0.99, 1.01 for 4 heads of 512 in splits; 128
-//   keys 0.94 to 1.03, 64 1.05 to 1.08.
-//   d = 64: where compute units have more than one workgroup and more than 160 keys 0.85 to 0.99; with
-//   a workgroup each at most, whose wavefronts wait for memory and not for the matrix cores, 1.00 to 1.05;
-//   160 keys 0.97 to 1.05, 64 1.06 to 1.09.
+//   d = 128: from more than 128 keys per split on 0.80 to 0.97; 128 keys 0.95 to 1.01, 64 1.02 to 1.06.
+//   d = 64: where compute units have more than one workgroup and more than 160 keys 0.82 to 0.99; with
+//   a workgroup each at most, whose wavefronts wait for memory and not for the matrix cores, 0.95 to 1.015, not
+//   worth the detour of a call whose scores end in fp64 after all; 160 keys 0.94 to 1.02, 64 1.05 to 1.07.
 static bool sliced_scores(const Problem& p, long workgroups) {
     const long blocks = (p.Lk + kF32Block - 1L) / kF32Block;
     const long most = p.causal ? std::min((long)p.Lk, (long)p.Lq + p.shift) : (long)p.Lk;

@@ -163,3 +163,61 @@ def test_sliced_scores(kind, B, H, Lq, Lk, d, causal):
         ref_k, ref_v = k[:, :, left].contiguous(), v[:, :, left].contiguous()
         k[:, :, 11::37, 3] = float("-inf")
     check(run_flashd(q, k, v, causal, scale, AUTO, 0), oa.attn(q, ref_k, ref_v, causal, scale), torch.float32, kind)
+
+
+@pytest.mark.parametrize("e", [5, 8, 12, 16, 20, 24, 30, 60])
+@pytest.mark.parametrize("kind", ["K column, Q zero", "K column, Q small", "Q column, K zero", "Q column, K small",
+                                  "one key", "crossed"])
+@pytest.mark.parametrize("B,H,Lq,Lk,d", [(2, 12, 176, 333, 64), (1, 2, 100, 700, 128)])
+def test_large_elements(kind, e, B, H, Lq, Lk, d):
+    """Elements of 2^e in rows that otherwise hold ordinary ones, with little or nothing on the other
+    side, so that the scores are ordinary too: what the slices of such a row keep of its other elements
+    is not enough."""
+    w = synthetic.small("t", B, H, H, Lq, Lk, d, "f32", True, seed=9900 + e)
+    q, k, v, _ = synthetic.make_qkv(w)
+    big, small = 2.0 ** e, 2.0 ** -e
+    if kind.startswith("K"):
+        k[..., 5] *= big
+        q[..., 5] *= 0.0 if kind.endswith("zero") else small
+    elif kind.startswith("Q"):
+        q[..., 5] *= big
+        k[..., 5] *= 0.0 if kind.endswith("zero") else small
+    elif kind == "one key":
+        k[:, :, Lk // 3, 7] = big
+        q[..., 7] *= small
+    else:
+        q[..., 3] *= big
+        k[..., 3] *= small
+        k[..., 9] *= big
+        q[..., 9] *= small
+    same_as_fp64_scores(q, k, v, True, w.scale)
+
+
+@pytest.mark.parametrize("kind", ["std 4", "std 30", "std 1000", "near ties", "large scale", "offset"])
+@pytest.mark.parametrize("B,H,Lq,Lk,d", [(2, 12, 176, 333, 64), (1, 2, 100, 700, 128)])
+def test_large_scores(kind, B, H, Lq, Lk, d):
+    """Scores far from zero, and keys that differ by little at scores of ten thousand and more; the
+    bound is that of ordinary scores."""
+    w = synthetic.small("t", B, H, H, Lq, Lk, d, "f32", True, seed=9950 + d)
+    q, k, v, _ = synthetic.make_qkv(w)
+    scale = w.scale
+    if kind.startswith("std"):
+        q, k = q * float(kind[4:]), k * float(kind[4:])
+    elif kind == "near ties":
+        q = q * 64.0
+        k = k[:, :, :1] * 64.0 + k * 2.0 ** -6
+    elif kind == "large scale":
+        scale = 40.0
+    else:
+        k[..., 11] += 1024.0
+    same_as_fp64_scores(q, k, v, True, scale)
+
+
+def same_as_fp64_scores(q, k, v, causal, scale):
+    """Scores in fp64, weights and short sums in fp32: 2e-7 of the output, 2-norm, on ordinary inputs, and
+    less where few keys weigh.  The bound is twice that."""
+    got = run_flashd(q, k, v, causal, scale, AUTO, 0)
+    ref = oa.attn(q, k, v, causal, scale)
+    check(got, ref, torch.float32)
+    err = np.linalg.norm(got.double().numpy() - ref) / np.linalg.norm(ref)
+    assert err <= 4e-7, err
