@@ -27,8 +27,10 @@
 //   * For 32 periods of 64 keys after that the wavefront's fused steps look at the top scores first, 46
 //     vector instructions more, and scale U themselves where a reference moves.  Scores of standard
 //     deviation 4 with planted dominant keys (us; plain steps after every risky block, and now): 6 x 32
-//     heads of 2841, causal 1146 and 814; 3 x 12, 5384 x 12133, fp16 2138 and 1604; 2 x 16 of 8000, fp16
-//     1186 and 822.  On scores that stay near their references level: 4 x 32 of 2048 158.5 and 159.2.
+//     heads of 2841, causal 1143 and 846; 3 x 12, 5384 x 12133, fp16 2146 and 1612; 2 x 16 of 8000, fp16
+//     1190 and 828.  On scores that stay near their references level: 4 x 32 of 2048 165.5 and 165.6.
+//     (References that move 2^40 above the top score in bf16 would move less often, 4 % less time on such
+//     scores, and the products of values of V below 2^-86 would leave the normal range of fp32.)
 //   * The output accumulators, the Q fragments and the matrix operands live in fixed
 //     accumulation registers that only inline assembly touches (flashd_wide_regs.h).
 //
@@ -59,12 +61,6 @@ constexpr float kWideMinStart = 0.125f;
 
 // Periods of 64 keys after the last moved reference for which a wavefront looks at the top scores first.
 constexpr int kWideWary = 32;
-// A reference that moves goes this far above the top score (log2 units), so that the next one to move it has to
-// lie that much higher.  bf16: weights of 2^-40 are as good as ones of 1, and 86 more powers of two are left below.
-// fp16 has no room for it.
-template <typename T> constexpr float kWideAbove = 0.0f;
-template <> constexpr float kWideAbove<BF16> = 40.0f;
-
 // A row's state in this kernel, the lazy form of flashd_mma.h with the blend factor kept as its
 // reciprocal: o = U / l, where l = 1 / beta is the sum of 2^{s_j - R} over the keys seen so far.
 // A lane holds the part of l that comes from the keys its own registers hold (the hh = 0 lane
@@ -374,9 +370,8 @@ __device__ __forceinline__ bool wide_step(const uint16_t* kb, const uint16_t* kb
                 m = fmaxf(m, MASKED && 8 * (r >> 2) + (r & 3) >= lim[rb] ? -__builtin_inff() : acc[rb][r]);
             m = pair_max(m) * c_log2;
             const bool move = m - ref[rb] > LazyLimit<T>::kMoveLog2;
-            const float to = m + kWideAbove<T>;
-            f[rb] = move ? exp2_fast(ref[rb] - to) : 1.0f;
-            ref[rb] = move ? to : ref[rb];
+            f[rb] = move ? exp2_fast(ref[rb] - m) : 1.0f;
+            ref[rb] = move ? m : ref[rb];
             l[rb] *= f[rb];
         }
         moved = __builtin_amdgcn_ballot_w64(f[0] != 1.0f || f[1] != 1.0f) != 0;
@@ -519,8 +514,8 @@ __device__ __forceinline__ void wide_first_general(WideRegs<D>& g, const f32x16 
         const bool empty = g.st[rb].one == 0.0f;
         const float mref = (m == ninf) ? 0.0f : m;
         const bool move = empty || (m - g.st[rb].R > LazyLimit<T>::kMoveLog2);
-        c.ref[rb] = move ? mref + kWideAbove<T> : g.st[rb].R;
-        c.f[rb] = empty ? 0.0f : (move ? exp2_fast(g.st[rb].R - c.ref[rb]) : 1.0f);
+        c.ref[rb] = move ? mref : g.st[rb].R;
+        c.f[rb] = empty ? 0.0f : (move ? exp2_fast(g.st[rb].R - mref) : 1.0f);
         c.empty[rb] = empty;
         // (an empty row holds zeros: nothing to scale)
         if (__builtin_amdgcn_ballot_w64(c.f[rb] != 1.0f && !empty) != 0) wide_scale_u<D>(rb, c.f[rb]);

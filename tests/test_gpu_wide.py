@@ -181,3 +181,29 @@ def test_row_tiles_in_pairs_or_one_by_one(variant, B, Hq, Hkv, Lq, Lk, d):
     q, k, v, _ = synthetic.make_qkv(w)
     got = run_flashd(q, k, v, True, w.scale, variant, 1)
     sampled(got, q, k, v, w, 512, 39, f"B={B} Hq={Hq} Lq={Lq} d={d}")
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("kind", ["low first block", "staircase", "planted"])
+def test_small_values_of_v(kind, causal):
+    """V of 2^-120 where references move: a weight far below 1 on the keys that matter would take the
+    products out of the range of fp32."""
+    torch.manual_seed(23)
+    if kind == "planted":
+        w = synthetic.small("small v", 1, 2, 2, 512, 1024, 128, "bf16", causal, seed=9900, qk_std=6.0,
+                            plant_frac=0.05)
+        q, k, v, _ = synthetic.make_qkv(w)
+        scale = w.scale
+    else:
+        Lq, Lk, d = 512, 1024, 128
+        q = torch.zeros(1, 2, Lq, d)
+        q[..., 0] = 1.0
+        q[..., 1:] = 0.1 * torch.randn(2, Lq, d - 1)
+        k = 0.1 * torch.randn(1, 2, Lk, d)
+        k[..., 0] = -4.0 if kind == "low first block" else torch.arange(Lk) // 96 * 12.0
+        v = torch.randn(1, 2, Lk, d)
+        q, k, v = (t.to(torch.bfloat16) for t in (q, k, v))
+        scale = 1.0
+    ref = oa.attn(q, k, v, causal, scale)
+    got = run_flashd(q, k, (v.float() * 2.0 ** -120).to(torch.bfloat16), causal, scale, WIDE, 1)
+    check(got.double() * 2.0 ** 120, ref, torch.bfloat16, kind)
