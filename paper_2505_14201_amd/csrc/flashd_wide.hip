@@ -719,7 +719,8 @@ void wide_kernel(Problem p, TileSched sc) {
         // long as no row is still empty: not if some row of the wavefront sees no key in block 0
         // (nor under a negative scale).  Block 0 as well, with zero standing in for the rows'
         // reference: good if every row's coefficients then add up to something between
-        // kWideMinStart and the limit of any fused step, else the plain steps take the block.
+        // kWideMinStart and the limit of any fused step, else they are formed again.  If a row is empty even
+        // then, all its scores being -inf, the row tile goes on by plain steps.
         const int nolim[kWideRB] = {64, 64};
         int wmin = cur.wmin;        // keys every row of the wavefront sees
         if (cur.wrow0 < p.Lq && cur.wrow0 + 32 * kWideRB > p.Lq) {
@@ -728,7 +729,7 @@ void wide_kernel(Problem p, TileSched sc) {
             visible_range(p, cur.wrow0, p.Lq - 1, most, wmin);
         }
         const int b_nomask = (wmin - cur.jbase) / kWideKB - 1;    // the last block without a mask
-        const int b_fused = (c_log2 >= 0.0f && wmin > cur.jbase) ? nbw - 1 : -1;
+        int b_fused = (c_log2 >= 0.0f && wmin > cur.jbase) ? nbw - 1 : -1;
         bool pending = false;       // the output product of the block before is still to come
         bool k_ahead = false;       // K operands 0..2 of the next score product are on their way
         // Tile t sits in K slot t % 4 and V slot t % 4.  Period t: start the copies of K(t + 3)
@@ -759,7 +760,7 @@ void wide_kernel(Problem p, TileSched sc) {
         auto nohook = [](int) __attribute__((always_inline)) {};
         // The last period both of whose blocks fused steps can take while its copies (both
         // there, both of tiles that lie wholly inside the keys) go out one at a time.
-        const int t_hi = min(min(min((b_fused - 1) >> 1, (b_nomask - 1) >> 1), n - 4),
+        int t_hi = min(min(min((b_fused - 1) >> 1, (b_nomask - 1) >> 1), n - 4),
                              (p.Lk - cur.jbase) / kBC - 4);
         int wary = 0;               // periods for which the fused steps look at the top scores first
         bool moved = false;
@@ -872,6 +873,10 @@ void wide_kernel(Problem p, TileSched sc) {
                     if (__builtin_expect(risky, 0)) {
                         wide_refit<T, D>(g, acc[KB], c_log2, cur.jbase + b * kWideKB + 4 * hh, nvis, pk[KB]);
                         if (b > 0) wary = kWideWary;
+                        // (a fused step would take zero for the reference of a row that is still empty)
+                        if (KB == 0 && b == 0 &&
+                            __builtin_amdgcn_ballot_w64(g.st[0].one * g.st[1].one == 0.0f) != 0)
+                            b_fused = t_hi = -1;
                     }
                     k_ahead = true;
                     pending = true;

@@ -207,3 +207,40 @@ def test_small_values_of_v(kind, causal):
     ref = oa.attn(q, k, v, causal, scale)
     got = run_flashd(q, k, (v.float() * 2.0 ** -120).to(torch.bfloat16), causal, scale, WIDE, 1)
     check(got.double() * 2.0 ** 120, ref, torch.bfloat16, kind)
+
+
+@pytest.mark.parametrize("dtype,rows", [("bf16", "all"), ("bf16", "some"), ("f16", "all")])
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("later", ["ordinary, then high", "far below zero", "low, -inf, ordinary"])
+@pytest.mark.parametrize("first", [32, 70])
+def test_wide_kernel_rows_whose_first_keys_weigh_nothing(first, later, rows, causal, dtype):
+    """Rows whose scores in the first block are all -inf are still empty where the others of their
+    wavefront are not; what follows must reach them, wherever their references then lie."""
+    torch.manual_seed(29)
+    Lq, Lk, d = 512, 1400, 128
+    q = torch.zeros(1, 2, Lq, d)
+    q[..., 0] = 1.0
+    q[..., 1:] = 0.1 * torch.randn(2, Lq, d - 1)
+    k = 0.1 * torch.randn(1, 2, Lk, d)
+    v = torch.randn(1, 2, Lk, d)
+    hidden = torch.zeros(Lk, dtype=torch.bool)
+    hidden[:first] = True
+    if later.startswith("ordinary"):
+        k[..., 700:, 0] = 300.0
+    elif later.startswith("far"):
+        k[..., 0] = -200.0
+    else:
+        k[..., first:200, 0] = -200.0
+        hidden[200:400] = True
+    # hidden: from the rows with a large element in column 5 (bf16: the product of two of 1e30 is infinite)
+    big = 6.0e4 if dtype == "f16" else 1.0e30
+    q[..., 5] = 0.0
+    q[:, :, ::3 if rows == "some" else 1, 5] = big
+    k[..., 5] = 0.0
+    k[:, :, hidden, 5] = -big
+    q, k, v = (t.to(DT[dtype]) for t in (q, k, v))
+    ref = oa.attn(q, k, v, causal, 1.0)
+    if dtype == "f16":
+        k[:, :, hidden, 5] = float("-inf")
+    got = run_flashd(q, k, v, causal, 1.0, WIDE, 1)
+    check(got, ref, DT[dtype], f"{later} {rows}")
