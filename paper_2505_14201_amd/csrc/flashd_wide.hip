@@ -850,7 +850,8 @@ void wide_kernel(Problem p, TileSched sc) {
                             risky = wide_step<T, D, true, true, false>(kn, ka, vp, g, acc[KB], acc[KB ^ 1],
                                                                            c_log2, ones, pk[KB ^ 1], pk[KB], lim,
                                                                            moved, nohook);
-                        } else {
+                        } else if constexpr (KB == 0) {
+                            // (the first block; every other fused step finds the block before it pending)
                             if (!k_ahead) wide_request_first_k<D>(kn, g);
                             risky = wide_step<T, D, false, true, false>(kn, ka, vp, g, acc[KB], acc[KB ^ 1],
                                                                         c_log2, ones, pk[KB ^ 1], pk[KB], lim,
