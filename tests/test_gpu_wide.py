@@ -5,7 +5,8 @@ the oracle, and against TILE where the call is one it cannot serve.
 The shapes cover what the kernel distinguishes: row tiles with many interior blocks (the fused
 steps), the first block and the diagonal blocks of a causal mask (plain steps), wavefronts that
 stop early under the mask, a ragged key tail, both storage types, scores that grow (references
-move: the fused steps hand the block to the plain ones), a negative scale (plain steps only)."""
+move: a block's coefficients are formed again, and the steps after it look at the top scores first), rows that
+stay empty and a negative scale (plain steps only)."""
 import numpy as np
 import pytest
 import torch
@@ -58,7 +59,7 @@ def test_wide_kernel_against_the_oracle(shape, causal, dtype):
 @pytest.mark.parametrize("causal", [False, True])
 def test_wide_kernel_with_large_and_growing_scores(dtype, qk_std, causal):
     """Large scores: references move often (f16 above all: a coefficient may be at most 2^13),
-    so blocks go back and forth between the fused and the plain steps."""
+    so many blocks are formed again and wavefronts go from looking first to not and back."""
     w = synthetic.small("wide big", 1, 2, 2, 512, 2048, 128, dtype, causal, seed=9400,
                         qk_std=qk_std, plant_frac=0.05)
     q, k, v, _ = synthetic.make_qkv(w)
@@ -91,8 +92,7 @@ def test_wide_kernel_first_block_far_from_zero(dtype, causal, level):
     """The first block of a row tile takes a fused step with zero standing in for the rows'
     reference; scores that all lie far below zero (the coefficients would vanish), a little
     below (the sum falls short of the least that is trusted) or far above (they would overflow)
-    must send it through the plain steps instead, and rows that see only a key or two must
-    come out right either way."""
+    must have it formed again, and rows that see only a key or two must come out right either way."""
     torch.manual_seed(17)
     Lq, Lk, d = 512, 768, 128
     q = torch.zeros(1, 2, Lq, d)
@@ -244,3 +244,64 @@ def test_wide_kernel_rows_whose_first_keys_weigh_nothing(first, later, rows, cau
         k[:, :, hidden, 5] = float("-inf")
     got = run_flashd(q, k, v, causal, 1.0, WIDE, 1)
     check(got, ref, DT[dtype], f"{later} {rows}")
+
+
+def jumps(at, Lq, Lk, dtype, seed, height=60.0):
+    """Scores that rise by `height` nats at every key of `at`, for every third row only from the second
+    jump on, and for the rows 64 to 127 (one wavefront's) not at all."""
+    torch.manual_seed(seed)
+    d = 128
+    q = torch.zeros(1, 2, Lq, d)
+    q[..., 0] = 1.0
+    q[..., 1] = 1.0
+    q[:, :, ::3, 1] = 0.0
+    q[:, :, 64:128, :2] = 0.0
+    q[..., 2:] = 0.1 * torch.randn(2, Lq, d - 2)
+    k = 0.1 * torch.randn(1, 2, Lk, d)
+    k[..., :2] = 0.0
+    for i, j in enumerate(at):
+        k[:, :, j:, 1 if i == 0 else 0] += height
+    v = torch.randn(1, 2, Lk, d)
+    return tuple(t.to(DT[dtype]) for t in (q, k, v))
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("at", [
+    (704, 3520),            # both in the first block of a period; 32 periods of 64 keys in which the steps look
+                            # first lie between them, and 12 in which they do not
+    (740, 3570),            # both in the second
+    (704, 740, 3570),       # in both blocks of a period's neighbours, then after the hand-over
+    (704, 736, 768, 800),   # every block
+    (704, 2750, 2784, 4830),   # in the last period that looks first, in the first that does not
+])
+def test_wide_kernel_between_looking_first_and_not(at, causal, dtype):
+    """After a reference has moved a wavefront's steps look at the top scores first, for 32 periods; then
+    they no longer do, until the next time."""
+    q, k, v = jumps(at, 512, 5600, dtype, 31)
+    got = run_flashd(q, k, v, causal, 1.0, WIDE, 1)
+    check(got, oa.attn(q, k, v, causal, 1.0), DT[dtype], f"{at} causal={causal}")
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("at", [(700,), (700, 735, 3000)])
+def test_wide_kernel_a_row_that_is_no_number(at, dtype):
+    """A row of NaN makes every block of its wavefront one to be formed again; its neighbours come out right."""
+    q, k, v = jumps(at, 256, 3600, dtype, 37)
+    ref = oa.attn(q, k, v, False, 1.0)
+    q[:, :, 5] = float("nan")
+    got = run_flashd(q, k, v, False, 1.0, WIDE, 1)
+    assert torch.isnan(got[:, :, 5]).all()
+    keep = [i for i in range(256) if i != 5]
+    check(got[:, :, keep], np.ascontiguousarray(ref[:, :, keep]), DT[dtype], f"{at}")
+
+
+@pytest.mark.parametrize("dtype,height", [("f16", 8.66), ("f16", 9.4), ("f16", 6.5), ("f16", 7.1), ("bf16", 37.0),
+                                          ("bf16", 41.0)])
+@pytest.mark.parametrize("causal", [False, True])
+def test_wide_kernel_scores_that_settle_near_the_limits(dtype, height, causal):
+    """Scores that stay just below and just above what a step trusts and what moves a reference (fp16 10
+    and 14 powers of two above it, bf16 54 and 60)."""
+    q, k, v = jumps((100,), 512, 1500, dtype, 41, height)
+    got = run_flashd(q, k, v, causal, 1.0, WIDE, 1)
+    check(got, oa.attn(q, k, v, causal, 1.0), DT[dtype], f"height={height}")
