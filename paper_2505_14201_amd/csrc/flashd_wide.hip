@@ -21,7 +21,7 @@
 //     and used one step later, after the sum of each row's coefficients has been looked at: a
 //     sum beyond LazyLimit::kMaxPsum means a score far above the row's reference, and the block's
 //     coefficients are formed again (wide_refit), by the checked step: it looks at the row's top score
-//     first and moves the reference if that lies more than LazyLimit::kMoveLog2 above it (the
+//     first and moves the reference if that lies more than kWideMoveLog2 above it (the
 //     saturation of Sec. III-C in tile form).  Nothing risky ever reaches U, and the block is used by
 //     the next step like any other.
 //   * For 32 periods of 64 keys after that the wavefront's fused steps look at the top scores first, 46
@@ -58,6 +58,16 @@ constexpr int kWideKB = 32;                     // keys per step of a wavefront 
 // reference (the largest of them is then at least 2^-8: far inside the range of either storage
 // type, whose rounding of a coefficient is relative).
 constexpr float kWideMinStart = 0.125f;
+
+// A reference moves once a top score lies this far above it (log2 units).  A lane's 16 coefficients of a
+// block then add up to what a fused step trusts, so that a checked step leaves nothing to form again: in fp16 at
+// 13, the limit of the other kernels, a row that had settled between the two had every further block formed
+// twice (2 x 16 heads of 4096, no mask, scores of standard deviation 1.5 settled 9.4 above the first block's
+// 472 us, now 262; 246 where they stay at its level).
+template <typename T> constexpr float kWideMoveLog2 = LazyLimit<T>::kMoveLog2;
+template <> constexpr float kWideMoveLog2<F16> = 10.0f;
+static_assert(16.0f * 1024.0f <= LazyLimit<F16>::kMaxPsum && 0x1p58f <= LazyLimit<BF16>::kMaxPsum,
+              "16 coefficients of 2^kWideMoveLog2");
 
 // Periods of 64 keys after the last moved reference for which a wavefront looks at the top scores first.
 constexpr int kWideWary = 32;
@@ -342,7 +352,7 @@ __device__ __forceinline__ void wide_request_first_k(const uint16_t* kb, const W
 // -inf and their coefficient is 0.  (Two more vector instructions per key; no row may be empty
 // as for any fused step.)
 // CHECKED: each row's top score is looked at first, and a reference that it lies more than
-// LazyLimit::kMoveLog2 above moves before the coefficients are formed; U, which the step has by its end
+// kWideMoveLog2 above moves before the coefficients are formed; U, which the step has by its end
 // multiplied all earlier blocks into, is scaled there.  No block is risky then (short of a sum that is no
 // number).  moved: some reference has.
 template <typename T, int D, bool PENDING, bool MASKED, bool CHECKED, typename Hook>
@@ -369,7 +379,7 @@ __device__ __forceinline__ bool wide_step(const uint16_t* kb, const uint16_t* kb
             for (int r = 0; r < 16; ++r)
                 m = fmaxf(m, MASKED && 8 * (r >> 2) + (r & 3) >= lim[rb] ? -__builtin_inff() : acc[rb][r]);
             m = pair_max(m) * c_log2;
-            const bool move = m - ref[rb] > LazyLimit<T>::kMoveLog2;
+            const bool move = m - ref[rb] > kWideMoveLog2<T>;
             f[rb] = move ? exp2_fast(ref[rb] - m) : 1.0f;
             ref[rb] = move ? m : ref[rb];
             l[rb] *= f[rb];
@@ -498,7 +508,7 @@ __device__ __forceinline__ bool wide_step(const uint16_t* kb, const uint16_t* kb
 // First half of the step of any other block (a mask applies, rows may be empty, any scale, or
 // a reference has to move), by plain steps: the checked step of flashd_mma.h.  For a row the
 // block's top score m is compared with the reference first; if the row is still empty or m
-// lies more than LazyLimit::kMoveLog2 above R the reference moves to m, every coefficient is
+// lies more than kWideMoveLog2 above R the reference moves to m, every coefficient is
 // then at most 1, and what the row holds is scaled by f = 2^{R - m} (here).  jb: index of the
 // key in accumulator register 0 for this lane.
 template <typename T, int D>
@@ -513,7 +523,7 @@ __device__ __forceinline__ void wide_first_general(WideRegs<D>& g, const f32x16 
         const float m = row_top_score<1, true>(a1, c_log2, jb, nvis[rb]);
         const bool empty = g.st[rb].one == 0.0f;
         const float mref = (m == ninf) ? 0.0f : m;
-        const bool move = empty || (m - g.st[rb].R > LazyLimit<T>::kMoveLog2);
+        const bool move = empty || (m - g.st[rb].R > kWideMoveLog2<T>);
         c.ref[rb] = move ? mref : g.st[rb].R;
         c.f[rb] = empty ? 0.0f : (move ? exp2_fast(g.st[rb].R - mref) : 1.0f);
         c.empty[rb] = empty;
