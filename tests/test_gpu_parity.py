@@ -334,7 +334,7 @@ def test_first_config_in_full():
 # rows of a few heads plus sampled rows everywhere.
 #   (B, Hq, Hkv, Lq, Lk, d, dtype, causal)
 SCHEDULE_SHAPES = [
-    (2, 64, 64, 1152, 1152, 128, "bf16", True),     # 9 row tiles: pairs + middle tile
+    (2, 64, 64, 1152, 1152, 128, "bf16", True),     # 9 row tiles
     (2, 64, 16, 1100, 1300, 128, "f16", True),      # ragged, Lq != Lk, GQA
     (1, 40, 40, 2048, 2048, 128, "bf16", False),    # no mask, units a multiple of 8
     (1, 36, 12, 2000, 1000, 128, "bf16", False),    # units not a multiple of 8, ragged

@@ -166,17 +166,28 @@ def test_the_automatic_choice_takes_the_wide_kernel_where_it_says_so():
     assert torch.equal(auto.view(torch.int16), tile.view(torch.int16))
 
 
-@pytest.mark.parametrize("variant,B,Hq,Hkv,Lq,Lk,d", [
-    (WIDE, 2, 32, 32, 2200, 2200, 128),                # 320 pairs for 256 compute units: row tiles one by one
-    (WIDE, 4, 32, 32, 1024, 1100, 128),                # 256 pairs: in pairs
-    (flashd.VARIANT_TILE, 2, 32, 32, 2200, 2200, 128), # 576 pairs for 512 workgroups: one by one
-    (flashd.VARIANT_TILE, 3, 12, 4, 4010, 4020, 128),  # heads of a group as one, 564 pairs
-    (flashd.VARIANT_TILE, 3, 32, 32, 2200, 2250, 64),  # 864 pairs for 768
-    (flashd.VARIANT_TILE, 8, 32, 32, 520, 520, 64),    # 768 pairs, the middle row tile by itself
-])
-def test_row_tiles_in_pairs_or_one_by_one(variant, B, Hq, Hkv, Lq, Lk, d):
+# (variant, B, Hq, Hkv, Lq, Lk, d), whether row tiles run in pairs; test_row_plan.py asks the rule itself.  The compute
+# units run 256 workgroups of the 256-row kernel at once, 512 of the 128-row one at d = 128 and 768 at d = 64.
+HAND_OUT = [
+    (WIDE, 2, 32, 32, 2200, 2200, 128, False),         # 320 pairs: 1.25 rounds
+    (WIDE, 4, 32, 32, 1024, 1100, 128, True),          # 256 pairs
+    (WIDE, 8, 32, 32, 700, 720, 128, True),            # 3 row tiles, the middle one by itself, ragged: 512
+    (flashd.VARIANT_TILE, 2, 32, 32, 2200, 2200, 128, False),   # 576 pairs
+    (flashd.VARIANT_TILE, 3, 12, 4, 4010, 4020, 128, False),    # heads of a group as one, 564 pairs
+    (flashd.VARIANT_TILE, 3, 32, 32, 2200, 2250, 64, False),    # 864 pairs
+    (flashd.VARIANT_TILE, 8, 32, 32, 520, 520, 64, False),      # 768 pairs, but not two rounds of row tiles
+    (flashd.VARIANT_TILE, 16, 32, 32, 300, 320, 128, True),     # 3 row tiles, ragged: 1024 pairs
+    (flashd.VARIANT_TILE, 32, 32, 8, 220, 230, 128, True),      # heads of a group as one, 7 row tiles: 1024
+    (flashd.VARIANT_TILE, 24, 32, 32, 300, 310, 64, True),      # 3 row tiles: 1536
+    (flashd.VARIANT_TILE, 8, 32, 32, 600, 610, 64, False),      # 5 row tiles: 768 pairs, 1280 row tiles
+    (flashd.VARIANT_TILE, 16, 32, 32, 560, 570, 64, True),      # 5 row tiles: 1536
+]
+
+
+@pytest.mark.parametrize("variant,B,Hq,Hkv,Lq,Lk,d,pairs", HAND_OUT)
+def test_row_tiles_in_pairs_or_one_by_one(variant, B, Hq, Hkv, Lq, Lk, d, pairs):
     """Both ways of handing out the row tiles of a causal call (rows_in_pairs), through both prefill
-    kernels: every row tile exactly once, wherever it runs."""
+    kernels: every row tile, wherever it runs (the output starts as NaN)."""
     w = synthetic.small("pairs", B, Hq, Hkv, Lq, Lk, d, "bf16", True, seed=9800 + B)
     q, k, v, _ = synthetic.make_qkv(w)
     got = run_flashd(q, k, v, True, w.scale, variant, 1)

@@ -161,3 +161,36 @@ def test_fp32_calls_that_run_whole(plan, H, Lq, Lk, d, causal, whole, with_state
     assert flashd.auto_splits(*call[:6], flashd.F32) > 1
     assert (plan([call], flashd.F32)[0][1] == 1) == bool(whole)
     assert (plan([(*call, None, 2)], flashd.F32)[0][1] == 1) == bool(with_state)
+
+
+HAND_OUT_PROGRAM = r"""
+#include <cstdio>
+#include "flashd_plan.h"
+int main() {
+    long m_tiles, units, slots;
+    int Lk, d;
+    double mb;
+    while (std::scanf("%ld %ld %ld %d %d %lf", &m_tiles, &units, &slots, &Lk, &d, &mb) == 6)
+        std::printf("%d\n", flashd::rows_in_pairs(m_tiles, units, slots, Lk, d, mb) ? 1 : 0);
+}
+"""
+
+
+def test_shapes_in_pairs_and_one_by_one(tmp_path):
+    """The shapes of test_gpu_wide.HAND_OUT reach the hand-out that they are meant for."""
+    from tests.test_gpu_wide import HAND_OUT, WIDE
+    if shutil.which("g++") is None:
+        pytest.skip("needs g++ to compile the header")
+    src, exe = tmp_path / "pairs.cpp", tmp_path / "pairs"
+    src.write_text(HAND_OUT_PROGRAM)
+    subprocess.run(["g++", "-O1", "-std=c++17", "-Wall", "-I", CSRC, "-o", str(exe), str(src)], check=True)
+    lines = []
+    for variant, B, Hq, Hkv, Lq, Lk, d, _ in HAND_OUT:
+        rows, slots = (256, 256) if variant == WIDE else (128, 512 if d == 128 else 768)
+        g = 1 if variant == WIDE else Hq // Hkv       # the 128-row kernel runs these heads of a group as one
+        lines.append(f"{(g * Lq + rows - 1) // rows} {B * Hq // g} {slots} {Lk} {d} {B * Hkv * Lk * d * 4e-6}")
+    out = subprocess.run([str(exe)], input="\n".join(lines), capture_output=True, text=True, check=True).stdout
+    assert [bool(int(x)) for x in out.split()] == [h[-1] for h in HAND_OUT]
+    pairs = [h for h in HAND_OUT if h[-1]]
+    odd = [h for h in pairs if (h[2] // h[3] * h[4] + 127) // 128 % 2 and h[0] != WIDE]
+    assert {h[6] for h in odd} == {64, 128} and any(h[2] != h[3] for h in odd)
