@@ -209,7 +209,7 @@ void decode_kernel(Problem p) {
     LazyRow st = {0.0f, 1.0f, 0.0f, 0.0f};      // FLASH-D state of the lane's row (lazy form)
     BlendRow bl = {0.0f, 0.0f};            // FLASH-D state, literal per-block blend
     float lam = ninf, beta = 0.0f;         // Alg. 2 state: running max, running sum
-    bool first = true;
+    bool first = true, holes = false;      // holes: some row that sees keys has met scores of -inf only
     Wary wary = {0, kWaryTiles};     // wavefront-uniform, see lazy_spec_pack
 
     constexpr int CHR = KV8 ? CH / 2 : CH;     // 16-byte loads per lane, block and tensor
@@ -265,7 +265,7 @@ void decode_kernel(Problem p) {
         // Coefficients of the block and the per-row state update (flashd_mma.h): the blend
         // factor is carried as a scalar per row, U is only scaled on the rare overflow path.
         // general: keys may be masked, or rows may still be empty (the wavefront's first block).
-        const bool general = first || j0 + kDecBlock > nvis_min;
+        const bool general = first || holes || j0 + kDecBlock > nvis_min;
         first = false;
         const int jb = j0 + 4 * hh;
         u32x4 bfrag[2];
@@ -281,6 +281,7 @@ void decode_kernel(Problem p) {
             if (general) risky = lazy_spec_pack<T, 1, true, true, TL>(acc, bfrag, st, c_log2, jb, nvis, lane, spec, wary);
             else risky = lazy_spec_pack<T, 1, false, false, TL>(acc, bfrag, st, c_log2, jb, nvis, lane, spec, wary);
             if (spec.any_moved) scale_u(spec.fu);
+            if (spec.none) holes = true;
             if (!spec.checked && __builtin_amdgcn_ballot_w64(risky) != 0) {
                 // rare: bf16 with a sum that is still a number moves the reference by a power
                 // of two in place; everything else takes the checked step on the raw scores
@@ -289,9 +290,10 @@ void decode_kernel(Problem p) {
                 bool moved;
                 if (std::is_same<T, BF16>::value && __builtin_amdgcn_ballot_w64(lost) == 0)
                     f = lazy_shift_inplace_bf16<TL>(bfrag, 2, st, risky, spec);
-                else if (general)
+                else if (general) {
                     f = lazy_checked_pack<T, 1, true, TL>(acc, bfrag, st, risky, c_log2, jb, nvis, moved);
-                else
+                    holes = __builtin_amdgcn_ballot_w64(row_ok && st.one == 0.0f && nvis > 0) != 0;
+                } else
                     f = lazy_checked_pack<T, 1, false, TL>(acc, bfrag, st, risky, c_log2, jb, nvis, moved);
                 wary.failed();
                 scale_u(f);
@@ -421,7 +423,7 @@ void decode_vskip_kernel(Problem p) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) U[i][r] = 0.0f;
     LazyRow st = {0.0f, 1.0f, 0.0f, 0.0f};
-    bool first = true;
+    bool first = true, holes = false;      // holes: some row that sees keys has met scores of -inf only
     Wary wary = {0, kWaryTiles};
     unsigned visited = 0, skipped = 0;         // wavefront-uniform
 
@@ -498,7 +500,7 @@ void decode_vskip_kernel(Problem p) {
         // coefficients were known
         if (pending) flush_pending();
 
-        const bool general = first || j0 + kDecBlock > nvis_min;
+        const bool general = first || holes || j0 + kDecBlock > nvis_min;
         first = false;
         const int jb = j0 + 4 * hh;
         u32x4 bfrag[2];
@@ -513,15 +515,17 @@ void decode_vskip_kernel(Problem p) {
             top = row_top_score<1, false>(acc, c_log2, jb, nvis);
         }
         if (spec.any_moved) scale_u(spec.fu);
+        if (spec.none) holes = true;
         if (!spec.checked && __builtin_amdgcn_ballot_w64(risky) != 0) {
             const bool lost = risky && !(spec.psum <= kLazyShiftMax);
             float f;
             bool moved;
             if (std::is_same<T, BF16>::value && __builtin_amdgcn_ballot_w64(lost) == 0)
                 f = lazy_shift_inplace_bf16<TL>(bfrag, 2, st, risky, spec);
-            else if (general)
+            else if (general) {
                 f = lazy_checked_pack<T, 1, true, TL>(acc, bfrag, st, risky, c_log2, jb, nvis, moved);
-            else
+                holes = __builtin_amdgcn_ballot_w64(row_ok && st.one == 0.0f && nvis > 0) != 0;
+            } else
                 f = lazy_checked_pack<T, 1, false, TL>(acc, bfrag, st, risky, c_log2, jb, nvis, moved);
             wary.failed();
             scale_u(f);

@@ -205,6 +205,8 @@ struct LazySpec {
     bool any_moved;   // wavefront-uniform: some row's fu is not 1
     bool checked;     // wavefront-uniform: the top scores were looked at first, so no row can be
                       // risky (short of a sum that is not a number)
+    bool none;        // wavefront-uniform: the top scores were looked at, and some row that sees keys is still empty,
+                      // its scores all -inf (where they were not, such a row is risky: -inf - (-inf))
 };
 
 // psum above this is treated as overflowed.  Below it one + beta psum (beta <= 2) stays far
@@ -284,7 +286,7 @@ __device__ __forceinline__ float row_top_score(const f32x16 (&acc)[NB], float c_
 // lane (tile start + 4 hh).  MASK = false: every key is visible to every row of the
 // wavefront.  Returns true if the row is risky; its state is then left untouched.
 // MAY_BE_EMPTY = false promises that no row of the wavefront is still empty (true from a
-// row's second unit on); the code is then free of the first-key logic.
+// row's second unit on, unless all scores before were -inf); the code is then free of the first-key logic.
 // TL: also carry the sum of the unrounded coefficients (LazyRow::ltrue).
 // wary (wavefront-uniform) > 0: the wavefront has lately needed the checked step, so the
 // rows' top scores are looked at before the exponentials (a few instructions, against a
@@ -318,6 +320,7 @@ __device__ __forceinline__ bool lazy_spec_pack(const f32x16 (&acc)[NB], u32x4 (&
     float ref = st.R;
     float fu = 1.0f;          // what the row holds (U, the carried sum) shrinks by this
     spec.any_moved = false;
+    spec.none = false;
     // a tile whose top scores have been looked at cannot hold a coefficient the storage type
     // does not: only a sum that is no number at all (NaN input) is then refused
     const float limit = (wary.left > 0) ? kLazyShiftMax : LazyLimit<T>::kMaxPsum;
@@ -335,7 +338,10 @@ __device__ __forceinline__ bool lazy_spec_pack(const f32x16 (&acc)[NB], u32x4 (&
         const float m = row_top_score<NB, MASK>(acc, c_log2, jb, nvis);
         const bool move = !empty && (m - st.R > LazyLimit<T>::kMoveLog2);
         // an empty row starts from its top score rather than its first: no coefficient above 1
-        if (MAY_BE_EMPTY) ref = (empty && m != ninf) ? m : ref;
+        if (MAY_BE_EMPTY) {
+            ref = empty ? (m == ninf ? 0.0f : m) : ref;
+            spec.none = __builtin_amdgcn_ballot_w64(empty && m == ninf && nvis > 0) != 0;
+        }
         fu = move ? exp2_fast(st.R - m) : 1.0f;
         ref = move ? m : ref;
         spec.any_moved = __builtin_amdgcn_ballot_w64(move) != 0;

@@ -94,12 +94,13 @@ __device__ __forceinline__ void phase_scores(const uint16_t* ks, const TileRegs<
 // the variant needs it, the scaling of U.  general = false promises that every key of the
 // tile is visible to every row of the wavefront and that no row is still empty (not the
 // first tile of a row); the common code path then carries neither the mask nor the
-// first-key logic.  wary (wavefront-uniform): see lazy_spec_pack.
+// first-key logic.  holes (wavefront-uniform): some row that sees keys has met scores of -inf only, and the next
+// tiles are general too.  wary (wavefront-uniform): see lazy_spec_pack.
 template <typename T, int D, int MODE, bool TL>
 __device__ __forceinline__ void phase_coeffs(const uint16_t* ks, const f32x16 (&acc)[2],
                                              u32x4 (&bfrag)[4], TileRegs<D>& g, int j0, int hh,
                                              int lane, int nvis, bool general, float c_log2,
-                                             Wary& wary) {
+                                             Wary& wary, bool& holes) {
     constexpr int NDB = D / 32;
     const int jb = j0 + 4 * hh;
     auto scale_u = [&](float f) __attribute__((always_inline)) {
@@ -118,6 +119,7 @@ __device__ __forceinline__ void phase_coeffs(const uint16_t* ks, const f32x16 (&
             risky = lazy_spec_pack<T, 2, false, false, TL>(acc, bfrag, g.st, c_log2, jb, nvis,
                                                            lane, spec, wary);
         if (spec.any_moved) scale_u(spec.fu);
+        if (spec.none) holes = true;
         if (!spec.checked && __builtin_amdgcn_ballot_w64(risky) != 0) {
             // rare: a flagged row's coefficients do not fit the storage type.  bf16 with a
             // sum that is still a number: the reference moves up by a power of two and the
@@ -134,10 +136,11 @@ __device__ __forceinline__ void phase_coeffs(const uint16_t* ks, const f32x16 (&
                 f32x16 acc2[2];
                 phase_scores<T, D>(ks, g, acc2);
                 bool moved;
-                if (general)
+                if (general) {
                     f = lazy_checked_pack<T, 2, true, TL>(acc2, bfrag, g.st, risky, c_log2, jb,
                                                           nvis, moved);
-                else
+                    holes = __builtin_amdgcn_ballot_w64(g.st.one == 0.0f && nvis > 0) != 0;
+                } else
                     f = lazy_checked_pack<T, 2, false, TL>(acc2, bfrag, g.st, risky, c_log2, jb,
                                                            nvis, moved);
                 wary.failed();
@@ -205,7 +208,7 @@ __device__ __forceinline__ void phase_output(const uint16_t* vs, TileRegs<D>& g,
 template <typename T, int D, int MODE, bool TL, int PAR>
 __device__ __forceinline__ void tile_math(const uint16_t* lds, TileRegs<D>& g, int j0, int hh,
                                           int lane, int nvis, bool general, float c_log2,
-                                          Wary& wary) {
+                                          Wary& wary, bool& holes) {
     constexpr int kTile = kBC * D;
     f32x16 acc[2];
     u32x4 bfrag[4];
@@ -222,7 +225,7 @@ __device__ __forceinline__ void tile_math(const uint16_t* lds, TileRegs<D>& g, i
     wait_copies();
     if (kEarlyV) prefetch_v<D>(lds + (2 + PAR) * kTile, g, va0);
     phase_coeffs<T, D, MODE, TL>(lds + PAR * kTile, acc, bfrag, g, j0, hh, lane, nvis,
-                                          general, c_log2, wary);
+                                          general, c_log2, wary, holes);
     if (!kEarlyV) prefetch_v<D>(lds + (2 + PAR) * kTile, g, va0);
     phase_output<T, D>(lds + (2 + PAR) * kTile, g, bfrag, va0);
 }
@@ -344,6 +347,8 @@ void tile_kernel(Problem p, TileSched sc) {
         }
         have0 = false;
 
+        bool holes = false;          // see phase_coeffs
+
         // Period t: start the copies of the next tile into the other slot, which was last
         // read in period t - 1; do the math of tile t; wait for the copies; barrier.  Tile t
         // of a row tile lives in slot t % 2, and the loop body is two periods, one per slot,
@@ -368,7 +373,7 @@ void tile_kernel(Problem p, TileSched sc) {
             }
             if (j0 < cur.wmax)
                 tile_math<T, D, MODE, kTL, PAR>(lds, g, j0, hh, lane, nvis,
-                                               t == 0 || j0 + kBC > cur.wmin, c_log2, wary);
+                                               t == 0 || holes || j0 + kBC > cur.wmin, c_log2, wary, holes);
             wait_copies();
             __syncthreads();
         };
