@@ -71,8 +71,9 @@ typedef enum {
 /* How the recurrence is evaluated.  All variants compute the same result. */
 typedef enum {
     FLASHD_VARIANT_AUTO = 0,     /* TILE (or TILE_256) for f16/bf16; for f32 the tile form on
-                                    the matrix cores with fp64 scores (reported as PER_KEY;
-                                    AUTO is the only way to ask for it)                      */
+                                    the matrix cores, scores in fp64 or from fp16 slices where
+                                    those are as good (reported as PER_KEY; AUTO is the only
+                                    way to ask for it)                                       */
     FLASHD_VARIANT_TILE = 1,     /* Alg. 3 lifted to key tiles on the matrix cores (f16/bf16),
                                     the (1 - W) factors of the blend deferred to the store;
                                     with splits == 0 small calls take kernels with 32 or 64
@@ -153,8 +154,8 @@ int flashd_auto_splits(int B, int Hq, int Hkv, int Lq, int Lk, int d, int dtype,
  * tiles come in whole rounds of the compute units; and not behind TILE by an estimate of both
  * times).  Host-only; -1 for invalid arguments.
  * Passed to flashd_attn_fwd_ex the answer gives the kernel that AUTO runs, save for f32: AUTO runs
- * its tile form there, at the precision of PER_KEY and up to twelve times faster, but not with the
- * same bits; pass FLASHD_VARIANT_AUTO itself to get it.  (Decode shapes, (Hq / Hkv) * Lq <= 32,
+ * its tile form there, whose output is as far from fp64 as that of PER_KEY, up to fourteen times
+ * faster, but not with the same bits; pass FLASHD_VARIANT_AUTO itself to get it.  (Decode shapes, (Hq / Hkv) * Lq <= 32,
  * report TILE: they run the tile form on the split-K decode kernel.)  The answer belongs with
  * splits == 0.
  */

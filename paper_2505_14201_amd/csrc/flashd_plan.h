@@ -123,7 +123,7 @@ inline double prefill_estimate(const PrefillCost& c, const Shape& s, bool causal
 // limits alone and pairs throughout gave, 0.62 to 1.04 (1.12 in one case), 1 % more than with the better of the two
 // kernels everywhere.  What is left lies outside the limits: there scores that keep passing the rows' references
 // (standard deviation 4, planted dominant keys) cost the 256-row kernel more than it gains on others (6 x 32
-// heads of 2841, causal, 1143 us and 488).
+// heads of 2841, causal, 841 us and 532).
 //   - a workgroup per compute unit, two under a causal mask;
 //   - 1536 keys without a mask, rows that see 1536 keys on average under a causal one, or 1024 where pairs of row tiles
 //     fill whole rounds: what it pays at every change of row tile with only one workgroup on the compute unit is
